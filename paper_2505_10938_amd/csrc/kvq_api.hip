@@ -343,7 +343,8 @@ int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t seq, const 
     d.unit0 += (int64_t)seq * cfg->kv_heads;
     d.units_per_layer = cfg->kv_heads;
     d.seq0 = seq;
-    if (kvq::launch_reset_pools(d, pool, s) != hipSuccess) return KVQ_ERR_LAUNCH;
+    // (where groups compete, the competition writes the pools' state whatever they held)
+    if ((n_groups == 0 || d.N == 0) && kvq::launch_reset_pools(d, pool, s) != hipSuccess) return KVQ_ERR_LAUNCH;
   }
   if (n_groups > 0) {
     hipError_t e = kvq::launch_prefill_trace(d, n_groups, (const __half*)k_rows, (const __half*)v_rows, unit_stride,

@@ -1,5 +1,5 @@
 // Outlier-token competition as kernels of its own: one group per launch (one workgroup of 4 wavefronts
-// per unit), or the groups of a whole prompt (scores in parallel, then one wavefront per unit).
+// per unit), or the groups of a whole prompt (all at once).
 #include "kvq_common.h"
 #include "kvq_trace_core.h"
 
@@ -34,273 +34,441 @@ __global__ void __launch_bounds__(trace_core::kWorkers) trace_kernel(
 }
 
 // ---- the competitions of a whole prompt -----------------------------------------------------------
-// One workgroup of 4 wavefronts per unit.  The L1 scores of the tokens are computed 1024 tokens at a time
-// into one of two LDS buffers; ONE wavefront walks the groups of a chunk in order on those scores while
-// the other three compute the next chunk's.  The pool is a sorted list held one entry per lane of that
-// wavefront; a stretch of tokens is looked at with one comparison per token against the pool's largest
-// key, and only tokens below it are inserted, one at a time (the N smallest of pool and group do not
-// depend on the order of insertion).  At the end the wavefront copies the rows of the final members from
-// the prompt.  The result is the state the group-by-group competitions leave: same index sets, scores,
-// rows, counts and flags (slot order is not part of it).
+// The state that the group-by-group competitions leave can be computed for all groups at once: a token is
+// selected if fewer than N tokens of its own and the earlier groups have a smaller key (score, index); the
+// pool is the N smallest of the selected tokens; with S_i tokens selected up to group i, S_i - min(N, (i+1)G)
+// have fallen out, and the first group where that exceeds A is where tracing stops.  None of it depends on
+// the order of insertion, and only selected tokens can displace one, so that counting needs few of them.
+//
+// Two launches.  prompt_candidates_kernel: one workgroup per unit and segment of 1024 tokens computes the
+// L1 scores and flags the tokens that may be selected, judged by the segment alone (for N = 8 and random
+// scores about 50 of 1024).  What bounds it is the read of the Keys.  prompt_compete_kernel: one workgroup
+// per unit gathers the flagged tokens, selects among them and writes flags, pool and state: a chain of
+// short phases that a single workgroup goes through in order, which is why all that can be done per segment
+// is done there.  A prompt of one segment needs the second launch only.
+//
+// Measured (kernel trace) against one wavefront per unit that walked the groups and inserted one token at a
+// time, with seven others computing scores ahead of it:
+//   8 units x 8064 tokens (64 workgroups, then 8)       93 us -> 9.8 + 15.2 us
+//   256 units x 3968 tokens (1024 workgroups, then 256) 84 us -> 53 + 17.8 us (the read alone: 52 us, 5.1 TB/s)
+//   128 units x 160 tokens (second launch only)         24 us -> 13 us
+// With 512 threads per workgroup and a first look by exact ranks instead of bounds: 25 + 25 us and 79 + 24 us.
 
-__device__ inline double lane_value(double v, int l) {     // v of lane l (uniform l)
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-// The value of lane - 1 (lane 0 keeps its own), as a DPP move over the whole wavefront: no LDS traffic.
-__device__ __forceinline__ uint32_t from_lane_below_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
-}
-__device__ __forceinline__ double from_lane_below(double v) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned long long lo = from_lane_below_u32((uint32_t)b), hi = from_lane_below_u32((uint32_t)(b >> 32));
-  return __longlong_as_double((long long)((hi << 32) | lo));
-}
-// (score, token index) ascending: the order of the competition
-__device__ inline bool key_less(double as, int ai, double bs, int bi) { return as < bs || (as == bs && ai < bi); }
+constexpr int kCompeteThreads = 1024;
+constexpr int kCompeteWaves = kCompeteThreads / 64;
+constexpr int kSegment = kCompeteThreads;              // tokens that compete at a time: one per thread
+constexpr int kRound = 128;                            // tokens ranked at a time: at least a whole group
+constexpr int kWindow = 8192;                          // tokens whose flags are looked at at a time
 
-constexpr int kScoreChunk = 1024;                      // scores staged in LDS at a time
-// wavefronts per unit: one walks the groups, the others score ahead.  Measured on a 4096-token prompt: 4 / 8 / 16
-// wavefronts 91 / 80 / 79 us for 256 units (the whole prompt 233 / 218 / 220 us), 810 / 811 .. 822 / 865 us for the
-// whole prompt of 1024 units.  With 8 the scores are ready well ahead and the walk itself, about 75 us, is what
-// remains; a raised priority for the walking wavefront changes nothing.
-constexpr int kTraceWaves = 8;
+typedef unsigned long long u64;
 
-// Requires empty pools on entry (a prompt starts a sequence).
+// A first look that is cheap and lets few entries through that will not be selected: an entry must be among
+// the N smallest of any prefix of the entries that ends with its group or before.  The N-th smallest score
+// of the first 32, 64, 128 and 256 entries is found by bisection over coarse scores (fp32 rounded, the first
+// 8 bits of the significand: the order is kept, only some neighbours become equal), one wavefront each.
+constexpr int kPrefixes = 4;
+constexpr int kCoarseBits = 16;
+__device__ __forceinline__ uint32_t coarse_score(double score) {
+  return score < 8388608.0 ? __float_as_uint((float)score) >> (31 - kCoarseBits) : (1u << kCoarseBits) - 1u;
+}
+__device__ __forceinline__ void prefix_bounds(const uint32_t* coarse, int n, int N, uint32_t* bound, int wave, int lane) {
+  if (wave >= kPrefixes) return;
+  constexpr int kWords = (32 << (kPrefixes - 1)) / 64;
+  const int p = min(32 << wave, n);
+  uint32_t v[kWords], t = 0;
+#pragma unroll
+  for (int k = 0; k < kWords; ++k) v[k] = k * 64 + lane < p ? coarse[k * 64 + lane] : ~0u;
+#pragma unroll
+  for (int b = kCoarseBits - 1; b >= 0; --b) {
+    int at_most = 0;
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) at_most += __popcll(__ballot(v[k] <= (t | ((1u << b) - 1u))));
+    t |= at_most < N ? 1u << b : 0u;
+  }
+  if (lane == 0) bound[wave] = t;                      // (fewer than N entries: the largest value there is)
+}
+
+// The order of the competition, (score, token index) ascending, as one integer.  A score is a multiple of
+// 2^-24 below 2^23: added to 2^28 it leaves score * 2^24 in the significand (47 bits).  Below it stands the
+// place among the entries that compete (ascending by token index), and 0 for a member of the pool, which is
+// older than all of them.  Sums that are no such number (infinities, NaN: not supported) rank last.
+constexpr int kPlaceBits = 11;
+constexpr u64 kPlaceMask = (1ull << kPlaceBits) - 1ull;
+__device__ __forceinline__ u64 competition_key(double score, int place) {
+  const u64 fixed = score < 8388608.0 ? (u64)__double_as_longlong(score + 268435456.0) & ((1ull << 52) - 1ull)
+                                      : (1ull << 47) - 1ull;
+  return (fixed << kPlaceBits) | (u64)place;
+}
+__device__ __forceinline__ u64 lane_value(u64 v, int l) {   // v of lane l (uniform l)
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+  return ((u64)hi << 32) | lo;
+}
+// Inclusive sums over the lanes, on the DPP path.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr:1 */, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142 /* row_bcast:15 */, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143 /* row_bcast:31 */, 0xc, 0xf, false);
+  return v;
+}
+
+struct CompeteLds {
+  u64 key[kSegment];                                   // the entries competing, ascending by token index
+  int32_t idx[kSegment];
+  uint32_t coarse[kSegment];                           // their scores, coarsely
+  uint32_t bound[kPrefixes];
+  u64 mask[kWindow / 64];                              // marked entries, 64 per word
+  u64 r_key[kRound];                                   // the round's
+  int32_t r_idx[kRound];
+  uint32_t r_less[kRound];                             // smaller keys: up to the entry's group, and << 16 in all
+  u64 p_key[2][64];                                    // the pool, ascending; two buffers taken in turn
+  uint32_t p_less[64];
+  uint8_t r_sel[kRound];
+  int32_t cut_group, cut_rank, cut_at;
+};
+
+// Ranks of marked entries: `before(w)` = marked entries in the words ahead of word w.  Every wavefront
+// computes the sums for itself (two words per lane), no barrier.
+struct MaskRanks {
+  int ex0, ex1, total;                                 // ahead of words 2 lane, 2 lane + 1; in all
+  __device__ __forceinline__ MaskRanks(const u64* mask, int n_words, int lane) {
+    const int c0 = 2 * lane < n_words ? __popcll(mask[2 * lane]) : 0;
+    const int c1 = 2 * lane + 1 < n_words ? __popcll(mask[2 * lane + 1]) : 0;
+    const int incl = wave_scan(c0 + c1);
+    ex0 = incl - c0 - c1;
+    ex1 = incl - c1;
+    total = __builtin_amdgcn_readlane(incl, 63);
+  }
+  __device__ __forceinline__ int before(int w) const {  // (uniform w)
+    return (w & 1) ? __builtin_amdgcn_readlane(ex1, w >> 1) : __builtin_amdgcn_readlane(ex0, w >> 1);
+  }
+};
+
+// Exact fp64 L1 scores of the Key rows row(0) .. row(n - 1), handed to put(e, score) by one lane each: 16 lanes
+// per row, eight rows of a team of lanes in flight.
+template <class Row, class Put>
+__device__ __forceinline__ void score_rows(int n, int tid, Row row, Put put) {
+  constexpr int kTeams = kCompeteThreads / 16;
+  const int team = tid >> 4, sub = tid & 15;
+  for (int i0 = 0; i0 < n; i0 += 8 * kTeams) {
+    uint4 w[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = *(const uint4*)(row(min(i0 + q * kTeams + team, n - 1)) + sub * 8);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int e = i0 + q * kTeams + team;
+      const double sc = trace_core::team_sum_f64(trace_core::abs_sum8(w[q]));
+      if (sub == 0 && e < n) put(e, sc);
+    }
+  }
+}
+
+// One round: ranks the next entries (from entry `pos` on, of the n in LDS) and updates the pool (P members in
+// buffer `cur`, which changes).  Entry j of the round, j < the result, is L.r_idx[j] and was selected if
+// L.r_sel[j].  `pos` becomes the first entry not looked at.  `may`: entry `tid` passed the first look.  Four
+// barriers, the last one at the end.
 template <int G>
-__global__ void __launch_bounds__(64 * kTraceWaves) prefill_trace_kernel(
-    Dims d, int32_t n_groups, const __half* __restrict__ k_rows, const __half* __restrict__ v_rows,
+__device__ __forceinline__ int compete_round(CompeteLds& L, int n, bool may, int& pos, int N, int& P, int& cur, int tid) {
+  constexpr int kGroupShift = G == 32 ? 5 : G == 64 ? 6 : 7;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const u64 max_key = L.p_key[cur][N - 1];             // (counts only where P == N)
+  const u64 key = L.key[tid];
+  const int ix = L.idx[tid];
+  const u64 m = __ballot(may && tid >= pos && tid < n && (P < N || key < max_key));
+  if (lane == 0) L.mask[wave] = m;
+  if (tid < kRound) L.r_less[tid] = 0;
+  if (tid < 64) L.p_less[tid] = 0;
+  __syncthreads();
+  const MaskRanks ranks(L.mask, kSegment / 64, lane);
+  const bool marked = (m >> lane) & 1ull;
+  const int rank = ranks.before(wave) + __popcll(m & ((1ull << lane) - 1ull));
+  int nr = ranks.total, next = n;
+  if (nr > kRound) {                                   // uniform: only the groups that are in whole
+    if (tid == 0) L.cut_rank = L.cut_at = kSegment;
+    if (marked && rank == kRound) L.cut_group = ix >> kGroupShift;
+    __syncthreads();
+    if (marked && (ix >> kGroupShift) >= L.cut_group) {
+      atomicMin(&L.cut_rank, rank);
+      atomicMin(&L.cut_at, tid);
+    }
+    __syncthreads();
+    nr = min(L.cut_rank, kRound);
+    next = L.cut_at;
+  }
+  if (marked && rank < nr) {
+    L.r_key[rank] = key;
+    L.r_idx[rank] = ix;
+  }
+  __syncthreads();
+  // A lane counts for entries lane, 64 + lane and for member lane; the wavefronts share what is counted.
+  const u64 none = ~0ull;
+  const u64 kp = lane < P ? L.p_key[cur][lane] : none;
+  const u64 k0 = lane < nr ? L.r_key[lane] : none, k1 = 64 + lane < nr ? L.r_key[64 + lane] : none;
+  const int end0 = L.r_idx[lane] | (G - 1), end1 = L.r_idx[64 + lane] | (G - 1);
+  uint32_t c0 = 0, c1 = 0, cp = 0;
+#pragma unroll
+  for (int i = 0; i < kRound / kCompeteWaves; ++i) {
+    const int j = i * kCompeteWaves + wave;
+    if (j < nr) {
+      const u64 jk = L.r_key[j];
+      const int jx = L.r_idx[j];
+      c0 += jk < k0 ? (jx <= end0 ? 0x10001u : 0x10000u) : 0u;
+      c1 += jk < k1 ? (jx <= end1 ? 0x10001u : 0x10000u) : 0u;
+      cp += jk < kp ? 1u : 0u;
+    }
+  }
+  for (int p = wave; p < P; p += kCompeteWaves) {
+    const u64 pk = L.p_key[cur][p];
+    c0 += pk < k0 ? 0x10001u : 0u;
+    c1 += pk < k1 ? 0x10001u : 0u;
+  }
+  if (lane < nr) atomicAdd(&L.r_less[lane], c0);
+  if (64 + lane < nr) atomicAdd(&L.r_less[64 + lane], c1);
+  if (lane < P) atomicAdd(&L.p_less[lane], cp);
+  __syncthreads();
+  if (tid < nr) {
+    const int own = (int)(L.r_less[tid] & 0xFFFFu), all = (int)(L.r_less[tid] >> 16);
+    L.r_sel[tid] = own < N ? 1 : 0;
+    if (all < N) L.p_key[cur ^ 1][all] = L.r_key[tid] & ~kPlaceMask;
+  } else if (tid >= kRound && tid < kRound + P) {
+    const int p = tid - kRound, to = p + (int)L.p_less[p];
+    if (to < N) L.p_key[cur ^ 1][to] = L.p_key[cur][p];
+  }
+  __syncthreads();
+  P = min(N, P + nr);
+  cur ^= 1;
+  pos = next;
+  return nr;
+}
+
+// Is entry e, token idx (n entries, `at(p)` = token of entry p), among those that the first look lets through?
+template <int G, class At>
+__device__ __forceinline__ bool may_be_selected(const uint32_t* coarse, const uint32_t* bound, int n, int e, int idx, At at) {
+  uint32_t b = ~0u;
+#pragma unroll
+  for (int i = 0; i < kPrefixes; ++i)
+    if ((32 << i) <= n && at((32 << i) - 1) <= (idx | (G - 1))) b = bound[i];   // (bounds fall with the prefix)
+  return coarse[e] <= b;
+}
+
+// grid (units, segments).  Requires N > 0.
+template <int G>
+__global__ void __launch_bounds__(kCompeteThreads) prompt_candidates_kernel(Dims d, int32_t n_tok,
+                                                                            const __half* __restrict__ k_rows,
+                                                                            int64_t unit_stride,
+                                                                            uint8_t* __restrict__ selected) {
+  __shared__ uint32_t coarse[kSegment];
+  __shared__ uint32_t bound[kPrefixes];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ul = blockIdx.x, t0 = blockIdx.y * kSegment;
+  const int n = min(kSegment, n_tok - t0);
+  const __half* rows = k_rows + (int64_t)ul * unit_stride + (int64_t)t0 * kHeadDim;
+  score_rows(n, tid, [&](int e) { return rows + e * kHeadDim; }, [&](int e, double sc) { coarse[e] = coarse_score(sc); });
+  __syncthreads();
+  prefix_bounds(coarse, n, d.N, bound, wave, lane);
+  __syncthreads();
+  // (segments begin with a group: token numbers inside the segment number its groups as well)
+  if (tid < n)
+    selected[(int64_t)ul * n_tok + t0 + tid] =
+        may_be_selected<G>(coarse, bound, n, tid, tid, [](int p) { return p; }) ? 1 : 0;
+}
+
+// grid (units).  `flagged`: the tokens that can be selected are flagged in `selected`, else all of them are
+// looked at.  Pools are taken to be empty on entry (a prompt starts a sequence) and are not read.
+template <int G>
+__global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
+    Dims d, int32_t n_tok, int32_t flagged, const __half* __restrict__ k_rows, const __half* __restrict__ v_rows,
     int64_t unit_stride, __half* pool_k, __half* pool_v, int32_t* pool_idx, double* pool_score, int32_t* pool_count,
     int32_t* aux_count, int32_t* frozen, uint8_t* __restrict__ selected) {
-  __shared__ double s_buf[2][kScoreChunk];
-  __shared__ double s_aux_score[64];
-  __shared__ int32_t s_aux_idx[64];
-  __shared__ int32_t s_stop[2];                         // set by the wavefront that holds the pool; slot = chunk parity
+  constexpr int kGroupShift = G == 32 ? 5 : G == 64 ? 6 : 7;
+  constexpr int kListed = 64 + 64 + kRound;            // at most N + A selected tokens before the last round
+  __shared__ CompeteLds L;
+  __shared__ u64 s_key[kListed];                       // every token selected so far, ascending by index
+  __shared__ int32_t s_idx[kListed];
+  __shared__ int32_t s_out[kListed];                   // the group at which it falls out (none: kStays)
+  __shared__ int32_t slot_idx[128];                    // token of each pool and auxiliary slot
+  constexpr int32_t kStays = 0x7FFFFFFF;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ul = blockIdx.x;
   const int64_t u = d.unit0 + ul;
-  const int n_tok = n_groups * G;
   uint8_t* sel = selected + (int64_t)ul * n_tok;
   const int N = d.N, A = d.A;
   if (N == 0) {                                        // no pool: nothing is ever selected
-    for (int i = tid; i < n_tok; i += 64 * kTraceWaves) sel[i] = 0;
+    for (int i = tid; i < n_tok; i += kCompeteThreads) sel[i] = 0;
     return;
   }
-  constexpr int kRounds = (G + 63) / 64;               // a group is looked at 64 tokens at a time
-  constexpr int kPer = kScoreChunk / 64;
-  // fp64 L1 scores of the chunk's tokens into `buf`, by the wavefronts w0 .. kTraceWaves - 1: 16 lanes per row, 4 rows
-  // per load instruction, eight of them in flight per wavefront
-  const __half* rows = k_rows + (int64_t)ul * unit_stride;
-  auto score_chunk = [&](int c0, double* buf, int w0) {
-    const int nw = kTraceWaves - w0;
-    const int n_here = min(kScoreChunk, n_tok - c0);
-    const int team = lane >> 4, sub = lane & 15;
-    for (int i0 = 0; ((wave - w0) + nw * i0) * 4 < n_here; i0 += 8) {
-      uint4 w[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int r = min(((wave - w0) + nw * (i0 + q)) * 4 + team, n_here - 1);
-        w[q] = *(const uint4*)(rows + (int64_t)(c0 + r) * kHeadDim + sub * 8);
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int r = ((wave - w0) + nw * (i0 + q)) * 4 + team;
-        const double sc = trace_core::team_sum_f64(trace_core::abs_sum8(w[q]));
-        if (sub == 0 && r < n_here) buf[r] = sc;
-      }
-    }
-  };
-  if (tid < 2) s_stop[tid] = 0;
-  score_chunk(0, s_buf[0], 0);
-  __syncthreads();
-  const double kInf = __longlong_as_double(0x7FF0000000000000ll);
-  double ps = kInf;                                    // the pool, ascending by key: entry `lane`, lanes below P
-  int pi = 0x7FFFFFFF;
-  int P = 0, aux_n = 0;
+  const __half* kr = k_rows + (int64_t)ul * unit_stride;
+  const __half* vr = v_rows + (int64_t)ul * unit_stride;
+  const u64 below = (1ull << lane) - 1ull;
+  int P = 0, cur = 0, S = 0;                           // pool members, pool buffer, selected tokens
   bool stopped = false;
-  int gi = 0;                                          // the next group
-  // One group on the sorted pool: tokens that belong to the N smallest keys seen so far are inserted one
-  // at a time, the largest key falling out each time the pool is full.
-  auto do_group = [&](int gl, const double* s_sc) {
-    const int first = gi * G;                          // the group's first token
-    const double ps0 = ps;                             // the pool before the group, should tracing stop here
-    const int pi0 = pi, P0 = P;
-    int E = 0;                                         // members of the old pool that fall out
-    unsigned long long selm[kRounds];
+  int t0 = 0;                                          // tokens before t0 have been looked at
+  while (t0 < n_tok && !stopped) {
+    // ---- the next candidates, at most kSegment (whole groups), and their scores
+    constexpr int kPer = kWindow / kCompeteThreads;
+    const int here = min(kWindow, n_tok - t0);
+    u64 m[kPer];
+    uint8_t f[kPer];
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) selm[r] = 0;
-    // (the rounds as calls with a constant round number: as a loop around the insertions it is not unrolled)
-    auto round = [&](auto round_number) {
-      constexpr int r = decltype(round_number)::value;
-      const int t = r * 64 + lane;
-      const double s = s_sc[gl * G + min(t, G - 1)];
-      const int idx = first + t;
-      bool pending = t < G;
-      while (true) {
-        // all tokens while the pool has room, else those below its largest key
-        const double max_s = lane_value(ps, max(P - 1, 0));
-        const int max_i = __builtin_amdgcn_readlane(pi, max(P - 1, 0));
-        const bool in = pending && (P < N || key_less(s, idx, max_s, max_i));
-        const unsigned long long m = __ballot(in);
-        if (m == 0) break;
-        const int l = __builtin_amdgcn_readfirstlane(__ffsll((long long)m) - 1);
-        const double cs = lane_value(s, l);
-        const int ci = first + r * 64 + l;
-        if (lane == l) pending = false;
-        const int pos = __popcll(__ballot(lane < P && key_less(ps, pi, cs, ci)));
-        if (P == N) {                                  // the largest key falls out
-          if (max_i < first) {                         // a member of the old pool: to the auxiliary pool
-            if (aux_n + E < A && lane == 0) {
-              s_aux_score[aux_n + E] = max_s;
-              s_aux_idx[aux_n + E] = max_i;
-            }
-            ++E;
-          } else {                                     // a token of this group that got in a moment ago
-            const int tt = max_i - first;
-#pragma unroll
-            for (int rr = 0; rr < kRounds; ++rr)
-              if ((tt >> 6) == rr) selm[rr] &= ~(1ull << (tt & 63));
-          }
-        }
-        const double up_s = from_lane_below(ps);
-        const int up_i = (int)from_lane_below_u32((uint32_t)pi);
-        if (lane > pos) {
-          ps = up_s;
-          pi = up_i;
-        } else if (lane == pos) {
-          ps = cs;
-          pi = ci;
-        }
-        if (P < N) ++P;
-        selm[r] |= 1ull << l;
-      }
-    };
-    round(std::integral_constant<int, 0>{});
-    if constexpr (kRounds > 1) round(std::integral_constant<int, 1>{});
-    if (aux_n + E > A) {                               // they do not fit: tracing stops, nothing changes
-      ps = ps0;
-      pi = pi0;
-      P = P0;
-      stopped = true;
-#pragma unroll
-      for (int r = 0; r < kRounds; ++r) selm[r] = 0;
-    } else {
-      aux_n += E;
+    for (int k = 0; k < kPer; ++k) {
+      const int t = k * kCompeteThreads + tid;
+      f[k] = flagged ? sel[t0 + min(t, here - 1)] : (uint8_t)1;
     }
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r)
-      if (r * 64 + lane < G) sel[first + r * 64 + lane] = (uint8_t)((selm[r] >> lane) & 1ull);
-    ++gi;
-  };
-  constexpr int kSpanTok = G > 64 ? G : 64;            // tokens that are ruled out together: whole groups, whole masks
-  constexpr int kMasksPerSpan = kSpanTok / 64, kGroupsPerSpan = kSpanTok / G;
-  // the groups of one chunk (the wavefront that holds the pool)
-  auto compete_chunk = [&](int c0, const double* s_sc) {
-    const int here = min(kScoreChunk, n_tok - c0) / G;
-    // Which tokens of the chunk lie below the pool's largest key as it is now (64 per mask, mask k kept by
-    // lane k): that key only falls, so tokens that are not below it now cannot change anything later, and
-    // most stretches of a long prompt hold no such token.
-    uint32_t below_lo = 0, below_hi = 0;
-    auto look = [&]() {
-      const double max_s = lane_value(ps, max(P - 1, 0));
-      const int max_i = __builtin_amdgcn_readlane(pi, max(P - 1, 0));
-      double v[kPer];
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) v[k] = s_sc[k * 64 + lane];
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int t = c0 + k * 64 + lane;
-        const unsigned long long b = __ballot(t < n_tok && (P < N || key_less(v[k], t, max_s, max_i)));
-        below_lo = lane == k ? (uint32_t)b : below_lo;
-        below_hi = lane == k ? (uint32_t)(b >> 32) : below_hi;
-      }
-    };
-    look();
-    for (int gl = 0; gl < here && !stopped;) {
-      const int k0 = (gl * G) >> 6;                    // the span's first mask
-      uint32_t any = 0;
-#pragma unroll
-      for (int m = 0; m < kMasksPerSpan; ++m)
-        any |= (uint32_t)__builtin_amdgcn_readlane((int)below_lo, k0 + m) |
-               (uint32_t)__builtin_amdgcn_readlane((int)below_hi, k0 + m);
-      const int n_here = min(kGroupsPerSpan, here - gl);
-      if (any == 0) {
-#pragma unroll
-        for (int m = 0; m < kMasksPerSpan; ++m) {
-          const int t = c0 + (k0 + m) * 64 + lane;
-          if (t < c0 + (gl + n_here) * G) sel[t] = 0;
-        }
-        gl += n_here;
-        gi += n_here;
-        continue;
-      }
-      for (int g2 = 0; g2 < n_here && !stopped; ++g2) do_group(gl + g2, s_sc);
-      gl += n_here;
-    }
-  };
-  int buf = 0;
-  for (int c0 = 0; c0 < n_tok; c0 += kScoreChunk, buf ^= 1) {
-    if (wave == 0) {
-      compete_chunk(c0, s_buf[buf]);
-      if (stopped && lane == 0) s_stop[buf] = 1;
-    } else if (c0 + kScoreChunk < n_tok) {
-      score_chunk(c0 + kScoreChunk, s_buf[buf ^ 1], 1);
+    for (int k = 0; k < kPer; ++k) {
+      const int t = k * kCompeteThreads + tid;
+      m[k] = __ballot(t < here && f[k]);
+      if (lane == 0) L.mask[k * kCompeteWaves + wave] = m[k];
     }
     __syncthreads();
-    if (s_stop[buf]) break;                            // (written before the barrier; the slot is not written again
-                                                       // before every wavefront has passed the next one)
+    const MaskRanks ranks(L.mask, kWindow / 64, lane);
+    auto rank_of = [&](int k) -> int {
+      return ((m[k] >> lane) & 1ull) ? ranks.before(k * kCompeteWaves + wave) + __popcll(m[k] & below) : kWindow;
+    };
+    int n = ranks.total, next = t0 + here;
+    if (n > kSegment) {                                // uniform
+      if (tid == 0) L.cut_rank = L.cut_at = kWindow;
+#pragma unroll
+      for (int k = 0; k < kPer; ++k)
+        if (rank_of(k) == kSegment) L.cut_group = (t0 + k * kCompeteThreads + tid) >> kGroupShift;
+      __syncthreads();
+      const int cut = L.cut_group;
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int t = k * kCompeteThreads + tid, r = rank_of(k);
+        if (r < kWindow && ((t0 + t) >> kGroupShift) >= cut) {
+          atomicMin(&L.cut_rank, r);
+          atomicMin(&L.cut_at, t);
+        }
+      }
+      __syncthreads();
+      n = min(L.cut_rank, kSegment);
+      next = t0 + L.cut_at;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int t = k * kCompeteThreads + tid, r = rank_of(k);
+      if (r < n) {
+        L.idx[r] = t0 + t;
+        sel[t0 + t] = 0;                               // the selected ones are flagged again at the end
+      }
+    }
+    __syncthreads();
+    score_rows(n, tid, [&](int e) { return kr + (int64_t)L.idx[e] * kHeadDim; },
+               [&](int e, double sc) {
+                 L.key[e] = competition_key(sc, e + 1);
+                 L.coarse[e] = coarse_score(sc);
+               });
+    __syncthreads();
+    prefix_bounds(L.coarse, n, N, L.bound, wave, lane);
+    __syncthreads();
+    const bool may = may_be_selected<G>(L.coarse, L.bound, n, tid, L.idx[tid], [&](int p) { return L.idx[p]; });
+    // ---- select among them
+    int pos = 0;
+    while (pos < n && !stopped) {
+      const int nr = compete_round<G>(L, n, may, pos, N, P, cur, tid);
+      // The round's selected tokens join the list.  With token k of the list (from 0), min(N, tokens so far)
+      // of k + 1 are in the pool; the others have fallen out and must fit in the auxiliary pool.
+      // (every wavefront works this out for itself: lane = entries lane, 64 + lane of the round)
+      const bool c0 = lane < nr && L.r_sel[lane], c1 = 64 + lane < nr && L.r_sel[64 + lane];
+      const int i0 = L.r_idx[lane], i1 = L.r_idx[64 + lane];
+      const u64 b0 = __ballot(c0), b1 = __ballot(c1);
+      const int k0 = S + __popcll(b0 & below), k1 = S + __popcll(b0) + __popcll(b1 & below);
+      const u64 o0 = __ballot(c0 && k0 + 1 - min(N, (i0 | (G - 1)) + 1) > A);
+      const u64 o1 = __ballot(c1 && k1 + 1 - min(N, (i1 | (G - 1)) + 1) > A);
+      u64 t0m = b0, t1m = b1;
+      if (o0 | o1) {                                   // uniform: tracing stops at the first group that overflows
+        const int first = o0 ? __builtin_amdgcn_readlane(i0, __ffsll((long long)o0) - 1)
+                             : __builtin_amdgcn_readlane(i1, __ffsll((long long)o1) - 1);
+        const int start = first & ~(G - 1);
+        t0m = __ballot(c0 && i0 < start);
+        t1m = __ballot(c1 && i1 < start);
+        stopped = true;
+      }
+      if (wave == 0 && c0) {
+        s_key[k0] = (L.r_key[lane] & ~kPlaceMask) | (u64)k0;
+        s_idx[k0] = i0;
+      }
+      if (wave == 1 && c1) {
+        s_key[k1] = (L.r_key[64 + lane] & ~kPlaceMask) | (u64)k1;
+        s_idx[k1] = i1;
+      }
+      S += __popcll(t0m) + __popcll(t1m);
+    }
+    t0 = next;
   }
-  if (wave != 0) return;
-  for (int i = gi * G + lane; i < n_tok; i += 64) sel[i] = 0;      // groups after the stop select nothing
-  // lane 0's writes of the auxiliary list, read by the other lanes below
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  // the unit's state
+  for (int t = t0 + tid; t < n_tok; t += kCompeteThreads) sel[t] = 0;   // after the stop nothing is selected
+  __syncthreads();
+  // ---- the S selected tokens (at most N + A): pool, ascending by key, or auxiliary pool, in the order they
+  // fall out (by group; inside a group the largest key first).  One wavefront per token, lane = the others.
+  u64 os[2];
+  int oi[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = 64 * h + lane;
+    os[h] = e < S ? s_key[e] : ~0ull;
+    oi[h] = e < S ? s_idx[e] : 0;
+  }
+  for (int e = wave; e < S; e += kCompeteWaves) {
+    const u64 es = s_key[e];
+    const int ei = s_idx[e];
+    const u64 b0 = __ballot(os[0] < es), b1 = __ballot(os[1] < es);
+    const int rank = __popcll(b0) + __popcll(b1);
+    int out = kStays;
+    if (rank >= N) {                                   // the N-th smaller key, in token order, displaces it
+      const u64 n0 = __ballot(((b0 >> lane) & 1ull) && __popcll(b0 & below) == N - 1);
+      const u64 n1 = __ballot(((b1 >> lane) & 1ull) && __popcll(b0) + __popcll(b1 & below) == N - 1);
+      out = (n0 ? __builtin_amdgcn_readlane(oi[0], __ffsll((long long)n0) - 1)
+                : __builtin_amdgcn_readlane(oi[1], __ffsll((long long)n1) - 1)) >> kGroupShift;
+    } else if (lane == 0) {
+      slot_idx[rank] = ei;
+    }
+    if (lane == 0) {
+      s_out[e] = out;
+      sel[ei] = 1;
+    }
+  }
+  __syncthreads();
+  const int in_pool = min(N, S), aux_n = S - in_pool;
+  if (aux_n > 0) {
+    const int out0 = lane < S ? s_out[lane] : kStays, out1 = 64 + lane < S ? s_out[64 + lane] : kStays;
+    for (int e = wave; e < S; e += kCompeteWaves) {
+      const int out = s_out[e];
+      if (out == kStays) continue;
+      const u64 es = s_key[e];
+      const u64 b0 = __ballot(out0 != kStays && (out0 < out || (out0 == out && es < os[0])));
+      const u64 b1 = __ballot(out1 != kStays && (out1 < out || (out1 == out && es < os[1])));
+      if (lane == 0) slot_idx[in_pool + __popcll(b0) + __popcll(b1)] = s_idx[e];
+    }
+    __syncthreads();
+  }
+  // the unit's state, and the members' rows bit for bit from the prompt: 16 lanes per row
   const int64_t slot0 = u * d.pool_slots;
-  if (lane < P) {
-    pool_idx[slot0 + lane] = pi;
-    pool_score[slot0 + lane] = ps;
-  }
-  if (lane < aux_n) {
-    pool_idx[slot0 + N + lane] = s_aux_idx[lane];
-    pool_score[slot0 + N + lane] = s_aux_score[lane];
-  }
-  if (lane == 0) {
-    pool_count[u] = P;
+  if (tid == 0) {
+    pool_count[u] = in_pool;
     aux_count[u] = aux_n;
     frozen[u] = stopped ? 1 : 0;
   }
-  // (3) the members' rows, bit for bit, from the prompt: 4 bytes per lane and row
-  const uint32_t* kr = (const uint32_t*)(k_rows + (int64_t)ul * unit_stride);
-  const uint32_t* vr = (const uint32_t*)(v_rows + (int64_t)ul * unit_stride);
-  uint32_t* pk = (uint32_t*)(pool_k + slot0 * kHeadDim);
-  uint32_t* pv = (uint32_t*)(pool_v + slot0 * kHeadDim);
-  // (eight rows' loads in flight at a time; a row's destination is its slot)
-  const int n_rows = P + aux_n;
-  for (int j0 = 0; j0 < n_rows; j0 += 8) {
-    uint32_t kw[8], vw[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int j = min(j0 + q, n_rows - 1);
-      const int idx = j < P ? __builtin_amdgcn_readlane(pi, min(j, 63)) : s_aux_idx[max(j - P, 0)];
-      const int64_t src = (int64_t)idx * (kHeadDim / 2) + lane;
-      kw[q] = kr[src];
-      vw[q] = vr[src];
+  for (int j = tid >> 4; j < S; j += kCompeteThreads / 16) {
+    const int sub = tid & 15, idx = slot_idx[j];
+    const int64_t slot = slot0 + (j < in_pool ? j : N + (j - in_pool));
+    const uint4 kw = *(const uint4*)(kr + (int64_t)idx * kHeadDim + sub * 8);
+    const uint4 vw = *(const uint4*)(vr + (int64_t)idx * kHeadDim + sub * 8);
+    const double sc = trace_core::team_sum_f64(trace_core::abs_sum8(kw));
+    if (sub == 0) {
+      pool_idx[slot] = idx;
+      pool_score[slot] = sc;
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int j = j0 + q;
-      if (j < n_rows) {
-        const int slot = j < P ? j : N + (j - P);
-        pk[slot * (kHeadDim / 2) + lane] = kw[q];
-        pv[slot * (kHeadDim / 2) + lane] = vw[q];
-      }
-    }
+    *(uint4*)(pool_k + slot * kHeadDim + sub * 8) = kw;
+    *(uint4*)(pool_v + slot * kHeadDim + sub * 8) = vw;
   }
 }
 
@@ -308,15 +476,20 @@ __global__ void __launch_bounds__(64 * kTraceWaves) prefill_trace_kernel(
 
 hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const __half* k_rows, const __half* v_rows,
                                 int64_t unit_stride, const kvq_pool& pool, uint8_t* selected, hipStream_t s) {
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(d.units_per_layer), dim3(64 * kTraceWaves), 0, s, d, n_groups, k_rows, v_rows, unit_stride,
-                       (__half*)pool.pool_k, (__half*)pool.pool_v, pool.pool_idx, pool.pool_score, pool.pool_count,
-                       pool.aux_count, pool.frozen, selected);
+  const int32_t n_tok = n_groups * d.G;
+  const int32_t flagged = d.N > 0 && n_tok > kSegment;   // (one segment: a launch of its own for the flags gains nothing)
+  auto go = [&](auto candidates, auto compete) {
+    if (flagged)
+      hipLaunchKernelGGL(candidates, dim3(d.units_per_layer, (n_tok + kSegment - 1) / kSegment), dim3(kCompeteThreads), 0,
+                         s, d, n_tok, k_rows, unit_stride, selected);
+    hipLaunchKernelGGL(compete, dim3(d.units_per_layer), dim3(kCompeteThreads), 0, s, d, n_tok, flagged, k_rows, v_rows,
+                       unit_stride, (__half*)pool.pool_k, (__half*)pool.pool_v, pool.pool_idx, pool.pool_score,
+                       pool.pool_count, pool.aux_count, pool.frozen, selected);
   };
   switch (d.G) {
-    case 32: go(prefill_trace_kernel<32>); break;
-    case 64: go(prefill_trace_kernel<64>); break;
-    default: go(prefill_trace_kernel<128>); break;
+    case 32: go(prompt_candidates_kernel<32>, prompt_compete_kernel<32>); break;
+    case 64: go(prompt_candidates_kernel<64>, prompt_compete_kernel<64>); break;
+    default: go(prompt_candidates_kernel<128>, prompt_compete_kernel<128>); break;
   }
   return hipGetLastError();
 }

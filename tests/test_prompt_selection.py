@@ -1,0 +1,63 @@
+"""Which tokens of a prompt are selected when all groups compete at once: flags, pools, counts and the stop
+rule against the oracle's group-by-group competition, at the places where the split of the work can go wrong."""
+import numpy as np
+import pytest
+
+from oracle import kvq_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+def keys(pattern, n, rng):
+    """fp16 [n, 128] Key rows."""
+    x = rng.standard_normal((n, 128))
+    t = np.arange(n)[:, None]
+    if pattern == "falling":                     # every token beats all before it: the first groups fill the pools
+        x *= np.linspace(40.0, 1.0, n)[:, None]
+    elif pattern == "rising":
+        x *= np.linspace(1.0, 40.0, n)[:, None]
+    elif pattern == "equal":                     # the token index decides everywhere
+        x = np.repeat(rng.standard_normal((1, 128)), n, 0)
+    elif pattern == "late":                      # the second half lies far below the first: every one of its tokens
+        x *= np.where(t < n // 2, 1.0, 0.01)     # is let through the first look
+    elif pattern == "saw":                       # falls inside every stretch of 200 tokens
+        x *= 1.0 + (199 - t % 200) / 50.0
+    elif pattern == "teeth":                     # falls inside every segment of 1024 tokens, all above the first one:
+        x *= np.where(t < 1024, 1.0, 40.0 - (t % 1024) / 50.0)   # thousands are let through, few are selected
+    return x.astype(np.float16)
+
+
+@pytest.mark.parametrize("pattern", ["noise", "falling", "rising", "equal", "late", "saw", "teeth"])
+@pytest.mark.parametrize("G,N,A,n", [
+    (32, 8, 32, 1024), (32, 8, 32, 1056), (128, 64, 64, 1024 + 128), (64, 1, 0, 2048), (32, 64, 64, 8192 + 32),
+    (128, 3, 64, 8192 + 1024 + 128), (32, 8, 64, 32), (32, 33, 7, 96),
+])
+def test_selection_of_a_prompt_equals_the_group_by_group_competition(G, N, A, n, pattern):
+    import torch
+    from paper_2505_10938_amd import cache as KC
+    heads = 2
+    rng = np.random.default_rng(n + N)
+    K = np.stack([keys(pattern, n, rng) for _ in range(heads)])
+    V = rng.standard_normal((heads, n, 128)).astype(np.float16)
+    cache = KC.KVCache(KC.make_config(1, 1, heads, heads, n, 2, G, 128, 0, N, A))
+    cache.prefill(0, torch.from_numpy(K)[None].cuda(), torch.from_numpy(V)[None].cuda())
+    torch.cuda.synchronize()
+    flags = cache.prefill_selected.cpu().numpy().reshape(-1)[:heads * n].reshape(heads, n)
+    slots = N + A
+    idx = cache.pool_idx.view(torch.int32).cpu().numpy()[:heads * slots].reshape(heads, slots)
+    score = cache.pool_score.view(torch.float64).cpu().numpy()[:heads * slots].reshape(heads, slots)
+    pk = cache.pool_k.view(torch.float16).cpu().numpy()[:heads * slots * 128].reshape(heads, slots, 128)
+    pv = cache.pool_v.view(torch.float16).cpu().numpy()[:heads * slots * 128].reshape(heads, slots, 128)
+    counts = [t.view(torch.int32).cpu().numpy()[:heads] for t in (cache.pool_count, cache.aux_count, cache.frozen)]
+    for h in range(heads):
+        st = O.UnitState(128, 2, G, 128, N, A)
+        want = np.concatenate([st.trace(K[h, i:i + G], V[h, i:i + G], i // G) for i in range(0, n, G)])
+        assert np.array_equal(flags[h], want.astype(np.uint8))
+        assert [c[h] for c in counts] == [len(st.pool), len(st.aux), int(st.frozen)]
+        for at, members in ((0, st.pool), (N, st.aux)):
+            m = len(members)
+            assert sorted(idx[h, at:at + m]) == sorted(x["idx"] for x in members)
+            rows = idx[h, at:at + m]
+            assert np.array_equal(score[h, at:at + m], O.l1_scores(K[h])[rows])
+            assert np.array_equal(pk[h, at:at + m].view(np.uint16), K[h][rows].view(np.uint16))
+            assert np.array_equal(pv[h, at:at + m].view(np.uint16), V[h][rows].view(np.uint16))
