@@ -36,7 +36,9 @@ namespace kvq {
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRowBytes = 272;   // LDS row of 128 fp16 + 16 bytes of padding (bank spread)
@@ -597,13 +599,43 @@ __device__ __forceinline__ void compute_minichunk(McRegs<BITS, NV>& R, WaveAcc<G
   if (more) load_codes<BITS>(R.vc, P.vc, P, mc_next, lane);
 }
 
-// Full-precision rows (residual ring, then outlier-pool slots, then auxiliary slots) in groups of
-// 16: q.k^T on the matrix cores (a K row is a B operand as it is), the weighted values on the
-// vector units (row-major V has the wrong operand shape).  Lane = channel pair for the values.
+// Full-precision rows (residual ring, then outlier-pool slots, then auxiliary slots) in groups of 16, both
+// products on the matrix cores: a K row is a B operand as it is; of the V rows a lane (m16, r) loads channels
+// 8 m16 .. 8 m16 + 7 of rows 4r .. 4r + 3, which are its share of the B operands of eight 16x16x16 products if
+// product e is given the channels 8n + e.  Row pair i of a result is that of head 2 (r % (GQ/2)) + i (one head:
+// of that one), for scores and weighted values alike, so the statistics of a lane's heads stay in the lane.
 template <int GQ>
 struct FpAcc {
-  float m[GQ], l[GQ];
-  float o[GQ][2];
+  float m[2], l[2];      // of the lane's two heads
+  float4v o[8];          // weighted values: column m16 of product e = channel 8 m16 + e
+};
+// The same, each value held by one lane only: what is kept while the quantized tokens are worked on.
+template <int GQ>
+struct FpResult {
+  static constexpr int kHeads = GQ == 1 ? 1 : 2;                     // heads per lane
+  static constexpr int kRowsOfHeads = GQ <= 2 ? 1 : GQ / 2;          // values of r that differ in their heads
+  static constexpr int kTiles = 2 * kRowsOfHeads;                    // channels kept per lane and head
+  float m[2], l[2];
+  float o[kHeads][kTiles];
+  static __device__ __forceinline__ int head(int r, int i) { return 2 * (r % kRowsOfHeads) + i; }
+  static __device__ __forceinline__ int first_tile(int r) { return kTiles * (r / kRowsOfHeads); }
+  __device__ __forceinline__ void take(const FpAcc<GQ>& F, int r) {
+#pragma unroll
+    for (int i = 0; i < kHeads; ++i) {
+      m[i] = F.m[i];
+      l[i] = F.l[i];
+#pragma unroll
+      for (int k = 0; k < kTiles; ++k) {
+        float v = F.o[k][2 * i] + F.o[k][2 * i + 1];
+#pragma unroll
+        for (int part = 1; part < 8 / kTiles; ++part) {
+          const float other = F.o[part * kTiles + k][2 * i] + F.o[part * kTiles + k][2 * i + 1];
+          v = r / kRowsOfHeads == part ? other : v;
+        }
+        o[i][k] = v;
+      }
+    }
+  }
 };
 
 // The state of the sequence a workgroup works on: the batch's (kernel arguments), or its own.
@@ -614,7 +646,7 @@ struct Seq {
 
 struct FpRegs {
   uint4 kf[4];       // K row of token first + (lane & 15): channels 32cb + 8(lane >> 4) ..
-  uint32_t vw[16];   // V rows of the 16 tokens: this lane's channel pair
+  u32x4 vf[4];       // V rows of tokens first + 4(lane >> 4) + i: channels 8(lane & 15) ..
   int group;
 };
 
@@ -663,10 +695,9 @@ __device__ __forceinline__ void fp_load(FpRegs& X, const DecodeArgs& a, const Se
   const unsigned char* kp = is_new ? (const unsigned char*)k_new_row + r * 16 : kb + m16 * (2 * kHeadDim) + r * 16;
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb) X.kf[cb] = ld<uint4>(kp, cb * 64u);
-  // Values: every lane its channel pair of each of the 16 rows
-  const unsigned char* vp = vb + lane * 4;
+  const unsigned char* vp = vb + r * (4 * 2 * kHeadDim) + m16 * 16;
 #pragma unroll
-  for (int t = 0; t < 16; ++t) X.vw[t] = ld<uint32_t>(vp, t * (2u * kHeadDim));
+  for (int i = 0; i < 4; ++i) X.vf[i] = __builtin_nontemporal_load((const u32x4*)(vp + i * (2u * kHeadDim)));
 }
 
 // Does row m16 of group g hold a token?
@@ -684,12 +715,17 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
   const int m16 = lane & 15, r = lane >> 4;
   const bool okk = fp_row_ok(a, sq, f, X.group, m16, n_pool, n_aux);
   if (X.group == f.new_group) {                                    // uniform, one group of the unit
+    // The token that comes with the call: its Value row is not in the ring yet, and a Key row that the launch
+    // rotates exists as one word per lane only (channels 2*lane, 2*lane + 1).  The lanes that own a piece of
+    // the row take its words from the lanes that hold them.
 #pragma unroll
-    for (int t = 0; t < 16; ++t) X.vw[t] = t == f.new_t ? v_new_word : X.vw[t];
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t v = (uint32_t)__shfl((int)v_new_word, 4 * m16 + k);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) X.vf[i][k] = 4 * r + i == f.new_t ? v : X.vf[i][k];
+    }
     if constexpr (ROPE) {
-      // The new Key row was loaded as the caller gave it; the rotated one exists as one word per lane
-      // (channels 2*lane, 2*lane + 1).  The lanes that own the row take their 16-byte pieces (channels
-      // 32 cb + 8 r ..) from the lanes that hold them: words 16 cb + 4 r .. + 3.
+      // pieces of 16 bytes (channels 32 cb + 8 r ..): words 16 cb + 4 r .. + 3
       const bool mine = m16 == f.new_t;
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) {
@@ -712,54 +748,75 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
   // which of the 16 rows hold a token, as a wave-uniform bit mask (lanes 0..15 are rows 0..15)
   const uint32_t ok_rows = (uint32_t)__ballot(okk) & 0xFFFFu;
   constexpr int R2 = 2 * GQ;
+  constexpr int kHeads = FpResult<GQ>::kHeads;
   const int arow = m16 % R2;
   float4v D = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
     D = __builtin_amdgcn_mfma_f32_16x16x32_f16(lds_operand(L.q0[arow], cb * 64 + r * 16),
                                                 __builtin_bit_cast(half8, X.kf[cb]), D, 0, 0, 0);
-  wave_sync();                                                     // earlier readers of sc are done
-  if (2 * r < GQ) L.sc()[2 * r][m16] = seen_by(2 * r) ? D[0] + D[1] : kNegBig;
-  if (2 * r + 1 < GQ) L.sc()[(2 * r + 1) % GQ][m16] = seen_by(2 * r + 1) ? D[2] + D[3] : kNegBig;
-  // a row that holds no token may hold anything, a NaN too: its Value words are cleared (most groups are
+  // a row that holds no token may hold anything, a NaN too: its Values are cleared (most groups are
   // full: one uniform test)
   if (ok_rows != 0xFFFFu) {
 #pragma unroll
-    for (int t = 0; t < 16; ++t) X.vw[t] = ((ok_rows >> t) & 1u) ? X.vw[t] : 0u;
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t keep = ((ok_rows >> (4 * r + i)) & 1u) ? ~0u : 0u;
+      X.vf[i] &= keep;
+    }
   }
-  wave_sync();
-  float alpha[GQ], x[GQ], red[GQ];
+  // scores of token m16 for the lane's heads, their maxima and sums over the row of 16 lanes
+  float x[kHeads], red[kHeads];
+  bool above = false;
 #pragma unroll
-  for (int j = 0; j < GQ; ++j) red[j] = x[j] = L.sc()[j][m16];      // every row of 16 lanes: the 16 scores
-  row16_max(red);
+  for (int i = 0; i < kHeads; ++i) {
+    const float s = D[2 * i] + D[2 * i + 1];
+    red[i] = x[i] = seen_by(FpResult<GQ>::head(r, i)) ? s : kNegBig;
+    above |= x[i] > F.m[i];
+  }
+  if (__any(above)) {                                              // wave-uniform
+    row16_max(red);
+    float alpha[2] = {1.f, 1.f};
 #pragma unroll
-  for (int j = 0; j < GQ; ++j) {
-    const float m = fmaxf(F.m[j], red[j]);
-    alpha[j] = __builtin_amdgcn_exp2f(F.m[j] - m);
-    F.m[j] = m;
-    x[j] = x[j] > 0.5f * kNegBig ? __builtin_amdgcn_exp2f(x[j] - m) : 0.f;   // now p
-    red[j] = x[j];
-    if (lane < 16) L.sc()[j][16 + lane] = x[j];
+    for (int i = 0; i < kHeads; ++i) {
+      const float m = fmaxf(F.m[i], red[i]);
+      alpha[i] = __builtin_amdgcn_exp2f(F.m[i] - m);
+      F.m[i] = m;
+      F.l[i] *= alpha[i];
+    }
+    if (kHeads == 1) alpha[1] = alpha[0];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      F.o[e][0] *= alpha[0];
+      F.o[e][1] *= alpha[0];
+      F.o[e][2] *= alpha[1];
+      F.o[e][3] *= alpha[1];
+    }
+  }
+  _Float16* prow = (_Float16*)&L.sc()[0][0];                       // p of the 16 tokens, [hi, lo of every head][16]
+  wave_sync();                                                     // earlier readers are done
+#pragma unroll
+  for (int i = 0; i < kHeads; ++i) {
+    const float p = x[i] > 0.5f * kNegBig ? __builtin_amdgcn_exp2f(x[i] - F.m[i]) : 0.f;
+    red[i] = p;
+    const _Float16 hi = (_Float16)p;
+    if (r < FpResult<GQ>::kRowsOfHeads) {
+      const int j = FpResult<GQ>::head(r, i);
+      prow[(2 * j) * 16 + m16] = hi;
+      prow[(2 * j + 1) * 16 + m16] = (_Float16)(p - (float)hi);
+    }
   }
   row16_sum(red);
 #pragma unroll
-  for (int j = 0; j < GQ; ++j) F.l[j] = F.l[j] * alpha[j] + red[j];
+  for (int i = 0; i < kHeads; ++i) F.l[i] += red[i];
   wave_sync();
+  const half4 ap = *(const half4*)(prow + arow * 16 + 4 * r);
 #pragma unroll
-  for (int j = 0; j < GQ; ++j) {
-    F.o[j][0] *= alpha[j];
-    F.o[j][1] *= alpha[j];
-  }
-  // (newest row first: loads return in order, so the wait for the last row's word covers all of them)
-#pragma unroll
-  for (int t = 15; t >= 0; --t) {
-    const float v0 = h2f_bits(X.vw[t] & 0xFFFFu), v1 = h2f_bits(X.vw[t] >> 16);
-#pragma unroll
-    for (int j = 0; j < GQ; ++j) {
-      const float p = L.sc()[j][16 + t];
-      F.o[j][0] += p * v0;
-      F.o[j][1] += p * v1;
-    }
+  for (int e = 0; e < 8; ++e) {
+    constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;    // the low / high halves of two words
+    u32x2 v;
+    v[0] = __builtin_amdgcn_perm(X.vf[1][e >> 1], X.vf[0][e >> 1], (e & 1) ? kHigh : kLow);
+    v[1] = __builtin_amdgcn_perm(X.vf[3][e >> 1], X.vf[2][e >> 1], (e & 1) ? kHigh : kLow);
+    F.o[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(ap, __builtin_bit_cast(half4, v), F.o[e], 0, 0, 0);
   }
 }
 
@@ -930,11 +987,12 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   // ---- full-precision part, while the first quantized loads are in flight --------------------------
   FpAcc<GQ> F;
 #pragma unroll
-  for (int j = 0; j < GQ; ++j) {
-    F.m[j] = kNegBig;
-    F.l[j] = 0.f;
-    F.o[j][0] = F.o[j][1] = 0.f;
+  for (int i = 0; i < 2; ++i) {
+    F.m[i] = kNegBig;
+    F.l[i] = 0.f;
   }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) F.o[e] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < GQ; ++j) {                         // the query rows, for both parts
     uint32_t hi, lo;
@@ -952,6 +1010,9 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
       fp_compute<GQ, NV, ROPE>(X, F, L, a, sq, fl, n_pool, n_aux, r0, k_new_word, v_new_word, lane);
     }
   }
+
+  FpResult<GQ> fp;
+  fp.take(F, r);
 
   WaveAcc<GQ> S;
 #pragma unroll
@@ -1023,13 +1084,19 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
     }
   }
 #pragma unroll
-  for (int j = 0; j < GQ; ++j) {
-    *(float2*)&mg.o[((nw + wave) * GQ + j) * kHeadDim + 2 * lane] = float2{F.o[j][0], F.o[j][1]};
-    if (lane == 0) {
-      mg.m[wave * GQ + j] = S.m[j];
-      mg.m[(nw + wave) * GQ + j] = F.m[j];
-      mg.l[(nw + wave) * GQ + j] = F.l[j];
+  for (int i = 0; i < FpResult<GQ>::kHeads; ++i) {
+    const int j = FpResult<GQ>::head(r, i);
+    float* row = &mg.o[((nw + wave) * GQ + j) * kHeadDim + 8 * m16 + FpResult<GQ>::first_tile(r)];
+#pragma unroll
+    for (int k = 0; k < FpResult<GQ>::kTiles; k += 2) *(float2*)(row + k) = float2{fp.o[i][k], fp.o[i][k + 1]};
+    if (m16 == 0 && r < FpResult<GQ>::kRowsOfHeads) {
+      mg.m[(nw + wave) * GQ + j] = fp.m[i];
+      mg.l[(nw + wave) * GQ + j] = fp.l[i];
     }
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int j = 0; j < GQ; ++j) mg.m[wave * GQ + j] = S.m[j];
   }
 
   // ---- merge the 2 nw results: the output itself if this workgroup is the unit's only one, else its partial
