@@ -139,6 +139,18 @@ KVQ_WAVE_REDUCE8(wave_sum)
 KVQ_ROW_REDUCE(row16_max, "v_max_f32_dpp")
 KVQ_ROW_REDUCE(row16_sum, "v_add_f32_dpp")
 
+// The value of lane l of the own row of 16 lanes (l: a constant after unrolling).
+__device__ __forceinline__ float row16_lane(float v, int l) {
+  const int w = __builtin_bit_cast(int, v);
+  switch (l) {
+#define KVQ_LANE(N) case N: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, w, 0x150 + N /* row_newbcast */, 0xf, 0xf, false));
+    KVQ_LANE(0) KVQ_LANE(1) KVQ_LANE(2) KVQ_LANE(3) KVQ_LANE(4) KVQ_LANE(5) KVQ_LANE(6) KVQ_LANE(7)
+    KVQ_LANE(8) KVQ_LANE(9) KVQ_LANE(10) KVQ_LANE(11) KVQ_LANE(12) KVQ_LANE(13) KVQ_LANE(14) KVQ_LANE(15)
+#undef KVQ_LANE
+  }
+  return v;
+}
+
 // fp16 hi/lo split of two floats: hi = fp16(x), lo = fp16(x - hi), both rounded to nearest, so that
 // hi + lo = x (1 + e) with |e| <= 2^-22 and no bias (truncating hi instead leaves 2^-21, one-sided);
 // packed pairs.
@@ -1103,32 +1115,57 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   __syncthreads();
   const int64_t part_slot0 = part_first >= 0 ? part_first : (int64_t)wl * n_splits;
   float* part_out = a.partials + (part_slot0 + split) * GQ * (kHeadDim + 2);
-  for (int i = tid; i < GQ * kHeadDim; i += nthreads) {
-    const int j = i / kHeadDim, c = i % kHeadDim;
-    const int jv = c / (kHeadDim / NV);
-    float m = kNegBig;
-    for (int w = 0; w < 2 * nw; ++w) m = fmaxf(m, mg.m[w * GQ + j]);
-    float o = 0.f, l = 0.f;
-    for (int w = 0; w < nw; ++w) {                       // quantized parts carry their zero-point sums
-      const float f = __builtin_amdgcn_exp2f(mg.m[w * GQ + j] - m);
-      o += (mg.o[(w * GQ + j) * kHeadDim + c] + mg.z[(w * GQ + j) * NV + jv]) * f;
-      l += mg.l[w * GQ + j] * f;
-    }
-    for (int w = nw; w < 2 * nw; ++w) {
-      const float f = __builtin_amdgcn_exp2f(mg.m[w * GQ + j] - m);
-      o += mg.o[(w * GQ + j) * kHeadDim + c] * f;
-      l += mg.l[w * GQ + j] * f;
-    }
-    if (n_splits == 1) {
-      a.out[row_elem(j) + c] = __float2half_rn(l > 0.f ? o / l : 0.f);
-    } else {
-      coherent_store(&part_out[j * (kHeadDim + 2) + 2 + c], o);
-      if (c == 0) {
+  // Thread = C channels of one row.  All values are asked for at once; meanwhile the weights of the results
+  // (lane & 15 = result) are formed inside rows of 16 lanes and handed round there.  What bounds it is the chain
+  // of LDS latencies; a loop over the results took one per result: 16 sequences of 301 .. 340 tokens 945 -> 920 us for 40 steps, a ragged batch 108.5 -> 104.6 us, one sequence
+  // of 4k 370 -> 361 us, batch 128 85.4 -> 84.1 us.  C: few enough channels that the threads suffice for all rows
+  // in about one pass, so that the copies of the weights' arithmetic are few as well (with eight wavefronts and
+  // four rows, C = 1 / 2 / 4: 940 / 911 / 912 us in the first workload; one row, C = 1 / 4: 361 / 376 us for one
+  // sequence of 4k).
+  auto merge_rows = [&](auto channels, auto slots) {
+    constexpr int C = decltype(channels)::value;
+    constexpr int SLOTS = decltype(slots)::value;          // at least the 2 nw results
+    typedef float floatc __attribute__((ext_vector_type(C)));
+    for (int i = tid; i < GQ * kHeadDim / C; i += nthreads) {
+      const int j = i / (kHeadDim / C), c = C * (i % (kHeadDim / C));
+      const int jv = c / (kHeadDim / NV);
+      const int slot = min(m16, 2 * nw - 1);
+      const float own = mg.m[slot * GQ + j], own_l = mg.l[slot * GQ + j];
+      floatc v[SLOTS];
+      float z[SLOTS / 2];
+#pragma unroll
+      for (int w = 0; w < SLOTS; ++w) v[w] = *(const floatc*)&mg.o[(min(w, 2 * nw - 1) * GQ + j) * kHeadDim + c];
+#pragma unroll
+      for (int w = 0; w < SLOTS / 2; ++w) z[w] = mg.z[(min(w, nw - 1) * GQ + j) * NV + jv];
+      float red[1] = {own};
+      row16_max(red);
+      const float m = red[0];
+      const float f = m16 < 2 * nw ? __builtin_amdgcn_exp2f(own - m) : 0.f;
+      floatc o = 0.f;
+      float l = 0.f;
+      // one result after the other: what has no part in the output (weight 0) does not change a bit of it,
+      // however many wavefronts there are
+#pragma unroll
+      for (int w = 0; w < SLOTS; ++w) {
+        const float wt = row16_lane(f, w);
+        if (w < SLOTS / 2) v[w] += w < nw ? z[w] : 0.f;    // quantized parts carry their zero-point sums
+        o += v[w] * wt;
+        l += row16_lane(own_l, w) * wt;
+      }
+#pragma unroll
+      for (int e = 0; e < C; ++e) {
+        if (n_splits == 1) a.out[row_elem(j) + c + e] = __float2half_rn(l > 0.f ? o[e] / l : 0.f);
+        else coherent_store(&part_out[j * (kHeadDim + 2) + 2 + c + e], o[e]);
+      }
+      if (n_splits > 1 && c == 0) {
         coherent_store(&part_out[j * (kHeadDim + 2) + 0], m);
         coherent_store(&part_out[j * (kHeadDim + 2) + 1], l);
       }
     }
-  }
+  };
+  if (nw <= 2) merge_rows(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+  else if (GQ > 1 && nw <= 4) merge_rows(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
+  else merge_rows(std::integral_constant<int, (GQ >= 4 ? 2 : 1)>{}, std::integral_constant<int, 16>{});
   if (n_splits == 1) return;
 
   // ---- the last workgroup of the unit to arrive merges the unit's partials ---------------------------
