@@ -37,32 +37,87 @@ int64_t res_rows_of(const kvq_config* c) {
   return G * ((c->residual + G + G - 1) / G);
 }
 
-// Split of one unit's decode work over wavefronts and workgroups.  Quantized tokens go in
-// mini-chunks of 128 (one wavefront each at a time), full-precision rows in groups of 16 that cost
-// about half a mini-chunk.  As many wavefronts are wanted over the whole launch as fit on the chip
-// at once (2 per SIMD by registers, fewer if a wavefront's LDS were larger), no more per unit than
-// it has items; they form as few workgroups as fit (one workgroup per unit needs no exchange
-// through memory).
+// Split of one unit's decode work over workgroups and wavefronts.  Quantized tokens go in mini-chunks of 128
+// (one wavefront each at a time), full-precision rows in groups of 16 that cost about half a mini-chunk.
+// The launch is to be resident as a whole: a compute unit holds 8 wavefronts (2 per SIMD by registers, fewer if
+// a wavefront's LDS were larger) and whole workgroups only, so one of 5, 6 or 7 wavefronts has a compute unit to
+// itself and a launch of more than 256 of them runs in two rounds.  Workgroups are therefore sized for 8, 4, 2
+// or 1 wavefronts (kernel trace, context 4100, 4 rows: 224 units 2 x 5 wavefronts 41.6 us, 1 x 8 24.4; 120 units
+// 3 x 6 27.8, 2 x 8 18.1; 400 units 1 x 5 57.1, 1 x 4 40.1).
+//  - The largest size that fits is taken, unless a smaller one lets so many more wavefronts be resident that each
+//    has a mini-chunk less (148 units, 1 x 8 / 3 x 4: context 1100 13.6 / 14.3 us, 4100 22.1 / 21.0, 12000 47.8 /
+//    38.6; 184 units, 1 x 8 / 2 x 4, which are equally many: 4100 23.0 / 26.0).
+//  - One workgroup per unit needs no exchange through memory (about 2 us).  Up to 32 mini-chunks, several are
+//    taken so that each has at most four, one per SIMD, the other wavefronts taking the full-precision rows
+//    (context in mini-chunks: 64 units x 15 in 3 x 7 13.6 us, 4 x 8 11.3; 32 x 31, 8 rows, 5 x 8 15.8, 8 x 8 13.8;
+//    128 x 5, 1 x 8 13.1, 2 x 8 11.0; 128 x 2, 1 x 8 9.9, 2 x 8 12.1).  Beyond, at least eight, or as many as give
+//    each eight mini-chunks (the partial results of eight workgroups are merged in one pass: 8 units x 127, 32 x 8
+//    13.8 us, 16 x 8 13.2).  More than 24 groups of full-precision rows: as many as give each sixteen.
+//  - With four or more rows per unit the workgroups of a split unit have all their wavefronts (64 units x 15, 4 x
+//    4 / 6 / 7 / 8: 11.8 / 12.0 / 12.2 / 11.3 us), with fewer as many as there is work for, at least one per SIMD
+//    (32 x 31, one row, 8 x 4 / 5 / 6 / 8: 10.2 / 10.3 / 10.4 / 11.2 us).
 struct Split {
   int32_t splits, nw, mc_per_split;
 };
+// A unit has at most so many workgroups when a launch has more units than compute units: the partial results of
+// all (8 rows of 130 floats each) stay below 4 MiB, the size of the library's own scratch array.
+constexpr int64_t kMaxSplitWorkgroups = 960;
+int64_t waves_per_compute_unit(int g, int vgroups) {
+  int64_t w = kvq::kLdsPerComputeUnit / kvq::decode_wave_lds_bytes(g, vgroups);
+  const int64_t by_registers = 4 * kvq::kDecodeWavesPerSimd;
+  if (w > by_registers) w = by_registers;
+  return w < 1 ? 1 : w;
+}
+int64_t resident_workgroups(int64_t waves_per_cu, int64_t nw) { return kvq::kComputeUnits * (waves_per_cu / nw); }
 Split decode_split(int64_t units_per_layer, int g, int vgroups, int64_t n_quant, int64_t fp_rows) {
-  Split s;
   const int64_t mc = (n_quant + kvq::kMiniChunk - 1) / kvq::kMiniChunk;
   const int64_t rg = (fp_rows + kvq::kFpGroupRows - 1) / kvq::kFpGroupRows;
   int64_t items = mc + (rg + 1) / 2;
   if (items < 1) items = 1;
-  int64_t waves_per_cu = kvq::kLdsPerComputeUnit / kvq::decode_wave_lds_bytes(g, vgroups);
-  const int64_t by_registers = 4 * kvq::kDecodeWavesPerSimd;
-  if (waves_per_cu > by_registers) waves_per_cu = by_registers;
-  if (waves_per_cu < 1) waves_per_cu = 1;
-  int64_t wpu = kvq::kComputeUnits * waves_per_cu / units_per_layer;
-  if (wpu > items) wpu = items;
-  if (wpu < 1) wpu = 1;
-  s.splits = (int32_t)((wpu + waves_per_cu - 1) / waves_per_cu);
-  s.nw = (int32_t)((wpu + s.splits - 1) / s.splits);
-  s.mc_per_split = (int32_t)((mc + s.splits - 1) / s.splits);
+  const int64_t waves_per_cu = waves_per_compute_unit(g, vgroups);
+  int64_t best_splits = 1, best_nw = 1, best_load = -1;    // (not even one wavefront per unit fits: one each)
+  for (int64_t size = waves_per_cu; size >= 1; size >>= 1) {
+    int64_t fit = resident_workgroups(waves_per_cu, size) / units_per_layer;
+    if (fit < 1) continue;
+    if (best_load >= 0 && (size < 2 || (size < 4 && units_per_layer <= kvq::kComputeUnits))) break;
+    int64_t splits;
+    if (size == waves_per_cu) splits = mc <= 32 ? (mc + 3) / 4 : (mc + 7) / 8 > 8 ? (mc + 7) / 8 : 8;
+    else splits = (mc + size - 1) / size;
+    if (rg > 24 && splits < (rg + 15) / 16) splits = (rg + 15) / 16;
+    if (fit > 1 && fit * units_per_layer > kMaxSplitWorkgroups) fit = kMaxSplitWorkgroups / units_per_layer;
+    if (fit < 1) fit = 1;
+    if (splits > fit) splits = fit;
+    if (splits < 1) splits = 1;
+    // mini-chunks (with few of them: row groups) of the wavefront that has most
+    const int64_t most = mc >= rg ? (mc + splits - 1) / splits : (items + splits - 1) / splits;
+    const int64_t load = (most + size - 1) / size;
+    if (best_load >= 0 && load >= best_load) continue;
+    int64_t nw = (items + splits - 1) / splits;
+    if (splits > 1 && nw < 4) nw = 4;
+    if ((splits > 1 && g >= 4) || nw > size) nw = size;
+    best_load = load;
+    best_splits = splits;
+    best_nw = nw;
+  }
+  Split s;
+  s.splits = (int32_t)best_splits;
+  s.nw = (int32_t)best_nw;
+  s.mc_per_split = (int32_t)((mc + best_splits - 1) / best_splits);
   return s;
+}
+// The most workgroups per unit that decode_split gives up to n_quant tokens and fp_rows full-precision rows.
+int64_t most_splits(int64_t units_per_layer, int g, int vgroups, int64_t n_quant, int64_t fp_rows) {
+  const int64_t waves_per_cu = waves_per_compute_unit(g, vgroups);
+  int64_t size = units_per_layer <= kvq::kComputeUnits ? 4 : 2;       // the smallest workgroups it splits a unit into
+  if (size > waves_per_cu) size = waves_per_cu;
+  int64_t fit = resident_workgroups(waves_per_cu, size) / units_per_layer;
+  if (fit > 1 && fit * units_per_layer > kMaxSplitWorkgroups) fit = kMaxSplitWorkgroups / units_per_layer;
+  int64_t wanted = ((n_quant + kvq::kMiniChunk - 1) / kvq::kMiniChunk + size - 1) / size;
+  const int64_t for_rows = (fp_rows + 16 * kvq::kFpGroupRows - 1) / (16 * kvq::kFpGroupRows);
+  if (wanted < 8) wanted = 8;
+  if (wanted < for_rows) wanted = for_rows;
+  if (fit > wanted) fit = wanted;
+  return fit < 1 ? 1 : fit;
 }
 constexpr int64_t kCounterBytes(int64_t upl) { return ((upl * 4 + 255) / 256) * 256; }
 
@@ -79,14 +134,11 @@ struct PlanShape {
 };
 PlanShape plan_shape(const kvq_config* c) {
   const int g = c->q_heads / c->kv_heads;
-  int64_t waves_per_cu = kvq::kLdsPerComputeUnit / kvq::decode_wave_lds_bytes(g, c->head_dim / c->group_v);
-  const int64_t by_registers = 4 * kvq::kDecodeWavesPerSimd;
-  if (waves_per_cu > by_registers) waves_per_cu = by_registers;
-  if (waves_per_cu < 1) waves_per_cu = 1;
+  const int64_t waves_per_cu = waves_per_compute_unit(g, c->head_dim / c->group_v);
   PlanShape best = {0, 0};
   if (c->batch > 1024) return best;
   for (int nw = (int)waves_per_cu; nw >= 1; nw >>= 1) {
-    const int64_t entries = kvq::kComputeUnits * (waves_per_cu / nw) / c->kv_heads;
+    const int64_t entries = resident_workgroups(waves_per_cu, nw) / c->kv_heads;
     if (entries < c->batch) continue;
     best.nw = nw;
     best.entries = (int32_t)(entries > 4096 ? 4096 : entries);
@@ -108,7 +160,7 @@ int64_t decode_workspace_bytes(const kvq_config* cfg, int64_t rows) {
   const int64_t hp = head_parts_of((int)rows, cfg->bits);
   const int64_t slots = (int64_t)cfg->outlier_budget + cfg->aux_capacity;
   const int64_t s_max =
-      decode_split(upl * hp, (int)(rows / hp), (int)(hd / cfg->group_v), cfg->max_seq, res_rows_of(cfg) + slots).splits;
+      most_splits(upl * hp, (int)(rows / hp), (int)(hd / cfg->group_v), cfg->max_seq, res_rows_of(cfg) + slots);
   int64_t slots_needed = upl * s_max;
   if (cfg->batch <= 1024) {                              // a planned launch: items per kv head
     const int64_t planned = (int64_t)plan_shape(cfg).entries * cfg->kv_heads;
@@ -250,9 +302,6 @@ int32_t kvq_query_sizes(const kvq_config* cfg, kvq_sizes* out) {
   out->pool_score_bytes = units * slots * 8;
   out->counter_bytes = units * 4;
   out->selected_bytes = upl * cfg->group_k;
-  // the split count grows with the amount of work: the largest is the one of a full cache
-  const int hp = head_parts_of((int)g, cfg->bits);
-  const int64_t s_max = decode_split(upl * hp, (int)g / hp, (int)(hd / cfg->group_v), cfg->max_seq, out->res_rows + slots).splits;
   out->workspace_bytes = decode_workspace_bytes(cfg, g);
   out->prefill_selected_bytes = upl * cfg->max_seq;
   return KVQ_OK;
