@@ -151,6 +151,17 @@ __device__ __forceinline__ double row_partner(double v) {
   return __longlong_as_double((long long)((hi << 32) | lo));
 }
 
+// Inclusive sums over the lanes, on the DPP path.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr:1 */, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142 /* row_bcast:15 */, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143 /* row_bcast:31 */, 0xc, 0xf, false);
+  return v;
+}
+
 // ---- packed layout ---------------------------------------------------------------------------
 // Byte offset (inside a block) of the u32 word that holds field f of lane l, and the bit
 // offset of code x = 2v + e inside that word.  A code occupies bits code_bit .. code_bit + bits - 1

@@ -932,7 +932,10 @@ __global__ void seq_advance_kernel(Dims d, int32_t* seq) {
 // full-precision rows at half a mini-chunk each), every sequence at least one; a sequence's workgroups
 // share its mini-chunks equally.  The share m of one workgroup is the smallest for which the sequences'
 // workgroups, ceil(work / m) each, are at most `entries` in all (found by bisection: that count does not
-// grow with m).  One workgroup, one thread per sequence.
+// grow with m).  One workgroup, one thread per sequence.  What bounds it is the bisection, one sum over the
+// sequences per step: up to 64 sequences are one wavefront's, which needs neither LDS nor barriers for it
+// (32 sequences of 128 .. 8192 tokens: 6.6 -> 4.6 us).
+template <bool ONE_WAVE>
 __global__ void __launch_bounds__(1024) seq_plan_kernel(Dims d, const int32_t* __restrict__ seq, int32_t max_nq,
                                                          int32_t max_nres, int32_t entries, int32_t* __restrict__ plan) {
   __shared__ int s_acc;
@@ -949,6 +952,7 @@ __global__ void __launch_bounds__(1024) seq_plan_kernel(Dims d, const int32_t* _
     w = 2 * mc + ((nr + kFpGroupRows - 1) / kFpGroupRows) + ((d.pool_slots + kFpGroupRows - 1) / kFpGroupRows);
   }
   auto block_sum = [&](int v) {
+    if (ONE_WAVE) return __builtin_amdgcn_readlane(wave_scan(v), 63);
     if (threadIdx.x == 0) s_acc = 0;
     __syncthreads();
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -959,9 +963,10 @@ __global__ void __launch_bounds__(1024) seq_plan_kernel(Dims d, const int32_t* _
     return r;
   };
   auto block_max = [&](int v) {
+    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off));
+    if (ONE_WAVE) return __builtin_amdgcn_readfirstlane(v);
     if (threadIdx.x == 0) s_acc = 0;
     __syncthreads();
-    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off));
     if ((threadIdx.x & 63) == 0) atomicMax(&s_acc, v);
     __syncthreads();
     const int r = s_acc;
@@ -977,17 +982,15 @@ __global__ void __launch_bounds__(1024) seq_plan_kernel(Dims d, const int32_t* _
   }
   const int sp = splits_for(lo);
   // exclusive prefix of the sequences' workgroup counts
-  int incl = sp;
-  for (int off = 1; off < 64; off <<= 1) {
-    const int up = __shfl_up(incl, off);
-    if ((threadIdx.x & 63) >= off) incl += up;
-  }
-  if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = incl;
-  __syncthreads();
+  const int incl = wave_scan(sp);
   int before = 0;
-  for (int k = 0; k < (int)(threadIdx.x >> 6); ++k) before += s_wave[k];
+  if (!ONE_WAVE) {
+    if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    for (int k = 0; k < (int)(threadIdx.x >> 6); ++k) before += s_wave[k];
+  }
   const int first = before + incl - sp;
-  if (threadIdx.x == 1023) plan[0] = min(first + sp, entries);
+  if (threadIdx.x == blockDim.x - 1) plan[0] = min(first + sp, entries);
   if (live) {
     const int per = (mc + sp - 1) / sp;                  // mini-chunks per workgroup of this sequence
     for (int k = 0; k < sp && first + k < entries; ++k) {
@@ -1000,7 +1003,10 @@ __global__ void __launch_bounds__(1024) seq_plan_kernel(Dims d, const int32_t* _
 
 hipError_t launch_seq_plan(const Dims& d, const int32_t* seq, int32_t max_n_quant, int32_t max_n_res, int32_t entries,
                            int32_t* plan, hipStream_t s) {
-  hipLaunchKernelGGL(seq_plan_kernel, dim3(1), dim3(1024), 0, s, d, seq, max_n_quant, max_n_res, entries, plan);
+  if (d.batch <= 64)
+    hipLaunchKernelGGL(seq_plan_kernel<true>, dim3(1), dim3(64), 0, s, d, seq, max_n_quant, max_n_res, entries, plan);
+  else
+    hipLaunchKernelGGL(seq_plan_kernel<false>, dim3(1), dim3(1024), 0, s, d, seq, max_n_quant, max_n_res, entries, plan);
   return hipGetLastError();
 }
 

@@ -47,3 +47,33 @@ def test_outputs_with_unit_counts_that_are_no_power_of_two(batch, kv_heads, g, b
     n = batch * kv_heads
     units = sorted({0, n // 2, n - 1})
     P.run_sampled(w, units, regimes=("peaky",))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65, 130])
+def test_launch_plan_of_any_number_of_sequences(batch):
+    """One wavefront plans up to 64 sequences, a workgroup more: the same deal, computed here again."""
+    import torch
+    rng = random.Random(batch)
+    cfg = KC.make_config(1, batch, 4, 1, 8192, 2, 32, 32, 128, 8, 32)
+    cache = KC.RaggedKVCache(cfg)
+    lengths = [rng.randrange(1, 8192) for _ in range(batch)]
+    state = []
+    for n in lengths:
+        nq = 32 * ((n - 128) // 32) if n >= 160 else 0
+        state.append([nq, 0, n - nq, 1])
+    cache.seq_state.copy_(torch.tensor(state, dtype=torch.int32))
+    cache.longest = max(lengths)
+    cache.make_plan()
+    plan = cache.plan.cpu().tolist()
+    entries = (len(plan) - 8) // 8
+    mc = [-(-s[0] // 128) for s in state]
+    work = [2 * m + -(-s[2] // 16) + -(-40 // 16) for m, s in zip(mc, state)]
+    deal = lambda share: [min(max(-(-w // share), 1), max(m, 1)) for w, m in zip(work, mc)]
+    share = next(s for s in range(1, max(work) + 1) if sum(deal(s)) <= entries)
+    want = []
+    for b, (parts, m, s) in enumerate(zip(deal(share), mc, state)):
+        per = -(-m // parts)
+        want += [[b, k, parts, min(k * per, m), s[0], 0, s[2], min((k + 1) * per, m)] for k in range(parts)]
+    assert plan[0] == len(want)
+    assert plan[8:8 + 8 * len(want)] == [x for e in want for x in e]
