@@ -150,6 +150,10 @@ def _ptr(x):
 def _stream(stream):
     if stream is None:
         import torch
+        # the current stream's handle without building a Stream object around it: 0.2 us per call, 2.9 us with one
+        # (a decode step's call takes the host 9.0 us with it, and a launch on a short context the GPU 8 us)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
