@@ -84,7 +84,13 @@ __device__ inline float lo_half(uint32_t w) { return __half2float(__ushort_as_ha
 __device__ inline float hi_half(uint32_t w) { return __half2float(__ushort_as_half((unsigned short)(w >> 16))); }
 
 constexpr int kQuantThreads = 1024;
-constexpr int64_t kPromptGroups = 1024;   // from this many groups in one launch on, prompt_quantize_kernel takes them
+// From this many groups in one launch on, prompt_quantize_kernel takes them: soon after quantize_kernel's
+// workgroups, of which 512 are resident, need a second round.  A prompt's whole call (selection included) with
+// quantize_kernel / prompt_quantize_kernel: G = 32, 2-bit, 512 / 768 / 960 groups 18.9 / 18.5, 22.3 / 19.4, 24.4 /
+// 20.5 us; 4-bit, 512 / 768 groups 19.3 / 20.5, 22.5 / 21.0; G = 64, 512 / 768 groups 22.6 / 24.0, 30.8 / 28.1, 4-bit,
+// 640 groups 31.7 / 31.1 us.  With G = 128 (four blocks per group, which a wavefront of prompt_quantize_kernel takes
+// one after the other) 640 groups were 29.3 / 30.3 us, the launch alone.
+constexpr int64_t prompt_groups(int G) { return G < 128 ? 768 : 1024; }
 
 // Minimum and maximum over groups of `n` adjacent lanes (n = 4, 8 or 16).
 __device__ inline void team_minmax(float& mn, float& mx, int n) {
@@ -745,7 +751,7 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
                                __half* v_res, hipStream_t s) {
   // many groups (a prompt): the kernel that spends the fewest instructions per group; few: the one that is
   // done with a group soonest
-  if ((int64_t)d.units_per_layer * n_groups >= kPromptGroups && !d.keys_only) {
+  if ((int64_t)d.units_per_layer * n_groups >= prompt_groups(G) && !d.keys_only) {
     const int tail_blocks = (tail_n * 16 + 127) / 128;
     hipLaunchKernelGGL((prompt_quantize_kernel<BITS, G>), dim3(d.units_per_layer, n_groups + tail_blocks), dim3(128), 0,
                        s, d, group_index, k_group, v_group, unit_stride, selected, selected_unit_stride,

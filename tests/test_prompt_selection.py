@@ -61,3 +61,25 @@ def test_selection_of_a_prompt_equals_the_group_by_group_competition(G, N, A, n,
             assert np.array_equal(score[h, at:at + m], O.l1_scores(K[h])[rows])
             assert np.array_equal(pk[h, at:at + m].view(np.uint16), K[h][rows].view(np.uint16))
             assert np.array_equal(pv[h, at:at + m].view(np.uint16), V[h][rows].view(np.uint16))
+
+
+@pytest.mark.parametrize("bits,G,Gv", [(2, 32, 32), (4, 32, 64), (2, 64, 128)])
+@pytest.mark.parametrize("batch", [47, 48, 49])
+def test_many_prompts_in_one_call_equal_each_on_its_own(bits, G, Gv, batch):
+    """752, 768 and 784 groups in one call, on both sides of where the quantization changes kernels, against the
+    same prompts one sequence at a time (16 groups per call)."""
+    import torch
+    from paper_2505_10938_amd import cache as KC
+    heads, groups, R = 4, 4, 32
+    n = groups * G + R + 5
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(batch)
+    K, V = (torch.randn(batch, heads, n, 128, generator=gen, device="cuda").half() for _ in range(2))
+    K[:, :, ::7] *= 0.05
+    cfg = KC.make_config(1, batch, heads, heads, groups * G, bits, G, Gv, R, 3, 32)
+    a, b = KC.KVCache(cfg), KC.RaggedKVCache(cfg)
+    a.prefill(0, K, V)
+    for i in range(batch):
+        b.prefill_sequence(i, [K[i]], [V[i]])
+    for name in ("k_codes", "k_meta", "v_codes", "v_meta", "mask", "k_res", "v_res", "pool_idx", "pool_count", "aux_count"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
