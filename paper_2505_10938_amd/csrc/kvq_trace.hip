@@ -322,25 +322,17 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
     auto rank_of = [&](int k) -> int {
       return ((m[k] >> lane) & 1ull) ? ranks.before(k * kCompeteWaves + wave) + __popcll(m[k] & below) : kWindow;
     };
+    // A group never competes in parts: t0 is always the first token of a group (a window holds whole groups, and
+    // where a window is cut short, it ends, and the next one begins, with a whole group, flagged or not).
     int n = ranks.total, next = t0 + here;
-    if (n > kSegment) {                                // uniform
-      if (tid == 0) L.cut_rank = L.cut_at = kWindow;
+    if (n > kSegment) {                                // uniform: only the groups that are in whole
 #pragma unroll
       for (int k = 0; k < kPer; ++k)
         if (rank_of(k) == kSegment) L.cut_group = (t0 + k * kCompeteThreads + tid) >> kGroupShift;
       __syncthreads();
-      const int cut = L.cut_group;
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int t = k * kCompeteThreads + tid, r = rank_of(k);
-        if (r < kWindow && ((t0 + t) >> kGroupShift) >= cut) {
-          atomicMin(&L.cut_rank, r);
-          atomicMin(&L.cut_at, t);
-        }
-      }
-      __syncthreads();
-      n = min(L.cut_rank, kSegment);
-      next = t0 + L.cut_at;
+      next = __builtin_amdgcn_readfirstlane(L.cut_group) << kGroupShift;
+      const int w = (next - t0) >> 6, bit = (next - t0) & 63;
+      n = ranks.before(w) + __popcll(L.mask[w] & ((1ull << bit) - 1ull));
     }
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {

@@ -27,18 +27,11 @@ def keys(pattern, n, rng):
     return x.astype(np.float16)
 
 
-@pytest.mark.parametrize("pattern", ["noise", "falling", "rising", "equal", "late", "saw", "teeth"])
-@pytest.mark.parametrize("G,N,A,n", [
-    (32, 8, 32, 1024), (32, 8, 32, 1056), (128, 64, 64, 1024 + 128), (64, 1, 0, 2048), (32, 64, 64, 8192 + 32),
-    (128, 3, 64, 8192 + 1024 + 128), (32, 8, 64, 32), (32, 33, 7, 96),
-])
-def test_selection_of_a_prompt_equals_the_group_by_group_competition(G, N, A, n, pattern):
+def check_selection(K, V, G, N, A):
+    """Flags, pools (slot by slot), counts and the stop flag of prompts K, V (fp16 [heads, n, 128], all quantized)."""
     import torch
     from paper_2505_10938_amd import cache as KC
-    heads = 2
-    rng = np.random.default_rng(n + N)
-    K = np.stack([keys(pattern, n, rng) for _ in range(heads)])
-    V = rng.standard_normal((heads, n, 128)).astype(np.float16)
+    heads, n, _ = K.shape
     cache = KC.KVCache(KC.make_config(1, 1, heads, heads, n, 2, G, 128, 0, N, A))
     cache.prefill(0, torch.from_numpy(K)[None].cuda(), torch.from_numpy(V)[None].cuda())
     torch.cuda.synchronize()
@@ -51,16 +44,62 @@ def test_selection_of_a_prompt_equals_the_group_by_group_competition(G, N, A, n,
     counts = [t.view(torch.int32).cpu().numpy()[:heads] for t in (cache.pool_count, cache.aux_count, cache.frozen)]
     for h in range(heads):
         st = O.UnitState(128, 2, G, 128, N, A)
-        want = np.concatenate([st.trace(K[h, i:i + G], V[h, i:i + G], i // G) for i in range(0, n, G)])
+        want, fallen = [], []
+        for i in range(0, n, G):
+            had = {x["idx"] for x in st.aux}
+            want.append(st.trace(K[h, i:i + G], V[h, i:i + G], i // G))
+            fallen += sorted((x for x in st.aux if x["idx"] not in had), key=lambda x: (-x["score"], -x["idx"]))
+        want = np.concatenate(want)
         assert np.array_equal(flags[h], want.astype(np.uint8))
         assert [c[h] for c in counts] == [len(st.pool), len(st.aux), int(st.frozen)]
-        for at, members in ((0, st.pool), (N, st.aux)):
+        # the pool ascending by (score, index); what has fallen out by group, inside a group the largest key first
+        ranked = sorted(st.pool, key=lambda x: (x["score"], x["idx"]))
+        for at, members in ((0, ranked), (N, fallen)):
             m = len(members)
-            assert sorted(idx[h, at:at + m]) == sorted(x["idx"] for x in members)
+            assert list(idx[h, at:at + m]) == [x["idx"] for x in members]
             rows = idx[h, at:at + m]
             assert np.array_equal(score[h, at:at + m], O.l1_scores(K[h])[rows])
             assert np.array_equal(pk[h, at:at + m].view(np.uint16), K[h][rows].view(np.uint16))
             assert np.array_equal(pv[h, at:at + m].view(np.uint16), V[h][rows].view(np.uint16))
+
+
+@pytest.mark.parametrize("pattern", ["noise", "falling", "rising", "equal", "late", "saw", "teeth"])
+@pytest.mark.parametrize("G,N,A,n", [
+    (32, 8, 32, 1024), (32, 8, 32, 1056), (128, 64, 64, 1024 + 128), (64, 1, 0, 2048), (32, 64, 64, 8192 + 32),
+    (128, 3, 64, 8192 + 1024 + 128), (32, 8, 64, 32), (32, 33, 7, 96),
+])
+def test_selection_of_a_prompt_equals_the_group_by_group_competition(G, N, A, n, pattern):
+    rng = np.random.default_rng(n + N)
+    K = np.stack([keys(pattern, n, rng) for _ in range(2)])
+    check_selection(K, rng.standard_normal((2, n, 128)).astype(np.float16), G, N, A)
+
+
+def plateau_keys(G, n, low, lower):
+    """Keys whose L1 norms are set one by one (128 equal channels): everything at 8 but for the tokens given.  The
+    first 1024 tokens hold 640 of norm 1 and the next 384 are of norm 1, so that the 1025th token that may be selected
+    is in the middle of the group that starts at token 1408: `low` and `lower` are the offsets, inside the group 8192
+    tokens after that one, of eight tokens of norm 1/2 each and of eight of norm 1/4."""
+    norm = np.full(n, 8.0)
+    norm[:640] = 1.0
+    norm[1024:1408] = 1.0
+    norm[1408 + G // 2 + 4:1408 + G] = 1.0
+    for s in range(2048, n, 1024):               # the other segments: few that may be selected
+        norm[s:s + 8] = 1.0
+    at = 1408 + 8192
+    norm[at + low:at + low + 8] = 0.5
+    norm[at + lower:at + lower + 8] = 0.25
+    return np.repeat((norm / 128.0)[:, None], 128, 1).astype(np.float16)
+
+
+@pytest.mark.parametrize("G", [32, 64, 128])
+@pytest.mark.parametrize("A", [8, 32])
+@pytest.mark.parametrize("n", [10240, 12288])
+def test_a_group_competes_as_a_whole_wherever_the_prompt_is_cut(G, A, n):
+    """Tokens of one group of which the later ones displace the earlier ones, around the place where 8192 tokens
+    counted from the middle of a group would end.  Taken in two parts the earlier ones would be selected as well,
+    and with A = 8 tracing would stop."""
+    K = np.stack([plateau_keys(G, n, G // 2 - 8, G // 2 + 4), plateau_keys(G, n, G // 2 + 4, G // 2 - 8)])
+    check_selection(K, np.random.default_rng(G + A).standard_normal(K.shape).astype(np.float16), G, 8, A)
 
 
 @pytest.mark.parametrize("bits,G,Gv", [(2, 32, 32), (4, 32, 64), (2, 64, 128)])
