@@ -614,22 +614,68 @@ __device__ __forceinline__ void compute_minichunk(McRegs<BITS, NV>& R, WaveAcc<G
 // Full-precision rows (residual ring, then outlier-pool slots, then auxiliary slots) in groups of 16, both
 // products on the matrix cores: a K row is a B operand as it is; of the V rows a lane (m16, r) loads channels
 // 8 m16 .. 8 m16 + 7 of rows 4r .. 4r + 3, which are its share of the B operands of eight 16x16x16 products if
-// product e is given the channels 8n + e.  Row pair i of a result is that of head 2 (r % (GQ/2)) + i (one head:
-// of that one), for scores and weighted values alike, so the statistics of a lane's heads stay in the lane.
+// product e is given the channels 8n + e.  Rows 4r .. 4r + 3 of a result are those of head r % GQ, for scores and
+// weighted values alike, so the statistics of a lane's head stay in the lane.  A weight takes four rows, so that
+// none of the 24 bits of its fp32 value is lost (WeightParts).
+// With eight heads (rows 4r .. 4r + 3 of the scores: heads 2r and 2r + 1) four rows each would take two results per
+// channel, and 64 accumulators more beside the operands spill: the weighted values are
+// then formed on the vector units, in fp32, every lane summing its own four rows for all heads; the values of r are
+// added once, when the wavefront is through with its groups.
+// What bounds it is the chain load -> scores -> statistics -> weights -> products of a wavefront's one or two groups.
+// Us per pass, Values 4 bytes at a time on the vector units / 16 bytes at a time, vector units / four parts:
+//   four heads: 16 sequences of 301 .. 340 tokens, 40 steps 1069 / 924 / 868; batch 128 86.6 / 84.1 / 83.1
+//   eight heads: 8 sequences of 2k, 8 tokens at once 98.4 / 90.9 / 89.9; 16 of 8k 130 / 124 / 128, 4-bit 155 / 150 / 239
 template <int GQ>
 struct FpAcc {
-  float m[2], l[2];      // of the lane's two heads
-  float4v o[8];          // weighted values: column m16 of product e = channel 8 m16 + e
+  static constexpr bool kParts = GQ < 8;
+  static constexpr int kHeads = kParts ? 1 : 2;                      // heads per lane
+  float m[kHeads], l[kHeads];
+  // weighted values, channels 8 m16 + e: [e] the four parts of the lane's head, or [head][e] of rows 4r .. 4r + 3
+  std::conditional_t<kParts, float4v[8], float[GQ][8]> o;
 };
-// The same, each value held by one lane only: what is kept while the quantized tokens are worked on.
+// A weight p <= 1 as fp16 numbers: p 2^15 = a + b + (c + d) 2^-22 with a the rounded value, b the rounded rest, c and d
+// the same of what then remains: exact for p >= 2^-38, off by 2^-62 at most below.  (As hi + lo of p itself it would
+// lose bits from 2^-14 down and vanish below 2^-25.)  sum() is the weighted sum from those of the parts; an infinite
+// Value makes an infinity of the first part's and a NaN of those whose part of the weight is zero.
+struct WeightParts {
+  _Float16 part[4];
+  __device__ __forceinline__ explicit WeightParts(float p) {
+    float rest = p * 32768.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k == 2) rest *= 4194304.f;
+      part[k] = (_Float16)rest;
+      rest -= (float)part[k];
+    }
+  }
+  static __device__ __forceinline__ float sum(const float4v& v) {
+    const float all = (v[0] + v[1]) * 0x1p-15f + (v[2] + v[3]) * 0x1p-37f;
+    return __builtin_fabsf(v[0]) == __builtin_inff() ? v[0] : all;
+  }
+};
+// lanes 0 .. 31: a + a of lane ^ 32; lanes 32 .. 63: b + b of lane ^ 32
+__device__ __forceinline__ float fold_halves(float a, float b) {
+  const auto s =
+      __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t s0 = s[0], s1 = s[1];   // (bit_cast of a vector's element would take element 0 whatever the index)
+  return __builtin_bit_cast(float, s0) + __builtin_bit_cast(float, s1);
+}
+// rows of 16 lanes 0 and 2: a + a of lane ^ 16; rows 1 and 3: b + b of lane ^ 16
+__device__ __forceinline__ float fold_rows(float a, float b) {
+  const auto s =
+      __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t s0 = s[0], s1 = s[1];
+  return __builtin_bit_cast(float, s0) + __builtin_bit_cast(float, s1);
+}
+// The sums over all rows, each value held by one lane only: what is kept while the quantized tokens are worked on.
 template <int GQ>
 struct FpResult {
-  static constexpr int kHeads = GQ == 1 ? 1 : 2;                     // heads per lane
-  static constexpr int kRowsOfHeads = GQ <= 2 ? 1 : GQ / 2;          // values of r that differ in their heads
+  static constexpr int kHeads = FpAcc<GQ>::kHeads;
+  static constexpr int kRowsOfHeads = GQ < 4 ? GQ : 4;               // values of r that differ in their heads
   static constexpr int kTiles = 2 * kRowsOfHeads;                    // channels kept per lane and head
-  float m[2], l[2];
+  float m[kHeads], l[kHeads];
   float o[kHeads][kTiles];
-  static __device__ __forceinline__ int head(int r, int i) { return 2 * (r % kRowsOfHeads) + i; }
+  static __device__ __forceinline__ int head(int r, int i) { return kHeads * (r % kRowsOfHeads) + i; }
   static __device__ __forceinline__ int first_tile(int r) { return kTiles * (r / kRowsOfHeads); }
   __device__ __forceinline__ void take(const FpAcc<GQ>& F, int r) {
 #pragma unroll
@@ -638,13 +684,17 @@ struct FpResult {
       l[i] = F.l[i];
 #pragma unroll
       for (int k = 0; k < kTiles; ++k) {
-        float v = F.o[k][2 * i] + F.o[k][2 * i + 1];
+        if constexpr (FpAcc<GQ>::kParts) {
+          float v = WeightParts::sum(F.o[k]);
 #pragma unroll
-        for (int part = 1; part < 8 / kTiles; ++part) {
-          const float other = F.o[part * kTiles + k][2 * i] + F.o[part * kTiles + k][2 * i + 1];
-          v = r / kRowsOfHeads == part ? other : v;
+          for (int part = 1; part < 8 / kTiles; ++part) {
+            const float other = WeightParts::sum(F.o[part * kTiles + k]);
+            v = r / kRowsOfHeads == part ? other : v;
+          }
+          o[i][k] = v;
+        } else {                                                     // over r: heads i, 2 + i, 4 + i, 6 + i to r = 0 .. 3
+          o[i][k] = fold_rows(fold_halves(F.o[i][k], F.o[4 + i][k]), fold_halves(F.o[2 + i][k], F.o[6 + i][k]));
         }
-        o[i][k] = v;
       }
     }
   }
@@ -759,13 +809,14 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
   };
   // which of the 16 rows hold a token, as a wave-uniform bit mask (lanes 0..15 are rows 0..15)
   const uint32_t ok_rows = (uint32_t)__ballot(okk) & 0xFFFFu;
-  constexpr int R2 = 2 * GQ;
   constexpr int kHeads = FpResult<GQ>::kHeads;
-  const int arow = m16 % R2;
+  constexpr int kRowsOfHeads = FpResult<GQ>::kRowsOfHeads;
+  // rows of the scores: hi and lo of the query, twice where a lane has one head
+  const int qrow = kHeads == 2 ? m16 : 2 * ((m16 >> 2) % kRowsOfHeads) + (m16 & 1);
   float4v D = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
-    D = __builtin_amdgcn_mfma_f32_16x16x32_f16(lds_operand(L.q0[arow], cb * 64 + r * 16),
+    D = __builtin_amdgcn_mfma_f32_16x16x32_f16(lds_operand(L.q0[qrow], cb * 64 + r * 16),
                                                 __builtin_bit_cast(half8, X.kf[cb]), D, 0, 0, 0);
   // a row that holds no token may hold anything, a NaN too: its Values are cleared (most groups are
   // full: one uniform test)
@@ -787,7 +838,7 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
   }
   if (__any(above)) {                                              // wave-uniform
     row16_max(red);
-    float alpha[2] = {1.f, 1.f};
+    float alpha[kHeads];
 #pragma unroll
     for (int i = 0; i < kHeads; ++i) {
       const float m = fmaxf(F.m[i], red[i]);
@@ -795,40 +846,61 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
       F.m[i] = m;
       F.l[i] *= alpha[i];
     }
-    if (kHeads == 1) alpha[1] = alpha[0];
+    if constexpr (FpAcc<GQ>::kParts) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      F.o[e][0] *= alpha[0];
-      F.o[e][1] *= alpha[0];
-      F.o[e][2] *= alpha[1];
-      F.o[e][3] *= alpha[1];
+      for (int e = 0; e < 8; ++e) F.o[e] *= alpha[0];
+    } else {
+#pragma unroll
+      for (int j = 0; j < GQ; ++j) {                               // (held by the lanes of r = j / 2)
+        const float al = __builtin_bit_cast(
+            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha[j % kHeads]), 16 * (j >> 1)));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) F.o[j][e] *= al;
+      }
     }
   }
-  _Float16* prow = (_Float16*)&L.sc()[0][0];                       // p of the 16 tokens, [hi, lo of every head][16]
-  wave_sync();                                                     // earlier readers are done
+  wave_sync();                                                     // earlier readers of the scores' storage are done
+  float p[kHeads];
 #pragma unroll
-  for (int i = 0; i < kHeads; ++i) {
-    const float p = x[i] > 0.5f * kNegBig ? __builtin_amdgcn_exp2f(x[i] - F.m[i]) : 0.f;
-    red[i] = p;
-    const _Float16 hi = (_Float16)p;
-    if (r < FpResult<GQ>::kRowsOfHeads) {
-      const int j = FpResult<GQ>::head(r, i);
-      prow[(2 * j) * 16 + m16] = hi;
-      prow[(2 * j + 1) * 16 + m16] = (_Float16)(p - (float)hi);
-    }
-  }
+  for (int i = 0; i < kHeads; ++i)
+    red[i] = p[i] = x[i] > 0.5f * kNegBig ? __builtin_amdgcn_exp2f(x[i] - F.m[i]) : 0.f;
   row16_sum(red);
 #pragma unroll
   for (int i = 0; i < kHeads; ++i) F.l[i] += red[i];
-  wave_sync();
-  const half4 ap = *(const half4*)(prow + arow * 16 + 4 * r);
+  if constexpr (FpAcc<GQ>::kParts) {
+    _Float16* prow = (_Float16*)&L.sc()[0][0];                     // parts of the 16 tokens' weights, [heads][4][16]
+    const WeightParts w(p[0]);
+    if (kRowsOfHeads == 4 || r < kRowsOfHeads) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;    // the low / high halves of two words
-    u32x2 v;
-    v[0] = __builtin_amdgcn_perm(X.vf[1][e >> 1], X.vf[0][e >> 1], (e & 1) ? kHigh : kLow);
-    v[1] = __builtin_amdgcn_perm(X.vf[3][e >> 1], X.vf[2][e >> 1], (e & 1) ? kHigh : kLow);
-    F.o[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(ap, __builtin_bit_cast(half4, v), F.o[e], 0, 0, 0);
+      for (int k = 0; k < 4; ++k) prow[(4 * r + k) * 16 + m16] = w.part[k];
+    }
+    wave_sync();
+    const half4 ap = *(const half4*)(prow + (m16 % (4 * kRowsOfHeads)) * 16 + 4 * r);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;  // the low / high halves of two words
+      u32x2 v;
+      v[0] = __builtin_amdgcn_perm(X.vf[1][e >> 1], X.vf[0][e >> 1], (e & 1) ? kHigh : kLow);
+      v[1] = __builtin_amdgcn_perm(X.vf[3][e >> 1], X.vf[2][e >> 1], (e & 1) ? kHigh : kLow);
+      F.o[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(ap, __builtin_bit_cast(half4, v), F.o[e], 0, 0, 0);
+    }
+  } else {
+    float* prow = &L.sc()[0][0];                                   // weights of the 16 tokens, [GQ][16]
+#pragma unroll
+    for (int i = 0; i < kHeads; ++i) prow[FpResult<GQ>::head(r, i) * 16 + m16] = p[i];
+    wave_sync();
+    float4v pr[GQ];                                                // of the lane's rows
+#pragma unroll
+    for (int j = 0; j < GQ; ++j) pr[j] = *(const float4v*)(prow + j * 16 + 4 * r);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t w = X.vf[i][e >> 1];
+        const float v = h2f_bits((e & 1) ? w >> 16 : w & 0xFFFFu);
+#pragma unroll
+        for (int j = 0; j < GQ; ++j) F.o[j][e] += pr[j][i] * v;
+      }
   }
 }
 
@@ -999,12 +1071,19 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   // ---- full-precision part, while the first quantized loads are in flight --------------------------
   FpAcc<GQ> F;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < FpAcc<GQ>::kHeads; ++i) {
     F.m[i] = kNegBig;
     F.l[i] = 0.f;
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) F.o[e] = float4v{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < 8; ++e) {
+    if constexpr (FpAcc<GQ>::kParts) {
+      F.o[e] = float4v{0.f, 0.f, 0.f, 0.f};
+    } else {
+#pragma unroll
+      for (int j = 0; j < GQ; ++j) F.o[j][e] = 0.f;
+    }
+  }
 #pragma unroll
   for (int j = 0; j < GQ; ++j) {                         // the query rows, for both parts
     uint32_t hi, lo;
