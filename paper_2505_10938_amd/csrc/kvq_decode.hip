@@ -1196,8 +1196,8 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   float* part_out = a.partials + (part_slot0 + split) * GQ * (kHeadDim + 2);
   // Thread = C channels of one row.  All values are asked for at once; meanwhile the weights of the results
   // (lane & 15 = result) are formed inside rows of 16 lanes and handed round there.  What bounds it is the chain
-  // of LDS latencies; a loop over the results took one per result: 16 sequences of 301 .. 340 tokens 945 -> 920 us for 40 steps, a ragged batch 108.5 -> 104.6 us, one sequence
-  // of 4k 370 -> 361 us, batch 128 85.4 -> 84.1 us.  C: few enough channels that the threads suffice for all rows
+  // of LDS latencies; a loop over the results took one per result: 16 sequences of 301 .. 340 tokens 945 -> 920 us for
+  // 40 steps, a ragged batch 108.5 -> 104.6 us, one sequence of 4k 370 -> 361 us, batch 128 85.4 -> 84.1 us.  C: few enough channels that the threads suffice for all rows
   // in about one pass, so that the copies of the weights' arithmetic are few as well (with eight wavefronts and
   // four rows, C = 1 / 2 / 4: 940 / 911 / 912 us in the first workload; one row, C = 1 / 4: 361 / 376 us for one
   // sequence of 4k).
@@ -1228,6 +1228,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
       for (int w = 0; w < SLOTS; ++w) {
         const float wt = row16_lane(f, w);
         if (w < SLOTS / 2) v[w] += w < nw ? z[w] : 0.f;    // quantized parts carry their zero-point sums
+        if (w >= 2 && w >= 2 * nw) v[w] = 0.f;             // a copy of the last result, which may be infinite
         o += v[w] * wt;
         l += row16_lane(own_l, w) * wt;
       }
@@ -1291,7 +1292,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
         for (int k = 0; k < kBatch; ++k) {
           const float w = (s0 + k < n_splits) ? __builtin_amdgcn_exp2f(pm[k] - mb) : 0.f;
           l += pl[k] * w;
-          o += po[k] * w;
+          o += (s0 + k < n_splits ? po[k] : 0.f) * w;      // (a copy of the last partial result may be infinite)
         }
         m = mb;
       }

@@ -66,3 +66,15 @@ def plant_and_compare(batch, kv_heads, g, context, residual, splits, waves):
 ])
 def test_infinite_value_in_a_full_precision_row(batch, kv_heads, g, context, residual, splits, waves):
     plant_and_compare(batch, kv_heads, g, context, residual, splits, waves)
+
+
+@pytest.mark.parametrize("batch,kv_heads,g,context,residual,splits,waves", [
+    (1, 1, 1, 40, 32, 1, 3), (1, 1, 1, 150, 32, 1, 4), (1, 1, 2, 300, 32, 1, 5), (1, 1, 8, 400, 32, 1, 6),
+    (1, 1, 4, 200, 128, 1, 7), (1, 1, 2, 600, 32, 2, 4), (1, 4, 1, 1100, 128, 2, 7), (1, 1, 8, 1100, 32, 3, 8),
+    (1, 4, 1, 2100, 128, 4, 6), (1, 1, 4, 2100, 32, 4, 8), (1, 1, 2, 4200, 128, 8, 5),
+])
+def test_infinite_value_where_fewer_results_are_merged_than_a_merge_has_room_for(batch, kv_heads, g, context, residual,
+                                                                                 splits, waves):
+    """The merge of a workgroup's wavefronts takes 4, 8 or 16 results, that of a unit's workgroups eight at a time: the
+    places beyond the last result count for nothing, also when the last result is infinite."""
+    plant_and_compare(batch, kv_heads, g, context, residual, splits, waves)
