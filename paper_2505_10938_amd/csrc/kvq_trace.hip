@@ -3,6 +3,7 @@
 #include "kvq_common.h"
 #include "kvq_trace_core.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace kvq {
@@ -40,25 +41,24 @@ __global__ void __launch_bounds__(trace_core::kWorkers) trace_kernel(
 // have fallen out, and the first group where that exceeds A is where tracing stops.  None of it depends on
 // the order of insertion, and only selected tokens can displace one, so that counting needs few of them.
 //
-// Two launches.  prompt_candidates_kernel: one workgroup per unit and segment of 1024 tokens computes the
-// L1 scores and flags the tokens that may be selected, judged by the segment alone (for N = 8 and random
-// scores about 50 of 1024).  What bounds it is the read of the Keys.  prompt_compete_kernel: one workgroup
-// per unit gathers the flagged tokens, selects among them and writes flags, pool and state: a chain of
-// short phases that a single workgroup goes through in order, which is why all that can be done per segment
-// is done there.  A prompt of one segment needs the second launch only.
+// prompt_compete_kernel, one workgroup per unit, does all of it, T tokens (one per thread) at a time: scores, a first
+// look by the segment's own bounds or the pool's largest key, then a count among the few tokens left; the Key rows of
+// the next T tokens are in flight meanwhile, and nothing is read any more once tracing has stopped.  With as many
+// units as compute units the read of the Keys bounds it; one workgroup alone reads about 1024 tokens in 10 us.
+// Few units and a long prompt: prompt_candidates_kernel, one workgroup per unit and segment of 1024 tokens, computes
+// the scores and flags the tokens that may be selected, judged by the segment alone (for N = 8 and random scores about
+// 50 of 1024); prompt_compete_kernel then gathers the flagged ones.  It reads all Keys, however early tracing stops.
 //
-// Measured (kernel trace) against one wavefront per unit that walked the groups and inserted one token at a
-// time, with seven others computing scores ahead of it:
-//   8 units x 8064 tokens (64 workgroups, then 8)       93 us -> 9.8 + 15.2 us
-//   256 units x 3968 tokens (1024 workgroups, then 256) 84 us -> 53 + 17.8 us (the read alone: 52 us, 5.1 TB/s)
-//   128 units x 160 tokens (second launch only)         24 us -> 13 us
-// With 512 threads per workgroup and a first look by exact ranks instead of bounds: 25 + 25 us and 79 + 24 us.
+// Us of a prompt's whole call (G = 32, N = 8; the quantization, about 125 us per 256 x 4096 tokens, included), with one
+// wavefront per unit that walked the groups and inserted one token at a time / by segments / one workgroup per unit:
+//   8 units x 8192 tokens, A = 32       101 /  34 /  93
+//   64 x 16384, A = 32; A = 16          300 / 209 / 285; 181 / 200 / 157
+//   256 x 4096, A = 32; A = 16          205 / 190 / 189; 183 / 187 / 165
+//   1024 x 4096, A = 32; A = 16         767 / 775 / 743; 677 / 777 / 616   (T = 512)
+//   1024 x 300, A = 32; N = 1, A = 0     85 /  92 /  64;  58 /  81 /  53   (T = 256)
 
-constexpr int kCompeteThreads = 1024;
-constexpr int kCompeteWaves = kCompeteThreads / 64;
-constexpr int kSegment = kCompeteThreads;              // tokens that compete at a time: one per thread
+constexpr int kSegment = 1024;                         // tokens of a workgroup of prompt_candidates_kernel
 constexpr int kRound = 128;                            // tokens ranked at a time: at least a whole group
-constexpr int kWindow = 8192;                          // tokens whose flags are looked at at a time
 
 typedef unsigned long long u64;
 
@@ -99,17 +99,13 @@ __device__ __forceinline__ u64 competition_key(double score, int place) {
                                       : (1ull << 47) - 1ull;
   return (fixed << kPlaceBits) | (u64)place;
 }
-__device__ __forceinline__ u64 lane_value(u64 v, int l) {   // v of lane l (uniform l)
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-  return ((u64)hi << 32) | lo;
-}
+template <int T>
 struct CompeteLds {
-  u64 key[kSegment];                                   // the entries competing, ascending by token index
-  int32_t idx[kSegment];
-  uint32_t coarse[kSegment];                           // their scores, coarsely
+  u64 key[T];                                          // the entries competing, ascending by token index
+  int32_t idx[T];
+  uint32_t coarse[T];                                  // their scores, coarsely
   uint32_t bound[kPrefixes];
-  u64 mask[kWindow / 64];                              // marked entries, 64 per word
+  u64 mask[8 * T / 64];                                // marked entries, 64 per word
   u64 r_key[kRound];                                   // the round's
   int32_t r_idx[kRound];
   uint32_t r_less[kRound];                             // smaller keys: up to the entry's group, and << 16 in all
@@ -140,14 +136,15 @@ struct MaskRanks {
 // per row, eight rows of a team of lanes in flight.
 template <class Row, class Put>
 __device__ __forceinline__ void score_rows(int n, int tid, Row row, Put put) {
-  constexpr int kTeams = kCompeteThreads / 16;
+  constexpr int kTeams = kSegment / 16;
+  constexpr int kInFlight = 8;
   const int team = tid >> 4, sub = tid & 15;
-  for (int i0 = 0; i0 < n; i0 += 8 * kTeams) {
-    uint4 w[8];
+  for (int i0 = 0; i0 < n; i0 += kInFlight * kTeams) {
+    uint4 w[kInFlight];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) w[q] = *(const uint4*)(row(min(i0 + q * kTeams + team, n - 1)) + sub * 8);
+    for (int q = 0; q < kInFlight; ++q) w[q] = *(const uint4*)(row(min(i0 + q * kTeams + team, n - 1)) + sub * 8);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < kInFlight; ++q) {
       const int e = i0 + q * kTeams + team;
       const double sc = trace_core::team_sum_f64(trace_core::abs_sum8(w[q]));
       if (sub == 0 && e < n) put(e, sc);
@@ -159,9 +156,10 @@ __device__ __forceinline__ void score_rows(int n, int tid, Row row, Put put) {
 // buffer `cur`, which changes).  Entry j of the round, j < the result, is L.r_idx[j] and was selected if
 // L.r_sel[j].  `pos` becomes the first entry not looked at.  `may`: entry `tid` passed the first look.  Four
 // barriers, the last one at the end.
-template <int G>
-__device__ __forceinline__ int compete_round(CompeteLds& L, int n, bool may, int& pos, int N, int& P, int& cur, int tid) {
+template <int G, int T>
+__device__ __forceinline__ int compete_round(CompeteLds<T>& L, int n, bool may, int& pos, int N, int& P, int& cur, int tid) {
   constexpr int kGroupShift = G == 32 ? 5 : G == 64 ? 6 : 7;
+  constexpr int kWaves = T / 64;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const u64 max_key = L.p_key[cur][N - 1];             // (counts only where P == N)
@@ -172,12 +170,17 @@ __device__ __forceinline__ int compete_round(CompeteLds& L, int n, bool may, int
   if (tid < kRound) L.r_less[tid] = 0;
   if (tid < 64) L.p_less[tid] = 0;
   __syncthreads();
-  const MaskRanks ranks(L.mask, kSegment / 64, lane);
+  const MaskRanks ranks(L.mask, T / 64, lane);
   const bool marked = (m >> lane) & 1ull;
   const int rank = ranks.before(wave) + __popcll(m & ((1ull << lane) - 1ull));
   int nr = ranks.total, next = n;
+  if (nr == 0) {                                       // uniform: nothing can enter the pool any more
+    __syncthreads();                                   // (the marks have been read by all)
+    pos = n;
+    return 0;
+  }
   if (nr > kRound) {                                   // uniform: only the groups that are in whole
-    if (tid == 0) L.cut_rank = L.cut_at = kSegment;
+    if (tid == 0) L.cut_rank = L.cut_at = T;
     if (marked && rank == kRound) L.cut_group = ix >> kGroupShift;
     __syncthreads();
     if (marked && (ix >> kGroupShift) >= L.cut_group) {
@@ -200,8 +203,8 @@ __device__ __forceinline__ int compete_round(CompeteLds& L, int n, bool may, int
   const int end0 = L.r_idx[lane] | (G - 1), end1 = L.r_idx[64 + lane] | (G - 1);
   uint32_t c0 = 0, c1 = 0, cp = 0;
 #pragma unroll
-  for (int i = 0; i < kRound / kCompeteWaves; ++i) {
-    const int j = i * kCompeteWaves + wave;
+  for (int i = 0; i < kRound / kWaves; ++i) {
+    const int j = i * kWaves + wave;
     if (j < nr) {
       const u64 jk = L.r_key[j];
       const int jx = L.r_idx[j];
@@ -210,7 +213,7 @@ __device__ __forceinline__ int compete_round(CompeteLds& L, int n, bool may, int
       cp += jk < kp ? 1u : 0u;
     }
   }
-  for (int p = wave; p < P; p += kCompeteWaves) {
+  for (int p = wave; p < P; p += kWaves) {
     const u64 pk = L.p_key[cur][p];
     c0 += pk < k0 ? 0x10001u : 0u;
     c1 += pk < k1 ? 0x10001u : 0u;
@@ -246,7 +249,7 @@ __device__ __forceinline__ bool may_be_selected(const uint32_t* coarse, const ui
 
 // grid (units, segments).  Requires N > 0.
 template <int G>
-__global__ void __launch_bounds__(kCompeteThreads) prompt_candidates_kernel(Dims d, int32_t n_tok,
+__global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int32_t n_tok,
                                                                             const __half* __restrict__ k_rows,
                                                                             int64_t unit_stride,
                                                                             uint8_t* __restrict__ selected) {
@@ -268,16 +271,18 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_candidates_kernel(Dims
         may_be_selected<G>(coarse, bound, n, tid, tid, [](int p) { return p; }) ? 1 : 0;
 }
 
-// grid (units).  `flagged`: the tokens that can be selected are flagged in `selected`, else all of them are
-// looked at.  Pools are taken to be empty on entry (a prompt starts a sequence) and are not read.
-template <int G>
-__global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
-    Dims d, int32_t n_tok, int32_t flagged, const __half* __restrict__ k_rows, const __half* __restrict__ v_rows,
+// grid (units).  FLAGGED: the tokens that can be selected are flagged in `selected`, else all of them are looked at, T
+// at a time, the Key rows of the next T in flight meanwhile.  Pools are taken to be empty on entry (a prompt starts a
+// sequence) and are not read.
+template <int G, int T, bool FLAGGED>
+__global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) prompt_compete_kernel(
+    Dims d, int32_t n_tok, const __half* __restrict__ k_rows, const __half* __restrict__ v_rows,
     int64_t unit_stride, __half* pool_k, __half* pool_v, int32_t* pool_idx, double* pool_score, int32_t* pool_count,
     int32_t* aux_count, int32_t* frozen, uint8_t* __restrict__ selected) {
   constexpr int kGroupShift = G == 32 ? 5 : G == 64 ? 6 : 7;
   constexpr int kListed = 64 + 64 + kRound;            // at most N + A selected tokens before the last round
-  __shared__ CompeteLds L;
+  constexpr int kWaves = T / 64;
+  __shared__ CompeteLds<T> L;
   __shared__ u64 s_key[kListed];                       // every token selected so far, ascending by index
   __shared__ int32_t s_idx[kListed];
   __shared__ int32_t s_out[kListed];                   // the group at which it falls out (none: kStays)
@@ -291,7 +296,7 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
   uint8_t* sel = selected + (int64_t)ul * n_tok;
   const int N = d.N, A = d.A;
   if (N == 0) {                                        // no pool: nothing is ever selected
-    for (int i = tid; i < n_tok; i += kCompeteThreads) sel[i] = 0;
+    for (int i = tid; i < n_tok; i += T) sel[i] = 0;
     return;
   }
   const __half* kr = k_rows + (int64_t)ul * unit_stride;
@@ -300,62 +305,95 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
   int P = 0, cur = 0, S = 0;                           // pool members, pool buffer, selected tokens
   bool stopped = false;
   int t0 = 0;                                          // tokens before t0 have been looked at
+  // Key rows of tokens t .., sixteen per team of 16 lanes
+  constexpr int kTeams = T / 16, kRows = 16;
+  const int team = tid >> 4, sub = tid & 15;
+  uint4 w[kRows];
+  auto load_rows = [&](int t) {
+#pragma unroll
+    for (int q = 0; q < kRows; ++q)
+      if (t + q * kTeams < n_tok)                      // uniform
+        w[q] = *(const uint4*)(kr + (int64_t)min(t + q * kTeams + team, n_tok - 1) * kHeadDim + sub * 8);
+  };
+  auto put_score = [&](int e, double sc) {
+    L.key[e] = competition_key(sc, e + 1);
+    L.coarse[e] = coarse_score(sc);
+  };
+  if constexpr (!FLAGGED) load_rows(0);
   while (t0 < n_tok && !stopped) {
-    // ---- the next candidates, at most kSegment (whole groups), and their scores
-    constexpr int kPer = kWindow / kCompeteThreads;
-    const int here = min(kWindow, n_tok - t0);
-    u64 m[kPer];
-    uint8_t f[kPer];
+    int n, next;                                       // entries that compete now, first token of the next ones
+    if constexpr (FLAGGED) {
+      // ---- the next candidates, at most T (whole groups), and their scores
+      constexpr int kPer = 8;
+      const int here = min(kPer * T, n_tok - t0);
+      u64 m[kPer];
+      uint8_t f[kPer];
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int t = k * kCompeteThreads + tid;
-      f[k] = flagged ? sel[t0 + min(t, here - 1)] : (uint8_t)1;
-    }
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int t = k * kCompeteThreads + tid;
-      m[k] = __ballot(t < here && f[k]);
-      if (lane == 0) L.mask[k * kCompeteWaves + wave] = m[k];
-    }
-    __syncthreads();
-    const MaskRanks ranks(L.mask, kWindow / 64, lane);
-    auto rank_of = [&](int k) -> int {
-      return ((m[k] >> lane) & 1ull) ? ranks.before(k * kCompeteWaves + wave) + __popcll(m[k] & below) : kWindow;
-    };
-    // A group never competes in parts: t0 is always the first token of a group (a window holds whole groups, and
-    // where a window is cut short, it ends, and the next one begins, with a whole group, flagged or not).
-    int n = ranks.total, next = t0 + here;
-    if (n > kSegment) {                                // uniform: only the groups that are in whole
-#pragma unroll
-      for (int k = 0; k < kPer; ++k)
-        if (rank_of(k) == kSegment) L.cut_group = (t0 + k * kCompeteThreads + tid) >> kGroupShift;
-      __syncthreads();
-      next = __builtin_amdgcn_readfirstlane(L.cut_group) << kGroupShift;
-      const int w = (next - t0) >> 6, bit = (next - t0) & 63;
-      n = ranks.before(w) + __popcll(L.mask[w] & ((1ull << bit) - 1ull));
-    }
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int t = k * kCompeteThreads + tid, r = rank_of(k);
-      if (r < n) {
-        L.idx[r] = t0 + t;
-        sel[t0 + t] = 0;                               // the selected ones are flagged again at the end
+      for (int k = 0; k < kPer; ++k) {
+        const int t = k * T + tid;
+        f[k] = sel[t0 + min(t, here - 1)];
       }
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int t = k * T + tid;
+        m[k] = __ballot(t < here && f[k]);
+        if (lane == 0) L.mask[k * kWaves + wave] = m[k];
+      }
+      __syncthreads();
+      const MaskRanks ranks(L.mask, kPer * T / 64, lane);
+      auto rank_of = [&](int k) -> int {
+        return ((m[k] >> lane) & 1ull) ? ranks.before(k * kWaves + wave) + __popcll(m[k] & below) : kPer * T;
+      };
+      // A group never competes in parts: t0 is always the first token of a group (a window holds whole groups, and
+      // where a window is cut short, it ends, and the next one begins, with a whole group, flagged or not).
+      n = ranks.total;
+      next = t0 + here;
+      if (n > T) {                                // uniform: only the groups that are in whole
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+          if (rank_of(k) == T) L.cut_group = (t0 + k * T + tid) >> kGroupShift;
+        __syncthreads();
+        next = __builtin_amdgcn_readfirstlane(L.cut_group) << kGroupShift;
+        const int w = (next - t0) >> 6, bit = (next - t0) & 63;
+        n = ranks.before(w) + __popcll(L.mask[w] & ((1ull << bit) - 1ull));
+      }
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int t = k * T + tid, r = rank_of(k);
+        if (r < n) {
+          L.idx[r] = t0 + t;
+          sel[t0 + t] = 0;                               // the selected ones are flagged again at the end
+        }
+      }
+      __syncthreads();
+      score_rows(n, tid, [&](int e) { return kr + (int64_t)L.idx[e] * kHeadDim; }, put_score);
+    } else {
+      n = min(T, n_tok - t0);
+      next = t0 + n;
+#pragma unroll
+      for (int q = 0; q < kRows; ++q) {
+        if (q * kTeams >= n) break;                    // uniform
+        const int e = q * kTeams + team;
+        const double sc = trace_core::team_sum_f64(trace_core::abs_sum8(w[q]));
+        if (sub == 0 && e < n) put_score(e, sc);
+      }
+      if (tid < n) {
+        L.idx[tid] = t0 + tid;
+        sel[t0 + tid] = 0;                             // the selected ones are flagged at the end
+      }
+      if (next < n_tok) load_rows(next);
     }
     __syncthreads();
-    score_rows(n, tid, [&](int e) { return kr + (int64_t)L.idx[e] * kHeadDim; },
-               [&](int e, double sc) {
-                 L.key[e] = competition_key(sc, e + 1);
-                 L.coarse[e] = coarse_score(sc);
-               });
-    __syncthreads();
-    prefix_bounds(L.coarse, n, N, L.bound, wave, lane);
-    __syncthreads();
-    const bool may = may_be_selected<G>(L.coarse, L.bound, n, tid, L.idx[tid], [&](int p) { return L.idx[p]; });
+    bool may = true;
+    if (FLAGGED || P < N) {                            // (once the pool is full its largest key lets fewer through)
+      prefix_bounds(L.coarse, n, N, L.bound, wave, lane);
+      __syncthreads();
+      may = may_be_selected<G>(L.coarse, L.bound, n, tid, L.idx[tid], [&](int p) { return L.idx[p]; });
+    }
     // ---- select among them
     int pos = 0;
     while (pos < n && !stopped) {
-      const int nr = compete_round<G>(L, n, may, pos, N, P, cur, tid);
+      const int nr = compete_round<G, T>(L, n, may, pos, N, P, cur, tid);
       // The round's selected tokens join the list.  With token k of the list (from 0), min(N, tokens so far)
       // of k + 1 are in the pool; the others have fallen out and must fit in the auxiliary pool.
       // (every wavefront works this out for itself: lane = entries lane, 64 + lane of the round)
@@ -386,7 +424,7 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
     }
     t0 = next;
   }
-  for (int t = t0 + tid; t < n_tok; t += kCompeteThreads) sel[t] = 0;   // after the stop nothing is selected
+  for (int t = t0 + tid; t < n_tok; t += T) sel[t] = 0;   // after the stop nothing is selected
   __syncthreads();
   // ---- the S selected tokens (at most N + A): pool, ascending by key, or auxiliary pool, in the order they
   // fall out (by group; inside a group the largest key first).  One wavefront per token, lane = the others.
@@ -398,7 +436,7 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
     os[h] = e < S ? s_key[e] : ~0ull;
     oi[h] = e < S ? s_idx[e] : 0;
   }
-  for (int e = wave; e < S; e += kCompeteWaves) {
+  for (int e = wave; e < S; e += kWaves) {
     const u64 es = s_key[e];
     const int ei = s_idx[e];
     const u64 b0 = __ballot(os[0] < es), b1 = __ballot(os[1] < es);
@@ -421,7 +459,7 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
   const int in_pool = min(N, S), aux_n = S - in_pool;
   if (aux_n > 0) {
     const int out0 = lane < S ? s_out[lane] : kStays, out1 = 64 + lane < S ? s_out[64 + lane] : kStays;
-    for (int e = wave; e < S; e += kCompeteWaves) {
+    for (int e = wave; e < S; e += kWaves) {
       const int out = s_out[e];
       if (out == kStays) continue;
       const u64 es = s_key[e];
@@ -438,8 +476,8 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
     aux_count[u] = aux_n;
     frozen[u] = stopped ? 1 : 0;
   }
-  for (int j = tid >> 4; j < S; j += kCompeteThreads / 16) {
-    const int sub = tid & 15, idx = slot_idx[j];
+  for (int j = tid >> 4; j < S; j += T / 16) {
+    const int idx = slot_idx[j];
     const int64_t slot = slot0 + (j < in_pool ? j : N + (j - in_pool));
     const uint4 kw = *(const uint4*)(kr + (int64_t)idx * kHeadDim + sub * 8);
     const uint4 vw = *(const uint4*)(vr + (int64_t)idx * kHeadDim + sub * 8);
@@ -453,24 +491,55 @@ __global__ void __launch_bounds__(kCompeteThreads) prompt_compete_kernel(
   }
 }
 
+// Do the segments of a prompt go to workgroups of their own (if there are several)?  By segments a call's Keys take
+// 10 us per 250 units and segment plus about 20 us for two launches one after the other, by unit 10 us per segment and
+// about 12: `early` is the number of segments at which the two are even (whole call, 4096 tokens, by segments / by
+// unit: 128 units 97 / 105 us, 192 137 / 143, 256 190 / 189; 16384 tokens: 192 units 628 / 623).
+// By unit it is as well if tracing has stopped by then in all units, to be expected with a small auxiliary pool: were
+// the scores independent, group i would displace N / i tokens on average, about Poisson, E = N ln(groups, or tokens / N)
+// in all; Chernoff's bound on at most A of them, for all units, is held against e^-2.  (If that is wrong for the
+// prompt at hand the call is as long as with the walk above, or reads what it need not.)
+bool by_segments(const Dims& d, int32_t n_tok) {
+  if (d.N == 0 || n_tok <= kSegment) return false;
+  const double segments = (double)n_tok / kSegment, early = 0.75 + d.units_per_layer * segments / 250.0;
+  if (early >= segments) return false;
+  const double groups = early * kSegment / (d.G > d.N ? d.G : d.N), e = d.N * std::log(groups > 1.0 ? groups : 1.0);
+  if (e <= d.A) return true;
+  const double log_p = d.A - e + (d.A > 0 ? d.A * std::log(e / d.A) : 0.0);
+  return log_p + std::log((double)d.units_per_layer) >= -2.0;
+}
+
 }  // namespace
 
 hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const __half* k_rows, const __half* v_rows,
                                 int64_t unit_stride, const kvq_pool& pool, uint8_t* selected, hipStream_t s) {
   const int32_t n_tok = n_groups * d.G;
-  const int32_t flagged = d.N > 0 && n_tok > kSegment;   // (one segment: a launch of its own for the flags gains nothing)
-  auto go = [&](auto candidates, auto compete) {
-    if (flagged)
-      hipLaunchKernelGGL(candidates, dim3(d.units_per_layer, (n_tok + kSegment - 1) / kSegment), dim3(kCompeteThreads), 0,
-                         s, d, n_tok, k_rows, unit_stride, selected);
-    hipLaunchKernelGGL(compete, dim3(d.units_per_layer), dim3(kCompeteThreads), 0, s, d, n_tok, flagged, k_rows, v_rows,
-                       unit_stride, (__half*)pool.pool_k, (__half*)pool.pool_v, pool.pool_idx, pool.pool_score,
-                       pool.pool_count, pool.aux_count, pool.frozen, selected);
+  auto compete = [&](auto kern, int threads) {
+    hipLaunchKernelGGL(kern, dim3(d.units_per_layer), dim3(threads), 0, s, d, n_tok, k_rows, v_rows, unit_stride,
+                       (__half*)pool.pool_k, (__half*)pool.pool_v, pool.pool_idx, pool.pool_score, pool.pool_count,
+                       pool.aux_count, pool.frozen, selected);
+  };
+  // Threads of a workgroup: 1024 where every unit can have a compute unit to itself; with more units 512, so that two
+  // workgroups fit one, and 256 for prompts no longer than that.  1024 units x 300 tokens, T = 1024 / 512 / 256: 92 /
+  // 70 / 64 us; x 600: 138 / 120 / 121.
+  auto go = [&](auto group) {
+    constexpr int G = decltype(group)::value;
+    if (by_segments(d, n_tok)) {
+      hipLaunchKernelGGL(prompt_candidates_kernel<G>, dim3(d.units_per_layer, (n_tok + kSegment - 1) / kSegment),
+                         dim3(kSegment), 0, s, d, n_tok, k_rows, unit_stride, selected);
+      compete(prompt_compete_kernel<G, 1024, true>, 1024);
+    } else if (d.units_per_layer > 2 * kComputeUnits && n_tok <= 256) {
+      compete(prompt_compete_kernel<G, 256, false>, 256);
+    } else if (d.units_per_layer > kComputeUnits) {
+      compete(prompt_compete_kernel<G, 512, false>, 512);
+    } else {
+      compete(prompt_compete_kernel<G, 1024, false>, 1024);
+    }
   };
   switch (d.G) {
-    case 32: go(prompt_candidates_kernel<32>, prompt_compete_kernel<32>); break;
-    case 64: go(prompt_candidates_kernel<64>, prompt_compete_kernel<64>); break;
-    default: go(prompt_candidates_kernel<128>, prompt_compete_kernel<128>); break;
+    case 32: go(std::integral_constant<int, 32>{}); break;
+    case 64: go(std::integral_constant<int, 64>{}); break;
+    default: go(std::integral_constant<int, 128>{}); break;
   }
   return hipGetLastError();
 }

@@ -27,21 +27,24 @@ def keys(pattern, n, rng):
     return x.astype(np.float16)
 
 
-def check_selection(K, V, G, N, A):
-    """Flags, pools (slot by slot), counts and the stop flag of prompts K, V (fp16 [heads, n, 128], all quantized)."""
+def check_selection(K, V, G, N, A, units=None):
+    """Flags, pools (slot by slot), counts and the stop flag of prompts K, V (fp16 [heads, n, 128], all quantized).
+    `units`: that many units in the call, the prompts given taken in turn."""
     import torch
     from paper_2505_10938_amd import cache as KC
     heads, n, _ = K.shape
-    cache = KC.KVCache(KC.make_config(1, 1, heads, heads, n, 2, G, 128, 0, N, A))
-    cache.prefill(0, torch.from_numpy(K)[None].cuda(), torch.from_numpy(V)[None].cuda())
+    units = units or heads
+    of = torch.arange(units) % heads
+    cache = KC.KVCache(KC.make_config(1, 1, units, units, n, 2, G, 128, 0, N, A))
+    cache.prefill(0, torch.from_numpy(K).cuda()[of][None], torch.from_numpy(V).cuda()[of][None])
     torch.cuda.synchronize()
-    flags = cache.prefill_selected.cpu().numpy().reshape(-1)[:heads * n].reshape(heads, n)
+    flags = cache.prefill_selected.cpu().numpy().reshape(-1)[:units * n].reshape(units, n)
     slots = N + A
-    idx = cache.pool_idx.view(torch.int32).cpu().numpy()[:heads * slots].reshape(heads, slots)
-    score = cache.pool_score.view(torch.float64).cpu().numpy()[:heads * slots].reshape(heads, slots)
-    pk = cache.pool_k.view(torch.float16).cpu().numpy()[:heads * slots * 128].reshape(heads, slots, 128)
-    pv = cache.pool_v.view(torch.float16).cpu().numpy()[:heads * slots * 128].reshape(heads, slots, 128)
-    counts = [t.view(torch.int32).cpu().numpy()[:heads] for t in (cache.pool_count, cache.aux_count, cache.frozen)]
+    idx = cache.pool_idx.view(torch.int32).cpu().numpy()[:units * slots].reshape(units, slots)
+    score = cache.pool_score.view(torch.float64).cpu().numpy()[:units * slots].reshape(units, slots)
+    pk = cache.pool_k.view(torch.float16).cpu().numpy()[:units * slots * 128].reshape(units, slots, 128)
+    pv = cache.pool_v.view(torch.float16).cpu().numpy()[:units * slots * 128].reshape(units, slots, 128)
+    counts = [t.view(torch.int32).cpu().numpy()[:units] for t in (cache.pool_count, cache.aux_count, cache.frozen)]
     for h in range(heads):
         st = O.UnitState(128, 2, G, 128, N, A)
         want, fallen = [], []
@@ -49,21 +52,26 @@ def check_selection(K, V, G, N, A):
             had = {x["idx"] for x in st.aux}
             want.append(st.trace(K[h, i:i + G], V[h, i:i + G], i // G))
             fallen += sorted((x for x in st.aux if x["idx"] not in had), key=lambda x: (-x["score"], -x["idx"]))
-        want = np.concatenate(want)
-        assert np.array_equal(flags[h], want.astype(np.uint8))
-        assert [c[h] for c in counts] == [len(st.pool), len(st.aux), int(st.frozen)]
+        want = np.concatenate(want).astype(np.uint8)
+        scores = O.l1_scores(K[h])
         # the pool ascending by (score, index); what has fallen out by group, inside a group the largest key first
         ranked = sorted(st.pool, key=lambda x: (x["score"], x["idx"]))
-        for at, members in ((0, ranked), (N, fallen)):
-            m = len(members)
-            assert list(idx[h, at:at + m]) == [x["idx"] for x in members]
-            rows = idx[h, at:at + m]
-            assert np.array_equal(score[h, at:at + m], O.l1_scores(K[h])[rows])
-            assert np.array_equal(pk[h, at:at + m].view(np.uint16), K[h][rows].view(np.uint16))
-            assert np.array_equal(pv[h, at:at + m].view(np.uint16), V[h][rows].view(np.uint16))
+        for u in range(h, units, heads):
+            assert np.array_equal(flags[u], want)
+            assert [c[u] for c in counts] == [len(st.pool), len(st.aux), int(st.frozen)]
+            for at, members in ((0, ranked), (N, fallen)):
+                m = len(members)
+                assert list(idx[u, at:at + m]) == [x["idx"] for x in members]
+                rows = idx[u, at:at + m]
+                assert np.array_equal(score[u, at:at + m], scores[rows])
+                assert np.array_equal(pk[u, at:at + m].view(np.uint16), K[h][rows].view(np.uint16))
+                assert np.array_equal(pv[u, at:at + m].view(np.uint16), V[h][rows].view(np.uint16))
 
 
-@pytest.mark.parametrize("pattern", ["noise", "falling", "rising", "equal", "late", "saw", "teeth"])
+PATTERNS = ["noise", "falling", "rising", "equal", "late", "saw", "teeth"]
+
+
+@pytest.mark.parametrize("pattern", PATTERNS)
 @pytest.mark.parametrize("G,N,A,n", [
     (32, 8, 32, 1024), (32, 8, 32, 1056), (128, 64, 64, 1024 + 128), (64, 1, 0, 2048), (32, 64, 64, 8192 + 32),
     (128, 3, 64, 8192 + 1024 + 128), (32, 8, 64, 32), (32, 33, 7, 96),
@@ -72,6 +80,24 @@ def test_selection_of_a_prompt_equals_the_group_by_group_competition(G, N, A, n,
     rng = np.random.default_rng(n + N)
     K = np.stack([keys(pattern, n, rng) for _ in range(2)])
     check_selection(K, rng.standard_normal((2, n, 128)).astype(np.float16), G, N, A)
+
+
+@pytest.mark.parametrize("units,G,N,A,n", [
+    # a workgroup per unit and segment, then one per unit
+    (100, 64, 8, 32, 5120 + 64), (60, 32, 3, 64, 9216 + 32), (30, 128, 8, 64, 2048 + 128),
+    # one workgroup of 1024 threads per unit: few units that stop early, as many as there are compute units
+    (7, 32, 32, 16, 4096 + 32), (14, 128, 64, 0, 1024 + 128), (256, 32, 8, 16, 1024 + 32), (250, 128, 32, 32, 2048 + 128),
+    # 512 threads
+    (257, 32, 8, 16, 512 + 32), (257, 64, 8, 64, 2048 + 64), (300, 32, 1, 0, 2080), (513, 32, 8, 64, 4096 + 32),
+    (515, 128, 64, 64, 1024 + 128),
+    # 256 threads
+    (513, 32, 8, 32, 32), (513, 32, 8, 32, 160), (600, 64, 3, 32, 256), (1030, 32, 64, 64, 224), (520, 128, 32, 32, 128),
+    (520, 32, 0, 8, 64),
+])
+def test_selection_in_calls_of_many_units(units, G, N, A, n):
+    rng = np.random.default_rng(n + N)
+    K = np.stack([keys(p, n, rng) for p in PATTERNS])
+    check_selection(K, rng.standard_normal((len(PATTERNS), n, 128)).astype(np.float16), G, N, A, units)
 
 
 def plateau_keys(G, n, low, lower):
