@@ -611,24 +611,24 @@ __device__ __forceinline__ void compute_minichunk(McRegs<BITS, NV>& R, WaveAcc<G
   if (more) load_codes<BITS>(R.vc, P.vc, P, mc_next, lane);
 }
 
-// Full-precision rows (residual ring, then outlier-pool slots, then auxiliary slots) in groups of 16, both
-// products on the matrix cores: a K row is a B operand as it is; of the V rows a lane (m16, r) loads channels
-// 8 m16 .. 8 m16 + 7 of rows 4r .. 4r + 3, which are its share of the B operands of eight 16x16x16 products if
-// product e is given the channels 8n + e.  Rows 4r .. 4r + 3 of a result are those of head r % GQ, for scores and
-// weighted values alike, so the statistics of a lane's head stay in the lane.  A weight takes four rows, so that
-// none of the 24 bits of its fp32 value is lost (WeightParts).
-// With eight heads (rows 4r .. 4r + 3 of the scores: heads 2r and 2r + 1) four rows each would take two results per
-// channel, and 64 accumulators more beside the operands spill: the weighted values are
-// then formed on the vector units, in fp32, every lane summing its own four rows for all heads; the values of r are
-// added once, when the wavefront is through with its groups.
+// Full-precision rows (residual ring, then outlier-pool slots, then auxiliary slots) in groups of 16.  Scores on the
+// matrix cores: a K row is a B operand as it is.  Rows 4r .. 4r + 3 of the result are those of head r % GQ (with eight
+// heads: of 2r and 2r + 1), so that a lane keeps the statistics of its own head.  Of the V rows a lane (m16, r) loads
+// channels 8 m16 .. 8 m16 + 7 of rows 4r .. 4r + 3.
+// Two and four heads: that is its share of the B operands of eight 16x16x16 products if product e is given the channels
+// 8n + e; a weight takes four rows of the A operand, so that none of the 24 bits of its fp32 value is lost (WeightParts).
+// One head, and eight (for which four rows each would take two results per channel, and 64 accumulators more beside the
+// operands spill): on the vector units, in fp32, every lane summing its own four rows for all heads; the values of r
+// are added once, when the wavefront is through with its groups.
 // What bounds it is the chain load -> scores -> statistics -> weights -> products of a wavefront's one or two groups.
 // Us per pass, Values 4 bytes at a time on the vector units / 16 bytes at a time, vector units / four parts:
+//   one head: one sequence of 4k, 32 layers 376 / 320 / 328; 8 sequences, 4 layers 92.8 / 91.8 / 92.2
 //   four heads: 16 sequences of 301 .. 340 tokens, 40 steps 1069 / 924 / 868; batch 128 86.6 / 84.1 / 83.1
 //   eight heads: 8 sequences of 2k, 8 tokens at once 98.4 / 90.9 / 89.9; 16 of 8k 130 / 124 / 128, 4-bit 155 / 150 / 239
 template <int GQ>
 struct FpAcc {
-  static constexpr bool kParts = GQ < 8;
-  static constexpr int kHeads = kParts ? 1 : 2;                      // heads per lane
+  static constexpr bool kParts = GQ == 2 || GQ == 4;
+  static constexpr int kHeads = GQ == 8 ? 2 : 1;                     // heads per lane
   float m[kHeads], l[kHeads];
   // weighted values, channels 8 m16 + e: [e] the four parts of the lane's head, or [head][e] of rows 4r .. 4r + 3
   std::conditional_t<kParts, float4v[8], float[GQ][8]> o;
@@ -692,7 +692,9 @@ struct FpResult {
             v = r / kRowsOfHeads == part ? other : v;
           }
           o[i][k] = v;
-        } else {                                                     // over r: heads i, 2 + i, 4 + i, 6 + i to r = 0 .. 3
+        } else if constexpr (GQ == 1) {                              // over r: channels 2r, 2r + 1
+          o[i][k] = fold_rows(fold_halves(F.o[i][k], F.o[i][4 + k]), fold_halves(F.o[i][2 + k], F.o[i][6 + k]));
+        } else {                                                     // heads 2r, 2r + 1
           o[i][k] = fold_rows(fold_halves(F.o[i][k], F.o[4 + i][k]), fold_halves(F.o[2 + i][k], F.o[6 + i][k]));
         }
       }
@@ -852,8 +854,9 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
     } else {
 #pragma unroll
       for (int j = 0; j < GQ; ++j) {                               // (held by the lanes of r = j / 2)
-        const float al = __builtin_bit_cast(
-            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha[j % kHeads]), 16 * (j >> 1)));
+        const float al = GQ == 1 ? alpha[0]
+                                 : __builtin_bit_cast(float, __builtin_amdgcn_readlane(
+                                                                 __builtin_bit_cast(int, alpha[j % kHeads]), 16 * (j >> 1)));
 #pragma unroll
         for (int e = 0; e < 8; ++e) F.o[j][e] *= al;
       }
@@ -887,7 +890,8 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
   } else {
     float* prow = &L.sc()[0][0];                                   // weights of the 16 tokens, [GQ][16]
 #pragma unroll
-    for (int i = 0; i < kHeads; ++i) prow[FpResult<GQ>::head(r, i) * 16 + m16] = p[i];
+    for (int i = 0; i < kHeads; ++i)
+      if (GQ > 1 || r == 0) prow[FpResult<GQ>::head(r, i) * 16 + m16] = p[i];
     wave_sync();
     float4v pr[GQ];                                                // of the lane's rows
 #pragma unroll
