@@ -152,8 +152,9 @@ def _stream(stream):
         import torch
         # the current stream's handle without building a Stream object around it: 0.2 us per call, 2.9 us with one
         # (a decode step's call takes the host 9.0 us with it, and a launch on a short context the GPU 8 us)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw and device and torch.cuda.is_initialized():
+            return raw(device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
