@@ -6,6 +6,8 @@ libkvq.so through `binding`.
 """
 from __future__ import annotations
 
+import contextlib
+
 import torch
 
 from . import binding as B
@@ -15,6 +17,17 @@ def make_config(layers, batch, q_heads, kv_heads, max_seq, bits=2, group_k=32, g
                 outlier_budget=8, aux_capacity=32, head_dim=128, untraced_layers=0, value_per_step=0) -> B.kvq_config:
     return B.kvq_config(layers, batch, q_heads, kv_heads, head_dim, max_seq, bits, group_k, group_v, residual,
                         outlier_budget, aux_capacity, untraced_layers, value_per_step)
+
+
+def _on(stream, device):
+    """Context in which what torch allocates, fills and copies belongs to and is ordered on `stream` (as the calls
+    take it: None = torch's current stream, a stream object or a handle)."""
+    if stream is None:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        handle = stream if isinstance(stream, int) else stream.cuda_stream
+        stream = torch.cuda.ExternalStream(handle, device) if handle else torch.cuda.default_stream(device)
+    return torch.cuda.stream(stream)
 
 
 class KVCache:
@@ -165,15 +178,23 @@ class KVCache:
                 view[u0:u1, 0:n - first] = src[:, first:]
         self.n_res[layer] = n
 
+    def _need_prefill_selected(self, stream):
+        if getattr(self, "prefill_selected", None) is None:
+            with _on(stream, self.device):
+                self.prefill_selected = torch.zeros(max(int(self.sizes.prefill_selected_bytes), 16),
+                                                    dtype=torch.uint8, device=self.device)
+
+    def _new_output(self, q, stream):
+        with _on(stream, self.device):
+            return torch.empty_like(q)
+
     def prefill(self, layer, k_rows, v_rows, stream=None):
         """Quantize a whole prompt (fp16 [batch, kv_heads, n, head_dim], contiguous) into the empty cache
         of `layer`: the state that n appends would leave."""
         cfg = self.cfg
         n = k_rows.shape[2]
         assert self.n_quant[layer] == 0 and self.n_res[layer] == 0 and k_rows.is_contiguous() and v_rows.is_contiguous()
-        if getattr(self, "prefill_selected", None) is None:
-            self.prefill_selected = torch.zeros(max(int(self.sizes.prefill_selected_bytes), 16), dtype=torch.uint8,
-                                                device=self.device)
+        self._need_prefill_selected(stream)
         B.kvq_prefill_quantize(cfg, layer, k_rows, v_rows, n * cfg.head_dim, n, self.pool, self.prefill_selected,
                                self.qcache, self.res, stream)
         G, R = cfg.group_k, cfg.residual
@@ -183,7 +204,7 @@ class KVCache:
     def decode(self, layer, q, out=None, stream=None):
         """Attention output (fp16 [batch, q_heads, head_dim]) of one decode step."""
         if out is None:
-            out = torch.empty_like(q)
+            out = self._new_output(q, stream)
         B.kvq_decode_attention(self.cfg, layer, q, self.qcache, self.n_quant[layer], self.res,
                                self.res_start[layer], self.n_res[layer], self.pool, out, self.workspace,
                                self.workspace.numel(), stream)
@@ -193,11 +214,13 @@ class KVCache:
         """Attention outputs of the q.shape[1] newest tokens at once (q: fp16 [batch, tokens, q_heads,
         head_dim]; their Keys and Values are in the cache already), each attending up to itself."""
         if out is None:
-            out = torch.empty_like(q)
+            out = self._new_output(q, stream)
         tokens = q.shape[1]
         need = B.kvq_decode_workspace_bytes(self.cfg, tokens)
         if self.workspace.numel() < need:
-            self.workspace = torch.zeros(need, dtype=torch.uint8, device=self.device)
+            with _on(stream, self.device):
+                self.workspace.record_stream(torch.cuda.current_stream(self.device))   # an earlier call may be using it
+                self.workspace = torch.zeros(need, dtype=torch.uint8, device=self.device)
         B.kvq_decode_attention_multi(self.cfg, layer, q, tokens, self.qcache, self.n_quant[layer], self.res,
                                      self.res_start[layer], self.n_res[layer], self.pool, out, self.workspace,
                                      self.workspace.numel(), stream)
@@ -212,10 +235,11 @@ class KVCache:
         per sequence if rope_stride > 0): q and k_new are given unrotated and the library rotates them,
         inside the decode launch where there is one launch, with two small launches where the ring fills."""
         if out is None:
-            out = torch.empty_like(q)
+            out = self._new_output(q, stream)
         if self.n_res[layer] + 1 == self.cfg.residual + self.cfg.group_k:
             if rope is not None:
-                k_rot, q_rot = torch.empty_like(k_new), torch.empty_like(q)
+                with _on(stream, self.device):
+                    k_rot, q_rot = torch.empty_like(k_new), torch.empty_like(q)
                 B.kvq_rope_rotate(self.cfg, k_new, self.cfg.kv_heads, rope, rope_stride, k_rot, stream)
                 B.kvq_rope_rotate(self.cfg, q, self.cfg.q_heads, rope, rope_stride, q_rot, stream)
                 k_new, q = k_rot, q_rot
@@ -278,16 +302,15 @@ class RaggedKVCache(KVCache):
         n = k_rows[0].shape[1]
         G, R = cfg.group_k, cfg.residual
         nq = G * ((n - R) // G) if n >= R + G else 0
-        if getattr(self, "prefill_selected", None) is None:
-            self.prefill_selected = torch.zeros(max(int(self.sizes.prefill_selected_bytes), 16), dtype=torch.uint8,
-                                                device=self.device)
+        self._need_prefill_selected(stream)
         for layer in range(cfg.layers):
             k, v = k_rows[layer], v_rows[layer]
             assert k.shape == (cfg.kv_heads, n, cfg.head_dim) and k.is_contiguous() and v.is_contiguous()
             B.kvq_prefill_quantize_seq(cfg, layer, b, k, v, n * cfg.head_dim, n, self.pool, self.prefill_selected,
                                        self.qcache, self.res, stream)
         state = torch.tensor([nq, 0, n - nq, 1 if active else 0], dtype=torch.int32)
-        self.seq_state[b].copy_(state.to(self.device), non_blocking=False)
+        with _on(stream, self.device):
+            self.seq_state[b].copy_(state.to(self.device), non_blocking=False)
         self.longest = max(self.longest, n)
 
     def advance(self, stream=None):
@@ -299,7 +322,8 @@ class RaggedKVCache(KVCache):
         """Deal the decode launches of the next step by the sequences' current lengths (once per step,
         after advance(); then decode(..., planned=True) for every layer)."""
         if getattr(self, "plan", None) is None:
-            self.plan = torch.zeros(B.kvq_seq_plan_bytes(self.cfg) // 4, dtype=torch.int32, device=self.device)
+            with _on(stream, self.device):
+                self.plan = torch.zeros(B.kvq_seq_plan_bytes(self.cfg) // 4, dtype=torch.int32, device=self.device)
         nq, nr = self.bounds()
         B.kvq_seq_plan(self.cfg, self.seq_state, nq, nr, self.plan, stream)
 
@@ -312,7 +336,7 @@ class RaggedKVCache(KVCache):
 
     def decode(self, layer, q, out=None, stream=None, planned=False):
         if out is None:
-            out = torch.empty_like(q)
+            out = self._new_output(q, stream)
         nq, nr = self.bounds()
         if planned:
             B.kvq_decode_attention_planned(self.cfg, layer, q, self.qcache, self.res, self.plan, nq, nr, self.pool, out,
