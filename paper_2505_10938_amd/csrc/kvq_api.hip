@@ -59,8 +59,10 @@ int64_t res_rows_of(const kvq_config* c) {
 struct Split {
   int32_t splits, nw, mc_per_split;
 };
-// A unit has at most so many workgroups when a launch has more units than compute units: the partial results of
-// all (8 rows of 130 floats each) stay below 4 MiB, the size of the library's own scratch array.
+// A split launch has at most so many workgroups in all: their partial results (8 rows of 130 floats each) and the
+// units' counters stay below 4 MiB, the size of the library's own scratch array.  (It binds only with more units than
+// compute units, where 1024 workgroups of two wavefronts would be resident.  The static entry point asks for room for
+// a launch plan's partial results too, which can be more: 1024 for 300 sequences of one kv head.)
 constexpr int64_t kMaxSplitWorkgroups = 960;
 int64_t waves_per_compute_unit(int g, int vgroups) {
   int64_t w = kvq::kLdsPerComputeUnit / kvq::decode_wave_lds_bytes(g, vgroups);

@@ -11,14 +11,15 @@ from tests import test_gpu_parity as P
 COMPUTE_UNITS, WAVES = 256, 8
 
 
-@pytest.mark.parametrize("units", [1, 8, 37, 92, 128, 148, 184, 255, 256, 257, 304, 341, 400, 513, 600, 1024, 1500, 3000])
+@pytest.mark.parametrize("units", [1, 8, 37, 92, 128, 148, 184, 255, 256, 257, 304, 341, 400, 512, 513, 600, 1024, 1500, 3000])
 @pytest.mark.parametrize("g", [1, 4, 8])
 def test_every_state_fits_and_is_resident(units, g):
     rng = random.Random(units * 16 + g)
     for G, R, N, A in ((32, 128, 8, 32), (128, 32, 3, 64), (64, 0, 0, 0), (32, 4096, 8, 32)):
         top = 32768
         cfg = KC.make_config(1, units, g, 1, top, 2, G, 32, R, N, A)
-        room = B.kvq_decode_workspace_bytes(cfg, 1) - (units * 4 + 255) // 256 * 256
+        counters = (units * 4 + 255) // 256 * 256
+        room = B.kvq_decode_workspace_bytes(cfg, 1) - counters
         if units <= 960:
             assert room <= 2048 * g * 130 * 4
         states = [0, G, 128, 1024, 4096, 4224, top] + [G * rng.randrange(top // G + 1) for _ in range(40)]
@@ -27,6 +28,8 @@ def test_every_state_fits_and_is_resident(units, g):
                 splits, waves, per = B.kvq_decode_launch_shape(cfg, 1, n_quant, fp_rows)
                 assert 1 <= waves <= WAVES and splits >= 1 and splits * per * 128 >= n_quant
                 assert units * splits * g * 130 * 4 <= room
+                if splits > 1:                     # the library's own scratch array, 4 MiB, would hold what is exchanged
+                    assert counters + units * splits * g * 130 * 4 <= 4 << 20
                 if units <= COMPUTE_UNITS * WAVES:
                     assert units * splits <= COMPUTE_UNITS * (WAVES // waves)
 
