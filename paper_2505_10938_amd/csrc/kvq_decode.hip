@@ -143,7 +143,8 @@ KVQ_ROW_REDUCE(row16_sum, "v_add_f32_dpp")
 __device__ __forceinline__ float row16_lane(float v, int l) {
   const int w = __builtin_bit_cast(int, v);
   switch (l) {
-#define KVQ_LANE(N) case N: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, w, 0x150 + N /* row_newbcast */, 0xf, 0xf, false));
+#define KVQ_LANE(N) /* row_newbcast */ \
+  case N: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, w, 0x150 + N, 0xf, 0xf, false));
     KVQ_LANE(0) KVQ_LANE(1) KVQ_LANE(2) KVQ_LANE(3) KVQ_LANE(4) KVQ_LANE(5) KVQ_LANE(6) KVQ_LANE(7)
     KVQ_LANE(8) KVQ_LANE(9) KVQ_LANE(10) KVQ_LANE(11) KVQ_LANE(12) KVQ_LANE(13) KVQ_LANE(14) KVQ_LANE(15)
 #undef KVQ_LANE
@@ -854,9 +855,9 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
     } else {
 #pragma unroll
       for (int j = 0; j < GQ; ++j) {                               // (held by the lanes of r = j / 2)
-        const float al = GQ == 1 ? alpha[0]
-                                 : __builtin_bit_cast(float, __builtin_amdgcn_readlane(
-                                                                 __builtin_bit_cast(int, alpha[j % kHeads]), 16 * (j >> 1)));
+        const int al_bits = __builtin_bit_cast(int, alpha[j % kHeads]);
+        const float al = __builtin_bit_cast(
+            float, GQ == 1 ? al_bits : __builtin_amdgcn_readlane(al_bits, 16 * (j >> 1)));
 #pragma unroll
         for (int e = 0; e < 8; ++e) F.o[j][e] *= al;
       }
@@ -1201,10 +1202,10 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   // Thread = C channels of one row.  All values are asked for at once; meanwhile the weights of the results
   // (lane & 15 = result) are formed inside rows of 16 lanes and handed round there.  What bounds it is the chain
   // of LDS latencies; a loop over the results took one per result: 16 sequences of 301 .. 340 tokens 945 -> 920 us for
-  // 40 steps, a ragged batch 108.5 -> 104.6 us, one sequence of 4k 370 -> 361 us, batch 128 85.4 -> 84.1 us.  C: few enough channels that the threads suffice for all rows
-  // in about one pass, so that the copies of the weights' arithmetic are few as well (with eight wavefronts and
-  // four rows, C = 1 / 2 / 4: 940 / 911 / 912 us in the first workload; one row, C = 1 / 4: 361 / 376 us for one
-  // sequence of 4k).
+  // 40 steps, a ragged batch 108.5 -> 104.6 us, one sequence of 4k 370 -> 361 us, batch 128 85.4 -> 84.1 us.
+  // C: few enough channels that the threads suffice for all rows in about one pass, so that the copies of the weights'
+  // arithmetic are few as well (with eight wavefronts and four rows, C = 1 / 2 / 4: 940 / 911 / 912 us in the first
+  // workload; one row, C = 1 / 4: 361 / 376 us for one sequence of 4k).
   auto merge_rows = [&](auto channels, auto slots) {
     constexpr int C = decltype(channels)::value;
     constexpr int SLOTS = decltype(slots)::value;          // at least the 2 nw results

@@ -267,26 +267,6 @@ __device__ __forceinline__ void compete(Loaded<G>& in, const Dims& d, int group_
     *p.pool_count = n_old - n_ev + n_new;
     *p.aux_count = n_aux + n_ev;
   }
-  in.n_old = n_old - n_ev + n_new;
-  in.n_aux = n_aux + n_ev;
-}
-
-// Loads for the next group of the same unit inside one kernel: the stored scores and indices as
-// they stand after the previous competition (whose stores were completed and ordered by the
-// caller) and the next group's Key rows; the counts and the frozen flag are carried in `in`.
-template <int G>
-__device__ __forceinline__ void load_next(Loaded<G>& in, const Dims& d, const UnitPool& p, const __half* gk, int tid) {
-  in.old_score = 0.0;
-  in.old_idx = 0;
-  if (tid < d.N) {
-    in.old_score = __hip_atomic_load(&p.psc[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    in.old_idx = __hip_atomic_load(&p.pidx[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
-  const int team = (tid & (kWorkers - 1)) >> 4, sub = tid & 15;
-  if (tid < kWorkers) {
-#pragma unroll
-    for (int q = 0; q < G / 16; ++q) in.kr[q] = *(const uint4*)(gk + (q * 16 + team) * kHeadDim + sub * 8);
-  }
 }
 
 }  // namespace trace_core
