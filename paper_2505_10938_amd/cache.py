@@ -219,7 +219,8 @@ class KVCache:
         need = B.kvq_decode_workspace_bytes(self.cfg, tokens)
         if self.workspace.numel() < need:
             with _on(stream, self.device):
-                self.workspace.record_stream(torch.cuda.current_stream(self.device))   # an earlier call may be using it
+                if stream is not None:             # an earlier call on it may still be using the old one
+                    self.workspace.record_stream(torch.cuda.current_stream(self.device))
                 self.workspace = torch.zeros(need, dtype=torch.uint8, device=self.device)
         B.kvq_decode_attention_multi(self.cfg, layer, q, tokens, self.qcache, self.n_quant[layer], self.res,
                                      self.res_start[layer], self.n_res[layer], self.pool, out, self.workspace,
