@@ -614,44 +614,47 @@ __device__ __forceinline__ void compute_minichunk(McRegs<BITS, NV>& R, WaveAcc<G
 
 // Full-precision rows (residual ring, then outlier-pool slots, then auxiliary slots) in groups of 16.  Scores on the
 // matrix cores: a K row is a B operand as it is.  Rows 4r .. 4r + 3 of the result are those of head r % GQ (with eight
-// heads: of 2r and 2r + 1), so that a lane keeps the statistics of its own head.  Of the V rows a lane (m16, r) loads
-// channels 8 m16 .. 8 m16 + 7 of rows 4r .. 4r + 3.
-// Two and four heads: that is its share of the B operands of eight 16x16x16 products if product e is given the channels
-// 8n + e; a weight takes four rows of the A operand, so that none of the 24 bits of its fp32 value is lost (WeightParts).
-// One head, and eight (for which four rows each would take two results per channel, and 64 accumulators more beside the
-// operands spill): on the vector units, in fp32, every lane summing its own four rows for all heads; the values of r
-// are added once, when the wavefront is through with its groups.
+// heads: of 2r and 2r + 1), so that a lane keeps the statistics of its own heads.  Of the V rows a lane (m16, r) loads
+// channels 8 m16 .. 8 m16 + 7 of rows 4r .. 4r + 3, and the weighted values are formed
+//  - on the matrix cores (MATRIX): that is its share of the B operands of eight 16x16x16 products if product e is given
+//    the channels 8n + e.  A weight takes four rows of the A operand, so that none of the 24 bits of its fp32 value is
+//    lost (WeightParts); with eight heads two rows each of two products, of which the second is scaled into the first.
+//  - or on the vector units, in fp32, every lane summing its own four rows for all heads; the values of r are added
+//    once, when the wavefront is through with its groups.
 // What bounds it is the chain load -> scores -> statistics -> weights -> products of a wavefront's one or two groups.
-// Us per pass, Values 4 bytes at a time on the vector units / 16 bytes at a time, vector units / four parts:
+// Us per pass, Values 4 bytes at a time on the vector units / 16 bytes at a time, vector units / matrix cores:
 //   one head: one sequence of 4k, 32 layers 376 / 320 / 328; 8 sequences, 4 layers 92.8 / 91.8 / 92.2
-//   four heads: 16 sequences of 301 .. 340 tokens, 40 steps 1069 / 924 / 868; batch 128 86.6 / 84.1 / 83.1
-//   eight heads: 8 sequences of 2k, 8 tokens at once 98.4 / 90.9 / 89.9; 16 of 8k 130 / 124 / 128, 4-bit 155 / 150 / 239
-template <int GQ>
+//   four heads: 16 sequences of 301 .. 340 tokens, 40 steps 1071 / 924 / 867; batch 128 86.6 / 84.1 / 83.1
+//   eight heads: 16 sequences of 400 tokens 57.4 / 48.5 / 44.0; 8 sequences of 2k, 8 tokens at once 97.6 / 90.3 / 86.1
+//   eight heads, 4-bit (whose instances spill with the second product): 16 of 8k 153 / 146 / 155
+// hence the vector units for one head, and for eight with 4-bit codes.
+template <int GQ, int BITS>
+constexpr bool fp_on_matrix_cores() { return GQ > 1 && !(GQ == 8 && BITS == 4); }
+template <int GQ, bool MATRIX>
 struct FpAcc {
-  static constexpr bool kParts = GQ == 2 || GQ == 4;
   static constexpr int kHeads = GQ == 8 ? 2 : 1;                     // heads per lane
   float m[kHeads], l[kHeads];
-  // weighted values, channels 8 m16 + e: [e] the four parts of the lane's head, or [head][e] of rows 4r .. 4r + 3
-  std::conditional_t<kParts, float4v[8], float[GQ][8]> o;
+  // weighted values of channel 8 m16 + e: [e] the parts of the lane's heads, or [head][e] of rows 4r .. 4r + 3
+  std::conditional_t<MATRIX, float4v[8], float[GQ][8]> o;
 };
 // A weight p <= 1 as fp16 numbers: p 2^15 = a + b + (c + d) 2^-22 with a the rounded value, b the rounded rest, c and d
 // the same of what then remains: exact for p >= 2^-38, off by 2^-62 at most below.  (As hi + lo of p itself it would
 // lose bits from 2^-14 down and vanish below 2^-25.)  sum() is the weighted sum from those of the parts; an infinite
 // Value makes an infinity of the first part's and a NaN of those whose part of the weight is zero.
+constexpr float kLowParts = 0x1p-22f;
 struct WeightParts {
   _Float16 part[4];
   __device__ __forceinline__ explicit WeightParts(float p) {
-    float rest = p * 32768.f;
+    float rest = p * 0x1p15f;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      if (k == 2) rest *= 4194304.f;
+      if (k == 2) rest *= 1.f / kLowParts;
       part[k] = (_Float16)rest;
       rest -= (float)part[k];
     }
   }
-  static __device__ __forceinline__ float sum(const float4v& v) {
-    const float all = (v[0] + v[1]) * 0x1p-15f + (v[2] + v[3]) * 0x1p-37f;
-    return __builtin_fabsf(v[0]) == __builtin_inff() ? v[0] : all;
+  static __device__ __forceinline__ float sum(float first, float others) {
+    return __builtin_fabsf(first) == __builtin_inff() ? first : (first + others) * 0x1p-15f;
   }
 };
 // lanes 0 .. 31: a + a of lane ^ 32; lanes 32 .. 63: b + b of lane ^ 32
@@ -669,33 +672,37 @@ __device__ __forceinline__ float fold_rows(float a, float b) {
   return __builtin_bit_cast(float, s0) + __builtin_bit_cast(float, s1);
 }
 // The sums over all rows, each value held by one lane only: what is kept while the quantized tokens are worked on.
-template <int GQ>
+template <int GQ, bool MATRIX>
 struct FpResult {
-  static constexpr int kHeads = FpAcc<GQ>::kHeads;
+  static constexpr int kHeads = FpAcc<GQ, MATRIX>::kHeads;
   static constexpr int kRowsOfHeads = GQ < 4 ? GQ : 4;               // values of r that differ in their heads
   static constexpr int kTiles = 2 * kRowsOfHeads;                    // channels kept per lane and head
   float m[kHeads], l[kHeads];
   float o[kHeads][kTiles];
   static __device__ __forceinline__ int head(int r, int i) { return kHeads * (r % kRowsOfHeads) + i; }
   static __device__ __forceinline__ int first_tile(int r) { return kTiles * (r / kRowsOfHeads); }
-  __device__ __forceinline__ void take(const FpAcc<GQ>& F, int r) {
+  __device__ __forceinline__ void take(const FpAcc<GQ, MATRIX>& F, int r) {
 #pragma unroll
     for (int i = 0; i < kHeads; ++i) {
       m[i] = F.m[i];
       l[i] = F.l[i];
 #pragma unroll
       for (int k = 0; k < kTiles; ++k) {
-        if constexpr (FpAcc<GQ>::kParts) {
-          float v = WeightParts::sum(F.o[k]);
+        if constexpr (MATRIX && GQ == 8) {
+          o[i][k] = WeightParts::sum(F.o[k][2 * i], F.o[k][2 * i + 1]);
+        } else if constexpr (MATRIX) {
+          auto sum = [](const float4v& v) { return WeightParts::sum(v[0], v[1] + (v[2] + v[3]) * kLowParts); };
+          float v = sum(F.o[k]);
 #pragma unroll
           for (int part = 1; part < 8 / kTiles; ++part) {
-            const float other = WeightParts::sum(F.o[part * kTiles + k]);
+            const float other = sum(F.o[part * kTiles + k]);
             v = r / kRowsOfHeads == part ? other : v;
           }
           o[i][k] = v;
         } else if constexpr (GQ == 1) {                              // over r: channels 2r, 2r + 1
           o[i][k] = fold_rows(fold_halves(F.o[i][k], F.o[i][4 + k]), fold_halves(F.o[i][2 + k], F.o[i][6 + k]));
         } else {                                                     // heads 2r, 2r + 1
+          static_assert(GQ == 8);
           o[i][k] = fold_rows(fold_halves(F.o[i][k], F.o[4 + i][k]), fold_halves(F.o[2 + i][k], F.o[6 + i][k]));
         }
       }
@@ -773,8 +780,8 @@ __device__ __forceinline__ bool fp_row_ok(const DecodeArgs& a, const Seq& sq, co
   return slot < a.d.N ? (slot < n_pool) : (slot < a.d.pool_slots && slot - a.d.N < n_aux);
 }
 
-template <int GQ, int NV, bool ROPE>
-__device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, NV>& L, const DecodeArgs& a,
+template <int GQ, int NV, bool ROPE, bool MATRIX>
+__device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ, MATRIX>& F, WaveLds<GQ, NV>& L, const DecodeArgs& a,
                                            const Seq& sq, const FpLayout& f, int n_pool, int n_aux, int r0,
                                            uint32_t k_new_word, uint32_t v_new_word, int lane) {
   const int m16 = lane & 15, r = lane >> 4;
@@ -812,8 +819,8 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
   };
   // which of the 16 rows hold a token, as a wave-uniform bit mask (lanes 0..15 are rows 0..15)
   const uint32_t ok_rows = (uint32_t)__ballot(okk) & 0xFFFFu;
-  constexpr int kHeads = FpResult<GQ>::kHeads;
-  constexpr int kRowsOfHeads = FpResult<GQ>::kRowsOfHeads;
+  constexpr int kHeads = FpResult<GQ, MATRIX>::kHeads;
+  constexpr int kRowsOfHeads = FpResult<GQ, MATRIX>::kRowsOfHeads;
   // rows of the scores: hi and lo of the query, twice where a lane has one head
   const int qrow = kHeads == 2 ? m16 : 2 * ((m16 >> 2) % kRowsOfHeads) + (m16 & 1);
   float4v D = {0.f, 0.f, 0.f, 0.f};
@@ -836,7 +843,7 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
 #pragma unroll
   for (int i = 0; i < kHeads; ++i) {
     const float s = D[2 * i] + D[2 * i + 1];
-    red[i] = x[i] = seen_by(FpResult<GQ>::head(r, i)) ? s : kNegBig;
+    red[i] = x[i] = seen_by(FpResult<GQ, MATRIX>::head(r, i)) ? s : kNegBig;
     above |= x[i] > F.m[i];
   }
   if (__any(above)) {                                              // wave-uniform
@@ -849,9 +856,9 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
       F.m[i] = m;
       F.l[i] *= alpha[i];
     }
-    if constexpr (FpAcc<GQ>::kParts) {
+    if constexpr (MATRIX) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) F.o[e] *= alpha[0];
+      for (int e = 0; e < 8; ++e) F.o[e] *= float4v{alpha[0], alpha[0], alpha[kHeads - 1], alpha[kHeads - 1]};
     } else {
 #pragma unroll
       for (int j = 0; j < GQ; ++j) {                               // (held by the lanes of r = j / 2)
@@ -871,15 +878,25 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
   row16_sum(red);
 #pragma unroll
   for (int i = 0; i < kHeads; ++i) F.l[i] += red[i];
-  if constexpr (FpAcc<GQ>::kParts) {
-    _Float16* prow = (_Float16*)&L.sc()[0][0];                     // parts of the 16 tokens' weights, [heads][4][16]
-    const WeightParts w(p[0]);
-    if (kRowsOfHeads == 4 || r < kRowsOfHeads) {
+  if constexpr (MATRIX) {
+    // parts of the 16 tokens' weights as rows of 16: [heads][4], or the high and behind them the low ones, [2][heads][2]
+    constexpr int kRows = kHeads == 2 ? 16 : 4 * kRowsOfHeads;
+    _Float16* prow = (_Float16*)&L.sc()[0][0];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) prow[(4 * r + k) * 16 + m16] = w.part[k];
+    for (int i = 0; i < kHeads; ++i) {
+      const WeightParts w(p[i]);
+      if (kRowsOfHeads == 4 || r < kRowsOfHeads) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int row = kHeads == 2 ? 16 * (k >> 1) + 4 * r + 2 * i + (k & 1) : 4 * r + k;
+          prow[row * 16 + m16] = w.part[k];
+        }
+      }
     }
     wave_sync();
-    const half4 ap = *(const half4*)(prow + (m16 % (4 * kRowsOfHeads)) * 16 + 4 * r);
+    const half4 ap = *(const half4*)(prow + (m16 % kRows) * 16 + 4 * r);
+    half4 ap_low;
+    if constexpr (kHeads == 2) ap_low = *(const half4*)(prow + (16 + m16) * 16 + 4 * r);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;  // the low / high halves of two words
@@ -887,12 +904,18 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ>& F, WaveLds<GQ, 
       v[0] = __builtin_amdgcn_perm(X.vf[1][e >> 1], X.vf[0][e >> 1], (e & 1) ? kHigh : kLow);
       v[1] = __builtin_amdgcn_perm(X.vf[3][e >> 1], X.vf[2][e >> 1], (e & 1) ? kHigh : kLow);
       F.o[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(ap, __builtin_bit_cast(half4, v), F.o[e], 0, 0, 0);
+      if constexpr (kHeads == 2) {                                 // (the first part's sums stay as they are)
+        const float4v zero = {0.f, 0.f, 0.f, 0.f};
+        const float4v low = __builtin_amdgcn_mfma_f32_16x16x16f16(ap_low, __builtin_bit_cast(half4, v), zero, 0, 0, 0);
+        F.o[e][1] += (low[0] + low[1]) * kLowParts;
+        F.o[e][3] += (low[2] + low[3]) * kLowParts;
+      }
     }
   } else {
     float* prow = &L.sc()[0][0];                                   // weights of the 16 tokens, [GQ][16]
 #pragma unroll
     for (int i = 0; i < kHeads; ++i)
-      if (GQ > 1 || r == 0) prow[FpResult<GQ>::head(r, i) * 16 + m16] = p[i];
+      if (GQ > 1 || r == 0) prow[FpResult<GQ, MATRIX>::head(r, i) * 16 + m16] = p[i];
     wave_sync();
     float4v pr[GQ];                                                // of the lane's rows
 #pragma unroll
@@ -1074,16 +1097,17 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   }
 
   // ---- full-precision part, while the first quantized loads are in flight --------------------------
-  FpAcc<GQ> F;
+  constexpr bool MATRIX = fp_on_matrix_cores<GQ, BITS>();
+  FpAcc<GQ, MATRIX> F;
 #pragma unroll
-  for (int i = 0; i < FpAcc<GQ>::kHeads; ++i) {
+  for (int i = 0; i < FpAcc<GQ, MATRIX>::kHeads; ++i) {
     F.m[i] = kNegBig;
     F.l[i] = 0.f;
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    if constexpr (FpAcc<GQ>::kParts) {
-      F.o[e] = float4v{0.f, 0.f, 0.f, 0.f};
+    if constexpr (MATRIX) {
+      F.o[e] = 0.f;
     } else {
 #pragma unroll
       for (int j = 0; j < GQ; ++j) F.o[j][e] = 0.f;
@@ -1100,14 +1124,14 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   if (has_fp) {
     n_pool = __builtin_amdgcn_readfirstlane(n_pool);
     n_aux = __builtin_amdgcn_readfirstlane(n_aux);
-    fp_compute<GQ, NV, ROPE>(X, F, L, a, sq, fl, n_pool, n_aux, r0, k_new_word, v_new_word, lane);
+    fp_compute<GQ, NV, ROPE, MATRIX>(X, F, L, a, sq, fl, n_pool, n_aux, r0, k_new_word, v_new_word, lane);
     for (rg += unit_waves; rg < n_rg; rg += unit_waves) {          // the wavefront's further groups
       fp_load(X, a, sq, fl, u, k_new_row, rg, lane);
-      fp_compute<GQ, NV, ROPE>(X, F, L, a, sq, fl, n_pool, n_aux, r0, k_new_word, v_new_word, lane);
+      fp_compute<GQ, NV, ROPE, MATRIX>(X, F, L, a, sq, fl, n_pool, n_aux, r0, k_new_word, v_new_word, lane);
     }
   }
 
-  FpResult<GQ> fp;
+  FpResult<GQ, MATRIX> fp;
   fp.take(F, r);
 
   WaveAcc<GQ> S;
@@ -1180,12 +1204,12 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
     }
   }
 #pragma unroll
-  for (int i = 0; i < FpResult<GQ>::kHeads; ++i) {
-    const int j = FpResult<GQ>::head(r, i);
-    float* row = &mg.o[((nw + wave) * GQ + j) * kHeadDim + 8 * m16 + FpResult<GQ>::first_tile(r)];
+  for (int i = 0; i < FpResult<GQ, MATRIX>::kHeads; ++i) {
+    const int j = FpResult<GQ, MATRIX>::head(r, i);
+    float* row = &mg.o[((nw + wave) * GQ + j) * kHeadDim + 8 * m16 + FpResult<GQ, MATRIX>::first_tile(r)];
 #pragma unroll
-    for (int k = 0; k < FpResult<GQ>::kTiles; k += 2) *(float2*)(row + k) = float2{fp.o[i][k], fp.o[i][k + 1]};
-    if (m16 == 0 && r < FpResult<GQ>::kRowsOfHeads) {
+    for (int k = 0; k < FpResult<GQ, MATRIX>::kTiles; k += 2) *(float2*)(row + k) = float2{fp.o[i][k], fp.o[i][k + 1]};
+    if (m16 == 0 && r < FpResult<GQ, MATRIX>::kRowsOfHeads) {
       mg.m[(nw + wave) * GQ + j] = fp.m[i];
       mg.l[(nw + wave) * GQ + j] = fp.l[i];
     }

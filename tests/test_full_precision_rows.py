@@ -9,15 +9,15 @@ from paper_2505_10938_amd import binding as B, cache as KC
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("g", [1, 2, 4, 8])
+@pytest.mark.parametrize("g,bits", [(1, 2), (2, 2), (4, 2), (8, 2), (8, 4)])
 @pytest.mark.parametrize("drop", [12.3, 16.5, 20.7, 24.5, 26.0, 34.0])
-def test_many_tokens_of_small_weight(g, drop):
+def test_many_tokens_of_small_weight(g, bits, drop):
     """One token that takes nearly all the weight and has Values of zero, 3999 tokens of 2^-drop of it whose Values
     make up the whole output.  The output is 4000 equal terms in fp32 and one rounding to fp16: a relative error of
     2^-11, and of the weights what their scores are off by, |score| 2^-22 < 1e-5."""
     import torch
     n, kv_heads = 4000, 2
-    cache = KC.KVCache(KC.make_config(1, 1, g * kv_heads, kv_heads, 32, 2, 32, 32, 4096, 8, 32))
+    cache = KC.KVCache(KC.make_config(1, 1, g * kv_heads, kv_heads, 32, bits, 32, 32, 4096, 8, 32))
     K = np.zeros((kv_heads, n, 128), np.float16)
     K[:, 1234, 0] = drop * math.sqrt(128) / math.log2(math.e)
     V = np.full((kv_heads, n, 128), 30000.0, np.float16) * np.linspace(0.5, 1.0, 128).astype(np.float16)
@@ -32,13 +32,13 @@ def test_many_tokens_of_small_weight(g, drop):
     assert np.all(np.abs(out - want) <= 2.0 ** -11 * 1.02 * np.abs(want) + 2.0 ** -25)
 
 
-def plant_and_compare(batch, kv_heads, g, context, residual, splits, waves):
+def plant_and_compare(batch, kv_heads, g, context, residual, splits, waves, bits=2):
     """An infinite Value in one channel of one full-precision row is an infinity in that channel of the outputs that
     attend to the row, and changes nothing else."""
     import torch
     G = 32
     nq = G * ((context - residual) // G) if context >= residual + G else 0
-    cfg = KC.make_config(1, batch, g * kv_heads, kv_heads, max(nq, G), 2, G, 32, residual, 8, 32)
+    cfg = KC.make_config(1, batch, g * kv_heads, kv_heads, max(nq, G), bits, G, 32, residual, 8, 32)
     assert B.kvq_decode_launch_shape(cfg, 1, nq, context - nq + 40)[:2] == (splits, waves)
     cache = KC.KVCache(cfg)
     gen = torch.Generator(device="cuda")
@@ -64,8 +64,9 @@ def plant_and_compare(batch, kv_heads, g, context, residual, splits, waves):
     (128, 8, 1, 150, 128, 1, 2), (64, 8, 2, 150, 128, 1, 4), (64, 8, 4, 1100, 128, 1, 4), (64, 8, 8, 300, 128, 1, 4),
     (1, 1, 1, 400, 128, 1, 8), (1, 4, 8, 400, 128, 1, 8), (1, 1, 4, 4200, 128, 8, 8),
 ])
-def test_infinite_value_in_a_full_precision_row(batch, kv_heads, g, context, residual, splits, waves):
-    plant_and_compare(batch, kv_heads, g, context, residual, splits, waves)
+@pytest.mark.parametrize("bits", [2, 4])
+def test_infinite_value_in_a_full_precision_row(batch, kv_heads, g, context, residual, splits, waves, bits):
+    plant_and_compare(batch, kv_heads, g, context, residual, splits, waves, bits)
 
 
 @pytest.mark.parametrize("batch,kv_heads,g,context,residual,splits,waves", [
