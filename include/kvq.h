@@ -257,6 +257,11 @@ int32_t kvq_quantize_value_tokens(const kvq_config* cfg, int32_t layer, int32_t 
  *              cache while |q_c| * step_c < 32 000 for every channel c and Key group
  *              (step = the group's quantization step of that channel) and every Value step < 4000;
  *              beyond that an operand overflows fp16 and outputs become infinite or NaN
+ *              The softmax weights of the full-precision rows (ring and pools) and their sums are
+ *              fp32 in precision (24 bits; a weight below 2^-38 of the largest is off by 2^-62 at
+ *              most).  An infinite Value in such a row, of a token whose weight is above 2^-40 of the
+ *              largest, makes that channel of the outputs infinite and changes nothing else; Keys and
+ *              quantized rows must be finite
  *   out      : device fp16 [batch][q_heads][head_dim]
  *   workspace: device scratch of at least kvq_sizes.workspace_bytes, 256-byte aligned.  It must
  *              be zero-filled once before its first use; every call leaves the part it relies on
