@@ -74,7 +74,7 @@ PATTERNS = ["noise", "falling", "rising", "equal", "late", "saw", "teeth"]
 @pytest.mark.parametrize("pattern", PATTERNS)
 @pytest.mark.parametrize("G,N,A,n", [
     (32, 8, 32, 1024), (32, 8, 32, 1056), (128, 64, 64, 1024 + 128), (64, 1, 0, 2048), (32, 64, 64, 8192 + 32),
-    (128, 3, 64, 8192 + 1024 + 128), (32, 8, 64, 32), (32, 33, 7, 96),
+    (128, 3, 64, 8192 + 1024 + 128), (32, 8, 64, 32), (32, 33, 7, 96), (32, 8, 32, 20480),
 ])
 def test_selection_of_a_prompt_equals_the_group_by_group_competition(G, N, A, n, pattern):
     rng = np.random.default_rng(n + N)
