@@ -941,16 +941,17 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ, MATRIX>& F, Wave
 template <int GQ, int BITS, int NV, bool PAGED, int SB, bool ROPE>
 __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* smem, int& s_last, int entry) {
   const Dims& d = a.d;
-  // Every argument the loads below depend on is fetched here, in one round trip (left to
-  // itself the compiler fetches an argument where it is first used, and each such place waits
-  // for everything that is in flight on the scalar side).
+  // Every argument the loads below depend on is fetched here, in one round trip of 1.2 us: a launch
+  // finds none of them in the scalar cache.  (Left to itself the compiler fetches an argument where it
+  // is first used, and each such place waits for everything that is in flight on the scalar side.  No
+  // test of an argument may come ahead of this point: what follows it would wait for a trip of its own.)
   asm volatile("" ::"s"(a.nw), "s"(a.splits), "s"(a.head_parts), "s"(a.mc_per_split), "s"(a.n_quant), "s"(a.res_start),
                "s"(a.n_res), "s"(d.kv_heads), "s"(d.q_heads), "s"(d.unit0), "s"(d.pool_slots), "s"(d.res_rows), "s"(d.N),
                "s"(d.bpg_shift), "s"(d.block_bytes), "s"(d.blocks_per_unit), "s"(d.groups_per_unit), "s"(a.q),
                "s"(a.k_codes), "s"(a.k_meta), "s"(a.v_codes), "s"(a.v_meta), "s"(a.mask), "s"(a.k_res), "s"(a.v_res),
                "s"(a.pool_k), "s"(a.pool_v), "s"(a.pool_count), "s"(a.aux_count), "s"(a.seq));
   asm volatile("" ::"s"(a.k_new), "s"(a.v_new), "s"(d.page_table), "s"(d.table_stride), "s"(d.n_pages), "s"(d.plane0),
-               "s"(a.q_tokens), "s"(a.g_shift));
+               "s"(a.q_tokens), "s"(a.g_shift), "s"(a.plan), "s"(a.plan_entries));
   if constexpr (ROPE) asm volatile("" ::"s"(a.rope), "s"(a.rope_stride));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -967,8 +968,13 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   int plan_mc_begin = 0, plan_mc_end = 0;
   if (entry >= 0) {
     const int32_t* e = a.plan + 8 + 8 * entry;
-    const int4 e0 = *(const int4*)e;
+    int in_use = a.plan[0];                              // (the entry is in the plan's memory, used or not)
+    int4 e0 = *(const int4*)e;
     planned = *(const int4*)(e + 4);
+    asm volatile("" : "+v"(in_use), "+v"(e0.x), "+v"(planned.x));   // one trip for all three
+    e0.x = __builtin_amdgcn_readfirstlane(e0.x);         // (uniform, which the line above hides from the compiler)
+    planned.x = __builtin_amdgcn_readfirstlane(planned.x);
+    if (__builtin_amdgcn_readfirstlane(in_use) <= entry) return;
     b = min(max(e0.x, 0), d.batch - 1);
     n_splits = min(max(e0.z, 1), a.plan_entries);
     split = min(max(e0.y, 0), n_splits - 1);
@@ -1339,12 +1345,7 @@ __global__ void __launch_bounds__(64 * 4 * kDecodeWavesPerSimd) __attribute__((a
 decode_kernel(DecodeArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_last;
-  int entry = -1;
-  if (a.plan) {
-    entry = blockIdx.x;
-    if (entry >= min(a.plan[0], a.plan_entries)) return;
-  }
-  decode_item<GQ, BITS, NV, PAGED, SB, ROPE>(a, smem, s_last, entry);
+  decode_item<GQ, BITS, NV, PAGED, SB, ROPE>(a, smem, s_last, a.plan ? (int)blockIdx.x : -1);
 }
 
 template <int GQ, int BITS, int NV, bool PAGED, int SB, bool ROPE>
