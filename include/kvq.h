@@ -343,9 +343,8 @@ int32_t kvq_decode_launch_shape(const kvq_config* cfg, int32_t q_tokens, int32_t
  *   selected       : device uint8 scratch of kvq_sizes.prefill_selected_bytes; on return
  *                    selected[(unit * (n_q/G) + group) * G + t] = 1 if token t of that group entered
  *                    the pool at its competition
- * The competitions of a unit run in order in one wavefront, on scores that the other wavefronts of its
- * workgroup compute a stretch of tokens ahead; the groups are then quantized in parallel over units and
- * groups.
+ * The competitions of a unit's groups are decided by counting, for many groups at a time; the groups are
+ * then quantized in parallel over units and groups.
  */
 int32_t kvq_prefill_quantize(const kvq_config* cfg, int32_t layer, const void* k_rows, const void* v_rows,
                              int64_t unit_stride, int32_t n_tokens, kvq_pool pool, uint8_t* selected,
@@ -361,10 +360,24 @@ int32_t kvq_prefill_quantize(const kvq_config* cfg, int32_t layer, const void* k
  *   selected       : device uint8 scratch, at least kv_heads * n_q bytes
  * Everything else as kvq_prefill_quantize.  With per-sequence state (kvq_decode_attention_ragged) the
  * caller then writes {n_q, 0, n_tokens - n_q, active} into the sequence's entry of that array.
+ *
+ * kvq_prefill_sequence: the same for every layer of the configuration at once, in one set of launches
+ * for as many layers as `selected` has room for, and the sequence's state with it.
+ *   k_rows, v_rows : HOST arrays [layers] of device pointers, one per layer, each as above (the arrays
+ *                    may go when the call returns)
+ *   selected       : device uint8 scratch; selected_bytes >= kv_heads * n_q (one layer at a time,
+ *                    KVQ_ERR_WORKSPACE below), layers * kv_heads * n_q for all of them at once.  Its
+ *                    contents on return are unspecified
+ *   seq_state      : the array of kvq_decode_attention_ragged, whose entry `seq` becomes
+ *                    {n_q, 0, n_tokens - n_q, active != 0}, or NULL
  */
 int32_t kvq_prefill_quantize_seq(const kvq_config* cfg, int32_t layer, int32_t seq, const void* k_rows,
                                  const void* v_rows, int64_t unit_stride, int32_t n_tokens, kvq_pool pool,
                                  uint8_t* selected, kvq_qcache qcache, kvq_residual res, void* stream);
+int32_t kvq_prefill_sequence(const kvq_config* cfg, int32_t seq, const void* const* k_rows,
+                             const void* const* v_rows, int64_t unit_stride, int32_t n_tokens, kvq_pool pool,
+                             uint8_t* selected, int64_t selected_bytes, kvq_qcache qcache, kvq_residual res,
+                             int32_t* seq_state, int32_t active, void* stream);
 
 /*
  * The whole group step in one launch, for the decode steps on which the ring fills: append the

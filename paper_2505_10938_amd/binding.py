@@ -16,9 +16,10 @@ LIB_PATH = os.path.join(HERE, "libkvq.so")
 
 KVQ_OK, KVQ_ERR_INVALID_ARG, KVQ_ERR_UNSUPPORTED, KVQ_ERR_WORKSPACE, KVQ_ERR_LAUNCH, KVQ_ERR_SCRATCH = 0, -1, -2, -3, -4, -5
 
-INTERFACE_VERSION = 6       # kvq_version() of the library these structures and signatures match
+INTERFACE_VERSION = 7       # kvq_version() of the library these structures and signatures match
 EXPORTS = ["kvq_query_sizes", "kvq_append_residual", "kvq_trace_outliers", "kvq_quantize_group",
-           "kvq_append_trace_quantize", "kvq_prefill_quantize", "kvq_prefill_quantize_seq", "kvq_decode_attention",
+           "kvq_append_trace_quantize", "kvq_prefill_quantize", "kvq_prefill_quantize_seq", "kvq_prefill_sequence",
+           "kvq_decode_attention",
            "kvq_append_decode_attention", "kvq_append_decode_attention_rope", "kvq_rope_rotate",
            "kvq_append_trace_quantize_ragged", "kvq_seq_advance",
            "kvq_decode_attention_ragged", "kvq_decode_attention_multi", "kvq_decode_workspace_bytes",
@@ -96,6 +97,9 @@ def load_library() -> C.CDLL:
     lib.kvq_prefill_quantize.argtypes = [cfgp, i32, vp, vp, i64, i32, kvq_pool, vp, kvq_qcache, kvq_residual, vp]
     lib.kvq_prefill_quantize_seq.restype = i32
     lib.kvq_prefill_quantize_seq.argtypes = [cfgp, i32, i32, vp, vp, i64, i32, kvq_pool, vp, kvq_qcache, kvq_residual, vp]
+    lib.kvq_prefill_sequence.restype = i32
+    lib.kvq_prefill_sequence.argtypes = [cfgp, i32, C.POINTER(vp), C.POINTER(vp), i64, i32, kvq_pool, vp, i64, kvq_qcache,
+                                         kvq_residual, vp, i32, vp]
     lib.kvq_append_trace_quantize.restype = i32
     lib.kvq_append_trace_quantize.argtypes = [cfgp, i32, vp, vp, kvq_residual, i32, i32, i32, kvq_pool, vp, kvq_qcache, vp]
     lib.kvq_decode_attention.restype = i32
@@ -229,6 +233,19 @@ def kvq_prefill_quantize_seq(cfg, layer, seq, k_rows, v_rows, unit_stride, n_tok
                                                  n_tokens, pool, _ptr(selected), qcache, res, _stream(stream))
     if st != KVQ_OK:
         raise KvqError(st, "kvq_prefill_quantize_seq")
+
+
+def kvq_prefill_sequence(cfg, seq, k_rows, v_rows, unit_stride, n_tokens, pool: kvq_pool, selected, selected_bytes,
+                         qcache: kvq_qcache, res: kvq_residual, seq_state, active, stream=None):
+    """k_rows, v_rows: a tensor (or pointer) per layer."""
+    if len(k_rows) != cfg.layers or len(v_rows) != cfg.layers:
+        raise KvqError(KVQ_ERR_INVALID_ARG, "kvq_prefill_sequence")
+    pointers = C.c_void_p * cfg.layers
+    st = load_library().kvq_prefill_sequence(C.byref(cfg), seq, pointers(*map(_ptr, k_rows)), pointers(*map(_ptr, v_rows)),
+                                             unit_stride, n_tokens, pool, _ptr(selected), selected_bytes, qcache, res,
+                                             _ptr(seq_state), active, _stream(stream))
+    if st != KVQ_OK:
+        raise KvqError(st, "kvq_prefill_sequence")
 
 
 def kvq_decode_workspace_bytes(cfg, q_tokens) -> int:

@@ -178,11 +178,14 @@ class KVCache:
                 view[u0:u1, 0:n - first] = src[:, first:]
         self.n_res[layer] = n
 
+    def _prefill_selected_bytes(self):
+        return max(int(self.sizes.prefill_selected_bytes), 16)
+
     def _need_prefill_selected(self, stream):
         if getattr(self, "prefill_selected", None) is None:
             with _on(stream, self.device):
-                self.prefill_selected = torch.zeros(max(int(self.sizes.prefill_selected_bytes), 16),
-                                                    dtype=torch.uint8, device=self.device)
+                self.prefill_selected = torch.zeros(self._prefill_selected_bytes(), dtype=torch.uint8,
+                                                    device=self.device)
 
     def _new_output(self, q, stream):
         with _on(stream, self.device):
@@ -284,6 +287,9 @@ class RaggedKVCache(KVCache):
         self.seq_state = torch.zeros(cfg.batch, 4, dtype=torch.int32, device=self.device)
         self.longest = 0                                  # tokens of the longest sequence, at most
 
+    def _prefill_selected_bytes(self):             # (all layers of one sequence, or all sequences of one layer)
+        return max(super()._prefill_selected_bytes(), self.cfg.layers * self.cfg.kv_heads * self.cfg.max_seq)
+
     def set_active(self, active):
         """active: bool / int tensor or list [batch]: the sequences that take part in the next steps."""
         self.seq_state[:, 3] = torch.as_tensor(active, device=self.device).to(torch.int32)
@@ -297,21 +303,20 @@ class RaggedKVCache(KVCache):
 
     def prefill_sequence(self, b, k_rows, v_rows, active=True, stream=None):
         """A new sequence in slot `b`: its prompt (per layer: fp16 [kv_heads, n, head_dim], contiguous;
-        `k_rows`, `v_rows` are lists over the layers) quantized in one call per layer, whatever the slot
+        `k_rows`, `v_rows` are lists over the layers) quantized in one call for all layers, whatever the slot
         held before; the other sequences are not touched."""
         cfg = self.cfg
         n = k_rows[0].shape[1]
-        G, R = cfg.group_k, cfg.residual
-        nq = G * ((n - R) // G) if n >= R + G else 0
-        self._need_prefill_selected(stream)
-        for layer in range(cfg.layers):
-            k, v = k_rows[layer], v_rows[layer]
+        k_rows, v_rows = list(k_rows[:cfg.layers]), list(v_rows[:cfg.layers])
+        for k, v in zip(k_rows, v_rows):
             assert k.shape == (cfg.kv_heads, n, cfg.head_dim) and k.is_contiguous() and v.is_contiguous()
-            B.kvq_prefill_quantize_seq(cfg, layer, b, k, v, n * cfg.head_dim, n, self.pool, self.prefill_selected,
-                                       self.qcache, self.res, stream)
-        state = torch.tensor([nq, 0, n - nq, 1 if active else 0], dtype=torch.int32)
-        with _on(stream, self.device):
-            self.seq_state[b].copy_(state.to(self.device), non_blocking=False)
+        self._need_prefill_selected(stream)
+        if stream is not None:                 # the rows may be given back before that stream is through with them
+            with _on(stream, self.device):
+                for t in k_rows + v_rows:
+                    t.record_stream(torch.cuda.current_stream(self.device))
+        B.kvq_prefill_sequence(cfg, b, k_rows, v_rows, n * cfg.head_dim, n, self.pool, self.prefill_selected,
+                               self.prefill_selected.numel(), self.qcache, self.res, self.seq_state, bool(active), stream)
         self.longest = max(self.longest, n)
 
     def advance(self, stream=None):

@@ -190,6 +190,7 @@ Dims make_dims(const kvq_config* c, int32_t layer) {
   d.R = c->residual;
   d.pool_slots = c->outlier_budget + c->aux_capacity;
   d.units_per_layer = c->batch * c->kv_heads;
+  d.layer_units = d.units_per_layer;
   d.unit0 = (int64_t)layer * d.units_per_layer;
   d.block_bytes = 512 * c->bits;
   d.blocks_per_unit = c->max_seq / kvq::kBlockTokens;
@@ -259,7 +260,7 @@ __global__ void __launch_bounds__(256) stream_read_kernel(const uint4* __restric
 
 extern "C" {
 
-int32_t kvq_version(void) { return 6; }
+int32_t kvq_version(void) { return 7; }
 
 int32_t kvq_stream_read(const void* buf, size_t bytes, void* sink, void* stream) {
   if (!buf || !sink || bytes == 0 || bytes % 16 != 0 || ((uintptr_t)buf & 15) != 0) return KVQ_ERR_INVALID_ARG;
@@ -309,6 +310,20 @@ int32_t kvq_query_sizes(const kvq_config* cfg, kvq_sizes* out) {
   return KVQ_OK;
 }
 
+namespace {
+
+kvq::PromptRows rows_of(const void* const* k, const void* const* v, int32_t layers, int64_t unit_stride) {
+  kvq::PromptRows r = {};
+  r.unit_stride = unit_stride;
+  for (int32_t i = 0; i < layers; ++i) {
+    r.k[i] = (const __half*)k[i];
+    r.v[i] = (const __half*)v[i];
+  }
+  return r;
+}
+
+}  // namespace
+
 int32_t kvq_append_residual(const kvq_config* cfg, int32_t layer, const void* k_new, const void* v_new,
                             kvq_residual res, int32_t res_start, int32_t n_res, void* stream) {
   const int32_t st = check_config(cfg);
@@ -354,23 +369,27 @@ int32_t kvq_quantize_group(const kvq_config* cfg, int32_t layer, int32_t group_i
   if ((((uintptr_t)k_group) | ((uintptr_t)v_group)) & 15) return KVQ_ERR_INVALID_ARG;
   if (!qcache_ok(cfg, qc)) return KVQ_ERR_INVALID_ARG;
   const Dims d = make_dims(cfg, layer, qc);
-  return from_hip(kvq::launch_quantize(d, group_index, 1, (const __half*)k_group, (const __half*)v_group,
-                                       unit_stride, selected, cfg->group_k, qc, (hipStream_t)stream));
+  const kvq::PromptRows rows = rows_of(&k_group, &v_group, 1, unit_stride);
+  return from_hip(kvq::launch_quantize(d, group_index, 1, rows, 1, selected, cfg->group_k, qc, (hipStream_t)stream));
 }
 
 namespace {
 
-// Whole-prompt quantization of every sequence of the batch (seq < 0) or of sequence `seq` alone,
-// whose pools are emptied first.
-int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t seq, const void* k_rows, const void* v_rows,
-                       int64_t unit_stride, int32_t n_tokens, kvq_pool pool, uint8_t* selected, kvq_qcache qc,
-                       kvq_residual res, void* stream) {
+// Whole-prompt quantization of `layers` consecutive layers, each with the rows its entry of k_rows and v_rows names:
+// of every sequence of the batch (seq < 0) or of sequence `seq` alone, whose pools are emptied first.  The layers go
+// into one set of launches, as many as `selected` has room for the flags of (the caller's word is taken for one).
+int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t layers, int32_t seq, const void* const* k_rows,
+                       const void* const* v_rows, int64_t unit_stride, int32_t n_tokens, kvq_pool pool,
+                       uint8_t* selected, int64_t selected_bytes, kvq_qcache qc, kvq_residual res, int32_t* seq_state,
+                       int32_t active, void* stream) {
   const int32_t st = check_config(cfg);
   if (st != KVQ_OK) return st;
   if (layer < 0 || layer >= cfg->layers) return KVQ_ERR_INVALID_ARG;
-  if (!k_rows || !v_rows || !res.k_res || !res.v_res) return KVQ_ERR_INVALID_ARG;
-  if ((((uintptr_t)k_rows) | ((uintptr_t)v_rows) | ((uintptr_t)res.k_res) | ((uintptr_t)res.v_res)) & 15)
-    return KVQ_ERR_INVALID_ARG;
+  if (!res.k_res || !res.v_res || ((((uintptr_t)res.k_res) | ((uintptr_t)res.v_res)) & 15)) return KVQ_ERR_INVALID_ARG;
+  for (int32_t i = 0; i < layers; ++i) {
+    if (!k_rows[i] || !v_rows[i]) return KVQ_ERR_INVALID_ARG;
+    if ((((uintptr_t)k_rows[i]) | ((uintptr_t)v_rows[i])) & 15) return KVQ_ERR_INVALID_ARG;
+  }
   const int32_t G = cfg->group_k, R = cfg->residual;
   if (n_tokens < 1 || (int64_t)n_tokens > (int64_t)cfg->max_seq + R + G - 1) return KVQ_ERR_INVALID_ARG;
   if (unit_stride < (int64_t)n_tokens * cfg->head_dim || unit_stride % 8 != 0) return KVQ_ERR_INVALID_ARG;
@@ -387,32 +406,42 @@ int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t seq, const 
   if (n_more_values > 0 && !qcache_ok(cfg, qc)) return KVQ_ERR_INVALID_ARG;
   if (cfg->value_per_step && seq >= 0) return KVQ_ERR_UNSUPPORTED;
   if (n_more_values > 0 && n_tokens - R > cfg->max_seq) return KVQ_ERR_INVALID_ARG;
-  Dims d = (n_groups > 0 || n_more_values > 0) ? make_dims(cfg, layer, qc) : make_dims(cfg, layer);
-  d.keys_only = 0;                                       // whole groups: Keys and Values in one pass
+  const int64_t flags = (int64_t)(seq >= 0 ? 1 : cfg->batch) * cfg->kv_heads * n_groups * G;   // bytes, one layer
+  if (selected_bytes < flags) return KVQ_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  if (seq >= 0) {                                        // the launches cover the units of this sequence only
-    d.unit0 += (int64_t)seq * cfg->kv_heads;
-    d.units_per_layer = cfg->kv_heads;
-    d.seq0 = seq;
-    // (where groups compete, the competition writes the pools' state whatever they held)
-    if ((n_groups == 0 || d.N == 0) && kvq::launch_reset_pools(d, pool, s) != hipSuccess) return KVQ_ERR_LAUNCH;
-  }
-  if (n_groups > 0) {
-    hipError_t e = kvq::launch_prefill_trace(d, n_groups, (const __half*)k_rows, (const __half*)v_rows, unit_stride,
-                                             pool, selected, s);
+  const int32_t end = layer + layers;
+  for (int32_t first = layer, count; first < end; first += count) {
+    count = end - first < kvq::kPromptLayers ? end - first : kvq::kPromptLayers;
+    if (first < cfg->untraced_layers && first + count > cfg->untraced_layers) count = cfg->untraced_layers - first;
+    if (flags > 0 && selected_bytes / flags < count) count = (int32_t)(selected_bytes / flags);
+    Dims d = (n_groups > 0 || n_more_values > 0) ? make_dims(cfg, first, qc) : make_dims(cfg, first);
+    d.keys_only = 0;                                     // whole groups: Keys and Values in one pass
+    if (seq >= 0) {                                      // the launches cover the units of this sequence only
+      d.unit0 += (int64_t)seq * cfg->kv_heads;
+      d.units_per_layer = cfg->kv_heads;
+      d.seq0 = seq;
+      // (where groups compete, the competition writes the pools' state whatever they held)
+      if ((n_groups == 0 || d.N == 0) && kvq::launch_reset_pools(d, count, pool, s) != hipSuccess) return KVQ_ERR_LAUNCH;
+    }
+    kvq::SeqEntry entry = {};
+    if (seq_state && first + count == end) entry = {seq_state + 4 * (int64_t)seq, n_groups * G, n_tokens - n_groups * G, active};
+    const kvq::PromptRows rows = rows_of(k_rows + (first - layer), v_rows + (first - layer), count, unit_stride);
+    const int32_t tail = n_tokens - n_groups * G;
+    hipError_t e;
+    if (n_groups > 0) {
+      e = kvq::launch_prefill_trace(d, n_groups, rows, count, pool, selected, s);
+      if (e != hipSuccess) return KVQ_ERR_LAUNCH;
+      // (the rows behind the last group go to the ring in the same launch)
+      e = kvq::launch_quantize(d, 0, n_groups, rows, count, selected, (int64_t)n_groups * G, qc, s, tail,
+                               (__half*)res.k_res, (__half*)res.v_res, entry);
+    } else {
+      e = kvq::launch_tail_copy(d, rows, count, tail, (__half*)res.k_res, (__half*)res.v_res, entry, s);
+    }
+    if (e == hipSuccess && n_more_values > 0)
+      e = kvq::launch_value_tokens(d, n_groups * G, n_more_values, (__half*)res.v_res, 0, qc, s);
     if (e != hipSuccess) return KVQ_ERR_LAUNCH;
-    // (the rows behind the last group go to the ring in the same launch)
-    e = kvq::launch_quantize(d, 0, n_groups, (const __half*)k_rows, (const __half*)v_rows, unit_stride, selected,
-                             (int64_t)n_groups * G, qc, s, n_tokens - n_groups * G, (__half*)res.k_res,
-                             (__half*)res.v_res);
-    if (e != hipSuccess) return KVQ_ERR_LAUNCH;
   }
-  hipError_t e = n_groups > 0 ? hipSuccess
-                              : kvq::launch_tail_copy(d, (const __half*)k_rows, (const __half*)v_rows, unit_stride, 0,
-                                                      n_tokens, (__half*)res.k_res, (__half*)res.v_res, s);
-  if (e == hipSuccess && n_more_values > 0)
-    e = kvq::launch_value_tokens(d, n_groups * G, n_more_values, (__half*)res.v_res, 0, qc, s);
-  return from_hip(e);
+  return KVQ_OK;
 }
 
 }  // namespace
@@ -420,14 +449,26 @@ int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t seq, const 
 int32_t kvq_prefill_quantize(const kvq_config* cfg, int32_t layer, const void* k_rows, const void* v_rows,
                              int64_t unit_stride, int32_t n_tokens, kvq_pool pool, uint8_t* selected, kvq_qcache qc,
                              kvq_residual res, void* stream) {
-  return prefill_common(cfg, layer, -1, k_rows, v_rows, unit_stride, n_tokens, pool, selected, qc, res, stream);
+  return prefill_common(cfg, layer, 1, -1, &k_rows, &v_rows, unit_stride, n_tokens, pool, selected, INT64_MAX, qc, res,
+                        nullptr, 0, stream);
 }
 
 int32_t kvq_prefill_quantize_seq(const kvq_config* cfg, int32_t layer, int32_t seq, const void* k_rows,
                                  const void* v_rows, int64_t unit_stride, int32_t n_tokens, kvq_pool pool,
                                  uint8_t* selected, kvq_qcache qc, kvq_residual res, void* stream) {
   if (!cfg || seq < 0 || seq >= cfg->batch) return KVQ_ERR_INVALID_ARG;
-  return prefill_common(cfg, layer, seq, k_rows, v_rows, unit_stride, n_tokens, pool, selected, qc, res, stream);
+  return prefill_common(cfg, layer, 1, seq, &k_rows, &v_rows, unit_stride, n_tokens, pool, selected, INT64_MAX, qc, res,
+                        nullptr, 0, stream);
+}
+
+int32_t kvq_prefill_sequence(const kvq_config* cfg, int32_t seq, const void* const* k_rows, const void* const* v_rows,
+                             int64_t unit_stride, int32_t n_tokens, kvq_pool pool, uint8_t* selected,
+                             int64_t selected_bytes, kvq_qcache qc, kvq_residual res, int32_t* seq_state,
+                             int32_t active, void* stream) {
+  if (!cfg || seq < 0 || seq >= cfg->batch || !k_rows || !v_rows) return KVQ_ERR_INVALID_ARG;
+  if (((uintptr_t)seq_state) & 15) return KVQ_ERR_INVALID_ARG;
+  return prefill_common(cfg, 0, cfg->layers, seq, k_rows, v_rows, unit_stride, n_tokens, pool, selected, selected_bytes,
+                        qc, res, seq_state, active ? 1 : 0, stream);
 }
 
 int32_t kvq_append_trace_quantize(const kvq_config* cfg, int32_t layer, const void* k_new, const void* v_new,

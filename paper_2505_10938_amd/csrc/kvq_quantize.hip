@@ -319,42 +319,51 @@ __device__ __forceinline__ void quantize_body(const Dims& d, int64_t u, int32_t 
   }
 }
 
+// (one thread of a launch; nothing in the launch reads the array)
+__device__ __forceinline__ void write_seq_entry(const SeqEntry& e) {
+  if (e.at && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0)
+    *(int4*)e.at = make_int4(e.n_quant, 0, e.n_res, e.active);
+}
+
 // One workgroup of 16 wavefronts per unit.  Every global load of the kernel is issued before the
 // first wait, so a launch costs one trip to memory; the work after it is spread over all 1024
 // threads because nothing else hides latency.  LDS: 2 * G * 272 bytes (<= 68 KB) + meta.
 template <int BITS, int G>
 __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
-    Dims d, int32_t group_index, const __half* __restrict__ k_group, const __half* __restrict__ v_group,
-    int64_t unit_stride, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
+    Dims d, int32_t group_index, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
-    __half* __restrict__ k_res, __half* __restrict__ v_res) {
-  // grid (units, groups + tail blocks): workgroup (ul, gy) with gy < n_groups quantizes the G rows from row
+    __half* __restrict__ k_res, __half* __restrict__ v_res, SeqEntry entry, PromptRows rows) {
+  // grid (units, groups + tail blocks, layers): workgroup (ul, gy) with gy < n_groups quantizes the G rows from row
   // gy * G of the unit's rows as group group_index + gy; its flags are
-  // selected[ul * selected_unit_stride + gy * G ..].  The workgroups behind them copy the tail_n rows that
-  // follow the last group into ring rows 0 .. of the unit (a whole prompt: the rows that stay in full
+  // selected[(layer * units + ul) * selected_unit_stride + gy * G ..].  The workgroups behind them copy the tail_n
+  // rows that follow the last group into ring rows 0 .. of the unit (a whole prompt: the rows that stay in full
   // precision), 16 bytes of K and of V per thread.
   extern __shared__ __align__(16) unsigned char smem[];
   const QuantLds<G> L(smem, d.vgroups);
   const int tid = threadIdx.x;
-  const int ul = blockIdx.x, gy = blockIdx.y;
+  const int ul = blockIdx.x, gy = blockIdx.y, layer = blockIdx.z;
+  const __half* __restrict__ k_rows = rows.k[layer];
+  const __half* __restrict__ v_rows = rows.v[layer];
+  write_seq_entry(entry);
   if (gy >= n_groups) {
     const int i = (gy - n_groups) * kQuantThreads + tid;
     if (i < tail_n * 16) {
-      const int64_t src = (int64_t)ul * unit_stride + (int64_t)n_groups * G * kHeadDim;
-      const int64_t dst = (d.unit0 + ul) * d.res_rows * kHeadDim;
-      ((uint4*)(k_res + dst))[i] = ((const uint4*)(k_group + src))[i];
-      ((uint4*)(v_res + dst))[i] = ((const uint4*)(v_group + src))[i];
+      const int64_t src = (int64_t)ul * rows.unit_stride + (int64_t)n_groups * G * kHeadDim;
+      const int64_t dst = (d.unit0 + (int64_t)layer * d.layer_units + ul) * d.res_rows * kHeadDim;
+      ((uint4*)(k_res + dst))[i] = ((const uint4*)(k_rows + src))[i];
+      ((uint4*)(v_res + dst))[i] = ((const uint4*)(v_rows + src))[i];
     }
     return;
   }
-  GroupRows<G> rows;
-  const int64_t row0 = (int64_t)ul * unit_stride + (int64_t)gy * G * kHeadDim;
-  rows_issue<G>(rows, k_group + row0, v_group + row0, tid);
+  GroupRows<G> group;
+  const int64_t row0 = (int64_t)ul * rows.unit_stride + (int64_t)gy * G * kHeadDim;
+  rows_issue<G>(group, k_rows + row0, v_rows + row0, tid);
+  const int64_t sel0 = ((int64_t)layer * d.units_per_layer + ul) * selected_unit_stride + (int64_t)gy * G;
   uint8_t flag = 0;
-  if (tid < G && selected) flag = selected[(int64_t)ul * selected_unit_stride + gy * G + tid];
-  const GroupPlace at = place_of_group(d, ul, group_index + gy);
-  rows_to_lds<G>(rows, L, tid);
+  if (tid < G && selected) flag = selected[sel0 + tid];
+  const GroupPlace at = place_of_group(d, ul, group_index + gy, layer);
+  rows_to_lds<G>(group, L, tid);
   quantize_body<BITS, G>(d, at.row, at.slot, L, flag, k_codes, k_meta, v_codes, v_meta, mask, tid);
 }
 
@@ -387,22 +396,24 @@ __device__ __forceinline__ void lds_order() {   // LDS traffic of one wavefront 
 
 template <int BITS, int G>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))) prompt_quantize_kernel(
-    Dims d, int32_t group_index, const __half* __restrict__ k_rows, const __half* __restrict__ v_rows,
-    int64_t unit_stride, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
+    Dims d, int32_t group_index, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
-    __half* __restrict__ k_res, __half* __restrict__ v_res) {
+    __half* __restrict__ k_res, __half* __restrict__ v_res, SeqEntry entry, PromptRows rows) {
   // grid (units, groups + tail blocks), as quantize_kernel's
   __shared__ uint4 vrow[32 * 16];                      // 32 Value rows of 128 fp16 (mean-replaced where flagged)
   __shared__ float2 vms[32 * 4];                       // their {zero, step / 2} per channel group
   __shared__ uint32_t vpr[32 * 4];                     // and before that {minimum, -maximum} as an fp16 pair
   const int tid = threadIdx.x;
-  const int ul = blockIdx.x, gy = blockIdx.y;
+  const int ul = blockIdx.x, gy = blockIdx.y, layer = blockIdx.z;
+  const __half* __restrict__ k_rows = rows.k[layer];
+  const __half* __restrict__ v_rows = rows.v[layer];
+  write_seq_entry(entry);
   if (gy >= n_groups) {
     const int i = (gy - n_groups) * 128 + tid;
     if (i < tail_n * 16) {
-      const int64_t src = (int64_t)ul * unit_stride + (int64_t)n_groups * G * kHeadDim;
-      const int64_t dst = (d.unit0 + ul) * d.res_rows * kHeadDim;
+      const int64_t src = (int64_t)ul * rows.unit_stride + (int64_t)n_groups * G * kHeadDim;
+      const int64_t dst = (d.unit0 + (int64_t)layer * d.layer_units + ul) * d.res_rows * kHeadDim;
       ((uint4*)(k_res + dst))[i] = ((const uint4*)(k_rows + src))[i];
       ((uint4*)(v_res + dst))[i] = ((const uint4*)(v_rows + src))[i];
     }
@@ -410,8 +421,9 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t row0 = (int64_t)ul * unit_stride + (int64_t)gy * G * kHeadDim;
-  const GroupPlace at = place_of_group(d, ul, group_index + gy);
+  const int64_t row0 = (int64_t)ul * rows.unit_stride + (int64_t)gy * G * kHeadDim;
+  const int64_t sel0 = ((int64_t)layer * d.units_per_layer + ul) * selected_unit_stride + (int64_t)gy * G;
+  const GroupPlace at = place_of_group(d, ul, group_index + gy, layer);
   constexpr int nblk = G / kBlockTokens;
   const int64_t block0 = at.row * d.blocks_per_unit + (int64_t)at.slot * nblk;   // the group's first packed block
   // the flags of the group's tokens as bit masks (uniform)
@@ -421,7 +433,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
 #pragma unroll
   for (int w = 0; w < kSelWords; ++w) {
     const int t = 64 * w + lane;
-    const bool f = selected && t < G && selected[(int64_t)ul * selected_unit_stride + (int64_t)gy * G + t] != 0;
+    const bool f = selected && t < G && selected[sel0 + t] != 0;
     sel[w] = __ballot(f);
     any |= sel[w] != 0;
   }
@@ -659,15 +671,14 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   else values(std::false_type{});
 }
 
-// Rows n0 .. n0 + n - 1 of every unit's rows into ring rows 0 .. n - 1 (16 bytes per thread).
-__global__ void __launch_bounds__(256) tail_copy_kernel(Dims d, const __half* __restrict__ k_rows,
-                                                        const __half* __restrict__ v_rows, int64_t unit_stride,
-                                                        int32_t n0, int32_t n, __half* __restrict__ k_res,
-                                                        __half* __restrict__ v_res) {
-  const int ul = blockIdx.x;
-  const int64_t u = d.unit0 + ul;
-  const uint4* sk = (const uint4*)(k_rows + (int64_t)ul * unit_stride + (int64_t)n0 * kHeadDim);
-  const uint4* sv = (const uint4*)(v_rows + (int64_t)ul * unit_stride + (int64_t)n0 * kHeadDim);
+// The n rows of every unit into ring rows 0 .. n - 1 (16 bytes per thread).  grid (units, blocks, layers).
+__global__ void __launch_bounds__(256) tail_copy_kernel(Dims d, int32_t n, __half* __restrict__ k_res,
+                                                        __half* __restrict__ v_res, SeqEntry entry, PromptRows rows) {
+  const int ul = blockIdx.x, layer = blockIdx.z;
+  const int64_t u = d.unit0 + (int64_t)layer * d.layer_units + ul;
+  write_seq_entry(entry);
+  const uint4* sk = (const uint4*)(rows.k[layer] + (int64_t)ul * rows.unit_stride);
+  const uint4* sv = (const uint4*)(rows.v[layer] + (int64_t)ul * rows.unit_stride);
   uint4* dk = (uint4*)(k_res + u * d.res_rows * kHeadDim);
   uint4* dv = (uint4*)(v_res + u * d.res_rows * kHeadDim);
   for (int i = blockIdx.y * 256 + threadIdx.x; i < n * 16; i += gridDim.y * 256) {
@@ -745,44 +756,29 @@ __global__ void __launch_bounds__(kQuantThreads) group_step_kernel(
 }
 
 template <int BITS, int G>
-hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_groups, const __half* k_group,
-                               const __half* v_group, int64_t unit_stride, const uint8_t* selected,
-                               int64_t selected_unit_stride, const kvq_qcache& qc, int32_t tail_n, __half* k_res,
-                               __half* v_res, hipStream_t s) {
+hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows,
+                               int32_t layers, const uint8_t* selected, int64_t selected_unit_stride,
+                               const kvq_qcache& qc, int32_t tail_n, __half* k_res, __half* v_res,
+                               const SeqEntry& entry, hipStream_t s) {
   // many groups (a prompt): the kernel that spends the fewest instructions per group; few: the one that is
   // done with a group soonest
-  if ((int64_t)d.units_per_layer * n_groups >= prompt_groups(G) && !d.keys_only) {
-    const int tail_blocks = (tail_n * 16 + 127) / 128;
-    hipLaunchKernelGGL((prompt_quantize_kernel<BITS, G>), dim3(d.units_per_layer, n_groups + tail_blocks), dim3(128), 0,
-                       s, d, group_index, k_group, v_group, unit_stride, selected, selected_unit_stride,
+  const bool many = (int64_t)d.units_per_layer * layers * n_groups >= prompt_groups(G) && !d.keys_only;
+  const int threads = many ? 128 : kQuantThreads;
+  const dim3 grid(d.units_per_layer, n_groups + (tail_n * 16 + threads - 1) / threads, layers);
+  auto go = [&](auto kern, size_t smem) {
+    hipLaunchKernelGGL(kern, grid, dim3(threads), smem, s, d, group_index, selected, selected_unit_stride,
                        (uint8_t*)qc.k_codes, (uint32_t*)qc.k_meta, (uint8_t*)qc.v_codes, (uint32_t*)qc.v_meta,
-                       (uint32_t*)qc.mask, n_groups, tail_n, k_res, v_res);
+                       (uint32_t*)qc.mask, n_groups, tail_n, k_res, v_res, entry, rows);
     return hipGetLastError();
-  }
+  };
+  if (many) return go(prompt_quantize_kernel<BITS, G>, 0);
   const size_t smem = quant_lds_bytes<G>(d.vgroups);
   if (smem > 48 * 1024) {  // more than the default limit of dynamic LDS per workgroup
     hipError_t e = hipFuncSetAttribute((const void*)quantize_kernel<BITS, G>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)smem);
     if (e != hipSuccess) return e;
   }
-  const int tail_blocks = (tail_n * 16 + kQuantThreads - 1) / kQuantThreads;
-  hipLaunchKernelGGL((quantize_kernel<BITS, G>), dim3(d.units_per_layer, n_groups + tail_blocks), dim3(kQuantThreads),
-                     smem, s, d, group_index, k_group, v_group, unit_stride, selected, selected_unit_stride,
-                     (uint8_t*)qc.k_codes, (uint32_t*)qc.k_meta, (uint8_t*)qc.v_codes, (uint32_t*)qc.v_meta,
-                     (uint32_t*)qc.mask, n_groups, tail_n, k_res, v_res);
-  return hipGetLastError();
-}
-
-template <int BITS>
-hipError_t launch_quantize_bits(const Dims& d, int32_t group_index, int32_t n_groups, const __half* k_group,
-                                const __half* v_group, int64_t unit_stride, const uint8_t* selected,
-                                int64_t selected_unit_stride, const kvq_qcache& qc, int32_t tail_n, __half* k_res,
-                                __half* v_res, hipStream_t s) {
-  switch (d.G) {
-    case 32: return launch_quantize_one<BITS, 32>(d, group_index, n_groups, k_group, v_group, unit_stride, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s);
-    case 64: return launch_quantize_one<BITS, 64>(d, group_index, n_groups, k_group, v_group, unit_stride, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s);
-    default: return launch_quantize_one<BITS, 128>(d, group_index, n_groups, k_group, v_group, unit_stride, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s);
-  }
+  return go(quantize_kernel<BITS, G>, smem);
 }
 
 }  // namespace
@@ -1029,20 +1025,29 @@ hipError_t launch_group_step(const Dims& d, int32_t group_index, const __half* k
                      : launch_group_step_bits<4>(d, group_index, k_new, v_new, k_res, v_res, append_row, group_row0, seq, pool, selected, qc, s);
 }
 
-hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const __half* k_group,
-                           const __half* v_group, int64_t unit_stride, const uint8_t* selected,
-                           int64_t selected_unit_stride, const kvq_qcache& qc, hipStream_t s, int32_t tail_n,
-                           __half* k_res, __half* v_res) {
-  return d.bits == 2 ? launch_quantize_bits<2>(d, group_index, n_groups, k_group, v_group, unit_stride, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s)
-                     : launch_quantize_bits<4>(d, group_index, n_groups, k_group, v_group, unit_stride, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s);
+hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows, int32_t layers,
+                           const uint8_t* selected, int64_t selected_unit_stride, const kvq_qcache& qc, hipStream_t s,
+                           int32_t tail_n, __half* k_res, __half* v_res, const SeqEntry& entry) {
+  auto go = [&](auto bits, auto group) {
+    return launch_quantize_one<decltype(bits)::value, decltype(group)::value>(
+        d, group_index, n_groups, rows, layers, selected, selected_unit_stride, qc, tail_n, k_res, v_res, entry, s);
+  };
+  auto of_bits = [&](auto bits) {
+    switch (d.G) {
+      case 32: return go(bits, std::integral_constant<int, 32>{});
+      case 64: return go(bits, std::integral_constant<int, 64>{});
+      default: return go(bits, std::integral_constant<int, 128>{});
+    }
+  };
+  return d.bits == 2 ? of_bits(std::integral_constant<int, 2>{}) : of_bits(std::integral_constant<int, 4>{});
 }
 
-hipError_t launch_tail_copy(const Dims& d, const __half* k_rows, const __half* v_rows, int64_t unit_stride, int32_t n0,
-                            int32_t n, __half* k_res, __half* v_res, hipStream_t s) {
+hipError_t launch_tail_copy(const Dims& d, const PromptRows& rows, int32_t layers, int32_t n, __half* k_res,
+                            __half* v_res, const SeqEntry& entry, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int by = (n * 16 + 255) / 256;
-  hipLaunchKernelGGL(tail_copy_kernel, dim3(d.units_per_layer, by > 16 ? 16 : by), dim3(256), 0, s, d, k_rows, v_rows,
-                     unit_stride, n0, n, k_res, v_res);
+  hipLaunchKernelGGL(tail_copy_kernel, dim3(d.units_per_layer, by > 16 ? 16 : by, layers), dim3(256), 0, s, d, n, k_res,
+                     v_res, entry, rows);
   return hipGetLastError();
 }
 

@@ -247,38 +247,35 @@ __device__ __forceinline__ bool may_be_selected(const uint32_t* coarse, const ui
   return coarse[e] <= b;
 }
 
-// grid (units, segments).  Requires N > 0.
+// grid (units, segments, layers).  Requires N > 0.
 template <int G>
 __global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int32_t n_tok,
-                                                                            const __half* __restrict__ k_rows,
-                                                                            int64_t unit_stride,
-                                                                            uint8_t* __restrict__ selected) {
+                                                                     uint8_t* __restrict__ selected, PromptRows src) {
   __shared__ uint32_t coarse[kSegment];
   __shared__ uint32_t bound[kPrefixes];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ul = blockIdx.x, t0 = blockIdx.y * kSegment;
+  const int ul = blockIdx.x, t0 = blockIdx.y * kSegment, layer = blockIdx.z;
   const int n = min(kSegment, n_tok - t0);
-  const __half* rows = k_rows + (int64_t)ul * unit_stride + (int64_t)t0 * kHeadDim;
+  const __half* rows = src.k[layer] + (int64_t)ul * src.unit_stride + (int64_t)t0 * kHeadDim;
   score_rows(n, tid, [&](int e) { return rows + e * kHeadDim; }, [&](int e, double sc) { coarse[e] = coarse_score(sc); });
   __syncthreads();
   prefix_bounds(coarse, n, d.N, bound, wave, lane);
   __syncthreads();
   // (segments begin with a group: token numbers inside the segment number its groups as well)
   if (tid < n)
-    selected[(int64_t)ul * n_tok + t0 + tid] =
+    selected[((int64_t)layer * d.units_per_layer + ul) * n_tok + t0 + tid] =
         may_be_selected<G>(coarse, bound, n, tid, tid, [](int p) { return p; }) ? 1 : 0;
 }
 
-// grid (units).  FLAGGED: the tokens that can be selected are flagged in `selected`, else all of them are looked at, T
+// grid (units, 1, layers).  FLAGGED: the tokens that can be selected are flagged in `selected`, else all of them are looked at, T
 // at a time, the Key rows of the next T in flight meanwhile.  Pools are taken to be empty on entry (a prompt starts a
 // sequence) and are not read.
 template <int G, int T, bool FLAGGED>
 __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) prompt_compete_kernel(
-    Dims d, int32_t n_tok, const __half* __restrict__ k_rows, const __half* __restrict__ v_rows,
-    int64_t unit_stride, __half* pool_k, __half* pool_v, int32_t* pool_idx, double* pool_score, int32_t* pool_count,
-    int32_t* aux_count, int32_t* frozen, uint8_t* __restrict__ selected) {
+    Dims d, int32_t n_tok, __half* pool_k, __half* pool_v, int32_t* pool_idx, double* pool_score, int32_t* pool_count,
+    int32_t* aux_count, int32_t* frozen, uint8_t* __restrict__ selected, PromptRows src) {
   constexpr int kGroupShift = G == 32 ? 5 : G == 64 ? 6 : 7;
   constexpr int kListed = 64 + 64 + kRound;            // at most N + A selected tokens before the last round
   constexpr int kWaves = T / 64;
@@ -291,16 +288,16 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) pro
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ul = blockIdx.x;
-  const int64_t u = d.unit0 + ul;
-  uint8_t* sel = selected + (int64_t)ul * n_tok;
+  const int ul = blockIdx.x, layer = blockIdx.z;
+  const int64_t u = d.unit0 + (int64_t)layer * d.layer_units + ul;
+  uint8_t* sel = selected + ((int64_t)layer * d.units_per_layer + ul) * n_tok;
   const int N = d.N, A = d.A;
   if (N == 0) {                                        // no pool: nothing is ever selected
     for (int i = tid; i < n_tok; i += T) sel[i] = 0;
     return;
   }
-  const __half* kr = k_rows + (int64_t)ul * unit_stride;
-  const __half* vr = v_rows + (int64_t)ul * unit_stride;
+  const __half* __restrict__ kr = src.k[layer] + (int64_t)ul * src.unit_stride;
+  const __half* __restrict__ vr = src.v[layer] + (int64_t)ul * src.unit_stride;
   const u64 below = (1ull << lane) - 1ull;
   int P = 0, cur = 0, S = 0;                           // pool members, pool buffer, selected tokens
   bool stopped = false;
@@ -499,38 +496,38 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) pro
 // the scores independent, group i would displace N / i tokens on average, about Poisson, E = N ln(groups, or tokens / N)
 // in all; Chernoff's bound on at most A of them, for all units, is held against e^-2.  (If that is wrong for the
 // prompt at hand the call is as long as with the walk above, or reads what it need not.)
-bool by_segments(const Dims& d, int32_t n_tok) {
+bool by_segments(const Dims& d, int32_t units, int32_t n_tok) {
   if (d.N == 0 || n_tok <= kSegment) return false;
-  const double segments = (double)n_tok / kSegment, early = 0.75 + d.units_per_layer * segments / 250.0;
+  const double segments = (double)n_tok / kSegment, early = 0.75 + units * segments / 250.0;
   if (early >= segments) return false;
   const double groups = early * kSegment / (d.G > d.N ? d.G : d.N), e = d.N * std::log(groups > 1.0 ? groups : 1.0);
   if (e <= d.A) return true;
   const double log_p = d.A - e + (d.A > 0 ? d.A * std::log(e / d.A) : 0.0);
-  return log_p + std::log((double)d.units_per_layer) >= -2.0;
+  return log_p + std::log((double)units) >= -2.0;
 }
 
 }  // namespace
 
-hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const __half* k_rows, const __half* v_rows,
-                                int64_t unit_stride, const kvq_pool& pool, uint8_t* selected, hipStream_t s) {
-  const int32_t n_tok = n_groups * d.G;
+hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const PromptRows& rows, int32_t layers,
+                                const kvq_pool& pool, uint8_t* selected, hipStream_t s) {
+  const int32_t n_tok = n_groups * d.G, units = d.units_per_layer * layers;
   auto compete = [&](auto kern, int threads) {
-    hipLaunchKernelGGL(kern, dim3(d.units_per_layer), dim3(threads), 0, s, d, n_tok, k_rows, v_rows, unit_stride,
-                       (__half*)pool.pool_k, (__half*)pool.pool_v, pool.pool_idx, pool.pool_score, pool.pool_count,
-                       pool.aux_count, pool.frozen, selected);
+    hipLaunchKernelGGL(kern, dim3(d.units_per_layer, 1, layers), dim3(threads), 0, s, d, n_tok, (__half*)pool.pool_k,
+                       (__half*)pool.pool_v, pool.pool_idx, pool.pool_score, pool.pool_count, pool.aux_count,
+                       pool.frozen, selected, rows);
   };
   // Threads of a workgroup: 1024 where every unit can have a compute unit to itself; with more units 512, so that two
   // workgroups fit one, and 256 for prompts no longer than that.  1024 units x 300 tokens, T = 1024 / 512 / 256: 92 /
   // 70 / 64 us; x 600: 138 / 120 / 121.
   auto go = [&](auto group) {
     constexpr int G = decltype(group)::value;
-    if (by_segments(d, n_tok)) {
-      hipLaunchKernelGGL(prompt_candidates_kernel<G>, dim3(d.units_per_layer, (n_tok + kSegment - 1) / kSegment),
-                         dim3(kSegment), 0, s, d, n_tok, k_rows, unit_stride, selected);
+    if (by_segments(d, units, n_tok)) {
+      hipLaunchKernelGGL(prompt_candidates_kernel<G>, dim3(d.units_per_layer, (n_tok + kSegment - 1) / kSegment, layers),
+                         dim3(kSegment), 0, s, d, n_tok, selected, rows);
       compete(prompt_compete_kernel<G, 1024, true>, 1024);
-    } else if (d.units_per_layer > 2 * kComputeUnits && n_tok <= 256) {
+    } else if (units > 2 * kComputeUnits && n_tok <= 256) {
       compete(prompt_compete_kernel<G, 256, false>, 256);
-    } else if (d.units_per_layer > kComputeUnits) {
+    } else if (units > kComputeUnits) {
       compete(prompt_compete_kernel<G, 512, false>, 512);
     } else {
       compete(prompt_compete_kernel<G, 1024, false>, 1024);
@@ -544,17 +541,18 @@ hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const __half* k
   return hipGetLastError();
 }
 
-// Empty pools for the units of the launch (a new sequence in a slot that held another).
+// Empty pools for the units of the launch (a new sequence in a slot that held another).  grid (units, layers).
 __global__ void reset_pools_kernel(Dims d, int32_t* pool_count, int32_t* aux_count, int32_t* frozen) {
   const int ul = blockIdx.x * blockDim.x + threadIdx.x;
   if (ul >= d.units_per_layer) return;
-  pool_count[d.unit0 + ul] = 0;
-  aux_count[d.unit0 + ul] = 0;
-  frozen[d.unit0 + ul] = 0;
+  const int64_t u = d.unit0 + (int64_t)blockIdx.y * d.layer_units + ul;
+  pool_count[u] = 0;
+  aux_count[u] = 0;
+  frozen[u] = 0;
 }
-hipError_t launch_reset_pools(const Dims& d, const kvq_pool& pool, hipStream_t s) {
-  hipLaunchKernelGGL(reset_pools_kernel, dim3((d.units_per_layer + 63) / 64), dim3(64), 0, s, d, pool.pool_count,
-                     pool.aux_count, pool.frozen);
+hipError_t launch_reset_pools(const Dims& d, int32_t layers, const kvq_pool& pool, hipStream_t s) {
+  hipLaunchKernelGGL(reset_pools_kernel, dim3((d.units_per_layer + 63) / 64, layers), dim3(64), 0, s, d,
+                     pool.pool_count, pool.aux_count, pool.frozen);
   return hipGetLastError();
 }
 
