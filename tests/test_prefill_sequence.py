@@ -103,3 +103,22 @@ def test_rows_given_back_before_a_side_stream_reads_them():
     del later
     for x in NAMES + ("seq_state",):
         assert torch.equal(getattr(got, x), getattr(want, x)), x
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,G,groups", [(2, 32, 127), (2, 32, 128), (4, 64, 64), (2, 128, 32)])
+def test_a_large_batch_equals_each_sequence_on_its_own(bits, G, groups):
+    """128 units: from 4096 quantized tokens each (2^27 bytes of Keys) the quantization takes the last groups first."""
+    import torch
+    n = groups * G + 43
+    cfg = KC.make_config(1, 16, 8, 8, groups * G, bits, G, residual=43)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(groups)
+    k, v = (torch.randn(16, 8, n, 128, generator=gen, device="cuda").half() for _ in range(2))
+    a, b = KC.KVCache(cfg), KC.RaggedKVCache(cfg)
+    a.prefill(0, k, v)
+    for i in range(16):
+        b.prefill_sequence(i, [k[i]], [v[i]])
+    torch.cuda.synchronize()
+    for x in NAMES:
+        assert torch.equal(getattr(a, x), getattr(b, x)), x
