@@ -149,26 +149,19 @@ PlanShape plan_shape(const kvq_config* c) {
   return best;
 }
 constexpr int64_t kPlanEntryWords = 8;
-// Workgroup rows that share the query rows of a kv head.  Every supported count (1, 2, 4, 8) has a kernel
-// instance of its own, so it is 1; the kernel still takes any divisor (a count without an instance would
-// run as several rows of a smaller one, all reading the unit's cache).
-constexpr int head_parts_of(int rows, int bits) { return (void)rows, (void)bits, 1; }
-
 // Workspace of a decode launch whose kv heads have `rows` query rows each (rows = query heads per kv
 // head times query tokens): arrival counters, then partial results for the largest split the launch
 // shape can get.
 int64_t decode_workspace_bytes(const kvq_config* cfg, int64_t rows) {
   const int64_t upl = (int64_t)cfg->batch * cfg->kv_heads, hd = cfg->head_dim;
-  const int64_t hp = head_parts_of((int)rows, cfg->bits);
   const int64_t slots = (int64_t)cfg->outlier_budget + cfg->aux_capacity;
-  const int64_t s_max =
-      most_splits(upl * hp, (int)(rows / hp), (int)(hd / cfg->group_v), cfg->max_seq, res_rows_of(cfg) + slots);
+  const int64_t s_max = most_splits(upl, (int)rows, (int)(hd / cfg->group_v), cfg->max_seq, res_rows_of(cfg) + slots);
   int64_t slots_needed = upl * s_max;
   if (cfg->batch <= 1024) {                              // a planned launch: items per kv head
     const int64_t planned = (int64_t)plan_shape(cfg).entries * cfg->kv_heads;
     if (planned > slots_needed) slots_needed = planned;
   }
-  return kCounterBytes(upl * hp) + slots_needed * rows * (hd + 2) * 4;
+  return kCounterBytes(upl) + slots_needed * rows * (hd + 2) * 4;
 }
 
 
@@ -645,30 +638,41 @@ int32_t decode_common(const kvq_config* cfg, int32_t layer, const void* q, int32
   kvq::DecodeArgs a;
   a.d = make_dims(cfg, layer, qc);
   a.q = (const __half*)q;
-  a.k_codes = (const uint8_t*)qc.k_codes;
-  a.k_meta = (const uint32_t*)qc.k_meta;
-  a.v_codes = (const uint8_t*)qc.v_codes;
-  a.v_meta = (const uint32_t*)qc.v_meta;
-  a.mask = (const uint32_t*)qc.mask;
-  a.k_res = (const __half*)res.k_res;
-  a.v_res = (const __half*)res.v_res;
-  a.pool_k = (const __half*)pool.pool_k;
-  a.pool_v = (const __half*)pool.pool_v;
-  a.pool_count = pool.pool_count;
-  a.aux_count = pool.aux_count;
+  // (at most 2^24 tokens per unit, and below 4 GiB of codes per plane: a unit's or a plane's bytes fit 32 bits)
+  const Dims& d = a.d;
+  const int64_t uq = d.page_table ? d.plane0 : d.unit0;
+  const int64_t row_bytes = 2 * cfg->head_dim;
+  a.code_stride = (uint32_t)((int64_t)d.blocks_per_unit * d.block_bytes);
+  a.k_meta_stride = (uint32_t)(d.groups_per_unit * 2 * row_bytes);
+  a.v_meta_stride = (uint32_t)((int64_t)d.blocks_per_unit * 128 * d.vgroups);
+  a.mask_stride = (uint32_t)((int64_t)d.blocks_per_unit * 4);
+  a.ring_stride = (uint32_t)(d.res_rows * row_bytes);
+  a.pool_stride = (uint32_t)(d.pool_slots * row_bytes);
+  a.pool_groups = (d.pool_slots + kvq::kFpGroupRows - 1) / kvq::kFpGroupRows;
+  auto at = [](const void* base, int64_t unit, uint32_t stride) { return (const uint8_t*)base + unit * stride; };
+  a.k_codes = at(qc.k_codes, uq, a.code_stride);
+  a.k_meta = at(qc.k_meta, uq, a.k_meta_stride);
+  a.v_codes = at(qc.v_codes, uq, a.code_stride);
+  a.v_meta = at(qc.v_meta, uq, a.v_meta_stride);
+  a.mask = at(qc.mask, uq, a.mask_stride);
+  a.k_res = at(res.k_res, d.unit0, a.ring_stride);
+  a.v_res = at(res.v_res, d.unit0, a.ring_stride);
+  a.pool_k = at(pool.pool_k, d.unit0, a.pool_stride);
+  a.pool_v = at(pool.pool_v, d.unit0, a.pool_stride);
+  a.pool_count = pool.pool_count + d.unit0;
+  a.aux_count = pool.aux_count + d.unit0;
   a.out = (__half*)out;
   a.counters = (int32_t*)workspace;
-  a.partials = (float*)((unsigned char*)workspace + kCounterBytes((int64_t)a.d.units_per_layer * head_parts_of(qrows, cfg->bits)));
+  a.partials = (float*)((unsigned char*)workspace + kCounterBytes(a.d.units_per_layer));
   a.n_quant = n_quant;
   a.res_start = res_start;
   a.n_res = n_res;
   a.seq = seq_state;
   a.k_new = (const __half*)k_new;
   a.v_new = (const __half*)v_new;
-  a.head_parts = head_parts_of(qrows, cfg->bits);
   a.q_tokens = q_tokens;
   a.g_shift = g == 1 ? 0 : g == 2 ? 1 : g == 4 ? 2 : 3;
-  const Split sp = decode_split((int64_t)a.d.units_per_layer * a.head_parts, qrows / a.head_parts, a.d.vgroups, n_quant,
+  const Split sp = decode_split(a.d.units_per_layer, qrows, a.d.vgroups, n_quant,
                                 (int64_t)n_res + (k_new ? 1 : 0) + a.d.pool_slots);
   a.splits = sp.splits;
   a.nw = sp.nw;
@@ -689,7 +693,7 @@ int32_t decode_common(const kvq_config* cfg, int32_t layer, const void* q, int32
   if (static_scratch && sp.splits > 1) {
     // The array is shared by every call on this device, whatever its shape: where this launch keeps its
     // arrival counters an earlier one may have left partial results.  They must start at zero.
-    const int words = (int)(kCounterBytes((int64_t)a.d.units_per_layer * a.head_parts) / 4);
+    const int words = (int)(kCounterBytes(a.d.units_per_layer) / 4);
     hipLaunchKernelGGL(zero_words_kernel, dim3((words + 255) / 256), dim3(256), 0, (hipStream_t)stream,
                        (uint32_t*)workspace, words);
     if (hipGetLastError() != hipSuccess) return KVQ_ERR_LAUNCH;
@@ -731,9 +735,7 @@ int32_t kvq_decode_launch_shape(const kvq_config* cfg, int32_t q_tokens, int32_t
   const int32_t qrows = q_tokens * (cfg->q_heads / cfg->kv_heads);
   if (qrows != 1 && qrows != 2 && qrows != 4 && qrows != 8) return KVQ_ERR_UNSUPPORTED;
   if (n_quant < 0 || n_quant > cfg->max_seq || n_quant % cfg->group_k != 0) return KVQ_ERR_INVALID_ARG;
-  const int hp = head_parts_of(qrows, cfg->bits);
-  const Split sp = decode_split((int64_t)cfg->batch * cfg->kv_heads * hp, qrows / hp, cfg->head_dim / cfg->group_v,
-                                n_quant, fp_rows);
+  const Split sp = decode_split((int64_t)cfg->batch * cfg->kv_heads, qrows, cfg->head_dim / cfg->group_v, n_quant, fp_rows);
   *splits = sp.splits;
   *waves = sp.nw;
   *minichunks_per_split = sp.mc_per_split;

@@ -80,17 +80,23 @@ struct SeqEntry {
 struct DecodeArgs {
   Dims d;
   const __half* q;
+  // The arrays of the launch's first unit (unit0); in a paged cache the first five are those of its first plane.  The
+  // data of the next unit (plane) begins the given number of bytes behind: Keys and Values, and both pools' arrays,
+  // alike.  (Worked out here once, and not by every wavefront, whose first loads wait for its addresses.)
   const uint8_t* k_codes;
-  const uint32_t* k_meta;
+  const uint8_t* k_meta;
   const uint8_t* v_codes;
-  const uint32_t* v_meta;
-  const uint32_t* mask;
-  const __half* k_res;
-  const __half* v_res;
-  const __half* pool_k;
-  const __half* pool_v;
+  const uint8_t* v_meta;
+  const uint8_t* mask;
+  const uint8_t* k_res;
+  const uint8_t* v_res;
+  const uint8_t* pool_k;
+  const uint8_t* pool_v;
   const int32_t* pool_count;
   const int32_t* aux_count;
+  uint32_t code_stride, k_meta_stride, v_meta_stride, mask_stride;
+  uint32_t ring_stride, pool_stride;
+  int32_t pool_groups;  // groups of 16 pool slots, the last one perhaps in part
   __half* out;
   float* partials;      // [units_per_layer][splits][g][head_dim + 2]
   int32_t* counters;    // [units_per_layer], zero on entry and on exit
@@ -100,7 +106,6 @@ struct DecodeArgs {
   const __half* v_new;  // attended as the newest residual row, and stored in the ring by the launch), or null
   int32_t splits;       // workgroups per unit
   int32_t nw;           // wavefronts per workgroup
-  int32_t head_parts;   // workgroup rows that share a kv head's query rows (the host passes 1: every row count has its instance)
   int32_t q_tokens;     // consecutive query tokens attended at once (1 in a plain decode step); the rows of a
   int32_t g_shift;      // kv head are its q_tokens * g (token, query head) pairs, token-major; g = 1 << g_shift
   int32_t mc_per_split; // 128-token mini-chunks of the quantized segment per workgroup

@@ -306,7 +306,6 @@ struct UnitPtrs {
   int nblocks;                // quantized blocks of the unit
   int last_block;             // the last of them (0 if there is none: the cache holds at least one block)
   int bpg_shift;
-  uint32_t block_bytes;
   const int32_t* table;       // paged: the sequence's row of the page table
   int n_pages;                // paged: pages per plane
   uint32_t pb0, pb1, pb2, pb3;  // paged: where the four blocks of the mini-chunk being loaded are stored
@@ -384,7 +383,7 @@ __device__ __forceinline__ void load_k_meta(McRegs<BITS, NV>& R, const PT& P, in
 template <int BITS, class PT>
 __device__ __forceinline__ void load_codes_block(uint32_t (&w)[4][2 * BITS], const unsigned char* codes,
                                                  const PT& P, int mc, int i, int lane) {
-  const unsigned char* bp = codes + P.block(mc, i) * P.block_bytes;   // uniform
+  const unsigned char* bp = codes + P.block(mc, i) * (512u * BITS);     // uniform
 #pragma unroll
   for (int hf = 0; hf < BITS / 2; ++hf) {
     const uint4 t = ld<uint4>(bp + hf * 1024, lane * 16u);
@@ -741,7 +740,7 @@ struct FpLayout {
 __device__ __forceinline__ FpLayout fp_layout(const DecodeArgs& a, const Seq& sq) {
   FpLayout f;
   f.ring_groups = (sq.n_res + 15) >> 4;
-  f.pool_groups = (a.d.pool_slots + 15) >> 4;
+  f.pool_groups = a.pool_groups;
   f.new_group = sq.n_res > sq.n_ring ? sq.n_ring >> 4 : -1;
   f.new_t = sq.n_ring & 15;
   return f;
@@ -750,17 +749,16 @@ __device__ __forceinline__ FpLayout fp_layout(const DecodeArgs& a, const Seq& sq
 // Issue the loads of group g (a wavefront without a group passes one that exists: the same loads are then
 // in flight on every path; the ring always has a first group of 16 rows).  Every pool slot is read, filled or
 // not: the slot counts are looked at only when the data is used, so that these loads do not wait for them.
-__device__ __forceinline__ void fp_load(FpRegs& X, const DecodeArgs& a, const Seq& sq, const FpLayout& f, int64_t u,
+__device__ __forceinline__ void fp_load(FpRegs& X, const DecodeArgs& a, const Seq& sq, const FpLayout& f, uint32_t ul,
                                         const __half* k_new_row, int g, int lane) {
-  const Dims& d = a.d;
   const int m16 = lane & 15, r = lane >> 4;
   const bool is_ring = g < f.ring_groups;                            // uniform
-  int ring0 = sq.res_start + 16 * (is_ring ? g : 0);
-  ring0 -= ring0 >= d.res_rows ? d.res_rows : 0;
-  const int slot0 = 16 * (g - f.ring_groups);
-  const int64_t row0 = is_ring ? u * d.res_rows + ring0 : u * d.pool_slots + slot0;
-  const unsigned char* kb = (const unsigned char*)((is_ring ? a.k_res : a.pool_k) + row0 * kHeadDim);
-  const unsigned char* vb = (const unsigned char*)((is_ring ? a.v_res : a.pool_v) + row0 * kHeadDim);
+  uint32_t row = (uint32_t)(sq.res_start + 16 * g);                  // inside the unit's ring, or its pools
+  row -= row >= (uint32_t)a.d.res_rows ? (uint32_t)a.d.res_rows : 0u;
+  row = is_ring ? row : 16u * (uint32_t)(g - f.ring_groups);
+  const uint64_t at = (uint64_t)ul * (is_ring ? a.ring_stride : a.pool_stride) + row * (2u * kHeadDim);
+  const unsigned char* kb = (is_ring ? a.k_res : a.pool_k) + at;
+  const unsigned char* vb = (is_ring ? a.v_res : a.pool_v) + at;
   X.group = g;
   // Keys: lane (row m16, quarter r) reads its 16 bytes of each 64-byte run of its row
   const bool is_new = g == f.new_group && m16 == f.new_t;
@@ -782,7 +780,7 @@ __device__ __forceinline__ bool fp_row_ok(const DecodeArgs& a, const Seq& sq, co
 
 template <int GQ, int NV, bool ROPE, bool MATRIX>
 __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ, MATRIX>& F, WaveLds<GQ, NV>& L, const DecodeArgs& a,
-                                           const Seq& sq, const FpLayout& f, int n_pool, int n_aux, int r0,
+                                           const Seq& sq, const FpLayout& f, int n_pool, int n_aux,
                                            uint32_t k_new_word, uint32_t v_new_word, int lane) {
   const int m16 = lane & 15, r = lane >> 4;
   const bool okk = fp_row_ok(a, sq, f, X.group, m16, n_pool, n_aux);
@@ -810,10 +808,10 @@ __device__ __forceinline__ void fp_compute(FpRegs& X, FpAcc<GQ, MATRIX>& F, Wave
     }
   }
   // Several query tokens at once: token i of q_tokens does not see the q_tokens - 1 - i tokens after it,
-  // which are the newest residual rows (one query token: nothing is hidden).  Row j of this workgroup
-  // belongs to token (r0 + j) >> g_shift.
+  // which are the newest residual rows (one query token: nothing is hidden).  Row j belongs to token
+  // j >> g_shift.
   auto seen_by = [&](int j) {
-    const int after = a.q_tokens - 1 - ((r0 + j) >> a.g_shift);
+    const int after = a.q_tokens - 1 - (j >> a.g_shift);
     const int row = 16 * X.group + m16;                              // its place among the residual tokens
     return okk && !(X.group < f.ring_groups && row >= sq.n_res - after);
   };
@@ -945,13 +943,13 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   // finds none of them in the scalar cache.  (Left to itself the compiler fetches an argument where it
   // is first used, and each such place waits for everything that is in flight on the scalar side.  No
   // test of an argument may come ahead of this point: what follows it would wait for a trip of its own.)
-  asm volatile("" ::"s"(a.nw), "s"(a.splits), "s"(a.head_parts), "s"(a.mc_per_split), "s"(a.n_quant), "s"(a.res_start),
-               "s"(a.n_res), "s"(d.kv_heads), "s"(d.q_heads), "s"(d.unit0), "s"(d.pool_slots), "s"(d.res_rows), "s"(d.N),
-               "s"(d.bpg_shift), "s"(d.block_bytes), "s"(d.blocks_per_unit), "s"(d.groups_per_unit), "s"(a.q),
-               "s"(a.k_codes), "s"(a.k_meta), "s"(a.v_codes), "s"(a.v_meta), "s"(a.mask), "s"(a.k_res), "s"(a.v_res),
-               "s"(a.pool_k), "s"(a.pool_v), "s"(a.pool_count), "s"(a.aux_count), "s"(a.seq));
-  asm volatile("" ::"s"(a.k_new), "s"(a.v_new), "s"(d.page_table), "s"(d.table_stride), "s"(d.n_pages), "s"(d.plane0),
-               "s"(a.q_tokens), "s"(a.g_shift), "s"(a.plan), "s"(a.plan_entries));
+  asm volatile("" ::"s"(a.nw), "s"(a.splits), "s"(a.mc_per_split), "s"(a.n_quant), "s"(a.res_start), "s"(a.n_res),
+               "s"(d.kv_heads), "s"(d.q_heads), "s"(d.pool_slots), "s"(d.res_rows), "s"(d.N), "s"(d.bpg_shift),
+               "s"(a.code_stride), "s"(a.k_meta_stride), "s"(a.v_meta_stride), "s"(a.mask_stride), "s"(a.ring_stride),
+               "s"(a.pool_stride), "s"(a.pool_groups), "s"(a.q), "s"(a.k_codes), "s"(a.k_meta), "s"(a.v_codes),
+               "s"(a.v_meta), "s"(a.mask), "s"(a.k_res), "s"(a.v_res), "s"(a.pool_k), "s"(a.pool_v));
+  asm volatile("" ::"s"(a.pool_count), "s"(a.aux_count), "s"(a.seq), "s"(a.k_new), "s"(a.v_new), "s"(d.page_table),
+               "s"(d.table_stride), "s"(d.n_pages), "s"(a.q_tokens), "s"(a.g_shift), "s"(a.plan), "s"(a.plan_entries));
   if constexpr (ROPE) asm volatile("" ::"s"(a.rope), "s"(a.rope_stride));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -959,9 +957,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   const int nw = a.nw;
   const int nthreads = nw * 64;
   const int m16 = lane & 15, r = lane >> 4;
-  // the query heads of a kv head may be dealt to `head_parts` workgroup rows (part-major in
-  // blockIdx.y, so that the parts of one kv head tend to land on the same compute die)
-  const int h = blockIdx.y % d.kv_heads, part = blockIdx.y / d.kv_heads;
+  const int h = blockIdx.y;
   int split = blockIdx.x, b = blockIdx.z, n_splits = a.splits;
   int64_t part_first = -1;                               // first slot of the unit's partial results (plan only)
   int4 planned = {0, 0, 0, 0};
@@ -980,28 +976,26 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
     split = min(max(e0.y, 0), n_splits - 1);
     plan_mc_begin = e0.w;
     plan_mc_end = planned.w;
-    part_first = (int64_t)blockIdx.y * a.plan_entries + min(max(entry - split, 0), a.plan_entries - n_splits);
+    part_first = (int64_t)h * a.plan_entries + min(max(entry - split, 0), a.plan_entries - n_splits);
   }
-  const int ul = b * d.kv_heads + h;                     // the unit whose cache is read
-  const int wl = ul * a.head_parts + part;               // its slice of the workspace
-  // The rows handled here: GQ consecutive (query token, query head) pairs of the kv head, token-major
-  // (a plain decode step has one token: the rows are the kv head's query heads).
-  const int r0 = part * GQ;
-  auto row_elem = [&](int j) -> int64_t {                // element offset of row j's query and output row
-    const int r = r0 + j, tj = r >> a.g_shift, hj = r & ((1 << a.g_shift) - 1);
-    return (((int64_t)b * a.q_tokens + tj) * d.q_heads + (h << a.g_shift) + hj) * kHeadDim;
-  };
-  const int64_t u = d.unit0 + ul;
+  // the unit whose cache is read (batch * kv_heads, the workgroup rows of a launch, is below 2^31)
+  const uint32_t ul = (uint32_t)b * (uint32_t)d.kv_heads + (uint32_t)h;
+  // The rows handled here: the kv head's GQ (query token, query head) pairs, token-major (a plain decode step has
+  // one token: the rows are the kv head's query heads).  Byte offset of row j's query and output row behind row 0's:
+  const uint64_t row0_bytes =
+      ((((uint64_t)((uint32_t)b * (uint32_t)a.q_tokens) * (uint32_t)d.kv_heads + (uint32_t)h) << a.g_shift) * (2u * kHeadDim));
+  const uint32_t token_skip = (uint32_t)(d.q_heads - (1 << a.g_shift));    // from a token's last row to the next one's first
+  auto row_offset = [&](int j) -> uint32_t { return ((uint32_t)j + (uint32_t)(j >> a.g_shift) * token_skip) * (2u * kHeadDim); };
   const float qscale = 1.4426950408889634f * 0.08838834764831845f;   // log2(e) / sqrt(128)
   WaveLds<GQ, NV>& L = ((WaveLds<GQ, NV>*)smem)[wave];
-  const __half* qbase = a.q + row_elem(0);               // also stands in for rows that do not exist
+  const unsigned char* qbase = (const unsigned char*)a.q + row0_bytes;   // also stands in for rows that do not exist
   // A batch of sequences of different lengths: each sequence's own state, read from memory.  The
   // arguments' values bound it (the host has checked them against the buffers), so that whatever
   // the array holds every access below stays inside the buffers.
   Seq sq = {a.n_quant, a.res_start, a.n_res, a.n_res};
   if (a.k_new) sq.n_res += 1;                            // the token being decoded: the newest residual row
   if (a.seq || entry >= 0) {
-    const int4 own = entry >= 0 ? planned : *(const int4*)(a.seq + 4 * b);   // uniform: one scalar load
+    const int4 own = entry >= 0 ? planned : *(const int4*)(a.seq + 4 * b);   // uniform
     sq.n_quant = min(max(own.x, 0), a.n_quant) & ~(kBlockTokens - 1);
     sq.res_start = (own.y >= 0 && own.y < d.res_rows) ? own.y & ~15 : 0;   // (a row group of 16 must not wrap)
     sq.n_res = min(max(own.z, 0), a.n_res);
@@ -1012,43 +1006,14 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   P.nblocks = sq.n_quant >> 5;
   P.last_block = max(P.nblocks - 1, 0);
   P.bpg_shift = d.bpg_shift;
-  P.block_bytes = (uint32_t)d.block_bytes;
   P.table = PAGED ? d.page_table + (int64_t)b * d.table_stride : nullptr;
   P.n_pages = d.n_pages;
   // the mini-chunks of the quantized segment that are this workgroup's: [mc_begin, mc_end)
-  const int n_mc = (sq.n_quant + kMiniChunk - 1) / kMiniChunk;
+  const int n_mc = (int)((uint32_t)(sq.n_quant + kMiniChunk - 1) / kMiniChunk);
   const int mc_begin = entry >= 0 ? min(max(plan_mc_begin, 0), n_mc) : split * a.mc_per_split;
   const int mc_end = entry >= 0 ? min(max(plan_mc_end, mc_begin), n_mc) : min(n_mc, (split + 1) * a.mc_per_split);
   int mc = mc_begin + wave;
-  // A paged cache: the page numbers of the wave's first two mini-chunks are asked for before
-  // everything else, so that the loads of the first mini-chunk can follow as soon as possible
-  // (from then on the entries of a mini-chunk are fetched one mini-chunk ahead of its loads).
-  typename UnitPtrs<PAGED>::Pages pages_now = {0, 0}, pages_next = {0, 0};
-  if constexpr (PAGED) {
-    pages_now = P.fetch_pages(mc, lane);
-    pages_next = P.fetch_pages(mc + nw, lane);
-  }
-
-  // Loads go out in the order their data is needed, and all of them before anything is waited
-  // on: the query, the wave's first group of full-precision rows, its first quantized mini-chunk.
-  uint32_t qw[GQ];
-#pragma unroll
-  for (int j = 0; j < GQ; ++j) qw[j] = ((const uint32_t*)(a.q + row_elem(j)))[lane];
-  // The rows of the token being decoded, if they come with the call: one wavefront of the unit
-  // stores them in the ring at the end (every wavefront loads them, so that all issue the same
-  // loads; without such rows the query row is read instead).
-  const __half* k_new_row = a.k_new ? a.k_new + (int64_t)ul * kHeadDim : qbase;
-  const __half* v_new_row = a.k_new ? a.v_new + (int64_t)ul * kHeadDim : qbase;
-  uint32_t k_new_word = ((const uint32_t*)k_new_row)[lane];
-  const uint32_t v_new_word = ((const uint32_t*)v_new_row)[lane];
-  // the angles of the new token's position, if the launch is to rotate the query and the new Key
-  float2 rope_cos = {1.f, 1.f}, rope_sin = {0.f, 0.f};
-  if constexpr (ROPE) {
-    const float* rope_row = a.rope + (int64_t)b * a.rope_stride;
-    rope_cos = ((const float2*)rope_row)[lane & 31];
-    rope_sin = ((const float2*)rope_row)[32 + (lane & 31)];
-  }
-
+  const bool has_q = mc < mc_end;                        // uniform over the wave
   // full-precision row groups go to the unit's wavefronts from the last one backwards (the
   // first wavefronts of a workgroup are the ones that may hold one more mini-chunk)
   const FpLayout fl = fp_layout(a, sq);
@@ -1056,54 +1021,38 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   const int unit_waves = n_splits * nw;
   int rg = unit_waves - 1 - (split * nw + wave);
   const bool has_fp = rg < n_rg;                         // uniform over the wave
+  // Loads go out in the order their data is needed, and all of them before anything is waited
+  // on: the query, the wave's first group of full-precision rows, its first quantized mini-chunk.
+  uint32_t qw[GQ];
+  // The rows of the token being decoded, if they come with the call: one wavefront of the unit
+  // stores them in the ring at the end (every wavefront loads them; without such rows the query row
+  // is read instead).
+  const __half* k_new_row = a.k_new ? a.k_new + (uint64_t)ul * kHeadDim : (const __half*)qbase;
+  const __half* v_new_row = a.k_new ? a.v_new + (uint64_t)ul * kHeadDim : (const __half*)qbase;
+  uint32_t k_new_word, v_new_word;
+  float2 rope_cos, rope_sin;                             // the angles of the new token's position (ROPE)
   // The unit's slot counts come through the vector memory path, ahead of the rows they qualify:
   // a scalar load in flight would hold up the next wait on the scalar side, which comes before
   // the quantized loads below.
-  // Every wavefront issues the same loads, whether or not it has rows or a mini-chunk to work on
-  // (a wavefront without a row group loads the unit's first one, one without a mini-chunk the unit's
-  // last block): only then are the loads in flight the same on every path, and only then can the
-  // waits leave the younger ones in flight.
-  FpRegs X;
-  int64_t uv = u;
-  asm("" : "+v"(uv));                                    // a vector address: a vector load
-  int n_pool = a.pool_count[uv];
-  int n_aux = a.aux_count[uv];
-  if (n_rg > 0) {                                        // (no residual token and no pool slot at all: nothing to load)
-    fp_load(X, a, sq, fl, u, k_new_row, has_fp ? rg : 0, lane);
-  }
-
-  // Quantized arrays: a dense cache keeps the blocks of unit u together, a paged one those of the
-  // plane (layer, kv head); there d.blocks_per_unit and d.groups_per_unit are the plane's.
-  const int64_t uq = PAGED ? d.plane0 + h : u;
-  P.kc = a.k_codes + uq * d.blocks_per_unit * (int64_t)d.block_bytes;
-  P.vc = a.v_codes + uq * d.blocks_per_unit * (int64_t)d.block_bytes;
-  P.km = (const unsigned char*)(a.k_meta + uq * d.groups_per_unit * kHeadDim);
-  P.vm = (const unsigned char*)a.v_meta + uq * d.blocks_per_unit * (int64_t)(128 * NV);
-  P.mask = (const unsigned char*)(a.mask + uq * d.blocks_per_unit);
-  const bool has_q = mc < mc_end;                        // uniform over the wave
-  McRegs<BITS, NV> R;
-  if constexpr (PAGED) P.resolve(mc, pages_now, lane);
-  load_k_meta<BITS, NV, SB>(R, P, mc, lane);
-  load_codes<BITS>(R.kc, P.kc, P, mc, lane);
-  load_v_meta(R, P, mc, lane);
-  load_codes<BITS>(R.vc, P.vc, P, mc, lane);
-
-  if constexpr (ROPE) {
+  int n_pool, n_aux;
+  auto load_query = [&]() {
 #pragma unroll
-    for (int j = 0; j < GQ; ++j)
-      qw[j] = rope_word(qw[j], (uint32_t)__shfl_xor((int)qw[j], 32), rope_cos, rope_sin, lane >= 32);
-    k_new_word = rope_word(k_new_word, (uint32_t)__shfl_xor((int)k_new_word, 32), rope_cos, rope_sin, lane >= 32);
-  }
-  // this lane's two channels (2*lane, 2*lane+1) of every query head, log2-domain scaled
-  float qa[GQ][2];
-#pragma unroll
-  for (int j = 0; j < GQ; ++j) {
-    qa[j][0] = h2f_bits(qw[j] & 0xFFFFu) * qscale;
-    qa[j][1] = h2f_bits(qw[j] >> 16) * qscale;
-  }
+    for (int j = 0; j < GQ; ++j) qw[j] = *(const uint32_t*)(qbase + row_offset(j) + 4 * lane);
+    k_new_word = ((const uint32_t*)k_new_row)[lane];
+    v_new_word = ((const uint32_t*)v_new_row)[lane];
+    if constexpr (ROPE) {
+      const float* rope_row = a.rope + (int64_t)b * a.rope_stride;
+      rope_cos = ((const float2*)rope_row)[lane & 31];
+      rope_sin = ((const float2*)rope_row)[32 + (lane & 31)];
+    }
+    uint64_t uv = ul;
+    asm("" : "+v"(uv));                                  // a vector address: a vector load
+    n_pool = a.pool_count[uv];
+    n_aux = a.aux_count[uv];
+  };
 
-  // ---- full-precision part, while the first quantized loads are in flight --------------------------
-  constexpr bool MATRIX = fp_on_matrix_cores<GQ, BITS>();
+  float qa[GQ][2];                                       // this lane's two channels (2*lane, 2*lane+1) of every query
+  constexpr bool MATRIX = fp_on_matrix_cores<GQ, BITS>();   // head, log2-domain scaled
   FpAcc<GQ, MATRIX> F;
 #pragma unroll
   for (int i = 0; i < FpAcc<GQ, MATRIX>::kHeads; ++i) {
@@ -1119,22 +1068,83 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
       for (int j = 0; j < GQ; ++j) F.o[j][e] = 0.f;
     }
   }
+  FpRegs X;
+  McRegs<BITS, NV> R;
+  auto load_rows = [&](FpRegs& regs, int g) { fp_load(regs, a, sq, fl, ul, k_new_row, g, lane); };
+  // A paged cache: the page numbers of the wave's first two mini-chunks are asked for before
+  // everything else, so that the loads of the first mini-chunk can follow as soon as possible
+  // (from then on the entries of a mini-chunk are fetched one mini-chunk ahead of its loads).
+  typename UnitPtrs<PAGED>::Pages pages_now = {0, 0}, pages_next = {0, 0};
+  auto load_first_minichunk = [&]() {
+    // Quantized arrays: a dense cache keeps the blocks of a unit together, a paged one those of the plane (layer, kv head)
+    const uint32_t uq = PAGED ? (uint32_t)h : ul;
+    const uint64_t code_at = (uint64_t)uq * a.code_stride;
+    P.kc = a.k_codes + code_at;
+    P.vc = a.v_codes + code_at;
+    P.km = a.k_meta + (uint64_t)uq * a.k_meta_stride;
+    P.vm = a.v_meta + (uint64_t)uq * a.v_meta_stride;
+    P.mask = a.mask + (uint64_t)uq * a.mask_stride;
+    if constexpr (PAGED) P.resolve(mc, pages_now, lane);
+    load_k_meta<BITS, NV, SB>(R, P, mc, lane);
+    load_codes<BITS>(R.kc, P.kc, P, mc, lane);
+    load_v_meta(R, P, mc, lane);
+    load_codes<BITS>(R.vc, P.vc, P, mc, lane);
+  };
+  auto take_query = [&]() {                              // the query rows, for both parts
 #pragma unroll
-  for (int j = 0; j < GQ; ++j) {                         // the query rows, for both parts
-    uint32_t hi, lo;
-    split_pair(qa[j][0], qa[j][1], hi, lo);
-    ((uint32_t*)L.q0[2 * j])[lane] = hi;
-    ((uint32_t*)L.q0[2 * j + 1])[lane] = lo;
-  }
-  wave_sync();
-  if (has_fp) {
-    n_pool = __builtin_amdgcn_readfirstlane(n_pool);
-    n_aux = __builtin_amdgcn_readfirstlane(n_aux);
-    fp_compute<GQ, NV, ROPE, MATRIX>(X, F, L, a, sq, fl, n_pool, n_aux, r0, k_new_word, v_new_word, lane);
-    for (rg += unit_waves; rg < n_rg; rg += unit_waves) {          // the wavefront's further groups
-      fp_load(X, a, sq, fl, u, k_new_row, rg, lane);
-      fp_compute<GQ, NV, ROPE, MATRIX>(X, F, L, a, sq, fl, n_pool, n_aux, r0, k_new_word, v_new_word, lane);
+    for (int j = 0; j < GQ; ++j) asm volatile("" : "+v"(qw[j])::"memory");   // first used here, behind the loads
+    if constexpr (ROPE) {
+#pragma unroll
+      for (int j = 0; j < GQ; ++j)
+        qw[j] = rope_word(qw[j], (uint32_t)__shfl_xor((int)qw[j], 32), rope_cos, rope_sin, lane >= 32);
+      k_new_word = rope_word(k_new_word, (uint32_t)__shfl_xor((int)k_new_word, 32), rope_cos, rope_sin, lane >= 32);
     }
+#pragma unroll
+    for (int j = 0; j < GQ; ++j) {
+      qa[j][0] = h2f_bits(qw[j] & 0xFFFFu) * qscale;
+      qa[j][1] = h2f_bits(qw[j] >> 16) * qscale;
+      uint32_t hi, lo;
+      split_pair(qa[j][0], qa[j][1], hi, lo);
+      ((uint32_t*)L.q0[2 * j])[lane] = hi;
+      ((uint32_t*)L.q0[2 * j + 1])[lane] = lo;
+    }
+    wave_sync();
+  };
+  auto work_on_rows = [&](FpRegs& regs) {
+    fp_compute<GQ, NV, ROPE, MATRIX>(regs, F, L, a, sq, fl, __builtin_amdgcn_readfirstlane(n_pool),
+                                     __builtin_amdgcn_readfirstlane(n_aux), k_new_word, v_new_word, lane);
+  };
+
+  // ---- full-precision part, while the first quantized loads are in flight --------------------------
+  // A wavefront loads what it has work for and nothing else: the loads of all eight go through one L1 at 64 bytes a
+  // cycle (20 KB each: 1.2 us), and two share a SIMD's issue slots, the older one first, so that what the idle ones load
+  // delays those that the launch waits for.  The two paths have their loads to themselves and one of them ends with
+  // none in flight: only then are the loads in flight the same on every way to a point, and only then can a wait leave
+  // the younger ones in flight.  (Rows may be left out ahead of the quantized loads, not the other way round; a path
+  // with its first rows ahead of its query, or a third copy of the rows' code, measured 1 .. 7 % slower.)  Us per launch
+  // with the same loads for every wavefront / as here, 16 sequences of 320 tokens 8.7 / 7.6, one of 4099 with 8 kv heads
+  // 10.5 / 9.5, with 32 kv heads 9.7 / 9.1, 4 of 32768 26.8 / 26.2; where every wavefront has both, as before.
+  if (has_q) {
+    asm volatile("; with quantized tokens" ::: "memory");   // (keeps the compiler from pulling the loads ahead of the branch)
+    if constexpr (PAGED) {
+      pages_now = P.fetch_pages(mc, lane);
+      pages_next = P.fetch_pages(mc + nw, lane);
+    }
+    load_query();
+    if (has_fp) load_rows(X, rg);
+    load_first_minichunk();
+    take_query();
+    if (has_fp) work_on_rows(X);
+    rg += unit_waves;
+  } else {
+    asm volatile("; full-precision rows alone" ::: "memory");
+    load_query();
+    take_query();
+    asm volatile("" ::"v"(n_pool), "v"(n_aux), "v"(k_new_word), "v"(v_new_word));
+  }
+  for (; rg < n_rg; rg += unit_waves) {                  // the wavefront's further groups
+    load_rows(X, rg);
+    work_on_rows(X);
   }
 
   FpResult<GQ, MATRIX> fp;
@@ -1187,11 +1197,12 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
     compute_minichunk<GQ, BITS, NV, SB, false>(R, S, L, qh, ql, lane, P, mc);
   }
   const float post_v = __builtin_amdgcn_exp2f((float)(24 - kShV));
-  if (a.k_new && split == 0 && part == 0 && wave == 0) {     // append: the ring row after the live ones
+  if (a.k_new && split == 0 && wave == 0) {     // append: the ring row after the live ones
     int row = sq.res_start + sq.n_ring;
     row -= row >= d.res_rows ? d.res_rows : 0;
-    ((uint32_t*)(const_cast<__half*>(a.k_res) + (u * d.res_rows + row) * kHeadDim))[lane] = k_new_word;
-    ((uint32_t*)(const_cast<__half*>(a.v_res) + (u * d.res_rows + row) * kHeadDim))[lane] = v_new_word;
+    const uint64_t at = (uint64_t)ul * a.ring_stride + (uint32_t)row * (2u * kHeadDim);
+    ((uint32_t*)(const_cast<uint8_t*>(a.k_res) + at))[lane] = k_new_word;
+    ((uint32_t*)(const_cast<uint8_t*>(a.v_res) + at))[lane] = v_new_word;
   }
 
   // ---- hand both results of the wave to the merge buffer ---------------------------------------------
@@ -1227,7 +1238,8 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
 
   // ---- merge the 2 nw results: the output itself if this workgroup is the unit's only one, else its partial
   __syncthreads();
-  const int64_t part_slot0 = part_first >= 0 ? part_first : (int64_t)wl * n_splits;
+  __half* out_rows = (__half*)((unsigned char*)a.out + row0_bytes);
+  const int64_t part_slot0 = part_first >= 0 ? part_first : (int64_t)ul * n_splits;
   float* part_out = a.partials + (part_slot0 + split) * GQ * (kHeadDim + 2);
   // Thread = C channels of one row.  All values are asked for at once; meanwhile the weights of the results
   // (lane & 15 = result) are formed inside rows of 16 lanes and handed round there.  What bounds it is the chain
@@ -1269,7 +1281,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
       }
 #pragma unroll
       for (int e = 0; e < C; ++e) {
-        if (n_splits == 1) a.out[row_elem(j) + c + e] = __float2half_rn(l > 0.f ? o[e] / l : 0.f);
+        if (n_splits == 1) out_rows[row_offset(j) / 2 + c + e] = __float2half_rn(l > 0.f ? o[e] / l : 0.f);
         else coherent_store(&part_out[j * (kHeadDim + 2) + 2 + c + e], o[e]);
       }
       if (n_splits > 1 && c == 0) {
@@ -1295,7 +1307,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __syncthreads();
   if (tid == 0) {
-    const int old = __hip_atomic_fetch_add(&a.counters[wl], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int old = __hip_atomic_fetch_add(&a.counters[ul], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_last = (old == n_splits - 1);
   }
   __syncthreads();
@@ -1331,14 +1343,14 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, unsigned char* 
         }
         m = mb;
       }
-      a.out[row_elem(j) + c] = __float2half_rn(l > 0.f ? o / l : 0.f);
+      out_rows[row_offset(j) / 2 + c] = __float2half_rn(l > 0.f ? o / l : 0.f);
     }
     if (tid == 0)                                        // leave the counter as it was found
-      __hip_atomic_store(&a.counters[wl], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&a.counters[ul], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-// grid (splits, kv_heads * head_parts, batch), or with a launch plan (entries, kv_heads, 1); 64 * a.nw threads
+// grid (splits, kv_heads, batch), or with a launch plan (entries, kv_heads, 1); 64 * a.nw threads
 // (a.nw at most what one compute unit holds of this instance), a.nw * sizeof(WaveLds) bytes of dynamic LDS.
 template <int GQ, int BITS, int NV, bool PAGED, int SB, bool ROPE>
 __global__ void __launch_bounds__(64 * 4 * kDecodeWavesPerSimd) __attribute__((amdgpu_waves_per_eu(kDecodeWavesPerSimd)))
@@ -1431,8 +1443,8 @@ int decode_wave_lds_bytes(int g, int nv) {
 }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s) {
-  const dim3 grid(a.plan ? a.plan_entries : a.splits, a.d.kv_heads * a.head_parts, a.plan ? 1 : a.d.batch);
-  switch ((a.q_tokens << a.g_shift) / a.head_parts) {
+  const dim3 grid(a.plan ? a.plan_entries : a.splits, a.d.kv_heads, a.plan ? 1 : a.d.batch);
+  switch (a.q_tokens << a.g_shift) {
     case 1: launch_bits<1>(a, grid, s); break;
     case 2: launch_bits<2>(a, grid, s); break;
     case 8: launch_bits<8>(a, grid, s); break;

@@ -80,3 +80,51 @@ def test_launch_plan_of_any_number_of_sequences(batch):
         want += [[b, k, parts, min(k * per, m), s[0], 0, s[2], min((k + 1) * per, m)] for k in range(parts)]
     assert plan[0] == len(want)
     assert plan[8:8 + 8 * len(want)] == [x for e in want for x in e]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,kv_heads,g,context,residual,budget,shape", [
+    (1, 1, 4, 4200, 128, 8, (8, 8)),      # some wavefronts have quantized tokens, some rows, some neither
+    (1, 2, 8, 1100, 100, 3, (2, 8)),
+    (2, 2, 1, 2100, 128, 8, (4, 6)),      # all have quantized tokens or rows, few have both
+    (16, 8, 4, 320, 128, 8, (1, 8)),      # two of eight have quantized tokens
+    (1, 2, 2, 100, 128, 8, (1, 5)),       # none has
+    (1, 1, 1, 9, 32, 0, (1, 1)),          # one wavefront with one group of rows
+    (40, 8, 4, 4150, 128, 8, (3, 2)),     # every wavefront has both
+])
+@pytest.mark.parametrize("paged", [False, True])
+def test_step_equals_its_parts_however_the_work_is_dealt(batch, kv_heads, g, context, residual, budget, shape, paged):
+    """Rotation, append and attention in one launch against a launch of its own for each: the same bits, in the
+    outputs and in the ring."""
+    import torch
+    nq = 32 * ((context - residual) // 32) if context >= residual + 32 else 0
+    cfg = KC.make_config(1, batch, g * kv_heads, kv_heads, max(nq, 32), 2, 32, 32, residual, budget, 32 if budget else 0)
+    slots = budget + 32 if budget else 0
+    assert B.kvq_decode_launch_shape(cfg, 1, nq, context - nq + 1 + slots)[:2] == shape
+    groups = cfg.max_seq // 32
+    cache = KC.KVCache(cfg, n_pages=batch * groups if paged else None)
+    if paged:
+        cache.page_table.copy_(torch.randperm(batch * groups, generator=torch.Generator().manual_seed(3)).view(batch, groups))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(context)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda").half()
+    cache.prefill(0, new(batch, kv_heads, context, 128), new(batch, kv_heads, context, 128))
+    k, v, q = new(batch, kv_heads, 128), new(batch, kv_heads, 128), new(batch, g * kv_heads, 128)
+    angle = torch.arange(64, device="cuda") / 7.0
+    rope = torch.cat([angle.cos(), angle.sin()]).float()
+    parts = KC.KVCache(cfg, n_pages=batch * groups) if paged else cache.clone()
+    if paged:
+        for name in ("k_codes", "k_meta", "v_codes", "v_meta", "mask", "page_table", "k_res", "v_res", "pool_k", "pool_v",
+                     "pool_idx", "pool_score", "pool_count", "aux_count", "frozen"):
+            getattr(parts, name).copy_(getattr(cache, name))
+        parts.n_quant, parts.n_res = list(cache.n_quant), list(cache.n_res)
+    got = cache.step(0, k, v, q, rope=rope)
+    kr, qr = torch.empty_like(k), torch.empty_like(q)
+    B.kvq_rope_rotate(cfg, k, kv_heads, rope, 0, kr)
+    B.kvq_rope_rotate(cfg, q, g * kv_heads, rope, 0, qr)
+    assert not parts.append(0, kr, v)
+    want = parts.decode(0, qr)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(got).all()) and float(got.abs().max()) > 0
+    assert torch.equal(got, want)
+    assert torch.equal(cache.k_res, parts.k_res) and torch.equal(cache.v_res, parts.v_res)
