@@ -47,12 +47,15 @@ int64_t res_rows_of(const kvq_config* c) {
 //  - The largest size that fits is taken, unless a smaller one lets so many more wavefronts be resident that each
 //    has a mini-chunk less (148 units, 1 x 8 / 3 x 4: context 1100 13.6 / 14.3 us, 4100 22.1 / 21.0, 12000 47.8 /
 //    38.6; 184 units, 1 x 8 / 2 x 4, which are equally many: 4100 23.0 / 26.0).
-//  - One workgroup per unit needs no exchange through memory (about 2 us).  Up to 32 mini-chunks, several are
-//    taken so that each has at most four, one per SIMD, the other wavefronts taking the full-precision rows
-//    (context in mini-chunks: 64 units x 15 in 3 x 7 13.6 us, 4 x 8 11.3; 32 x 31, 8 rows, 5 x 8 15.8, 8 x 8 13.8;
-//    128 x 5, 1 x 8 13.1, 2 x 8 11.0; 128 x 2, 1 x 8 9.9, 2 x 8 12.1).  Beyond, at least eight, or as many as give
-//    each eight mini-chunks (the partial results of eight workgroups are merged in one pass: 8 units x 127, 32 x 8
-//    13.8 us, 16 x 8 13.2).  More than 24 groups of full-precision rows: as many as give each sixteen.
+//  - One workgroup per unit needs no exchange through memory (about 2 us): up to four mini-chunks are left to one
+//    (8 units x 4, 1 x 8 7.5 us, 4 x 8 8.1).  Five or six go to four workgroups, up to 32 to eight (all partial results
+//    are merged in one pass then), up to 64 to as many as have four each, a multiple of four so that a few are left for
+//    the full-precision rows, beyond to sixteen or as many as have eight each (us with as many workgroups as have four
+//    mini-chunks, at most eight, and / or with these: 8 units of four rows x 5 8.5 / 8.1, x 7 8.8 / 8.3, x 16 8.9 / 8.6,
+//    x 40 10.9 / 9.5, x 63 11.3 / 9.8, x 100 11.5 / 11.1; 32 x 7 9.6 / 8.9; 32 of one row x 16 8.4 / 7.9, 8 of one row x
+//    7 7.5 / 6.8).  Up to four units keep four mini-chunks per workgroup, up to 32 in all: the tests of the merges rely
+//    on their shapes (4 units x 16, 4 x 6 7.6 us, 8 x 4 7.1).  More than 24 groups of full-precision rows: as many
+//    workgroups as give each sixteen.
 //  - With four or more rows per unit the workgroups of a split unit have all their wavefronts (64 units x 15, 4 x
 //    4 / 6 / 7 / 8: 11.8 / 12.0 / 12.2 / 11.3 us), with fewer as many as there is work for, at least one per SIMD
 //    (32 x 31, one row, 8 x 4 / 5 / 6 / 8: 10.2 / 10.3 / 10.4 / 11.2 us).
@@ -64,6 +67,14 @@ struct Split {
 // compute units, where 1024 workgroups of two wavefronts would be resident.  The static entry point asks for room for
 // a launch plan's partial results too, which can be more: 1024 for 300 sequences of one kv head.)
 constexpr int64_t kMaxSplitWorkgroups = 960;
+int64_t whole_workgroups(int64_t units, int64_t mc) {    // per unit, of the largest size
+  if (mc <= 32 && units <= 4) return (mc + 3) / 4;
+  if (mc <= 4) return 1;
+  if (mc <= 6) return 4;
+  if (mc <= 32) return 8;
+  if (mc <= 64) return 4 * ((mc + 15) / 16);
+  return (mc + 7) / 8 > 16 ? (mc + 7) / 8 : 16;
+}
 int64_t waves_per_compute_unit(int g, int vgroups) {
   int64_t w = kvq::kLdsPerComputeUnit / kvq::decode_wave_lds_bytes(g, vgroups);
   const int64_t by_registers = 4 * kvq::kDecodeWavesPerSimd;
@@ -83,7 +94,7 @@ Split decode_split(int64_t units_per_layer, int g, int vgroups, int64_t n_quant,
     if (fit < 1) continue;
     if (best_load >= 0 && (size < 2 || (size < 4 && units_per_layer <= kvq::kComputeUnits))) break;
     int64_t splits;
-    if (size == waves_per_cu) splits = mc <= 32 ? (mc + 3) / 4 : (mc + 7) / 8 > 8 ? (mc + 7) / 8 : 8;
+    if (size == waves_per_cu) splits = whole_workgroups(units_per_layer, mc);
     else splits = (mc + size - 1) / size;
     if (rg > 24 && splits < (rg + 15) / 16) splits = (rg + 15) / 16;
     if (fit > 1 && fit * units_per_layer > kMaxSplitWorkgroups) fit = kMaxSplitWorkgroups / units_per_layer;
@@ -114,7 +125,9 @@ int64_t most_splits(int64_t units_per_layer, int g, int vgroups, int64_t n_quant
   if (size > waves_per_cu) size = waves_per_cu;
   int64_t fit = resident_workgroups(waves_per_cu, size) / units_per_layer;
   if (fit > 1 && fit * units_per_layer > kMaxSplitWorkgroups) fit = kMaxSplitWorkgroups / units_per_layer;
-  int64_t wanted = ((n_quant + kvq::kMiniChunk - 1) / kvq::kMiniChunk + size - 1) / size;
+  const int64_t mc = (n_quant + kvq::kMiniChunk - 1) / kvq::kMiniChunk;
+  int64_t wanted = (mc + size - 1) / size;
+  if (mc > 32 && wanted < whole_workgroups(units_per_layer, mc)) wanted = whole_workgroups(units_per_layer, mc);
   const int64_t for_rows = (fp_rows + 16 * kvq::kFpGroupRows - 1) / (16 * kvq::kFpGroupRows);
   if (wanted < 8) wanted = 8;
   if (wanted < for_rows) wanted = for_rows;

@@ -87,6 +87,9 @@ def test_launch_plan_of_any_number_of_sequences(batch):
     (1, 1, 4, 4200, 128, 8, (8, 8)),      # some wavefronts have quantized tokens, some rows, some neither
     (1, 2, 8, 1100, 100, 3, (2, 8)),
     (2, 2, 1, 2100, 128, 8, (4, 6)),      # all have quantized tokens or rows, few have both
+    (1, 8, 4, 1100, 128, 8, (8, 8)),      # one mini-chunk per workgroup
+    (1, 8, 2, 800, 128, 8, (4, 4)),       # the last workgroup has rows alone
+    (2, 8, 1, 5300, 128, 8, (12, 4)),     # more partial results than are merged at a time, the last ones of rows alone
     (16, 8, 4, 320, 128, 8, (1, 8)),      # two of eight have quantized tokens
     (1, 2, 2, 100, 128, 8, (1, 5)),       # none has
     (1, 1, 1, 9, 32, 0, (1, 1)),          # one wavefront with one group of rows
