@@ -100,6 +100,23 @@ def test_selection_in_calls_of_many_units(units, G, N, A, n):
     check_selection(K, rng.standard_normal((len(PATTERNS), n, 128)).astype(np.float16), G, N, A, units)
 
 
+@pytest.mark.parametrize("units,n", [
+    (2, 992), (2, 1024), (256, 2048), (256, 2016), (300, 512), (300, 1056), (600, 256),   # 1024, 512, 256 threads
+    (2, 2048), (2, 1024 + 480),                                                           # candidates first
+])
+def test_scores_are_told_apart_by_their_last_bit(units, n):
+    """Rows of 64 times the largest fp16 value that differ by one subnormal, 2^-24 to 2^-13, in one channel or another:
+    sums of 47 bits, of which the last ones decide."""
+    rng = np.random.default_rng(n)
+    K = np.zeros((2, n, 128), np.float16)
+    K[:, :, ::2] = 65504.0
+    K[:, :, ::4] *= -1
+    t = np.arange(n)
+    for h in range(2):
+        K[h, t, (37 * t + h) % 64 * 2 + 1] = (rng.permutation(n) * 2.0 ** -24).astype(np.float16)
+    check_selection(K, rng.standard_normal(K.shape).astype(np.float16), 32, 8, 32, units)
+
+
 def plateau_keys(G, n, low, lower):
     """Keys whose L1 norms are set one by one (128 equal channels): everything at 8 but for the tokens given.  The
     first 1024 tokens hold 640 of norm 1 and the next 384 are of norm 1, so that the 1025th token that may be selected
