@@ -247,8 +247,8 @@ int32_t kvq_quantize_value_tokens(const kvq_config* cfg, int32_t layer, int32_t 
  *              (it is a multiple of group_k under the schedule of kvq_append_trace_quantize): the
  *              residual rows are read 16 at a time, and such a run must not wrap; n_quant + n_res >= 1
  *   qcache   : all five arrays must be valid device memory of the sizes kvq_query_sizes gives, also
- *              when n_quant == 0: every workgroup loads a first block whether or not it has quantized
- *              tokens to work on.  Likewise pool.pool_k / pool_v whenever outlier_budget +
+ *              when n_quant == 0 (a sequence's own count may stand in device memory, where the call
+ *              cannot look).  Likewise pool.pool_k / pool_v whenever outlier_budget +
  *              aux_capacity > 0 (every slot is loaded, filled or not, 16 slots at a time: up to 15 rows
  *              past a unit's last slot are read, never used; kvq_sizes.pool_rows_bytes includes those
  *              15 rows behind the last unit) and pool_count, aux_count

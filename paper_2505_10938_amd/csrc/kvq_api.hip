@@ -612,7 +612,7 @@ int32_t decode_common(const kvq_config* cfg, int32_t layer, const void* q, int32
   // a token must not see the tokens after it: those are hidden as the newest residual rows
   if (q_tokens > 1 && (seq_state || k_new || n_res < q_tokens - 1)) return KVQ_ERR_INVALID_ARG;
   if (!q || !out) return KVQ_ERR_INVALID_ARG;
-  // rows are read 16 bytes at a time (the query rows too: they stand in for rows past the last pool slot)
+  // rows are read 16 bytes at a time (the query rows are held to the same)
   if ((((uintptr_t)q) | ((uintptr_t)res.k_res) | ((uintptr_t)res.v_res) | ((uintptr_t)pool.pool_k) |
        ((uintptr_t)pool.pool_v) | ((uintptr_t)qc.k_codes) | ((uintptr_t)qc.v_codes)) & 15)
     return KVQ_ERR_INVALID_ARG;
@@ -632,8 +632,8 @@ int32_t decode_common(const kvq_config* cfg, int32_t layer, const void* q, int32
     if (!k_new || (((uintptr_t)rope) & 15)) return KVQ_ERR_INVALID_ARG;
     if (rope_stride != 0 && (rope_stride < cfg->head_dim || rope_stride % 4 != 0)) return KVQ_ERR_INVALID_ARG;
   }
-  // the arrays are needed even when nothing is quantized yet: every workgroup issues the loads of a
-  // first block (the last one, or block 0) whether or not it has quantized tokens to work on
+  // the arrays are asked for also where nothing is quantized yet (how many tokens are may stand in device memory, and
+  // is not known here then); the kernel reads them only for tokens that there are
   if (!qcache_ok(cfg, qc)) return KVQ_ERR_INVALID_ARG;
   if (n_res > 0 && (!res.k_res || !res.v_res)) return KVQ_ERR_INVALID_ARG;
   if (!pool.pool_count || !pool.aux_count) return KVQ_ERR_INVALID_ARG;

@@ -754,9 +754,8 @@ __device__ __forceinline__ FpLayout fp_layout(const DecodeArgs& a, const Seq& sq
   return f;
 }
 
-// Issue the loads of group g (a wavefront without a group passes one that exists: the same loads are then
-// in flight on every path; the ring always has a first group of 16 rows).  Every pool slot is read, filled or
-// not: the slot counts are looked at only when the data is used, so that these loads do not wait for them.
+// Issue the loads of group g, which must exist.  Every pool slot is read, filled or not: the slot counts are
+// looked at only when the data is used, so that these loads do not wait for them.
 __device__ __forceinline__ void fp_load(FpRegs& X, const DecodeArgs& a, const Seq& sq, const FpLayout& f, uint32_t ul,
                                         const __half* k_new_row, int g, int lane) {
   const int m16 = lane & 15, r = lane >> 4;
