@@ -369,7 +369,9 @@ int32_t kvq_prefill_quantize(const kvq_config* cfg, int32_t layer, const void* k
  *                    KVQ_ERR_WORKSPACE below), layers * kv_heads * n_q for all of them at once.  Its
  *                    contents on return are unspecified
  *   seq_state      : the array of kvq_decode_attention_ragged, whose entry `seq` becomes
- *                    {n_q, 0, n_tokens - n_q, active != 0}, or NULL
+ *                    {n_q, 0, n_tokens - n_q, active != 0} behind everything else that the call writes, or NULL
+ * Like every call it returns at once, with its work queued on `stream`: what another stream does with the rows, with
+ * `selected` or with what the call writes has to wait for it there.
  */
 int32_t kvq_prefill_quantize_seq(const kvq_config* cfg, int32_t layer, int32_t seq, const void* k_rows,
                                  const void* v_rows, int64_t unit_stride, int32_t n_tokens, kvq_pool pool,

@@ -429,8 +429,6 @@ int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t layers, int
       // (where groups compete, the competition writes the pools' state whatever they held)
       if ((n_groups == 0 || d.N == 0) && kvq::launch_reset_pools(d, count, pool, s) != hipSuccess) return KVQ_ERR_LAUNCH;
     }
-    kvq::SeqEntry entry = {};
-    if (seq_state && first + count == end) entry = {seq_state + 4 * (int64_t)seq, n_groups * G, n_tokens - n_groups * G, active};
     const kvq::PromptRows rows = rows_of(k_rows + (first - layer), v_rows + (first - layer), count, unit_stride);
     const int32_t tail = n_tokens - n_groups * G;
     hipError_t e;
@@ -439,15 +437,16 @@ int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t layers, int
       if (e != hipSuccess) return KVQ_ERR_LAUNCH;
       // (the rows behind the last group go to the ring in the same launch)
       e = kvq::launch_quantize(d, 0, n_groups, rows, count, selected, (int64_t)n_groups * G, qc, s, tail,
-                               (__half*)res.k_res, (__half*)res.v_res, entry);
+                               (__half*)res.k_res, (__half*)res.v_res);
     } else {
-      e = kvq::launch_tail_copy(d, rows, count, tail, (__half*)res.k_res, (__half*)res.v_res, entry, s);
+      e = kvq::launch_tail_copy(d, rows, count, tail, (__half*)res.k_res, (__half*)res.v_res, s);
     }
     if (e == hipSuccess && n_more_values > 0)
       e = kvq::launch_value_tokens(d, n_groups * G, n_more_values, (__half*)res.v_res, 0, qc, s);
     if (e != hipSuccess) return KVQ_ERR_LAUNCH;
   }
-  return KVQ_OK;
+  if (!seq_state) return KVQ_OK;
+  return from_hip(kvq::launch_seq_entry(seq_state + 4 * (int64_t)seq, n_groups * G, n_tokens - n_groups * G, active, s));
 }
 
 }  // namespace

@@ -71,11 +71,6 @@ struct PromptRows {
   const __half* k[kPromptLayers];
   const __half* v[kPromptLayers];
 };
-// The entry of a sequence in the array of states, if it is to be written with its prompt: {n_quant, 0, n_res, active}.
-struct SeqEntry {
-  int32_t* at;                                // null: none
-  int32_t n_quant, n_res, active;
-};
 
 struct DecodeArgs {
   Dims d;
@@ -132,12 +127,12 @@ hipError_t launch_trace(const Dims& d, int32_t group_index, const __half* k_grou
                         int64_t unit_stride, const kvq_pool& pool, uint8_t* selected, hipStream_t s);
 hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows, int32_t layers,
                            const uint8_t* selected, int64_t selected_unit_stride, const kvq_qcache& qc, hipStream_t s,
-                           int32_t tail_n = 0, __half* k_res = nullptr, __half* v_res = nullptr,
-                           const SeqEntry& entry = {});
+                           int32_t tail_n = 0, __half* k_res = nullptr, __half* v_res = nullptr);
 hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const PromptRows& rows, int32_t layers,
                                 const kvq_pool& pool, uint8_t* selected, hipStream_t s);
 hipError_t launch_tail_copy(const Dims& d, const PromptRows& rows, int32_t layers, int32_t n, __half* k_res,
-                            __half* v_res, const SeqEntry& entry, hipStream_t s);
+                            __half* v_res, hipStream_t s);
+hipError_t launch_seq_entry(int32_t* at, int32_t n_quant, int32_t n_res, int32_t active, hipStream_t s);
 hipError_t launch_group_step(const Dims& d, int32_t group_index, const __half* k_new, const __half* v_new, __half* k_res,
                              __half* v_res, int32_t append_row, int32_t group_row0, const int32_t* seq,
                              const kvq_pool& pool, uint8_t* selected, const kvq_qcache& qc, hipStream_t s);

@@ -319,12 +319,6 @@ __device__ __forceinline__ void quantize_body(const Dims& d, int64_t u, int32_t 
   }
 }
 
-// (one thread of a launch; nothing in the launch reads the array)
-__device__ __forceinline__ void write_seq_entry(const SeqEntry& e) {
-  if (e.at && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0)
-    *(int4*)e.at = make_int4(e.n_quant, 0, e.n_res, e.active);
-}
-
 // One workgroup of 16 wavefronts per unit.  Every global load of the kernel is issued before the
 // first wait, so a launch costs one trip to memory; the work after it is spread over all 1024
 // threads because nothing else hides latency.  LDS: 2 * G * 272 bytes (<= 68 KB) + meta.
@@ -333,7 +327,7 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
     Dims d, int32_t group_index, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
-    __half* __restrict__ k_res, __half* __restrict__ v_res, SeqEntry entry, PromptRows rows) {
+    __half* __restrict__ k_res, __half* __restrict__ v_res, PromptRows rows) {
   // grid (units, groups + tail blocks, layers): workgroup (ul, gy) with gy < n_groups quantizes the G rows from row
   // gy * G of the unit's rows as group group_index + gy; its flags are
   // selected[(layer * units + ul) * selected_unit_stride + gy * G ..].  The workgroups behind them copy the tail_n
@@ -345,7 +339,6 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
   const int ul = blockIdx.x, gy = blockIdx.y, layer = blockIdx.z;
   const __half* __restrict__ k_rows = rows.k[layer];
   const __half* __restrict__ v_rows = rows.v[layer];
-  write_seq_entry(entry);
   if (gy >= n_groups) {
     const int i = (gy - n_groups) * kQuantThreads + tid;
     if (i < tail_n * 16) {
@@ -405,7 +398,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
     Dims d, int32_t group_index, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
-    __half* __restrict__ k_res, __half* __restrict__ v_res, SeqEntry entry, PromptRows rows) {
+    __half* __restrict__ k_res, __half* __restrict__ v_res, PromptRows rows) {
   // grid (units, groups + tail blocks), as quantize_kernel's
   __shared__ uint4 vrow[32 * 16];                      // 32 Value rows of 128 fp16 (mean-replaced where flagged)
   __shared__ float2 vms[32 * 4];                       // their {zero, step / 2} per channel group
@@ -414,7 +407,6 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   const int ul = blockIdx.x, by = blockIdx.y, layer = blockIdx.z;
   const __half* __restrict__ k_rows = rows.k[layer];
   const __half* __restrict__ v_rows = rows.v[layer];
-  write_seq_entry(entry);
   // Where the competition has just read more Keys than the memory-side cache (256 MB) keeps besides everything else,
   // the last groups come first: their Keys are still there.  With that, and with loads and stores that do not displace
   // them: 256 units x 4096 tokens, the whole call 196 -> 180 us; 512 units 384 -> 350; 64 x 16384 225 -> 199.  (Fewer
@@ -687,10 +679,9 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
 
 // The n rows of every unit into ring rows 0 .. n - 1 (16 bytes per thread).  grid (units, blocks, layers).
 __global__ void __launch_bounds__(256) tail_copy_kernel(Dims d, int32_t n, __half* __restrict__ k_res,
-                                                        __half* __restrict__ v_res, SeqEntry entry, PromptRows rows) {
+                                                        __half* __restrict__ v_res, PromptRows rows) {
   const int ul = blockIdx.x, layer = blockIdx.z;
   const int64_t u = d.unit0 + (int64_t)layer * d.layer_units + ul;
-  write_seq_entry(entry);
   const uint4* sk = (const uint4*)(rows.k[layer] + (int64_t)ul * rows.unit_stride);
   const uint4* sv = (const uint4*)(rows.v[layer] + (int64_t)ul * rows.unit_stride);
   uint4* dk = (uint4*)(k_res + u * d.res_rows * kHeadDim);
@@ -772,8 +763,7 @@ __global__ void __launch_bounds__(kQuantThreads) group_step_kernel(
 template <int BITS, int G>
 hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows,
                                int32_t layers, const uint8_t* selected, int64_t selected_unit_stride,
-                               const kvq_qcache& qc, int32_t tail_n, __half* k_res, __half* v_res,
-                               const SeqEntry& entry, hipStream_t s) {
+                               const kvq_qcache& qc, int32_t tail_n, __half* k_res, __half* v_res, hipStream_t s) {
   // many groups (a prompt): the kernel that spends the fewest instructions per group; few: the one that is
   // done with a group soonest
   const bool many = (int64_t)d.units_per_layer * layers * n_groups >= prompt_groups(G) && !d.keys_only;
@@ -782,7 +772,7 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
   auto go = [&](auto kern, size_t smem) {
     hipLaunchKernelGGL(kern, grid, dim3(threads), smem, s, d, group_index, selected, selected_unit_stride,
                        (uint8_t*)qc.k_codes, (uint32_t*)qc.k_meta, (uint8_t*)qc.v_codes, (uint32_t*)qc.v_meta,
-                       (uint32_t*)qc.mask, n_groups, tail_n, k_res, v_res, entry, rows);
+                       (uint32_t*)qc.mask, n_groups, tail_n, k_res, v_res, rows);
     return hipGetLastError();
   };
   if (many) return go(prompt_quantize_kernel<BITS, G>, 0);
@@ -1039,12 +1029,22 @@ hipError_t launch_group_step(const Dims& d, int32_t group_index, const __half* k
                      : launch_group_step_bits<4>(d, group_index, k_new, v_new, k_res, v_res, append_row, group_row0, seq, pool, selected, qc, s);
 }
 
+// The entry of a sequence in the array of states, {n_quant, 0, n_res, active}.  A launch of its own, behind those that
+// write what the entry speaks of: a launch on another stream that finds the sequence active finds its rows and codes
+// too.  (Written by a workgroup of the quantization it is seen while others are still at work, and ahead of their loads
+// it cost each of them a test.  With it a prompt of 8191 tokens, 8 kv heads, 4 layers takes 60.4 us, 59.0 without.)
+__global__ void seq_entry_kernel(int4* at, int4 state) { *at = state; }
+hipError_t launch_seq_entry(int32_t* at, int32_t n_quant, int32_t n_res, int32_t active, hipStream_t s) {
+  hipLaunchKernelGGL(seq_entry_kernel, dim3(1), dim3(1), 0, s, (int4*)at, make_int4(n_quant, 0, n_res, active));
+  return hipGetLastError();
+}
+
 hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows, int32_t layers,
                            const uint8_t* selected, int64_t selected_unit_stride, const kvq_qcache& qc, hipStream_t s,
-                           int32_t tail_n, __half* k_res, __half* v_res, const SeqEntry& entry) {
+                           int32_t tail_n, __half* k_res, __half* v_res) {
   auto go = [&](auto bits, auto group) {
     return launch_quantize_one<decltype(bits)::value, decltype(group)::value>(
-        d, group_index, n_groups, rows, layers, selected, selected_unit_stride, qc, tail_n, k_res, v_res, entry, s);
+        d, group_index, n_groups, rows, layers, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s);
   };
   auto of_bits = [&](auto bits) {
     switch (d.G) {
@@ -1057,11 +1057,11 @@ hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups,
 }
 
 hipError_t launch_tail_copy(const Dims& d, const PromptRows& rows, int32_t layers, int32_t n, __half* k_res,
-                            __half* v_res, const SeqEntry& entry, hipStream_t s) {
+                            __half* v_res, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int by = (n * 16 + 255) / 256;
   hipLaunchKernelGGL(tail_copy_kernel, dim3(d.units_per_layer, by > 16 ? 16 : by, layers), dim3(256), 0, s, d, n, k_res,
-                     v_res, entry, rows);
+                     v_res, rows);
   return hipGetLastError();
 }
 

@@ -122,3 +122,41 @@ def test_a_large_batch_equals_each_sequence_on_its_own(bits, G, groups):
     torch.cuda.synchronize()
     for x in NAMES:
         assert torch.equal(getattr(a, x), getattr(b, x)), x
+
+
+@pytest.mark.gpu
+def test_an_active_entry_means_that_the_rows_are_there():
+    """Another stream looks at the entry and then at the codes, over and over while 32 layers of a prompt join: once
+    it finds the sequence active, it finds all codes, mask words and ring rows."""
+    import torch
+    layers, n = 32, 4240
+    cfg = KC.make_config(layers, 2, 8, 8, 4096)
+    k, v = ([torch.randn(8, n, 128, device="cuda").half() for _ in range(layers)] for _ in range(2))
+    cache = KC.RaggedKVCache(cfg)
+    flags = torch.empty(layers * 8 * 4096, dtype=torch.uint8, device="cuda")
+    watched = [getattr(cache, x).view(-1, 4)[::1024] for x in ("k_codes", "v_codes", "mask", "k_res", "v_res")]
+    side = torch.cuda.Stream()
+
+    def join():
+        B.kvq_prefill_sequence(cfg, 1, k, v, n * 128, n, cache.pool, flags, flags.numel(), cache.qcache, cache.res,
+                               cache.seq_state, 1, side)
+
+    torch.cuda.synchronize()
+    join()
+    torch.cuda.synchronize()
+    want = [t.clone() for t in watched]
+    for x in ("k_codes", "v_codes", "mask", "k_res", "v_res", "seq_state"):
+        getattr(cache, x).zero_()
+    torch.cuda.synchronize()
+    join()
+    seen = []
+    while not (seen and side.query()) and len(seen) < 1000:
+        entry = cache.seq_state[1].clone()
+        seen.append((entry, [t.clone() for t in watched]))
+    torch.cuda.synchronize()
+    assert cache.seq_state[1].tolist() == [4096, 0, 144, 1]
+    for entry, got in seen:
+        entry = entry.tolist()
+        assert entry in ([0, 0, 0, 0], [4096, 0, 144, 1])
+        if entry[3]:
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
