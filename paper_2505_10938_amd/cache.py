@@ -7,6 +7,7 @@ libkvq.so through `binding`.
 from __future__ import annotations
 
 import contextlib
+import threading
 
 import torch
 
@@ -193,7 +194,8 @@ class KVCache:
 
     def prefill(self, layer, k_rows, v_rows, stream=None):
         """Quantize a whole prompt (fp16 [batch, kv_heads, n, head_dim], contiguous) into the empty cache
-        of `layer`: the state that n appends would leave."""
+        of `layer`: the state that n appends would leave.  (The prompts of one cache share an array of flags:
+        calls on different streams have to be ordered.)"""
         cfg = self.cfg
         n = k_rows.shape[2]
         assert self.n_quant[layer] == 0 and self.n_res[layer] == 0 and k_rows.is_contiguous() and v_rows.is_contiguous()
@@ -280,24 +282,91 @@ class KVCache:
 class RaggedKVCache(KVCache):
     """A cache whose sequences differ in length.  The per-sequence state {n_quant, res_start,
     n_res, active} is a device array that the library reads and advances; the host keeps only
-    an upper bound of the longest sequence, which sizes the decode launch."""
+    an upper bound of the longest sequence, which sizes the decode launch.
+
+    A prompt (prefill_sequence, prefill) is queued on its stream and the call returns.  The methods called after
+    it, on whatever stream, go on behind it, on the device.  Anything else that another stream does with the cache's
+    tensors has to wait for the prompt's stream, and so has a captured graph (nothing is waited for, or recorded,
+    inside a capture)."""
 
     def __init__(self, cfg: B.kvq_config, device="cuda:0", n_pages=None):
         super().__init__(cfg, device, n_pages)
         self.seq_state = torch.zeros(cfg.batch, 4, dtype=torch.int32, device=self.device)
         self.longest = 0                                  # tokens of the longest sequence, at most
+        self._lock = threading.RLock()
+        self._prompt = None                               # the last prompt, if it may be under way: [stream, event]
+
+    def _behind_prompts(self, stream):
+        """`stream` goes on behind the last prompt, wherever that was issued.  (On the prompt's own stream there is
+        nothing to do, and an event costs the GPU 3 us: one behind a prompt on the current stream is recorded when
+        another stream comes along.  A stream that was handed over may be gone by then: there it is recorded at once.)"""
+        prompt = self._prompt
+        if prompt is None or (prompt[1] is None and prompt[0] == B._stream(stream)):
+            return
+        with self._lock, _on(stream, self.device):
+            prompt = self._prompt
+            if prompt is None or torch.cuda.is_current_stream_capturing():
+                return
+            if prompt[1] is None:
+                with _on(prompt[0], self.device):
+                    if torch.cuda.is_current_stream_capturing():
+                        return
+                    prompt[1] = torch.cuda.Event()
+                    prompt[1].record()
+            if not prompt[1].query():
+                torch.cuda.current_stream().wait_event(prompt[1])
+                return
+            self._prompt = None
+
+    def _issue_prompt(self, stream, rows, launch):
+        """launch(handle of `stream`) behind the prompts before it (all share the array of flags), noted for the calls
+        after it."""
+        here = B._stream(None)
+        at = here if stream is None else B._stream(stream)
+        with self._lock:
+            if at == here:
+                self._behind_prompts(at)
+                self._need_prefill_selected(None)
+                launch(at)
+                if not torch.cuda.is_current_stream_capturing():
+                    self._prompt = [at, None]
+                return
+            with _on(stream, self.device):
+                self._behind_prompts(None)
+                self._need_prefill_selected(None)
+                for t in rows:                            # they may be given back before that stream is through
+                    t.record_stream(torch.cuda.current_stream())
+                launch(at)
+                if torch.cuda.is_current_stream_capturing():
+                    return
+                event = torch.cuda.Event()
+                event.record()
+            self._prompt = [None, event]
+
+    def prefill(self, layer, k_rows, v_rows, stream=None):
+        self._issue_prompt(stream, [], lambda at: super(RaggedKVCache, self).prefill(layer, k_rows, v_rows, at))
+
+    def clone(self):
+        self._behind_prompts(None)
+        return super().clone()
+
+    def dense_quantized(self):
+        self._behind_prompts(None)
+        return super().dense_quantized()
 
     def _prefill_selected_bytes(self):             # (all layers of one sequence, or all sequences of one layer)
         return max(super()._prefill_selected_bytes(), self.cfg.layers * self.cfg.kv_heads * self.cfg.max_seq)
 
     def set_active(self, active):
         """active: bool / int tensor or list [batch]: the sequences that take part in the next steps."""
+        self._behind_prompts(None)
         self.seq_state[:, 3] = torch.as_tensor(active, device=self.device).to(torch.int32)
 
     def append(self, layer, k_new, v_new, stream=None):
         """One token per active sequence (fp16 [batch, kv_heads, head_dim] each; rows of inactive
         sequences are ignored) into `layer`; sequences whose ring fills have their oldest group
         traced and quantized in the same launch.  Call for every layer, then advance()."""
+        self._behind_prompts(stream)
         B.kvq_append_trace_quantize_ragged(self.cfg, layer, k_new, v_new, self.res, self.seq_state, self.pool, None,
                                            self.qcache, stream)
 
@@ -308,25 +377,24 @@ class RaggedKVCache(KVCache):
         cfg = self.cfg
         n = k_rows[0].shape[1]
         k_rows, v_rows = list(k_rows[:cfg.layers]), list(v_rows[:cfg.layers])
+        shape = torch.Size((cfg.kv_heads, n, cfg.head_dim))
         for k, v in zip(k_rows, v_rows):
-            assert k.shape == (cfg.kv_heads, n, cfg.head_dim) and k.is_contiguous() and v.is_contiguous()
-        self._need_prefill_selected(stream)
-        if stream is not None:                 # the rows may be given back before that stream is through with them
-            with _on(stream, self.device):
-                for t in k_rows + v_rows:
-                    t.record_stream(torch.cuda.current_stream(self.device))
-        B.kvq_prefill_sequence(cfg, b, k_rows, v_rows, n * cfg.head_dim, n, self.pool, self.prefill_selected,
-                               self.prefill_selected.numel(), self.qcache, self.res, self.seq_state, bool(active), stream)
+            assert k.shape == shape and k.is_contiguous() and v.is_contiguous()
+        self._issue_prompt(stream, k_rows + v_rows, lambda at: B.kvq_prefill_sequence(
+            cfg, b, k_rows, v_rows, n * cfg.head_dim, n, self.pool, self.prefill_selected, self.prefill_selected.numel(),
+            self.qcache, self.res, self.seq_state, bool(active), at))
         self.longest = max(self.longest, n)
 
     def advance(self, stream=None):
         """The sequences' states after the token just appended to every layer."""
+        self._behind_prompts(stream)
         B.kvq_seq_advance(self.cfg, self.seq_state, stream)
         self.longest += 1
 
     def make_plan(self, stream=None):
         """Deal the decode launches of the next step by the sequences' current lengths (once per step,
         after advance(); then decode(..., planned=True) for every layer)."""
+        self._behind_prompts(stream)
         if getattr(self, "plan", None) is None:
             with _on(stream, self.device):
                 self.plan = torch.zeros(B.kvq_seq_plan_bytes(self.cfg) // 4, dtype=torch.int32, device=self.device)
@@ -341,6 +409,7 @@ class RaggedKVCache(KVCache):
         return min(nq, self.cfg.max_seq), min(n, R + G - 1)
 
     def decode(self, layer, q, out=None, stream=None, planned=False):
+        self._behind_prompts(stream)
         if out is None:
             out = self._new_output(q, stream)
         nq, nr = self.bounds()

@@ -107,3 +107,133 @@ def test_rotated_rows_of_a_step_are_not_reused_on_another_stream(monkeypatch):
     assert len(used) == 2 and not set(used) & {t.data_ptr() for t in later}
     torch.cuda.synchronize()
     assert torch.equal(out, want)
+
+
+def ragged(layers=1, batch=2, heads=2, capacity=256, residual=32):
+    return KC.RaggedKVCache(KC.make_config(layers, batch, 2 * heads, heads, capacity, residual=residual))
+
+
+def contents(cache):
+    return {x: getattr(cache, x).clone() for x in ("k_codes", "k_meta", "v_codes", "v_meta", "mask", "k_res", "v_res", "pool_k",
+                                                   "pool_v", "pool_idx", "pool_score", "pool_count", "aux_count", "seq_state")}
+
+
+def on_streams(form, stream):
+    """Where the calls go: `stream` handed over as an object or as a handle, or made the current one."""
+    import contextlib
+    import torch
+    if form < 2:
+        return contextlib.nullcontext(), dict(stream=handles(stream)[form])
+    return torch.cuda.stream(stream), {}
+
+
+@pytest.mark.parametrize("first,second", [(0, 0), (1, 1), (2, 2), (2, 0), (1, 2)])
+def test_prompts_that_join_on_two_streams_share_the_flags(first, second):
+    """Two long prompts of 24 layers into two slots, and a third into the first one's slot behind a stream that is
+    busy: the same bytes as on one stream."""
+    import torch
+    layers, n = 24, 2083
+    prompts = [([], []), ([], []), ([], [])]
+    for i, (k, v) in enumerate(prompts):
+        for l in range(layers):
+            a, b = rows(n - 500 * i, heads=4, seed=100 * i + l)
+            k.append(a)
+            v.append(b)
+    want = ragged(layers, heads=4, capacity=2048)
+    for slot, (k, v) in zip((0, 1, 0), prompts):
+        want.prefill_sequence(slot, k, v)
+        torch.cuda.synchronize()
+    cache = ragged(layers, heads=4, capacity=2048)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    for (slot, busy, form), (k, v), s in zip(((0, False, first), (1, True, second), (0, False, first)), prompts, streams):
+        if busy:
+            with torch.cuda.stream(s):
+                torch.cuda._sleep(BUSY)
+        context, where = on_streams(form, s)
+        with context:
+            cache.prefill_sequence(slot, k, v, **where)
+    torch.cuda.synchronize()
+    a, b = contents(cache), contents(want)
+    for x in a:
+        assert torch.equal(a[x], b[x]), x
+
+
+@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("then", [0, 1, 2])
+def test_steps_on_another_stream_come_behind_a_prompt(form, then):
+    import torch
+    k, v = rows(300)
+    q, kn, vn = (torch.randn(2, h, 128, device="cuda").half() for h in (4, 2, 2))
+    outs = []
+    for busy in (False, True):
+        cache = ragged()
+        cache.prefill_sequence(0, [k[:, :200].contiguous()], [v[:, :200].contiguous()])
+        side, other = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        if busy:
+            with torch.cuda.stream(side):
+                torch.cuda._sleep(BUSY)
+        context, where = on_streams(form if busy else 0, side)
+        with context:
+            cache.prefill_sequence(1, [k], [v], **where)
+        if not busy:
+            torch.cuda.synchronize()
+        context, where = on_streams(then, other)
+        with context:
+            cache.append(0, kn, vn, **where)
+            cache.advance(**where)
+            cache.make_plan(**where)
+            out = [torch.full_like(q, float("nan")) for _ in range(2)]
+            cache.decode(0, q, out[0], planned=True, **where)
+            cache.decode(0, q, out[1], **where)
+        torch.cuda.synchronize()
+        outs.append({"planned": out[0], "ragged": out[1], **contents(cache)})
+    for x in outs[0]:
+        assert torch.equal(outs[0][x], outs[1][x]), x
+
+
+@pytest.mark.parametrize("form", [0, 1])
+def test_calls_on_the_current_stream_come_behind_a_prompt_on_a_side_stream(form):
+    import torch
+    k, v = rows(300)
+    cache = ragged()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(BUSY)
+    cache.prefill_sequence(1, [k], [v], stream=handles(side)[form])
+    cache.set_active([True, False])
+    twin = cache.clone()
+    torch.cuda.synchronize()
+    assert cache.seq_state.tolist() == [[0, 0, 0, 1], [256, 0, 44, 0]]
+    assert torch.equal(twin.k_codes, cache.k_codes) and int(twin.k_codes.sum()) > 0
+
+
+def test_a_prompt_under_capture_after_prompts_on_other_streams():
+    """A captured prompt waits for and leaves nothing outside of its graph; replays equal the eager call."""
+    import torch
+    k, v = rows(300)
+    k2, v2 = rows(300, seed=2)
+    cache, want = ragged(), ragged()
+    side = torch.cuda.Stream()
+    cache.prefill_sequence(0, [k2], [v2])
+    cache.prefill_sequence(0, [k], [v], stream=side)
+    want.prefill_sequence(0, [k2], [v2])                     # (pool slots beyond the counts keep what was there before)
+    want.prefill_sequence(0, [k], [v])
+    torch.cuda.synchronize()
+    kk, vv = k2.clone(), v2.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cache.prefill_sequence(1, [kk], [vv])
+    for source in ((k2, v2), (k, v), (k2, v2)):
+        kk.copy_(source[0])
+        vv.copy_(source[1])
+        want.prefill_sequence(1, [source[0]], [source[1]])
+        cache.prefill_sequence(0, [k], [v], stream=side)
+        torch.cuda.current_stream().wait_stream(side)
+        graph.replay()
+        torch.cuda.synchronize()
+        a, b = contents(cache), contents(want)
+        for x in a:
+            assert torch.equal(a[x], b[x]), x
