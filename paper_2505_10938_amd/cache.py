@@ -6,6 +6,7 @@ libkvq.so through `binding`.
 """
 from __future__ import annotations
 
+import collections
 import contextlib
 import threading
 
@@ -295,6 +296,8 @@ class RaggedKVCache(KVCache):
         self.longest = 0                                  # tokens of the longest sequence, at most
         self._lock = threading.RLock()
         self._prompt = None                               # the last prompt, if it may be under way: [stream, event]
+        self._held = collections.deque()                  # (event, rows that are not to be given back before it)
+        self._here = None                                 # (handle, stream) of a stream that was the current one
 
     def _behind_prompts(self, stream):
         """`stream` goes on behind the last prompt, wherever that was issued.  (On the prompt's own stream there is
@@ -317,10 +320,15 @@ class RaggedKVCache(KVCache):
                 torch.cuda.current_stream().wait_event(prompt[1])
                 return
             self._prompt = None
+            self._give_back()
+
+    def _give_back(self):
+        while self._held and self._held[0][0].query():
+            self._held.popleft()
 
     def _issue_prompt(self, stream, rows, launch):
         """launch(handle of `stream`) behind the prompts before it (all share the array of flags), noted for the calls
-        after it."""
+        after it, and the rows kept until it is through with them."""
         here = B._stream(None)
         at = here if stream is None else B._stream(stream)
         with self._lock:
@@ -330,18 +338,23 @@ class RaggedKVCache(KVCache):
                 launch(at)
                 if not torch.cuda.is_current_stream_capturing():
                     self._prompt = [at, None]
+                    if self._here is None or self._here[0] != at:
+                        self._here = at, torch.cuda.current_stream()
+                    for t in rows:                        # (of another stream's: the allocator keeps them)
+                        t.record_stream(self._here[1])
                 return
             with _on(stream, self.device):
                 self._behind_prompts(None)
                 self._need_prefill_selected(None)
-                for t in rows:                            # they may be given back before that stream is through
-                    t.record_stream(torch.cuda.current_stream())
                 launch(at)
                 if torch.cuda.is_current_stream_capturing():
                     return
                 event = torch.cuda.Event()
                 event.record()
             self._prompt = [None, event]
+            self._give_back()
+            if rows:
+                self._held.append((event, rows))
 
     def prefill(self, layer, k_rows, v_rows, stream=None):
         self._issue_prompt(stream, [], lambda at: super(RaggedKVCache, self).prefill(layer, k_rows, v_rows, at))
@@ -373,7 +386,7 @@ class RaggedKVCache(KVCache):
     def prefill_sequence(self, b, k_rows, v_rows, active=True, stream=None):
         """A new sequence in slot `b`: its prompt (per layer: fp16 [kv_heads, n, head_dim], contiguous;
         `k_rows`, `v_rows` are lists over the layers) quantized in one call for all layers, whatever the slot
-        held before; the other sequences are not touched."""
+        held before; the other sequences are not touched.  The rows may be given back when the call returns."""
         cfg = self.cfg
         n = k_rows[0].shape[1]
         k_rows, v_rows = list(k_rows[:cfg.layers]), list(v_rows[:cfg.layers])

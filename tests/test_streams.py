@@ -210,6 +210,55 @@ def test_calls_on_the_current_stream_come_behind_a_prompt_on_a_side_stream(form)
     assert torch.equal(twin.k_codes, cache.k_codes) and int(twin.k_codes.sum()) > 0
 
 
+def test_a_stream_handed_over_may_go_before_the_rows():
+    """Nothing of a stream given by its handle is touched once its work is done."""
+    import ctypes
+    import torch
+    torch.cuda.synchronize()
+    hip = KC.B.load_library()                                # (the runtime that it is linked with)
+    handle = ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(handle), 1) == 0     # (1: not ordered with the default stream)
+    k, v = rows(300)
+    want, cache = ragged(), ragged()
+    want.prefill_sequence(1, [k], [v])
+    torch.cuda.synchronize()
+    kk, vv = k.clone(), v.clone()
+    torch.cuda.synchronize()
+    cache.prefill_sequence(1, [kk], [vv], stream=handle.value)
+    assert hip.hipStreamSynchronize(handle) == 0 and hip.hipStreamDestroy(handle) == 0
+    del kk, vv
+    later = [torch.full_like(k, 7.0) for _ in range(4)]
+    out = cache.decode(0, torch.randn(2, 4, 128, device="cuda").half())
+    torch.cuda.synchronize()
+    assert torch.isfinite(out[1]).all() and not cache._held
+    a, b = contents(cache), contents(want)
+    for x in a:
+        assert torch.equal(a[x], b[x]), x
+    del later
+
+
+def test_rows_of_another_stream_are_kept_for_the_current_one():
+    import torch
+    k, v = rows(300)
+    want, cache = ragged(), ragged()
+    want.prefill_sequence(1, [k], [v])
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        kk, vv = k.clone(), v.clone()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(BUSY)
+    cache.prefill_sequence(1, [kk], [vv])
+    del kk, vv
+    with torch.cuda.stream(side):
+        later = [torch.full_like(k, 7.0) for _ in range(8)]
+    torch.cuda.synchronize()
+    a, b = contents(cache), contents(want)
+    for x in a:
+        assert torch.equal(a[x], b[x]), x
+    del later
+
+
 def test_a_prompt_under_capture_after_prompts_on_other_streams():
     """A captured prompt waits for and leaves nothing outside of its graph; replays equal the eager call."""
     import torch
