@@ -321,9 +321,10 @@ namespace {
 kvq::PromptRows rows_of(const void* const* k, const void* const* v, int32_t layers, int64_t unit_stride) {
   kvq::PromptRows r = {};
   r.unit_stride = unit_stride;
+  r.layers = layers;
   for (int32_t i = 0; i < layers; ++i) {
-    r.k[i] = (const __half*)k[i];
-    r.v[i] = (const __half*)v[i];
+    r.at.k[i] = (const __half*)k[i];
+    r.at.v[i] = (const __half*)v[i];
   }
   return r;
 }
@@ -376,7 +377,7 @@ int32_t kvq_quantize_group(const kvq_config* cfg, int32_t layer, int32_t group_i
   if (!qcache_ok(cfg, qc)) return KVQ_ERR_INVALID_ARG;
   const Dims d = make_dims(cfg, layer, qc);
   const kvq::PromptRows rows = rows_of(&k_group, &v_group, 1, unit_stride);
-  return from_hip(kvq::launch_quantize(d, group_index, 1, rows, 1, selected, cfg->group_k, qc, (hipStream_t)stream));
+  return from_hip(kvq::launch_quantize(d, group_index, 1, rows, selected, cfg->group_k, qc, (hipStream_t)stream));
 }
 
 namespace {
@@ -433,13 +434,13 @@ int32_t prefill_common(const kvq_config* cfg, int32_t layer, int32_t layers, int
     const int32_t tail = n_tokens - n_groups * G;
     hipError_t e;
     if (n_groups > 0) {
-      e = kvq::launch_prefill_trace(d, n_groups, rows, count, pool, selected, s);
+      e = kvq::launch_prefill_trace(d, n_groups, rows, pool, selected, s);
       if (e != hipSuccess) return KVQ_ERR_LAUNCH;
       // (the rows behind the last group go to the ring in the same launch)
-      e = kvq::launch_quantize(d, 0, n_groups, rows, count, selected, (int64_t)n_groups * G, qc, s, tail,
+      e = kvq::launch_quantize(d, 0, n_groups, rows, selected, (int64_t)n_groups * G, qc, s, tail,
                                (__half*)res.k_res, (__half*)res.v_res);
     } else {
-      e = kvq::launch_tail_copy(d, rows, count, tail, (__half*)res.k_res, (__half*)res.v_res, s);
+      e = kvq::launch_tail_copy(d, rows, tail, (__half*)res.k_res, (__half*)res.v_res, s);
     }
     if (e == hipSuccess && n_more_values > 0)
       e = kvq::launch_value_tokens(d, n_groups * G, n_more_values, (__half*)res.v_res, 0, qc, s);

@@ -65,12 +65,29 @@ __device__ inline GroupPlace place_of_group(const Dims& d, int ul, int group, in
 // first one's): a layer's rows are where k[z] and v[z] say, its units `unit_stride` elements apart.  (One sequence has
 // few units: its layers one after the other are three launches each of 10 .. 14 us that leave most of the device idle.
 // A prompt of 8191 tokens, 8 kv heads, 4 layers: 164 us layer by layer, 58 us with all layers in the same launches.)
+// The kernels are built for one layer too (LAYERS = 1): its pointers are ordinary arguments then, next to the others and
+// not behind an index.  Whole call, one layer of 300 tokens, 4 units, with an array of 32 / with one pointer: 13.1 / 12.7
+// us with G = 32, 14.4 / 14.1 with G = 64.
 constexpr int kPromptLayers = 32;
+template <int LAYERS>
+struct LayerRows {
+  const __half* k[LAYERS];
+  const __half* v[LAYERS];
+};
 struct PromptRows {
   int64_t unit_stride;
-  const __half* k[kPromptLayers];
-  const __half* v[kPromptLayers];
+  int32_t layers;
+  LayerRows<kPromptLayers> at;
 };
+template <int LAYERS>
+LayerRows<LAYERS> layer_rows(const PromptRows& rows) {
+  LayerRows<LAYERS> r;
+  for (int i = 0; i < LAYERS; ++i) {
+    r.k[i] = rows.at.k[i];
+    r.v[i] = rows.at.v[i];
+  }
+  return r;
+}
 
 struct DecodeArgs {
   Dims d;
@@ -125,12 +142,12 @@ hipError_t launch_dequantize(const Dims& d, int32_t block0, int32_t n_blocks, co
 hipError_t launch_reset_pools(const Dims& d, int32_t layers, const kvq_pool& pool, hipStream_t s);
 hipError_t launch_trace(const Dims& d, int32_t group_index, const __half* k_group, const __half* v_group,
                         int64_t unit_stride, const kvq_pool& pool, uint8_t* selected, hipStream_t s);
-hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows, int32_t layers,
+hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows,
                            const uint8_t* selected, int64_t selected_unit_stride, const kvq_qcache& qc, hipStream_t s,
                            int32_t tail_n = 0, __half* k_res = nullptr, __half* v_res = nullptr);
-hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const PromptRows& rows, int32_t layers,
+hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const PromptRows& rows,
                                 const kvq_pool& pool, uint8_t* selected, hipStream_t s);
-hipError_t launch_tail_copy(const Dims& d, const PromptRows& rows, int32_t layers, int32_t n, __half* k_res,
+hipError_t launch_tail_copy(const Dims& d, const PromptRows& rows, int32_t n, __half* k_res,
                             __half* v_res, hipStream_t s);
 hipError_t launch_seq_entry(int32_t* at, int32_t n_quant, int32_t n_res, int32_t active, hipStream_t s);
 hipError_t launch_group_step(const Dims& d, int32_t group_index, const __half* k_new, const __half* v_new, __half* k_res,

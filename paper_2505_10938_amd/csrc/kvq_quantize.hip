@@ -326,12 +326,12 @@ __device__ __forceinline__ void quantize_body(const Dims& d, int64_t u, int32_t 
 // One workgroup of 16 wavefronts per unit.  Every global load of the kernel is issued before the
 // first wait, so a launch costs one trip to memory; the work after it is spread over all 1024
 // threads because nothing else hides latency.  LDS: 2 * G * 272 bytes (<= 68 KB) + meta.
-template <int BITS, int G>
+template <int BITS, int G, int LAYERS>
 __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
-    Dims d, int32_t group_index, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
+    Dims d, int32_t group_index, int64_t unit_stride, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
-    __half* __restrict__ k_res, __half* __restrict__ v_res, PromptRows rows) {
+    __half* __restrict__ k_res, __half* __restrict__ v_res, LayerRows<LAYERS> rows) {
   // grid (units, groups + tail blocks, layers): workgroup (ul, gy) with gy < n_groups quantizes the G rows from row
   // gy * G of the unit's rows as group group_index + gy; its flags are
   // selected[(layer * units + ul) * selected_unit_stride + gy * G ..].  The workgroups behind them copy the tail_n
@@ -340,13 +340,13 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
   extern __shared__ __align__(16) unsigned char smem[];
   const QuantLds<G> L(smem, d.vgroups);
   const int tid = threadIdx.x;
-  const int ul = blockIdx.x, gy = blockIdx.y, layer = blockIdx.z;
+  const int ul = blockIdx.x, gy = blockIdx.y, layer = LAYERS > 1 ? blockIdx.z : 0;
   const __half* __restrict__ k_rows = rows.k[layer];
   const __half* __restrict__ v_rows = rows.v[layer];
   if (gy >= n_groups) {
     const int i = (gy - n_groups) * kQuantThreads + tid;
     if (i < tail_n * 16) {
-      const int64_t src = (int64_t)ul * rows.unit_stride + (int64_t)n_groups * G * kHeadDim;
+      const int64_t src = (int64_t)ul * unit_stride + (int64_t)n_groups * G * kHeadDim;
       const int64_t dst = (d.unit0 + (int64_t)layer * d.layer_units + ul) * d.res_rows * kHeadDim;
       ((uint4*)(k_res + dst))[i] = ((const uint4*)(k_rows + src))[i];
       ((uint4*)(v_res + dst))[i] = ((const uint4*)(v_rows + src))[i];
@@ -354,7 +354,7 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
     return;
   }
   GroupRows<G> group;
-  const int64_t row0 = (int64_t)ul * rows.unit_stride + (int64_t)gy * G * kHeadDim;
+  const int64_t row0 = (int64_t)ul * unit_stride + (int64_t)gy * G * kHeadDim;
   rows_issue<G>(group, k_rows + row0, v_rows + row0, tid);
   const int64_t sel0 = ((int64_t)layer * d.units_per_layer + ul) * selected_unit_stride + (int64_t)gy * G;
   uint8_t flag = 0;
@@ -396,30 +396,25 @@ __device__ __forceinline__ uint4 once(const __half* p) {   // 16 bytes that are 
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-template <int BITS, int G>
+template <int BITS, int G, int LAYERS>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))) prompt_quantize_kernel(
-    Dims d, int32_t group_index, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
+    Dims d, int32_t group_index, int64_t unit_stride, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
-    __half* __restrict__ k_res, __half* __restrict__ v_res, PromptRows rows) {
-  // grid (units, groups + tail blocks), as quantize_kernel's
+    __half* __restrict__ k_res, __half* __restrict__ v_res, int32_t last_first, LayerRows<LAYERS> rows) {
+  // grid (units, groups + tail blocks, layers), as quantize_kernel's
   __shared__ uint4 vrow[32 * 16];                      // 32 Value rows of 128 fp16 (mean-replaced where flagged)
   __shared__ float2 vms[32 * 4];                       // their {zero, step / 2} per channel group
   __shared__ uint32_t vpr[32 * 4];                     // and before that {minimum, -maximum} as an fp16 pair
   const int tid = threadIdx.x;
-  const int ul = blockIdx.x, by = blockIdx.y, layer = blockIdx.z;
+  const int ul = blockIdx.x, by = blockIdx.y, layer = LAYERS > 1 ? blockIdx.z : 0;
   const __half* __restrict__ k_rows = rows.k[layer];
   const __half* __restrict__ v_rows = rows.v[layer];
-  // Where the competition has just read more Keys than the memory-side cache (256 MB) keeps besides everything else,
-  // the last groups come first: their Keys are still there.  With that, and with loads and stores that do not displace
-  // them: 256 units x 4096 tokens, the whole call 196 -> 180 us; 512 units 384 -> 350; 64 x 16384 225 -> 199.  (Fewer
-  // Keys are there in any order: 32 units x 8191 58.8 / 59.8 us first to last / last to first, 64 x 4096 66.8 / 66.2.)
-  const bool last_first = (int64_t)d.units_per_layer * gridDim.z * n_groups * G * (2 * kHeadDim) >= (1ll << 27);
   const int gy = last_first && by < n_groups ? n_groups - 1 - by : by;
   if (gy >= n_groups) {
     const int i = (gy - n_groups) * 128 + tid;
     if (i < tail_n * 16) {
-      const int64_t src = (int64_t)ul * rows.unit_stride + (int64_t)n_groups * G * kHeadDim;
+      const int64_t src = (int64_t)ul * unit_stride + (int64_t)n_groups * G * kHeadDim;
       const int64_t dst = (d.unit0 + (int64_t)layer * d.layer_units + ul) * d.res_rows * kHeadDim;
       ((uint4*)(k_res + dst))[i] = ((const uint4*)(k_rows + src))[i];
       ((uint4*)(v_res + dst))[i] = ((const uint4*)(v_rows + src))[i];
@@ -428,7 +423,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t row0 = (int64_t)ul * rows.unit_stride + (int64_t)gy * G * kHeadDim;
+  const int64_t row0 = (int64_t)ul * unit_stride + (int64_t)gy * G * kHeadDim;
   const int64_t sel0 = ((int64_t)layer * d.units_per_layer + ul) * selected_unit_stride + (int64_t)gy * G;
   const GroupPlace at = place_of_group(d, ul, group_index + gy, layer);
   constexpr int nblk = G / kBlockTokens;
@@ -681,12 +676,13 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
 }
 
 // The n rows of every unit into ring rows 0 .. n - 1 (16 bytes per thread).  grid (units, blocks, layers).
-__global__ void __launch_bounds__(256) tail_copy_kernel(Dims d, int32_t n, __half* __restrict__ k_res,
-                                                        __half* __restrict__ v_res, PromptRows rows) {
-  const int ul = blockIdx.x, layer = blockIdx.z;
+template <int LAYERS>
+__global__ void __launch_bounds__(256) tail_copy_kernel(Dims d, int64_t unit_stride, int32_t n, __half* __restrict__ k_res,
+                                                        __half* __restrict__ v_res, LayerRows<LAYERS> rows) {
+  const int ul = blockIdx.x, layer = LAYERS > 1 ? blockIdx.z : 0;
   const int64_t u = d.unit0 + (int64_t)layer * d.layer_units + ul;
-  const uint4* sk = (const uint4*)(rows.k[layer] + (int64_t)ul * rows.unit_stride);
-  const uint4* sv = (const uint4*)(rows.v[layer] + (int64_t)ul * rows.unit_stride);
+  const uint4* sk = (const uint4*)(rows.k[layer] + (int64_t)ul * unit_stride);
+  const uint4* sv = (const uint4*)(rows.v[layer] + (int64_t)ul * unit_stride);
   uint4* dk = (uint4*)(k_res + u * d.res_rows * kHeadDim);
   uint4* dv = (uint4*)(v_res + u * d.res_rows * kHeadDim);
   for (int i = blockIdx.y * 256 + threadIdx.x; i < n * 16; i += gridDim.y * 256) {
@@ -763,29 +759,35 @@ __global__ void __launch_bounds__(kQuantThreads) group_step_kernel(
   quantize_body<BITS, G>(d, at.row, at.slot, L, flag, k_codes, k_meta, v_codes, v_meta, mask, tid);
 }
 
-template <int BITS, int G>
+template <int BITS, int G, int LAYERS>
 hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows,
-                               int32_t layers, const uint8_t* selected, int64_t selected_unit_stride,
+                               const uint8_t* selected, int64_t selected_unit_stride,
                                const kvq_qcache& qc, int32_t tail_n, __half* k_res, __half* v_res, hipStream_t s) {
   // many groups (a prompt): the kernel that spends the fewest instructions per group; few: the one that is
   // done with a group soonest
-  const bool many = (int64_t)d.units_per_layer * layers * n_groups >= prompt_groups(G) && !d.keys_only;
+  const int64_t groups = (int64_t)d.units_per_layer * rows.layers * n_groups;
+  const bool many = groups >= prompt_groups(G) && !d.keys_only;
   const int threads = many ? 128 : kQuantThreads;
-  const dim3 grid(d.units_per_layer, n_groups + (tail_n * 16 + threads - 1) / threads, layers);
-  auto go = [&](auto kern, size_t smem) {
-    hipLaunchKernelGGL(kern, grid, dim3(threads), smem, s, d, group_index, selected, selected_unit_stride,
-                       (uint8_t*)qc.k_codes, (uint32_t*)qc.k_meta, (uint8_t*)qc.v_codes, (uint32_t*)qc.v_meta,
-                       (uint32_t*)qc.mask, n_groups, tail_n, k_res, v_res, rows);
+  const dim3 grid(d.units_per_layer, n_groups + (tail_n * 16 + threads - 1) / threads, rows.layers);
+  auto go = [&](auto kern, size_t smem, auto... more) {
+    hipLaunchKernelGGL(kern, grid, dim3(threads), smem, s, d, group_index, rows.unit_stride, selected,
+                       selected_unit_stride, (uint8_t*)qc.k_codes, (uint32_t*)qc.k_meta, (uint8_t*)qc.v_codes,
+                       (uint32_t*)qc.v_meta, (uint32_t*)qc.mask, n_groups, tail_n, k_res, v_res, more...,
+                       layer_rows<LAYERS>(rows));
     return hipGetLastError();
   };
-  if (many) return go(prompt_quantize_kernel<BITS, G>, 0);
+  // Where the competition has just read more Keys than the memory-side cache (256 MB) keeps besides everything else,
+  // the last groups come first: their Keys are still there.  With that, and with loads and stores that do not displace
+  // them: 256 units x 4096 tokens, the whole call 196 -> 180 us; 512 units 384 -> 350; 64 x 16384 225 -> 199.  (Fewer
+  // Keys are there in any order: 32 units x 8191 58.8 / 59.8 us first to last / last to first, 64 x 4096 66.8 / 66.2.)
+  if (many) return go(prompt_quantize_kernel<BITS, G, LAYERS>, 0, (int32_t)(groups * G * (2 * kHeadDim) >= (1ll << 27)));
   const size_t smem = quant_lds_bytes<G>(d.vgroups);
   if (smem > 48 * 1024) {  // more than the default limit of dynamic LDS per workgroup
-    hipError_t e = hipFuncSetAttribute((const void*)quantize_kernel<BITS, G>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipError_t e = hipFuncSetAttribute((const void*)quantize_kernel<BITS, G, LAYERS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)smem);
     if (e != hipSuccess) return e;
   }
-  return go(quantize_kernel<BITS, G>, smem);
+  return go(quantize_kernel<BITS, G, LAYERS>, smem);
 }
 
 }  // namespace
@@ -1042,12 +1044,13 @@ hipError_t launch_seq_entry(int32_t* at, int32_t n_quant, int32_t n_res, int32_t
   return hipGetLastError();
 }
 
-hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows, int32_t layers,
+hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups, const PromptRows& rows,
                            const uint8_t* selected, int64_t selected_unit_stride, const kvq_qcache& qc, hipStream_t s,
                            int32_t tail_n, __half* k_res, __half* v_res) {
   auto go = [&](auto bits, auto group) {
-    return launch_quantize_one<decltype(bits)::value, decltype(group)::value>(
-        d, group_index, n_groups, rows, layers, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s);
+    constexpr int BITS = decltype(bits)::value, G = decltype(group)::value;
+    const auto one = rows.layers == 1 ? launch_quantize_one<BITS, G, 1> : launch_quantize_one<BITS, G, kPromptLayers>;
+    return one(d, group_index, n_groups, rows, selected, selected_unit_stride, qc, tail_n, k_res, v_res, s);
   };
   auto of_bits = [&](auto bits) {
     switch (d.G) {
@@ -1059,13 +1062,17 @@ hipError_t launch_quantize(const Dims& d, int32_t group_index, int32_t n_groups,
   return d.bits == 2 ? of_bits(std::integral_constant<int, 2>{}) : of_bits(std::integral_constant<int, 4>{});
 }
 
-hipError_t launch_tail_copy(const Dims& d, const PromptRows& rows, int32_t layers, int32_t n, __half* k_res,
+hipError_t launch_tail_copy(const Dims& d, const PromptRows& rows, int32_t n, __half* k_res,
                             __half* v_res, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int by = (n * 16 + 255) / 256;
-  hipLaunchKernelGGL(tail_copy_kernel, dim3(d.units_per_layer, by > 16 ? 16 : by, layers), dim3(256), 0, s, d, n, k_res,
-                     v_res, rows);
-  return hipGetLastError();
+  auto go = [&](auto kern, const auto& at) {
+    hipLaunchKernelGGL(kern, dim3(d.units_per_layer, by > 16 ? 16 : by, rows.layers), dim3(256), 0, s, d,
+                       rows.unit_stride, n, k_res, v_res, at);
+    return hipGetLastError();
+  };
+  return rows.layers == 1 ? go(tail_copy_kernel<1>, layer_rows<1>(rows))
+                          : go(tail_copy_kernel<kPromptLayers>, rows.at);
 }
 
 }  // namespace kvq

@@ -275,17 +275,18 @@ __device__ __forceinline__ bool may_be_selected(const uint32_t* coarse, const ui
 }
 
 // grid (units, segments, layers).  Requires N > 0.
-template <int G>
-__global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int32_t n_tok,
-                                                                     uint8_t* __restrict__ selected, PromptRows src) {
+template <int G, int LAYERS>
+__global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int32_t n_tok, int64_t unit_stride,
+                                                                     uint8_t* __restrict__ selected,
+                                                                     LayerRows<LAYERS> src) {
   __shared__ uint32_t coarse[kSegment];
   __shared__ uint32_t bound[kPrefixes];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ul = blockIdx.x, t0 = blockIdx.y * kSegment, layer = blockIdx.z;
+  const int ul = blockIdx.x, t0 = blockIdx.y * kSegment, layer = LAYERS > 1 ? blockIdx.z : 0;
   const int n = min(kSegment, n_tok - t0);
-  const __half* rows = src.k[layer] + (int64_t)ul * src.unit_stride + (int64_t)t0 * kHeadDim;
+  const __half* rows = src.k[layer] + (int64_t)ul * unit_stride + (int64_t)t0 * kHeadDim;
   score_rows(n, tid, [&](int e) { return rows + e * kHeadDim; }, [&](int e, double sc) { coarse[e] = coarse_score(sc); });
   __syncthreads();
   prefix_bounds(coarse, n, d.N, bound, wave, lane);
@@ -300,10 +301,10 @@ __global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int
 // at a time, the Key rows of the next T in flight meanwhile: each row is asked for when the one before it in its
 // registers has been added up, so that memory is not idle during the sums.  Pools are taken to be empty on entry (a
 // prompt starts a sequence) and are not read.
-template <int G, int T, bool FLAGGED>
+template <int G, int T, bool FLAGGED, int LAYERS>
 __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) prompt_compete_kernel(
-    Dims d, int32_t n_tok, __half* pool_k, __half* pool_v, int32_t* pool_idx, double* pool_score, int32_t* pool_count,
-    int32_t* aux_count, int32_t* frozen, uint8_t* __restrict__ selected, PromptRows src) {
+    Dims d, int32_t n_tok, int64_t unit_stride, __half* pool_k, __half* pool_v, int32_t* pool_idx, double* pool_score,
+    int32_t* pool_count, int32_t* aux_count, int32_t* frozen, uint8_t* __restrict__ selected, LayerRows<LAYERS> src) {
   constexpr int kGroupShift = G == 32 ? 5 : G == 64 ? 6 : 7;
   constexpr int kListed = 64 + 64 + kRound;            // at most N + A selected tokens before the last round
   constexpr int kWaves = T / 64;
@@ -316,7 +317,7 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) pro
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ul = blockIdx.x, layer = blockIdx.z;
+  const int ul = blockIdx.x, layer = LAYERS > 1 ? blockIdx.z : 0;
   const int64_t u = d.unit0 + (int64_t)layer * d.layer_units + ul;
   uint8_t* sel = selected + ((int64_t)layer * d.units_per_layer + ul) * n_tok;
   const int N = d.N, A = d.A;
@@ -324,8 +325,8 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) pro
     for (int i = tid; i < n_tok; i += T) sel[i] = 0;
     return;
   }
-  const __half* __restrict__ kr = src.k[layer] + (int64_t)ul * src.unit_stride;
-  const __half* __restrict__ vr = src.v[layer] + (int64_t)ul * src.unit_stride;
+  const __half* __restrict__ kr = src.k[layer] + (int64_t)ul * unit_stride;
+  const __half* __restrict__ vr = src.v[layer] + (int64_t)ul * unit_stride;
   const u64 below = (1ull << lane) - 1ull;
   int P = 0, cur = 0, S = 0;                           // pool members, pool buffer, selected tokens
   bool stopped = false;
@@ -544,30 +545,36 @@ bool by_segments(const Dims& d, int32_t units, int32_t n_tok) {
 
 }  // namespace
 
-hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const PromptRows& rows, int32_t layers,
+hipError_t launch_prefill_trace(const Dims& d, int32_t n_groups, const PromptRows& rows,
                                 const kvq_pool& pool, uint8_t* selected, hipStream_t s) {
-  const int32_t n_tok = n_groups * d.G, units = d.units_per_layer * layers;
-  auto compete = [&](auto kern, int threads) {
-    hipLaunchKernelGGL(kern, dim3(d.units_per_layer, 1, layers), dim3(threads), 0, s, d, n_tok, (__half*)pool.pool_k,
-                       (__half*)pool.pool_v, pool.pool_idx, pool.pool_score, pool.pool_count, pool.aux_count,
-                       pool.frozen, selected, rows);
+  const int32_t n_tok = n_groups * d.G, units = d.units_per_layer * rows.layers;
+  auto compete = [&](auto kern, int threads, const auto& at) {
+    hipLaunchKernelGGL(kern, dim3(d.units_per_layer, 1, rows.layers), dim3(threads), 0, s, d, n_tok, rows.unit_stride,
+                       (__half*)pool.pool_k, (__half*)pool.pool_v, pool.pool_idx, pool.pool_score, pool.pool_count,
+                       pool.aux_count, pool.frozen, selected, at);
   };
   // Threads of a workgroup: 1024 where every unit can have a compute unit to itself; with more units 512, so that two
   // workgroups fit one, and 256 for prompts no longer than that.  1024 units x 300 tokens, T = 1024 / 512 / 256: 92 /
   // 70 / 64 us; x 600: 138 / 120 / 121.
-  auto go = [&](auto group) {
-    constexpr int G = decltype(group)::value;
+  auto of_layers = [&](auto group, auto count) {
+    constexpr int G = decltype(group)::value, L = decltype(count)::value;
+    const LayerRows<L> at = layer_rows<L>(rows);
     if (by_segments(d, units, n_tok)) {
-      hipLaunchKernelGGL(prompt_candidates_kernel<G>, dim3(d.units_per_layer, (n_tok + kSegment - 1) / kSegment, layers),
-                         dim3(kSegment), 0, s, d, n_tok, selected, rows);
-      compete(prompt_compete_kernel<G, 1024, true>, 1024);
+      hipLaunchKernelGGL((prompt_candidates_kernel<G, L>),
+                         dim3(d.units_per_layer, (n_tok + kSegment - 1) / kSegment, rows.layers), dim3(kSegment), 0, s,
+                         d, n_tok, rows.unit_stride, selected, at);
+      compete(prompt_compete_kernel<G, 1024, true, L>, 1024, at);
     } else if (units > 2 * kComputeUnits && n_tok <= 256) {
-      compete(prompt_compete_kernel<G, 256, false>, 256);
+      compete(prompt_compete_kernel<G, 256, false, L>, 256, at);
     } else if (units > kComputeUnits) {
-      compete(prompt_compete_kernel<G, 512, false>, 512);
+      compete(prompt_compete_kernel<G, 512, false, L>, 512, at);
     } else {
-      compete(prompt_compete_kernel<G, 1024, false>, 1024);
+      compete(prompt_compete_kernel<G, 1024, false, L>, 1024, at);
     }
+  };
+  auto go = [&](auto group) {
+    if (rows.layers == 1) of_layers(group, std::integral_constant<int, 1>{});
+    else of_layers(group, std::integral_constant<int, kPromptLayers>{});
   };
   switch (d.G) {
     case 32: go(std::integral_constant<int, 32>{}); break;

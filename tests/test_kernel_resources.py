@@ -1,4 +1,5 @@
 """What the compiler gave the prompt's kernels, from the metadata of the built library."""
+import re
 import struct
 
 import pytest
@@ -40,6 +41,17 @@ def notes(elf):
                 return {k[".name"]: k for k in msgpack.unpackb(elf[body:body + desc])["amdhsa.kernels"]}
             p = body + (desc + 3) // 4 * 4
     return {}
+
+
+def test_kernels_of_one_layer_take_the_pointers_of_one():
+    """Up to 32 layers have two arrays of 256 bytes in the arguments, one layer two pointers."""
+    sizes = {1: [], 32: []}
+    for name, kernel in kernels().items():
+        if "9LayerRows" in name:
+            layers = int(re.search(r"Li(\d+)E(?:Lb\dE)?EEv", name).group(1))
+            sizes[layers].append([x[".size"] for x in kernel[".args"] if x[".value_kind"] == "by_value"][-1])
+    assert min(map(len, sizes.values())) >= 6 + 6 + 3 + 12 + 1
+    assert set(sizes[1]) == {16} and set(sizes[32]) == {512}
 
 
 @pytest.mark.parametrize("kernel,instances,bytes_of_scratch", [
