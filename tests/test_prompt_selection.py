@@ -103,6 +103,8 @@ def test_selection_in_calls_of_many_units(units, G, N, A, n):
 @pytest.mark.parametrize("units,n", [
     (2, 992), (2, 1024), (256, 2048), (256, 2016), (300, 512), (300, 1056), (600, 256),   # 1024, 512, 256 threads
     (2, 2048), (2, 1024 + 480),                                                           # candidates first
+    (2, 32), (2, 512), (2, 544), (256, 1024 + 512), (256, 1024 + 544),                    # eight rows per team, and more
+    (300, 256), (300, 288), (300, 512 + 256), (600, 128), (600, 160),
 ])
 def test_scores_are_told_apart_by_their_last_bit(units, n):
     """Rows of 64 times the largest fp16 value that differ by one subnormal, 2^-24 to 2^-13, in one channel or another:
