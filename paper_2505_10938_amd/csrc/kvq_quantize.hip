@@ -391,19 +391,26 @@ __device__ __forceinline__ void lds_order() {   // LDS traffic of one wavefront 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ uint4 once(const __half* p) {   // 16 bytes that are not needed again
-  const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
-  return make_uint4(v.x, v.y, v.z, v.w);
+// A load that is the last one, and a store that nothing soon reads: with ONCE they leave what the caches hold alone.
+template <bool ONCE, class T>
+__device__ __forceinline__ T last_load(const T* p) {
+  if constexpr (ONCE) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool ONCE, class T>
+__device__ __forceinline__ void put_away(T v, T* p) {
+  if constexpr (ONCE) __builtin_nontemporal_store(v, p);
+  else *p = v;
 }
 
-template <int BITS, int G, int LAYERS>
+template <int BITS, int G, int LAYERS, bool ONCE>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))) prompt_quantize_kernel(
     Dims d, int32_t group_index, int64_t unit_stride, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
     __half* __restrict__ k_res, __half* __restrict__ v_res, int32_t last_first, LayerRows<LAYERS> rows) {
   // grid (units, groups + tail blocks, layers), as quantize_kernel's
-  __shared__ uint4 vrow[32 * 16];                      // 32 Value rows of 128 fp16 (mean-replaced where flagged)
+  __shared__ u32x4 vrow[32 * 16];                      // 32 Value rows of 128 fp16 (mean-replaced where flagged)
   __shared__ float2 vms[32 * 4];                       // their {zero, step / 2} per channel group
   __shared__ uint32_t vpr[32 * 4];                     // and before that {minimum, -maximum} as an fp16 pair
   const int tid = threadIdx.x;
@@ -470,7 +477,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
       for (int blk = 0; blk < nblk; ++blk) {
 #pragma unroll
         for (int t = 0; t < 32; ++t)                   // (longer groups are read a second time for the codes)
-          y[t] = nblk == 1 ? __builtin_nontemporal_load(kr + t * 64) : kr[(blk * 32 + t) * 64];
+          y[t] = nblk == 1 ? last_load<ONCE>(kr + t * 64) : kr[(blk * 32 + t) * 64];
 #pragma unroll
         for (int t = 0; t < 32; ++t) {
           const h2 x = as_h2(y[t]);
@@ -513,7 +520,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
       for (int blk = 0; blk < nblk; ++blk) {
         if (nblk > 1) {
 #pragma unroll
-          for (int t = 0; t < 32; ++t) y[t] = __builtin_nontemporal_load(kr + (blk * 32 + t) * 64);
+          for (int t = 0; t < 32; ++t) y[t] = last_load<ONCE>(kr + (blk * 32 + t) * 64);
         }
         uint8_t* kb = k_codes + (block0 + blk) * (int64_t)d.block_bytes;
         if (ANY) {                                     // the flagged rows become the mean row
@@ -543,7 +550,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
           if ((t & (J - 1)) == J - 1) {                // every lane now holds the word of token t - (J - 1) + j
             const int tt = t - (J - 1) + j, m = tt & 15, th = tt >> 4;
             const int byte = BITS == 2 ? 16 * (16 * r + m) + 4 * (2 * th + hi) : 1024 * th + 16 * (16 * r + m) + 4 * cb;
-            __builtin_nontemporal_store(keep, (uint32_t*)(kb + byte));
+            put_away<ONCE>(keep, (uint32_t*)(kb + byte));
           }
         }
         if (lane == 0) {
@@ -591,15 +598,15 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
     }
 #pragma unroll 1
     for (int blk = 0; blk < nblk; ++blk) {
-      uint4 w[8];
+      u32x4 w[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) w[i] = once(vr + (blk * 32 + 4 * i + t4) * kHeadDim);
+      for (int i = 0; i < 8; ++i) w[i] = last_load<ONCE>((const u32x4*)(vr + (blk * 32 + 4 * i + t4) * kHeadDim));
       lds_order();                                      // the previous block's reads are done
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int t = 4 * i + t4, T = blk * 32 + t;
         if (ANY && ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull))
-          w[i] = make_uint4(mean4[0], mean4[1], mean4[2], mean4[3]);
+          w[i] = u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
         const h2 a = __builtin_elementwise_min(__builtin_elementwise_min(as_h2(w[i].x), as_h2(w[i].y)),
                                                __builtin_elementwise_min(as_h2(w[i].z), as_h2(w[i].w)));
         const h2 b = __builtin_elementwise_max(__builtin_elementwise_max(as_h2(w[i].x), as_h2(w[i].y)),
@@ -663,10 +670,10 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
           }
         }
         if (BITS == 2) {                                // fields 2 q and 2 q + 1: word q of the packed lane, the odd field 8 bits up
-          __builtin_nontemporal_store(wa | rotl32(wb, 8), (uint32_t*)(vb + 16 * (16 * r + n)) + q);
+          put_away<ONCE>(wa | rotl32(wb, 8), (uint32_t*)(vb + 16 * (16 * r + n)) + q);
         } else {                                        // words 2 (q & 1), 2 (q & 1) + 1 of half q >> 1
-          typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-          __builtin_nontemporal_store(u2v{wa, wb}, (u2v*)(vb + 1024 * (q >> 1) + 16 * (16 * r + n) + 8 * (q & 1)));
+          typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+          put_away<ONCE>(u32x2{wa, wb}, (u32x2*)(vb + 1024 * (q >> 1) + 16 * (16 * r + n) + 8 * (q & 1)));
         }
       }
     }
@@ -776,11 +783,24 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
                        layer_rows<LAYERS>(rows));
     return hipGetLastError();
   };
-  // Where the competition has just read more Keys than the memory-side cache (256 MB) keeps besides everything else,
-  // the last groups come first: their Keys are still there.  With that, and with loads and stores that do not displace
-  // them: 256 units x 4096 tokens, the whole call 196 -> 180 us; 512 units 384 -> 350; 64 x 16384 225 -> 199.  (Fewer
-  // Keys are there in any order: 32 units x 8191 58.8 / 59.8 us first to last / last to first, 64 x 4096 66.8 / 66.2.)
-  if (many) return go(prompt_quantize_kernel<BITS, G, LAYERS>, 0, (int32_t)(groups * G * (2 * kHeadDim) >= (1ll << 27)));
+  // Two rules on the Keys' size.  (Times of the whole call, MB of 2^20 bytes; the memory-side cache holds 256.)
+  // Where the competition has just read more Keys than the cache keeps besides everything else, the last groups come
+  // first: their Keys are still there.  G = 32, first to last / last to first: 2-bit, 260 MB (256 units x 4160 tokens)
+  // 197 / 186 us, 520 MB 385 / 372; 4-bit, 260 MB 240 / 233.  At 128 MB and below they are there in any order.
+  // ONCE keeps rows that are not needed again, and the codes, from displacing the rest.  It pays where there is more
+  // than the cache holds of what comes next, and costs where the codes or the next rows would have been found there:
+  // first 2-bit, then 4-bit codes, without / with it, G = 32: 96 MB 75.1 / 78.2 us, 100 / 102; 130 MB 97.0 / 96.6, 127.2
+  // / 127.1; 186 MB 139 / 132, 178 / 176; 260 MB 186 / 174, 233 / 232.  G = 64: 32 MB 45.9 / 45.6, 52.8 / 53.4; 64 MB
+  // 69.2 / 66.8, 81.5 / 82.0; 130 MB 112 / 101, 132 / 131; 260 MB 200 / 182, 240 / 234.  G = 128, whose Keys are read twice
+  // as it is: 64 MB 73.1 / 75.2, 87.7 / 89.7; 128 MB 123 / 129, 143 / 145; 188 MB 167 / 167, 193 / 189; 256 MB 219 / 223, 249
+  // / 247.  1032 MB: G = 32 706 / 727, 849 / 842; G = 64 758 / 800, 864 / 856.
+  const int64_t key_bytes = groups * G * (2 * kHeadDim);
+  const int32_t last_first = key_bytes >= (1ll << 27);
+  if constexpr (G < 128 || BITS == 4) {
+    if (many && key_bytes >= (G == 64 ? 3ll << 24 : 5ll << 25) && key_bytes < (1ll << 30))
+      return go(prompt_quantize_kernel<BITS, G, LAYERS, true>, 0, last_first);
+  }
+  if (many) return go(prompt_quantize_kernel<BITS, G, LAYERS, false>, 0, last_first);
   const size_t smem = quant_lds_bytes<G>(d.vgroups);
   if (smem > 48 * 1024) {  // more than the default limit of dynamic LDS per workgroup
     hipError_t e = hipFuncSetAttribute((const void*)quantize_kernel<BITS, G, LAYERS>, hipFuncAttributeMaxDynamicSharedMemorySize,
