@@ -791,15 +791,16 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
   // than the cache holds of what comes next, and costs where the codes or the next rows would have been found there:
   // first 2-bit, then 4-bit codes, without / with it, G = 32: 96 MB 75.1 / 78.2 us, 100 / 102; 130 MB 97.0 / 96.6, 127.2
   // / 127.1; 186 MB 139 / 132, 178 / 176; 260 MB 186 / 174, 233 / 232.  G = 64: 32 MB 45.9 / 45.6, 52.8 / 53.4; 64 MB
-  // 69.2 / 66.8, 81.5 / 82.0; 130 MB 112 / 101, 132 / 131; 260 MB 200 / 182, 240 / 234.  G = 128, whose Keys are read twice
-  // as it is: 64 MB 73.1 / 75.2, 87.7 / 89.7; 128 MB 123 / 129, 143 / 145; 188 MB 167 / 167, 193 / 189; 256 MB 219 / 223, 249
-  // / 247.  1032 MB: G = 32 706 / 727, 849 / 842; G = 64 758 / 800, 864 / 856.
+  // 69.2 / 66.8, 81.5 / 82.0; 130 MB 112 / 101, 132 / 131; 260 MB 200 / 182, 240 / 234.  G = 128, 128 units: 64 MB 73.1
+  // / 75.2, 87.7 / 89.7; 168 MB 152 / 152, 178 / 175; 260 MB 223 / 218, 257 / 252.  1032 MB: G = 32 706 / 727, 849 / 842; G =
+  // 64 758 / 800, 864 / 856.  With G = 128 the Keys are read twice as it is: a third time, behind the competition, they
+  // are found in the cache where many units each have few (2-bit, 260 MB: 96 units 221 / 214, 160 219 / 215, 192 220 / 219,
+  // 256 218 / 220, 384 229 / 231); without a competition ONCE pays from the same size on (200 MB, 256 units 121 / 109).
   const int64_t key_bytes = groups * G * (2 * kHeadDim);
   const int32_t last_first = key_bytes >= (1ll << 27);
-  if constexpr (G < 128 || BITS == 4) {
-    if (many && key_bytes >= (G == 64 ? 3ll << 24 : 5ll << 25) && key_bytes < (1ll << 30))
-      return go(prompt_quantize_kernel<BITS, G, LAYERS, true>, 0, last_first);
-  }
+  const bool once = key_bytes >= (G == 64 ? 3ll << 24 : 5ll << 25) && key_bytes < (1ll << 30) &&
+                    (G < 128 || BITS == 4 || d.units_per_layer * rows.layers <= 160 || d.N == 0);
+  if (many && once) return go(prompt_quantize_kernel<BITS, G, LAYERS, true>, 0, last_first);
   if (many) return go(prompt_quantize_kernel<BITS, G, LAYERS, false>, 0, last_first);
   const size_t smem = quant_lds_bytes<G>(d.vgroups);
   if (smem > 48 * 1024) {  // more than the default limit of dynamic LDS per workgroup
