@@ -35,18 +35,23 @@ def test_every_state_fits_and_is_resident(units, g):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("batch,kv_heads,g,bits,context", [
-    (19, 8, 4, 2, 128 * 33 + 150),    # 152 units, 3 workgroups of 4 wavefronts
-    (23, 4, 2, 4, 128 * 60 + 140),    # 92 units, 5 of 4
-    (38, 8, 1, 2, 128 * 20 + 129),    # 304 units, 3 of 2
-    (10, 4, 8, 2, 128 * 7 + 160),     # 40 units, 2 of 8
-    (1, 1, 4, 2, 128 * 200 + 130),    # 1 unit, 25 of 8
+@pytest.mark.parametrize("batch,kv_heads,g,bits,context,shape", [
+    (19, 8, 4, 2, 128 * 33 + 150, (3, 4)),    # 152 units
+    (23, 4, 2, 4, 128 * 60 + 140, (5, 4)),    # 92 units
+    (38, 8, 1, 2, 128 * 20 + 129, (3, 2)),    # 304 units
+    (10, 4, 8, 2, 128 * 7 + 160, (6, 8)),     # 40 units: 8 mini-chunks, the last two workgroups have none
+    (1, 1, 4, 2, 128 * 200 + 130, (25, 8)),   # 1 unit
+    (1, 1, 4, 2, 4200, (8, 8)),               # some wavefronts have quantized tokens, some rows, some neither
+    (1, 8, 4, 2, 1100, (8, 8)),               # one mini-chunk per workgroup
+    (1, 8, 2, 2, 800, (4, 4)),                # the last workgroup has rows alone
+    (2, 8, 1, 2, 5300, (12, 4)),              # more partial results than are merged at a time
+    (2, 8, 1, 4, 5300, (12, 4)),
 ])
-def test_outputs_with_unit_counts_that_are_no_power_of_two(batch, kv_heads, g, bits, context):
+def test_outputs_with_unit_counts_that_are_no_power_of_two(batch, kv_heads, g, bits, context, shape):
     w = S.Workload("split", 1, batch=batch, q_heads=kv_heads * g, kv_heads=kv_heads, context=context, bits=bits)
     cfg = KC.make_config(1, w.batch, w.q_heads, w.kv_heads, w.n_quant, bits, 32, 32, w.residual, w.outlier_budget,
                          w.aux_capacity)
-    assert B.kvq_decode_launch_shape(cfg, 1, w.n_quant, w.n_res + 40)[0] > 1
+    assert B.kvq_decode_launch_shape(cfg, 1, w.n_quant, w.n_res + 40)[:2] == shape
     n = batch * kv_heads
     units = sorted({0, n // 2, n - 1})
     P.run_sampled(w, units, regimes=("peaky",))
