@@ -787,18 +787,20 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
   // Where the competition has just read more Keys than the cache keeps besides everything else, the last groups come
   // first: their Keys are still there.  G = 32, first to last / last to first: 2-bit, 260 MB (256 units x 4160 tokens)
   // 197 / 186 us, 520 MB 385 / 372; 4-bit, 260 MB 240 / 233.  At 128 MB and below they are there in any order.
-  // ONCE keeps rows that are not needed again, and the codes, from displacing the rest.  It pays where there is more
-  // than the cache holds of what comes next, and costs where the codes or the next rows would have been found there:
-  // first 2-bit, then 4-bit codes, without / with it, G = 32: 96 MB 75.1 / 78.2 us, 100 / 102; 130 MB 97.0 / 96.6, 127.2
-  // / 127.1; 186 MB 139 / 132, 178 / 176; 260 MB 186 / 174, 233 / 232.  G = 64: 32 MB 45.9 / 45.6, 52.8 / 53.4; 64 MB
-  // 69.2 / 66.8, 81.5 / 82.0; 130 MB 112 / 101, 132 / 131; 260 MB 200 / 182, 240 / 234.  G = 128, 128 units: 64 MB 73.1
-  // / 75.2, 87.7 / 89.7; 168 MB 152 / 152, 178 / 175; 260 MB 223 / 218, 257 / 252.  1032 MB: G = 32 706 / 727, 849 / 842; G =
-  // 64 758 / 800, 864 / 856.  With G = 128 the Keys are read twice as it is: a third time, behind the competition, they
-  // are found in the cache where many units each have few (2-bit, 260 MB: 96 units 221 / 214, 160 219 / 215, 192 220 / 219,
-  // 256 218 / 220, 384 229 / 231); without a competition ONCE pays from the same size on (200 MB, 256 units 121 / 109).
+  // ONCE keeps rows that are not needed again, and the codes, from displacing the rest.  It pays where the rows have to
+  // come from memory, and costs where the next call would have found rows in the same place in the cache.  In per cent of
+  // the whole call, 128 units, 2-bit / 4-bit codes; the rows a) gone from the cache, b) just written, c) read again where
+  // they were:   36 MB of Keys                  64                              100                              200
+  //   G = 32     a 2 / 1, b 1 / 0, c -3 / 0     a 5 / 5, b 0 / 0, c -3 / -1     a 4 / 3, b -2 / -2, c -4 / -1    a 11 / 2, b 8 / 1, c 11 / 2
+  //   G = 64     a 3 / 2, b 2 / 0, c -1 / -1    a 8 / 4, b 4 / 0, c 4 / 0       a 4 / 2, b 2 / 1, c 6 / 1        a 9 / 2, b 7 / 1, c 11 / 3
+  //   G = 128    a 0 / 1, b -2 / -1, c -2 / -1  a 0 / 1, b -2 / 0, c -3 / -2    a 4 / 4, b -3 / -2, c -2 / -1    a 4 / 2, b 3 / 0, c 2 / 2
+  // Below 32 MB -4 .. 4 either way; at 1032 MB, 512 units, c: -3 / 1 (G = 32), -5 / 1 (G = 64).  With G = 128 the Keys are
+  // read twice as it is, and of many short units, 2-bit, they are found in the cache the second time (200 MB, 256 units:
+  // a 1, b -1, c -1); where there is no competition it pays for those too (c 12).
   const int64_t key_bytes = groups * G * (2 * kHeadDim);
   const int32_t last_first = key_bytes >= (1ll << 27);
-  const bool once = key_bytes >= (G == 64 ? 3ll << 24 : 5ll << 25) && key_bytes < (1ll << 30) &&
+  const int64_t from = G == 64 ? 1ll << 25 : G == 32 ? 3ll << 24 : BITS == 4 ? 1ll << 26 : 3ll << 25;
+  const bool once = key_bytes >= from && key_bytes < (1ll << 30) &&
                     (G < 128 || BITS == 4 || d.units_per_layer * rows.layers <= 160 || d.N == 0);
   if (many && once) return go(prompt_quantize_kernel<BITS, G, LAYERS, true>, 0, last_first);
   if (many) return go(prompt_quantize_kernel<BITS, G, LAYERS, false>, 0, last_first);

@@ -108,12 +108,11 @@ def test_rows_given_back_before_a_side_stream_reads_them():
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits,G,groups", [
     (2, 32, 127), (2, 32, 128), (4, 64, 64), (2, 128, 32),
-    (2, 32, 159), (2, 32, 160), (4, 32, 160), (2, 64, 23), (2, 64, 24), (4, 64, 24), (4, 128, 40), (2, 128, 39),
-    (2, 128, 40),
+    (2, 32, 47), (2, 32, 48), (4, 32, 48), (2, 64, 15), (2, 64, 16), (4, 64, 16), (2, 128, 23), (2, 128, 24), (4, 128, 16),
 ])
 def test_a_large_batch_equals_each_sequence_on_its_own(bits, G, groups):
     """128 units: from 4096 quantized tokens each (2^27 bytes of Keys) the quantization takes the last groups first; from
-    5120, with G = 64 from 1536, its loads and stores leave the caches alone."""
+    1024 .. 3072, by code and group size, its loads and stores leave the caches alone."""
     import torch
     n = groups * G + 43
     cfg = KC.make_config(1, 16, 8, 8, groups * G, bits, G, residual=43)
