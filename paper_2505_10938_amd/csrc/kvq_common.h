@@ -64,7 +64,7 @@ __device__ inline GroupPlace place_of_group(const Dims& d, int ul, int group, in
 // The rows that a launch quantizes, of up to kPromptLayers consecutive layers (blockIdx.z; unit0 and plane0 are the
 // first one's): a layer's rows are where k[z] and v[z] say, its units `unit_stride` elements apart.  (One sequence has
 // few units: its layers one after the other are three launches each of 10 .. 14 us that leave most of the device idle.
-// A prompt of 8191 tokens, 8 kv heads, 4 layers: 164 us layer by layer, 58 us with all layers in the same launches.)
+// A prompt of 8191 tokens, 8 kv heads, 4 layers: 165 us layer by layer, 59 us with all layers in the same launches.)
 // The kernels are built for one layer too (LAYERS = 1): its pointers are ordinary arguments then, next to the others and
 // not behind an index.  Whole call, one layer of 300 tokens, 4 units, with an array of 32 / with one pointer: 13.1 / 12.7
 // us with G = 32, 14.4 / 14.1 with G = 64.
