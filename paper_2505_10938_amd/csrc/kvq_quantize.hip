@@ -370,13 +370,18 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
 // group's Keys and wavefront 1 its Values, each with a lane-to-element mapping in which the packed words fall
 // out of the lanes that computed the codes:
 //   Keys:   a lane owns one channel pair for all tokens, so minimum and maximum over the tokens are packed
-//           fp16 operations inside the lane (exact: they only select).  The 8 (2-bit) or 4 (4-bit) lanes
-//           whose codes share a packed word are adjacent (for 2-bit the lanes are numbered accordingly) and
-//           combine it with 3 or 2 cross-lane ORs; over 8 or 4 tokens each of them keeps one word, then all
-//           store.
-//   Values: minimum and maximum per (token, channel group) with 8 channels per lane and a butterfly over
-//           Gv / 8 lanes on the packed pair {min, -max}; the rows and their {zero, step / 2} then go through
-//           LDS into the mapping in which a lane owns the two channels of one packed word for 8 tokens.
+//           fp16 operations inside the lane (exact: they only select).  It gathers its codes of 8 (2-bit) or
+//           4 (4-bit) tokens in one register; the 8 (4) lanes that share a packed word trade fields of it, 3 (2)
+//           exchanges after which each has the word of one of the tokens.
+//   Values: a lane has 8 channels of 8 tokens.  Minimum and maximum per (token, channel group) are folded over
+//           a quad on the packed pair {min, -max} so that each of its lanes ends up with two tokens, whose step, zero
+//           and thresholds it works out for the quad.  Codes become words by trades between lanes and between
+//           registers, and a lane stores 16 bytes.
+// Nothing goes through LDS.  What bounds it: the rows and codes on their way (256 units x 4096 tokens, 2-bit: 637 MB in
+// about 97 us, 6.5 TB/s, the Keys in part from the memory-side cache).  When every code was decided by fp32 comparisons, gathered
+// by an OR over the lanes token by token and the Values turned through LDS, it was the instructions, 1900 per group
+// of 32 where there are now about 900; whole calls, three sets of rows in turn: 183 -> 159 us, 4-bit 232 -> 175, G = 128 with 4 bits 246 -> 225; a joining prompt of 8191
+// tokens, 8 kv heads, 4 layers 59 -> 52 us.
 // Results are those of quantize_body bit for bit (same roundings in the same order; minimum, maximum and
 // the exact fp64 sums do not depend on the order they are taken in).
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -385,10 +390,10 @@ __device__ __forceinline__ uint32_t as_u32(h2 v) { return __builtin_bit_cast(uin
 __device__ __forceinline__ uint32_t rotl32(uint32_t w, int n) { return __builtin_amdgcn_alignbit(w, w, (32 - n) & 31); }
 __device__ __forceinline__ uint32_t half_bits(float x) { return (uint32_t)__half_as_ushort(__float2half_rn(x)); }
 __device__ __forceinline__ uint32_t mean_half_bits(double sum, int G) { return half_bits((float)(sum / (double)G)); }
-__device__ __forceinline__ void lds_order() {   // LDS traffic of one wavefront executes in order; this holds the compiler to it
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Is one of the two an infinity or a NaN?  (In integers: the compiler took a comparison with infinity for one that is true
+// of a NaN.)
+__device__ __forceinline__ uint32_t not_finite(h2 v) {
+  return ((as_u32(v) & 0x7C007C00u) + 0x04000400u) & 0x80008000u;
 }
 
 // A load that is the last one, and a store that nothing soon reads: with ONCE they leave what the caches hold alone.
@@ -403,6 +408,133 @@ __device__ __forceinline__ void put_away(T v, T* p) {
   else *p = v;
 }
 
+// 2-bit codes are decided two at a time, in packed fp16: code k is reached where fl32(x - mn) >= (2k - 1) h, which a
+// value of larger x reaches too, so that x >= T_k decides it, T_k being the smallest fp16 value that reaches it; and the
+// sign of the fp16 difference x - T_k is that decision, whatever the rounding (a difference of unequal numbers never
+// rounds to zero).  Kept is -T_k, a zero with the sign +: equal numbers, zeros of either sign among them, give +0.
+// T_k: fl32(v) >= t for t of at most 14 bits is v >= t - u / 2, u the distance to the number below t (a tie rounds to t,
+// whose last bit is 0), and v >= t - u / 4 at a power of two: in both cases the fp64 number 2^28 units below t.  mn + that
+// is exact in fp64 (a group whose extremes differ has a step of at least 2^-14 of |mn|); rounded up to fp32 and then
+// to fp16 it is the smallest fp16 number that is no less.  A step of zero has h = +infinity, and T_k = +infinity.
+// Finite rows only: where a minimum or maximum is not finite, codes2 compares as the other kernels do.
+struct Thresholds2 {
+  h2 neg[3];                                           // -T_1 .. -T_3 of two groups
+};
+__device__ __forceinline__ Thresholds2 thresholds2(float mn0, float h0, float mn1, float h1) {
+  double b[6];
+  const double m[2] = {(double)mn0, (double)mn1}, h[2] = {(double)h0, (double)h1};
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const unsigned long long t = (unsigned long long)__double_as_longlong((double)(2 * (i >> 1) + 1) * h[i & 1]);
+    b[i] = m[i & 1] + __longlong_as_double((long long)(t - (1ull << 28)));
+  }
+  float f[6];                                          // fp16 in the low half
+  asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 5\n\t"          // round up
+      "v_cvt_f32_f64 %0, %6\n\tv_cvt_f32_f64 %1, %7\n\tv_cvt_f32_f64 %2, %8\n\t"
+      "v_cvt_f32_f64 %3, %9\n\tv_cvt_f32_f64 %4, %10\n\tv_cvt_f32_f64 %5, %11\n\t"
+      "v_cvt_f16_f32 %0, %0\n\tv_cvt_f16_f32 %1, %1\n\tv_cvt_f16_f32 %2, %2\n\t"
+      "v_cvt_f16_f32 %3, %3\n\tv_cvt_f16_f32 %4, %4\n\tv_cvt_f16_f32 %5, %5\n\t"
+      "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0"
+      : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5])
+      : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]));
+  Thresholds2 r;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t lo = __float_as_uint(f[2 * k]), hi = __float_as_uint(f[2 * k + 1]);
+    r.neg[k] = h2{(_Float16)0.0f, (_Float16)0.0f} - as_h2(__builtin_amdgcn_perm(hi, lo, 0x05040100u));
+  }
+  return r;
+}
+// The bits of two codes (a pair of fp16 values) as the sign bits of two halves each.
+struct Bits2 {
+  uint32_t low, not_high;
+};
+__device__ __forceinline__ Bits2 bits2(uint32_t d1, uint32_t d2, uint32_t d3) {     // sign set: T_k not reached
+  return {(~d1 & d2) | ~d3, d2};
+}
+__device__ __forceinline__ Bits2 codes2(uint32_t x, h2 n1, h2 n2, h2 n3) {
+  return bits2(as_u32(as_h2(x) + n1), as_u32(as_h2(x) + n2), as_u32(as_h2(x) + n3));
+}
+__device__ __forceinline__ Bits2 codes2_compared(uint32_t x, float mn0, float h0, float mn1, float h1) {
+  const float a = lo_half(x) - mn0, b = hi_half(x) - mn1;
+  auto below = [&](float k) { return (a >= k * h0 ? 0u : 0x8000u) | (b >= k * h1 ? 0u : 0x80000000u); };
+  return bits2(below(1.0f), below(3.0f), below(5.0f));
+}
+// Two pairs of codes into pair i (0 .. 3) of each byte of a register of sixteen 2-bit codes: the low halves' codes of p
+// and q go to bytes 0 and 1, the high halves' to 2 and 3 (SWAPPED: 0 and 2, 1 and 3).  One byte permutation, which can
+// replicate sign bits, serves four codes.
+template <bool SWAPPED>
+__device__ __forceinline__ void gather2(uint32_t& acc, const Bits2& p, const Bits2& q, int i) {
+  constexpr uint32_t sel = SWAPPED ? 0x0B0A0908u : 0x0B090A08u;
+  const uint32_t low = __builtin_amdgcn_perm(q.low, p.low, sel), not_high = __builtin_amdgcn_perm(q.not_high, p.not_high, sel);
+  acc |= low & (0x01010101u << (2 * i));
+  acc |= ~not_high & (0x02020202u << (2 * i));
+}
+// 4-bit codes: k is the number of thresholds (2k - 1) h that t = fl32(x - mn) reaches, at most 15, that is t / step + 1/2
+// rounded down.  The product with the reciprocal is off by less than 2^-17 (t is at most 23 steps, where a step is the
+// smallest number there is), so that with 2^-16 more it is k or k + 1 rounded down; one exact threshold tells which.
+// A step of zero is taken with a reciprocal of zero: no threshold is reached.  Finite rows only, as above.
+struct Scale4 {
+  float mn, inv, step;
+};
+__device__ __forceinline__ Scale4 scale4(float mn, __half st) {
+  const float s = __half2float(st);
+  return {mn, s == 0.0f ? 0.0f : 1.0f / s, s};
+}
+__device__ __forceinline__ uint32_t code4(float t, const Scale4& q) {
+  uint32_t k = (uint32_t)__builtin_fmaf(t, q.inv, 0.5f + 0x1p-16f);
+  k = k < 15u ? k : 15u;
+  return k - (t < __builtin_fmaf((float)k, q.step, -0.5f * q.step) ? 1u : 0u);
+}
+__device__ __forceinline__ float low_less(uint32_t x, float mn) {       // fl32(low half - mn)
+  float t;
+  asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(t) : "v"(x), "v"(mn));
+  return t;
+}
+__device__ __forceinline__ float high_less(uint32_t x, float mn) {
+  float t;
+  asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(t) : "v"(x), "v"(mn));
+  return t;
+}
+__device__ __forceinline__ uint32_t code4_compared(float x, float mn, float h) { return (uint32_t)quant_code_twice<4>(x, mn, h) >> 1; }
+// The four rows of 16 lanes trade registers: row i gets register i of all rows, row k's as its register k.
+__device__ __forceinline__ void trade_rows(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3) {
+  auto s = __builtin_amdgcn_permlane32_swap(a0, a2, false, false);
+  a0 = s[0], a2 = s[1];
+  s = __builtin_amdgcn_permlane32_swap(a1, a3, false, false);
+  a1 = s[0], a3 = s[1];
+  s = __builtin_amdgcn_permlane16_swap(a0, a1, false, false);
+  a0 = s[0], a1 = s[1];
+  s = __builtin_amdgcn_permlane16_swap(a2, a3, false, false);
+  a2 = s[0], a3 = s[1];
+}
+// Two registers: those fields (`zeros` and as many next to each, `by` bits up) that a has second against those that b has first.
+__device__ __forceinline__ void trade_fields(uint32_t& a, uint32_t& b, uint32_t zeros, int by) {
+  const uint32_t x = (a & zeros) | ((b << by) & ~zeros);
+  b = ((a >> by) & zeros) | (b & ~zeros);
+  a = x;
+}
+// A register of sixteen 2-bit codes per lane, numbered 0 .. 15: what a lane keeps are the codes whose bit BIT of that number is
+// its own (`upper`), and in the place of the others it takes those that the partner lane has for it.  (4-bit codes: two numbers each.)
+template <int BIT>
+__device__ __forceinline__ uint32_t trade2(uint32_t own, uint32_t partner, bool upper) {
+  constexpr uint32_t zeros = BIT == 0 ? 0x33333333u : BIT == 1 ? 0x0F0F0F0Fu : 0x00FF00FFu;
+  constexpr int by = 2 << BIT;
+  const uint32_t keep = upper ? ~zeros : zeros;
+  const uint32_t turned = __builtin_amdgcn_alignbit(partner, partner, upper ? by : 32 - by);
+  return (own & keep) | (turned & ~keep);
+}
+// Lanes of a row of 16, by banks of four: bank BANK's get `v` from BY lanes below (modulo 16), the others keep `old`.
+template <int BANK, int BY>
+__device__ __forceinline__ uint32_t from_bank(uint32_t old, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, 0x120 + BY /* row_ror */, 0xf, 1 << BANK, false);
+}
+// Lanes of a quad: each gets lane S's.
+template <int S>
+__device__ __forceinline__ uint32_t of_quad_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, S * 0x55, 0xf, 0xf, false);
+}
+
 template <int BITS, int G, int LAYERS, bool ONCE>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))) prompt_quantize_kernel(
     Dims d, int32_t group_index, int64_t unit_stride, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
@@ -410,9 +542,6 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
     __half* __restrict__ k_res, __half* __restrict__ v_res, int32_t last_first, LayerRows<LAYERS> rows) {
   // grid (units, groups + tail blocks, layers), as quantize_kernel's
-  __shared__ u32x4 vrow[32 * 16];                      // 32 Value rows of 128 fp16 (mean-replaced where flagged)
-  __shared__ float2 vms[32 * 4];                       // their {zero, step / 2} per channel group
-  __shared__ uint32_t vpr[32 * 4];                     // and before that {minimum, -maximum} as an fp16 pair
   const int tid = threadIdx.x;
   const int ul = blockIdx.x, by = blockIdx.y, layer = LAYERS > 1 ? blockIdx.z : 0;
   const __half* __restrict__ k_rows = rows.k[layer];
@@ -435,59 +564,66 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   const GroupPlace at = place_of_group(d, ul, group_index + gy, layer);
   constexpr int nblk = G / kBlockTokens;
   const int64_t block0 = at.row * d.blocks_per_unit + (int64_t)at.slot * nblk;   // the group's first packed block
-  // the flags of the group's tokens as bit masks (uniform)
+  // The flags of the group's tokens, as bit masks (uniform).  The rows are asked for while they come where registers allow
+  // it (in the other instances they would have to be put away into scratch memory).
+  constexpr bool kAhead = BITS == 2 && G == 32;
   constexpr int kSelWords = (G + 63) / 64;
   unsigned long long sel[kSelWords];
-  bool any = false;
+  uint8_t flags[kSelWords];
 #pragma unroll
-  for (int w = 0; w < kSelWords; ++w) {
-    const int t = 64 * w + lane;
-    const bool f = selected && t < G && selected[sel0 + t] != 0;
-    sel[w] = __ballot(f);
-    any |= sel[w] != 0;
-  }
+  for (int w = 0; w < kSelWords; ++w) flags[w] = selected && 64 * w + lane < G ? selected[sel0 + 64 * w + lane] : (uint8_t)0;
+  auto any_flag = [&]() -> bool {
+    bool any = false;
+#pragma unroll
+    for (int w = 0; w < kSelWords; ++w) {
+      sel[w] = __ballot(flags[w] != 0);
+      any |= sel[w] != 0;
+    }
+    return any;
+  };
   auto is_sel = [&](int t) -> bool { return (sel[kSelWords == 1 ? 0 : t >> 6] >> (t & 63)) & 1ull; };
 
   if (wave == 0) {
     // ---- Keys ------------------------------------------------------------------------------------------
-    const int v = lane & 3;
-    int cp, r, hi = 0, p = 0, cb = 0;                  // cp: the lane's channel pair (channels 2 cp, 2 cp + 1)
+    int cp, r, hi = 0, p = 0, cb = 0, v = lane & 3;    // cp: the lane's channel pair (channels 2 cp, 2 cp + 1)
     if (BITS == 2) {
       hi = lane >> 5, r = (lane >> 3) & 3, p = (lane >> 2) & 1;
+      v ^= p ? 3 : 0;                                  // (so that the mirror lane inside 8 has the other p and the same v)
       cp = 16 * (2 * hi + p) + 4 * r + v;
     } else {
       cp = lane, cb = lane >> 4, r = (lane >> 2) & 3;
     }
     const uint32_t* kr = (const uint32_t*)(k_rows + row0) + cp;        // token t: kr[64 t]
-    // Where the lane's two codes of a token sit in the packed word: bit pos0 (channel 2 cp) and pos0 + 16
-    // (channel 2 cp + 1), the whole turned left by 8 for the odd fields of a 2-bit word.
-    const int pos0 = BITS == 2 ? 2 * (v + 1) : 2 + 4 * (v & 1) + 8 * (v >> 1);
-    const int turn = BITS == 2 ? 8 * p : 0;
-    const uint32_t bit_a0 = rotl32(1u << pos0, turn), bit_a1 = rotl32(2u << pos0, turn);         // 2-bit codes: their
-    const uint32_t bit_b0 = rotl32(1u << (pos0 + 16), turn), bit_b1 = rotl32(2u << (pos0 + 16), turn);   // two bits each
-    constexpr int J = BITS == 2 ? 8 : 4;               // lanes that share a word
-    const int j = lane & (J - 1);
+    uint32_t y[32];
+    auto load_rows = [&](int blk, auto last_c) {
+#pragma unroll
+      for (int t = 0; t < 32; ++t) {                   // (longer groups are read a second time for the codes)
+        if constexpr (decltype(last_c)::value) y[t] = last_load<ONCE>(kr + (blk * 32 + t) * 64);
+        else y[t] = kr[(blk * 32 + t) * 64];
+      }
+    };
+    if (kAhead) load_rows(0, std::bool_constant<nblk == 1>{});
     auto keys = [&](auto any_c) {
       constexpr bool ANY = decltype(any_c)::value;     // some token of the group is flagged (uniform)
-      uint32_t y[32];
+      double s0 = 0.0, s1 = 0.0;
       h2 mn = {(_Float16)__builtin_inff(), (_Float16)__builtin_inff()};
       h2 mx = {(_Float16)(-__builtin_inff()), (_Float16)(-__builtin_inff())};
-      double s0 = 0.0, s1 = 0.0;
+      // (a NaN among the rows is found out by its being the result; where it is passed over comes below)
+      auto lower = [](h2 a, h2 b) { return __builtin_elementwise_minimum(a, b); };
+      auto upper = [](h2 a, h2 b) { return __builtin_elementwise_maximum(a, b); };
 #pragma unroll 1
       for (int blk = 0; blk < nblk; ++blk) {
-#pragma unroll
-        for (int t = 0; t < 32; ++t)                   // (longer groups are read a second time for the codes)
-          y[t] = nblk == 1 ? last_load<ONCE>(kr + t * 64) : kr[(blk * 32 + t) * 64];
+        if (!kAhead || blk > 0) load_rows(blk, std::bool_constant<nblk == 1>{});
 #pragma unroll
         for (int t = 0; t < 32; ++t) {
           const h2 x = as_h2(y[t]);
           if (ANY) {
             const bool s = is_sel(blk * 32 + t);
-            mn = s ? mn : __builtin_elementwise_min(mn, x);
-            mx = s ? mx : __builtin_elementwise_max(mx, x);
+            mn = s ? mn : lower(mn, x);
+            mx = s ? mx : upper(mx, x);
           } else {
-            mn = __builtin_elementwise_min(mn, x);
-            mx = __builtin_elementwise_max(mx, x);
+            mn = lower(mn, x);
+            mx = upper(mx, x);
           }
         }
         if (ANY) {                                     // the exact sums of ALL rows as they came (two chains of
@@ -503,8 +639,20 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
       uint32_t mean = 0;
       if (ANY) {
         mean = mean_half_bits(s0, G) | (mean_half_bits(s1, G) << 16);
-        mn = __builtin_elementwise_min(mn, as_h2(mean));
-        mx = __builtin_elementwise_max(mx, as_h2(mean));
+        mn = lower(mn, as_h2(mean));
+        mx = upper(mx, as_h2(mean));
+      }
+      auto row = [&](int t) -> uint32_t { return ANY && is_sel(t) ? mean : kr[t * 64]; };
+      const bool finite = __ballot(not_finite(mn) | not_finite(mx)) == 0;
+      if (!finite) {                                   // (uniform; such rows are not supported, and nothing here is made to be fast)
+        mn = h2{(_Float16)__builtin_inff(), (_Float16)__builtin_inff()};
+        mx = -mn;
+#pragma unroll 1
+        for (int t = 0; t < G; ++t) {
+          const h2 x = as_h2(row(t));
+          mn = __builtin_elementwise_min(mn, x);
+          mx = __builtin_elementwise_max(mx, x);
+        }
       }
       const float mn0 = (float)mn[0] + 0.0f, mn1 = (float)mn[1] + 0.0f;   // a zero minimum is stored as +0
       const __half st0 = step_of(mn0, (float)mx[0], BITS), st1 = step_of(mn1, (float)mx[1], BITS);
@@ -514,43 +662,87 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
         gm[cp] = (uint32_t)__half_as_ushort(st0) | ((uint32_t)__half_as_ushort(st1) << 16);
         gm[64 + cp] = half_bits(mn0) | (half_bits(mn1) << 16);
       }
-      // 2-bit: the thresholds (2k - 1) h themselves (exact: h has 11 bits)
-      const float h0x3 = 3.0f * h0, h0x5 = 5.0f * h0, h1x3 = 3.0f * h1, h1x5 = 5.0f * h1;
+      Thresholds2 th = {};
+      Scale4 sc0 = {}, sc1 = {};
+      if (BITS == 2) th = thresholds2(mn0, h0, mn1, h1);
+      else sc0 = scale4(mn0, st0), sc1 = scale4(mn1, st1);
+      // The packed word of token 8 b + 4 p + v from the codes of tokens 8 b .. 8 b + 7 (2-bit), of token 4 b + v from those of
+      // tokens 4 b .. 4 b + 3 (4-bit): code(t) of the channel pair
+      auto word_of = [&](auto code) {
+        if constexpr (BITS == 4) {
+          uint32_t acc = 0;                            // code 4 * channel of the pair + token
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const uint2 c = code(i);
+            acc |= (c.x << (4 * i)) | (c.y << (16 + 4 * i));
+          }
+          acc = trade2<1>(acc, row_partner_u32<0>(acc), v & 1);
+          acc = trade2<2>(acc, row_partner_u32<1>(acc), v & 2);
+          return rotl32(acc, 2);
+        } else {
+        uint32_t acc = 0;                              // code 8 * channel of the pair + token
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gather2<false>(acc, code(i), code(4 + i), i);
+        acc = trade2<0>(acc, row_partner_u32<0>(acc), v & 1);
+        acc = trade2<1>(acc, row_partner_u32<1>(acc), v & 2);
+        acc = trade2<2>(acc, row_partner_u32<2>(acc), p);
+        return rotl32(acc, 2);
+        }
+      };
 #pragma unroll 1
       for (int blk = 0; blk < nblk; ++blk) {
-        if (nblk > 1) {
-#pragma unroll
-          for (int t = 0; t < 32; ++t) y[t] = last_load<ONCE>(kr + (blk * 32 + t) * 64);
-        }
+        if (nblk > 1) load_rows(blk, std::true_type{});
         uint8_t* kb = k_codes + (block0 + blk) * (int64_t)d.block_bytes;
         if (ANY) {                                     // the flagged rows become the mean row
 #pragma unroll
           for (int t = 0; t < 32; ++t) y[t] = is_sel(blk * 32 + t) ? mean : y[t];
         }
-        uint32_t keep = 0;
+        if constexpr (BITS == 2) {
+          if (finite) {                                // uniform
+            uint32_t word[4];
 #pragma unroll
-        for (int t = 0; t < 32; ++t) {
-          const uint32_t x = y[t];
-          uint32_t w;
-          if (BITS == 2) {
-            // code = [t >= 3h] * 2 + [t >= (5h if so, else h)]: the number of thresholds h, 3h, 5h reached
-            const float ta = lo_half(x) - mn0, tb = hi_half(x) - mn1;
-            const bool a1 = ta >= h0x3, b1 = tb >= h1x3;
-            const bool a0 = ta >= (a1 ? h0x5 : h0), b0 = tb >= (b1 ? h1x5 : h1);
-            w = (a1 ? bit_a1 : 0u) | (a0 ? bit_a0 : 0u) | (b1 ? bit_b1 : 0u) | (b0 ? bit_b0 : 0u);
+            for (int b = 0; b < 4; ++b) {
+              word[b] = word_of([&](int t) { return codes2(y[8 * b + t], th.neg[0], th.neg[1], th.neg[2]); });
+            }
+            // the two words of a token and half (tokens 0 .. 15, 16 .. 31) to one lane
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+              typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+              const auto sw = __builtin_amdgcn_permlane32_swap(word[b], word[2 + b], false, false);
+              put_away<ONCE>(u32x2{sw[0], sw[1]}, (u32x2*)(kb + 16 * (16 * r + 8 * b + 4 * p + v) + 8 * hi));
+            }
           } else {
-            const uint32_t ca = (uint32_t)quant_code_twice<BITS>(lo_half(x), mn0, h0);   // 2 * code
-            const uint32_t cb2 = (uint32_t)quant_code_twice<BITS>(hi_half(x), mn1, h1);
-            w = (ca << (pos0 - 1)) | rotl32(cb2 << (pos0 - 1), 16);
+#pragma unroll 1
+            for (int b = 0; b < 4; ++b) {
+              const uint32_t w = word_of([&](int t) { return codes2_compared(row(blk * 32 + 8 * b + t), mn0, h0, mn1, h1); });
+              *(uint32_t*)(kb + 16 * (16 * r + 8 * (b & 1) + 4 * p + v) + 4 * (2 * (b >> 1) + hi)) = w;
+            }
           }
-          w |= row_partner_u32<0>(w);
-          w |= row_partner_u32<1>(w);
-          if (BITS == 2) w |= row_partner_u32<2>(w);
-          keep = (t & (J - 1)) == j ? w : keep;
-          if ((t & (J - 1)) == J - 1) {                // every lane now holds the word of token t - (J - 1) + j
-            const int tt = t - (J - 1) + j, m = tt & 15, th = tt >> 4;
-            const int byte = BITS == 2 ? 16 * (16 * r + m) + 4 * (2 * th + hi) : 1024 * th + 16 * (16 * r + m) + 4 * cb;
-            put_away<ONCE>(keep, (uint32_t*)(kb + byte));
+        } else {
+          if (finite) {                                // uniform
+#pragma unroll
+            for (int th16 = 0; th16 < 2; ++th16) {     // tokens 0 .. 15, 16 .. 31
+              uint32_t word[4];
+#pragma unroll
+              for (int b = 0; b < 4; ++b)
+                word[b] = word_of([&](int t) {
+                  const uint32_t x = y[16 * th16 + 4 * b + t];
+                  return make_uint2(code4(low_less(x, sc0.mn), sc0), code4(high_less(x, sc1.mn), sc1));
+                });
+              // row i of lanes gets the words of tokens 4 i + v, all four of a token
+              trade_rows(word[0], word[1], word[2], word[3]);
+              put_away<ONCE>(u32x4{word[0], word[1], word[2], word[3]},
+                             (u32x4*)(kb + 1024 * th16 + 16 * (16 * r + 4 * cb + v)));
+            }
+          } else {
+#pragma unroll 1
+            for (int b = 0; b < 8; ++b) {
+              const uint32_t w = word_of([&](int t) {
+                const uint32_t x = row(blk * 32 + 4 * b + t);
+                return make_uint2(code4_compared(lo_half(x), mn0, h0), code4_compared(hi_half(x), mn1, h1));
+              });
+              *(uint32_t*)(kb + 1024 * (b >> 2) + 16 * (16 * r + 4 * (b & 3) + v) + 4 * cb) = w;
+            }
           }
         }
         if (lane == 0) {
@@ -559,7 +751,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
         }
       }
     };
-    if (any) keys(std::true_type{});
+    if (any_flag()) keys(std::true_type{});
     else keys(std::false_type{});
     return;
   }
@@ -568,11 +760,17 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   const int gv_shift = 31 - __clz(d.Gv);
   const int lanes = d.Gv >> 3;                          // lanes per (token, channel group) in the first mapping
   const int NV = d.vgroups;
-  const int nv_shift = NV == 4 ? 2 : NV == 2 ? 1 : 0;
-  const int t4 = lane >> 4, c16 = lane & 15;            // first mapping: token 4 i + t4, channels 8 c16 .. + 7
+  const int t4 = lane >> 4, c16 = lane & 15;            // the lane's channels are 8 c16 .. + 7, its tokens 8 r + 2 t4 + s
   const __half* vr = v_rows + row0 + 8 * c16;
-  const int n = lane & 15, q = lane >> 4;               // second mapping: channels 32 q + n and 32 q + 16 + n
-  const int jq = (32 * q) >> gv_shift;                  // their channel group
+  u32x4 w[8];
+  auto load_rows = [&](int blk) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      // row i = 2 r + s: the lane's tokens come in pairs, as steps and zeros are stored
+      w[i] = last_load<ONCE>((const u32x4*)(vr + (blk * 32 + 8 * (i >> 1) + 2 * t4 + (i & 1)) * kHeadDim));
+    }
+  };
+  if (kAhead) load_rows(0);
   auto values = [&](auto any_c) {
     constexpr bool ANY = decltype(any_c)::value;
     uint32_t mean4[4] = {0u, 0u, 0u, 0u};
@@ -598,87 +796,197 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
     }
 #pragma unroll 1
     for (int blk = 0; blk < nblk; ++blk) {
-      u32x4 w[8];
+      if (!kAhead || blk > 0) load_rows(blk);
+      if (ANY) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) w[i] = last_load<ONCE>((const u32x4*)(vr + (blk * 32 + 4 * i + t4) * kHeadDim));
-      lds_order();                                      // the previous block's reads are done
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int t = 4 * i + t4, T = blk * 32 + t;
-        if (ANY && ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull))
-          w[i] = u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
-        const h2 a = __builtin_elementwise_min(__builtin_elementwise_min(as_h2(w[i].x), as_h2(w[i].y)),
-                                               __builtin_elementwise_min(as_h2(w[i].z), as_h2(w[i].w)));
-        const h2 b = __builtin_elementwise_max(__builtin_elementwise_max(as_h2(w[i].x), as_h2(w[i].y)),
-                                               __builtin_elementwise_max(as_h2(w[i].z), as_h2(w[i].w)));
-        // the two halves against each other with the same instructions (they order -0 below +0, as the
-        // scalar minimum and maximum of the other kernel do; a comparison would not)
-        const h2 a2 = __builtin_elementwise_min(a, as_h2(rotl32(as_u32(a), 16)));
-        const h2 b2 = __builtin_elementwise_max(b, as_h2(rotl32(as_u32(b), 16)));
-        h2 pr = {a2[0], (_Float16)(-b2[0])};            // {min, -max}: one packed minimum reduces both
-        pr = __builtin_elementwise_min(pr, as_h2(row_partner_u32<0>(as_u32(pr))));
-        pr = __builtin_elementwise_min(pr, as_h2(row_partner_u32<1>(as_u32(pr))));
-        if (lanes > 4) pr = __builtin_elementwise_min(pr, as_h2(row_partner_u32<2>(as_u32(pr))));
-        if (lanes > 8) pr = __builtin_elementwise_min(pr, as_h2(row_partner_u32<3>(as_u32(pr))));
-        vrow[t * 16 + c16] = w[i];
-        if ((c16 & (lanes - 1)) == 0) vpr[t * 4 + ((8 * c16) >> gv_shift)] = as_u32(pr);
-      }
-      lds_order();
-      // steps and zeros of the block's 32 NV (token, channel group) pairs: one lane per (token pair, group),
-      // which is also one dword of each half of the block's meta (fp16 step[16 token pairs][NV][2], then
-      // fp16 zero[16 token pairs][NV][2])
-      if (lane < 16 * NV) {
-        const int tp = lane >> nv_shift, jv = lane & (NV - 1);
-        uint32_t stw = 0, zw = 0;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const h2 pr = as_h2(vpr[(2 * tp + k) * 4 + jv]);
-          const float mnf = (float)pr[0] + 0.0f, mxf = -(float)pr[1];
-          const __half st = step_of(mnf, mxf, BITS);
-          vms[(2 * tp + k) * 4 + jv] = make_float2(mnf, half_step_of(st));
-          stw |= (uint32_t)__half_as_ushort(st) << (16 * k);
-          zw |= half_bits(mnf) << (16 * k);
+        for (int i = 0; i < 8; ++i) {
+          const int T = blk * 32 + 8 * (i >> 1) + 2 * t4 + (i & 1);
+          if ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull)
+            w[i] = u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
         }
-        uint32_t* gm = v_meta + (block0 + blk) * 32 * NV;
-        gm[lane] = stw;
-        gm[16 * NV + lane] = zw;
       }
-      lds_order();
+      // {minimum, -maximum} of the rows in each channel group: lane `own` of a quad gets those of r = own, s = 0, 1.
+      // (A NaN is found out by its being the result; where it is passed over comes below.)
+      const int own = lane & 3;
+      auto channels = [](u32x4 x, auto lower, auto upper) {   // of one row's eight
+        const h2 a = lower(lower(as_h2(x.x), as_h2(x.y)), lower(as_h2(x.z), as_h2(x.w)));
+        const h2 b = upper(upper(as_h2(x.x), as_h2(x.y)), upper(as_h2(x.z), as_h2(x.w)));
+        const uint32_t nb = as_u32(b) ^ 0x80008000u;          // the halves against each other: {a0, -b0} and {a1, -b1}
+        return as_u32(lower(as_h2(__builtin_amdgcn_perm(nb, as_u32(a), 0x05040100u)),
+                            as_h2(__builtin_amdgcn_perm(nb, as_u32(a), 0x07060302u))));
+      };
+      auto quads = [&](uint32_t x, auto lower) {              // of the quads of a channel group
+        if (lanes > 4) {                             // uniform; the lane with the same place in the next quad
+          const uint32_t mirror = row_partner_u32<2>(x);
+          x = as_u32(lower(as_h2(x), as_h2((uint32_t)__builtin_amdgcn_mov_dpp((int)mirror, 0x1B, 0xf, 0xf, false))));
+        }
+        if (lanes > 8) x = as_u32(lower(as_h2(x), as_h2((uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128 /* row_ror:8 */, 0xf, 0xf, false))));
+        return x;
+      };
+      h2 pair[2];
+      {
+        auto lower = [](h2 a, h2 b) { return __builtin_elementwise_minimum(a, b); };
+        auto upper = [](h2 a, h2 b) { return __builtin_elementwise_maximum(a, b); };
+        uint32_t pr[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pr[i] = channels(w[i], lower, upper);
+        auto fold = [&](uint32_t a, uint32_t b, bool up, auto bit_c) {   // lanes with the bit keep b, the others a
+          return as_u32(lower(as_h2(up ? b : a), as_h2(row_partner_u32<decltype(bit_c)::value>(up ? a : b))));
+        };
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const uint32_t r01 = fold(pr[s], pr[2 + s], own & 1, std::integral_constant<int, 0>{});
+          const uint32_t r23 = fold(pr[4 + s], pr[6 + s], own & 1, std::integral_constant<int, 0>{});
+          pair[s] = as_h2(quads(fold(r01, r23, own & 2, std::integral_constant<int, 1>{}), lower));
+        }
+      }
+      auto row = [&](int r, int s) -> u32x4 {
+        const int t = 8 * r + 2 * t4 + s, T = blk * 32 + t;
+        if (ANY && ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull)) return u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
+        return *(const u32x4*)(vr + T * kHeadDim);
+      };
+      const bool finite = __ballot(not_finite(pair[0]) | not_finite(pair[1])) == 0;
+      if (!finite) {
+        auto lower = [](h2 a, h2 b) { return __builtin_elementwise_min(a, b); };
+        auto upper = [](h2 a, h2 b) { return __builtin_elementwise_max(a, b); };
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {
+          uint32_t x = channels(row(i >> 1, i & 1), lower, upper);
+          x = as_u32(lower(as_h2(x), as_h2(row_partner_u32<0>(x))));
+          x = as_u32(lower(as_h2(x), as_h2(row_partner_u32<1>(x))));
+          x = quads(x, lower);
+          pair[0] = (i >> 1) == own && !(i & 1) ? as_h2(x) : pair[0];
+          pair[1] = (i >> 1) == own && (i & 1) ? as_h2(x) : pair[1];
+        }
+      }
+      const float mn0 = (float)pair[0][0] + 0.0f, mn1 = (float)pair[1][0] + 0.0f;   // a zero minimum is stored as +0
+      const __half st0 = step_of(mn0, -(float)pair[0][1], BITS), st1 = step_of(mn1, -(float)pair[1][1], BITS);
+      const float h0 = half_step_of(st0), h1 = half_step_of(st1);
+      if ((c16 & (lanes - 1)) < 4) {                 // fp16 step[16 token pairs][NV][2], then fp16 zero[16 token pairs][NV][2]
+        uint32_t* gm = v_meta + (block0 + blk) * 32 * NV + (4 * own + t4) * NV + ((8 * c16) >> gv_shift);
+        gm[0] = (uint32_t)__half_as_ushort(st0) | ((uint32_t)__half_as_ushort(st1) << 16);
+        gm[16 * NV] = half_bits(mn0) | (half_bits(mn1) << 16);
+      }
       uint8_t* vb = v_codes + (block0 + blk) * (int64_t)d.block_bytes;
-      const __half* rows = (const __half*)vrow;
+      if constexpr (BITS == 4) {
+        uint32_t acc[4][2] = {};                       // r, half of the lane's channels: code 4 s + channel of the four
+        if (finite) {                                  // uniform
+          const Scale4 q0 = scale4(mn0, st0), q1 = scale4(mn1, st1);
+          auto codes = [&](auto r_c) {
+            constexpr int R = decltype(r_c)::value;
+            auto of_lane = [](float x) { return __uint_as_float(of_quad_lane<R>(__float_as_uint(x))); };
+            const Scale4 q[2] = {{of_lane(q0.mn), of_lane(q0.inv), of_lane(q0.step)}, {of_lane(q1.mn), of_lane(q1.inv), of_lane(q1.step)}};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        uint32_t wa = 0, wb = 0;
+            for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          const int t = 8 * r + x;
-          const float2 ms = vms[t * 4 + jq];
-          const _Float16 ha = ((const _Float16*)rows)[t * kHeadDim + 32 * q + n];
-          const _Float16 hb = ((const _Float16*)rows)[t * kHeadDim + 32 * q + 16 + n];
-          const float xa = (float)ha, xb = (float)hb;
-          if (BITS == 2) {
-            constexpr uint32_t one = 1u;
-            const int pos = code_bit(2, 0, x);          // at most 24: both bits fit
-            const float ta = xa - ms.x, tb = xb - ms.x, h3 = 3.0f * ms.y, h5 = 5.0f * ms.y;
-            const bool a1 = ta >= h3, b1 = tb >= h3;
-            const bool a0 = ta >= (a1 ? h5 : ms.y), b0 = tb >= (b1 ? h5 : ms.y);
-            wa |= (a1 ? one << (pos + 1) : 0u) | (a0 ? one << pos : 0u);
-            wb |= (b1 ? one << (pos + 1) : 0u) | (b0 ? one << pos : 0u);
-          } else {
-            wa |= place_twice<BITS>(quant_code_twice<BITS>(xa, ms.x, ms.y), code_bit(BITS, 0, x));
-            wb |= place_twice<BITS>(quant_code_twice<BITS>(xb, ms.x, ms.y), code_bit(BITS, 0, x));
+              for (int i = 0; i < 4; ++i) {
+                const uint32_t x = w[2 * R + s][i];
+                const int at = 16 * s + 8 * (i & 1);
+                acc[R][i >> 1] |= (code4(low_less(x, q[s].mn), q[s]) << at) | (code4(high_less(x, q[s].mn), q[s]) << (at + 4));
+              }
+          };
+          codes(std::integral_constant<int, 0>{});
+          codes(std::integral_constant<int, 1>{});
+          codes(std::integral_constant<int, 2>{});
+          codes(std::integral_constant<int, 3>{});
+        } else {
+#pragma unroll 1
+          for (int i = 0; i < 8; ++i) {
+            const int r = i >> 1, s = i & 1, from = (lane & ~3) | r;
+            const float m = __shfl(s ? mn1 : mn0, from), h = __shfl(s ? h1 : h0, from);
+            const u32x4 x = row(r, s);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const uint32_t c = code4_compared(k & 1 ? hi_half(x[k >> 1]) : lo_half(x[k >> 1]), m, h) << (16 * s + 4 * (k & 3));
+#pragma unroll
+              for (int b = 0; b < 4; ++b) acc[b][k >> 2] |= b == r ? c : 0u;
+            }
           }
         }
-        if (BITS == 2) {                                // fields 2 q and 2 q + 1: word q of the packed lane, the odd field 8 bits up
-          put_away<ONCE>(wa | rotl32(wb, 8), (uint32_t*)(vb + 16 * (16 * r + n)) + q);
-        } else {                                        // words 2 (q & 1), 2 (q & 1) + 1 of half q >> 1
-          typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-          put_away<ONCE>(u32x2{wa, wb}, (u32x2*)(vb + 1024 * (q >> 1) + 16 * (16 * r + n) + 8 * (q & 1)));
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          uint32_t x0 = acc[0][a], x1 = acc[1][a], x2 = acc[2][a], x3 = acc[3][a];
+          trade_rows(x0, x1, x2, x3);                  // row t4 gets r = t4, register i the tokens that row i had
+          // registers against channels: register i the codes of channel 4 a + i, numbered 4 s + t4: a word, but for its turn
+          trade_fields(x0, x1, 0x0F0F0F0Fu, 4);
+          trade_fields(x2, x3, 0x0F0F0F0Fu, 4);
+          trade_fields(x0, x2, 0x00FF00FFu, 8);
+          trade_fields(x1, x3, 0x00FF00FFu, 8);
+          // Registers against bits 1 and 2 of the lane, which with bit 3 number the field: a lane gets the four words of
+          // its 16 bytes.
+          const bool up = lane & 2;
+          auto swap1 = [&](uint32_t& p, uint32_t& q) {
+            const uint32_t got = row_partner_u32<1>(up ? p : q);
+            p = up ? got : p;
+            q = up ? q : got;
+          };
+          swap1(x0, x1);
+          swap1(x2, x3);
+          auto swap2 = [&](uint32_t& p, uint32_t& q) {
+            const uint32_t was = p;
+            p = from_bank<3, 4>(from_bank<1, 4>(p, q), q);
+            q = from_bank<2, 12>(from_bank<0, 12>(q, was), was);
+          };
+          swap2(x0, x2);
+          swap2(x1, x3);
+          put_away<ONCE>(u32x4{rotl32(x0, 2), rotl32(x1, 2), rotl32(x2, 2), rotl32(x3, 2)},
+                         (u32x4*)(vb + 1024 * (c16 >> 3) + 16 * (16 * t4 + 8 * (lane & 1) + 4 * a + ((lane >> 1) & 3))));
         }
+      } else {
+        const Thresholds2 th = thresholds2(mn0, h0, mn1, h1);
+        uint32_t acc[4] = {0, 0, 0, 0};                // r: code 8 s + 4 (channel & 1) + channel pair of the lane's four
+        if (finite) {                                  // uniform
+          auto codes = [&](auto r_c) {
+            constexpr int R = decltype(r_c)::value;
+            h2 n[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) n[k] = as_h2(of_quad_lane<R>(as_u32(th.neg[k])));
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              gather2<true>(acc[R], codes2(w[2 * R][i], h2{n[0][0], n[0][0]}, h2{n[1][0], n[1][0]}, h2{n[2][0], n[2][0]}),
+                            codes2(w[2 * R + 1][i], h2{n[0][1], n[0][1]}, h2{n[1][1], n[1][1]}, h2{n[2][1], n[2][1]}), i);
+          };
+          codes(std::integral_constant<int, 0>{});
+          codes(std::integral_constant<int, 1>{});
+          codes(std::integral_constant<int, 2>{});
+          codes(std::integral_constant<int, 3>{});
+        } else {
+#pragma unroll 1
+          for (int r = 0; r < 4; ++r) {
+            const int from = (lane & ~3) | r;
+            const float m0 = __shfl(mn0, from), m1 = __shfl(mn1, from), g0 = __shfl(h0, from), g1 = __shfl(h1, from);
+            const u32x4 x0 = row(r, 0), x1 = row(r, 1);
+            uint32_t a = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              gather2<true>(a, codes2_compared(x0[i], m0, g0, m0, g0), codes2_compared(x1[i], m1, g1, m1, g1), i);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] = k == r ? a : acc[k];
+          }
+        }
+        // row t4 of 16 lanes gets r = t4, register i the tokens that row i had
+        trade_rows(acc[0], acc[1], acc[2], acc[3]);
+        // registers against channel pairs: register i the codes of pair i, numbered 8 s + 4 (channel & 1) + t4
+        trade_fields(acc[0], acc[1], 0x33333333u, 2);
+        trade_fields(acc[2], acc[3], 0x33333333u, 2);
+        trade_fields(acc[0], acc[2], 0x0F0F0F0Fu, 4);
+        trade_fields(acc[1], acc[3], 0x0F0F0F0Fu, 4);
+        // Bit 1 of the lane, which tells channels c and c + 16 apart, against the parity of the channel: a word of both.
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = rotl32(trade2<2>(acc[i], row_partner_u32<1>(acc[i]), lane & 2), 2);
+        // Registers against the lanes' banks of four, so that a lane has the four words of its 16 bytes: bank b passes its
+        // register k to bank k, register b.
+        u32x4 words = {acc[0], acc[1], acc[2], acc[3]};
+        words[0] = from_bank<1, 4>(words[0], acc[1]), words[0] = from_bank<2, 8>(words[0], acc[2]), words[0] = from_bank<3, 12>(words[0], acc[3]);
+        words[1] = from_bank<0, 12>(words[1], acc[0]), words[1] = from_bank<2, 4>(words[1], acc[2]), words[1] = from_bank<3, 8>(words[1], acc[3]);
+        words[2] = from_bank<0, 8>(words[2], acc[0]), words[2] = from_bank<1, 12>(words[2], acc[1]), words[2] = from_bank<3, 4>(words[2], acc[3]);
+        words[3] = from_bank<0, 4>(words[3], acc[0]), words[3] = from_bank<1, 8>(words[3], acc[1]), words[3] = from_bank<2, 12>(words[3], acc[2]);
+        // lane: row r = t4, bank k = channel pair, bit 1 the parity of the channel, bit 0 the channel's bit 3
+        put_away<ONCE>(words, (u32x4*)(vb + 16 * (16 * t4 + 8 * (lane & 1) + 2 * (c16 >> 2) + ((lane >> 1) & 1))));
       }
     }
   };
-  if (any) values(std::true_type{});
+  if (any_flag()) values(std::true_type{});
   else values(std::false_type{});
 }
 

@@ -56,7 +56,7 @@ def test_kernels_of_one_layer_take_the_pointers_of_one():
 
 @pytest.mark.parametrize("kernel,instances,bytes_of_scratch", [
     ("15quantize_kernelILi", 6, lambda name: 0),
-    ("22prompt_quantize_kernelILi", 6, lambda name: 12 if "ILi4ELi32E" in name else 0),   # (two registers too many)
+    ("22prompt_quantize_kernelILi", 6, lambda name: 0),
     ("24prompt_candidates_kernelILi", 3, lambda name: 0),
     ("21prompt_compete_kernelILi", 12, lambda name: 0),
 ])

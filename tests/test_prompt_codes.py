@@ -1,0 +1,73 @@
+"""Codes, steps and zeros of a prompt of many groups where rounding decides: the kernel that takes many groups turns the
+thresholds of a group into fp16 values (2-bit) or multiplies by a reciprocal (4-bit); the kernel that takes few compares
+in fp32, as the definition does.  Both are given the same rows."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def hard_rows(seed, batch, heads, n, group, value_group, bits, non_finite):
+    """fp16 [batch, heads, n, 128] twice: each (group of tokens, channel) of the Keys and each (token, group of channels) of
+    the Values one of the kinds below, of very different magnitudes."""
+    rng = np.random.default_rng(seed)
+    levels = 2 ** bits - 1
+    f16 = np.float16
+
+    def groups(count, size):
+        step = f16(rng.random((count, 1)) * 2.0 ** rng.integers(-24, 12, (count, 1)) + 2.0 ** -24).astype(np.float64)
+        kind = rng.integers(0, 9, (count, 1))
+        half = rng.integers(0, 2 * levels + 1, (count, size)) * step / 2          # ties: odd multiples of step / 2
+        nudge = rng.integers(-1, 2, (count, size))
+        near = np.nextafter(f16(half), f16(1e4) * nudge.astype(f16)).astype(np.float64)
+        tiny = rng.integers(-3, 4, (count, size)) * 2.0 ** -24
+        lo = -(2 * rng.integers(1, levels + 1, (count, 1)) - 1) * step / 2        # a threshold at (about) zero
+        across = np.where(rng.random((count, size)) < 0.6, tiny, lo + rng.integers(0, levels + 1, (count, size)) * step)
+        normal = rng.standard_normal((count, size)) * step
+        offset = 16.0 * step * rng.integers(1, 2000, (count, 1)) + normal
+        zeros = np.where(rng.random((count, size)) < 0.5, -0.0, 0.0)
+        constant = np.broadcast_to(step, (count, size))
+        wide = rng.choice([-65504.0, 65504.0, 1.0, 2.0 ** -24, -0.0], (count, size))
+        x = np.select([kind == k for k in range(9)],
+                      [half, near, -half, across, np.where(rng.random((count, size)) < 0.1, lo, across), normal, offset,
+                       np.where(kind % 2, zeros, np.where(rng.random((count, 1)) < 0.5, zeros, constant)), wide])
+        if non_finite:
+            hit = (rng.random((count, 1)) < 0.02) & (rng.random((count, size)) < 0.1)
+            x = np.where(hit, rng.choice([np.inf, -np.inf, np.nan], (count, size)), x)
+        with np.errstate(over="ignore"):
+            return np.clip(f16(x), f16(-65504), f16(65504)) if not non_finite else f16(x)
+
+    units = batch * heads
+    k = groups(units * (n // group) * 128, group).reshape(units, n // group, 128, group).transpose(0, 1, 3, 2)
+    v = groups(units * n * (128 // value_group), value_group)
+    return (np.ascontiguousarray(k).reshape(batch, heads, n, 128), v.reshape(batch, heads, n, 128))
+
+
+@pytest.mark.parametrize("non_finite", [False, True])
+@pytest.mark.parametrize("budget", [0, 5])
+@pytest.mark.parametrize("bits,group,value_group", [(2, 32, 32), (2, 64, 64), (2, 128, 128), (4, 32, 64), (4, 64, 128), (4, 128, 32)])
+def test_many_groups_give_the_bytes_of_few(bits, group, value_group, budget, non_finite):
+    import torch
+    from paper_2505_10938_amd import cache as KC
+    if non_finite and budget:
+        pytest.skip("scores that are no numbers are not supported")
+    batch, heads, n = 32, 4, 8 * group                        # 1024 groups in one call, 32 in each of the others
+    k, v = (torch.from_numpy(x).cuda() for x in hard_rows(bits * group + value_group, batch, heads, n, group, value_group, bits, non_finite))
+    if budget:                                                # (scores are exact up to a sum of 2^23; tracing is not the point)
+        k = k.clamp(-3e4, 3e4)
+
+    def contents(b):
+        cache = KC.KVCache(KC.make_config(1, b, heads, heads, n, bits, group, value_group, 0, budget, 32 if budget else 0, 128))
+        return cache, lambda: [t.cpu() for t in (cache.k_codes, cache.k_meta, cache.v_codes, cache.v_meta, cache.mask)]
+
+    many, got = contents(batch)
+    many.prefill(0, k, v)
+    got = got()
+    parts = []
+    for b in range(batch):
+        few, one = contents(1)
+        few.prefill(0, k[b:b + 1].contiguous(), v[b:b + 1].contiguous())
+        parts.append(one())
+    for name, whole, of in zip(("k_codes", "k_meta", "v_codes", "v_meta", "mask"), got, zip(*parts)):
+        want = torch.cat([t.flatten().view(torch.uint8) for t in of])
+        assert torch.equal(whole.flatten().view(torch.uint8)[:want.numel()], want), name
