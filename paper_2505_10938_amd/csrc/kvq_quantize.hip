@@ -84,13 +84,11 @@ __device__ inline float lo_half(uint32_t w) { return __half2float(__ushort_as_ha
 __device__ inline float hi_half(uint32_t w) { return __half2float(__ushort_as_half((unsigned short)(w >> 16))); }
 
 constexpr int kQuantThreads = 1024;
-// From this many groups in one launch on, prompt_quantize_kernel takes them: soon after quantize_kernel's
-// workgroups, of which 512 are resident, need a second round.  A prompt's whole call (selection included) with
-// quantize_kernel / prompt_quantize_kernel: G = 32, 2-bit, 512 / 768 / 960 groups 18.9 / 18.5, 22.3 / 19.4, 24.4 /
-// 20.5 us; 4-bit, 512 / 768 groups 19.3 / 20.5, 22.5 / 21.0; G = 64, 512 / 768 groups 22.6 / 24.0, 30.8 / 28.1, 4-bit,
-// 640 groups 31.7 / 31.1 us.  With G = 128 (four blocks per group, which a wavefront of prompt_quantize_kernel takes
-// one after the other) 640 groups were 29.3 / 30.3 us, the launch alone.
-constexpr int64_t prompt_groups(int G) { return G < 128 ? 768 : 1024; }
+// From this many groups in one launch on, prompt_quantize_kernel takes them.  Whole calls of a prompt, quantize_kernel /
+// prompt_quantize_kernel, 2-bit (4-bit alike): G = 32, 64 / 192 / 384 / 640 groups 23.0 / 22.9, 22.2 / 22.5, 21.0 / 20.6, 26.1 / 22.4 us;
+// G = 64, 16 / 64 / 384 / 640 22.1 / 22.6, 22.4 / 22.0, 24.9 / 21.2, 39.9 / 33.5; G = 128, 4 / 32 / 256 / 640 22.8 / 22.5, 28.8 / 24.2,
+// 28.3 / 23.0, 52.0 / 39.0 (1024 threads keep a group of 128 tokens longest, and one workgroup of them fills half a compute unit).
+constexpr int64_t prompt_groups(int G) { return G == 32 ? 256 : G == 64 ? 32 : 1; }
 
 // Minimum and maximum over groups of `n` adjacent lanes (n = 4, 8 or 16).
 __device__ inline void team_minmax(float& mn, float& mx, int n) {
@@ -364,11 +362,11 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
   quantize_body<BITS, G>(d, at.row, at.slot, L, flag, k_codes, k_meta, v_codes, v_meta, mask, tid);
 }
 
-// ---- many groups per launch (a prompt): one workgroup of two wavefronts per group -------------------------
+// ---- many groups per launch (a prompt): one workgroup per group, two wavefronts per block of 32 tokens ----
 // The kernel above spreads one group over 1024 threads because a decode step waits for it.  A prompt has
-// thousands of groups, and what counts is the instructions spent per group.  Here wavefront 0 quantizes the
-// group's Keys and wavefront 1 its Values, each with a lane-to-element mapping in which the packed words fall
-// out of the lanes that computed the codes:
+// thousands of groups, and what counts is the instructions spent per group.  Here one wavefront quantizes a block's
+// Keys and one its Values, each with a lane-to-element mapping in which the packed words fall out of the lanes that
+// computed the codes:
 //   Keys:   a lane owns one channel pair for all tokens, so minimum and maximum over the tokens are packed
 //           fp16 operations inside the lane (exact: they only select).  It gathers its codes of 8 (2-bit) or
 //           4 (4-bit) tokens in one register; the 8 (4) lanes that share a packed word trade fields of it, 3 (2)
@@ -377,11 +375,14 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
 //           a quad on the packed pair {min, -max} so that each of its lanes ends up with two tokens, whose step, zero
 //           and thresholds it works out for the quad.  Codes become words by trades between lanes and between
 //           registers, and a lane stores 16 bytes.
-// Nothing goes through LDS.  What bounds it: the rows and codes on their way (256 units x 4096 tokens, 2-bit: 637 MB in
-// about 97 us, 6.5 TB/s, the Keys in part from the memory-side cache).  When every code was decided by fp32 comparisons, gathered
-// by an OR over the lanes token by token and the Values turned through LDS, it was the instructions, 1900 per group
-// of 32 where there are now about 900; whole calls, three sets of rows in turn: 183 -> 159 us, 4-bit 232 -> 175, G = 128 with 4 bits 246 -> 225; a joining prompt of 8191
-// tokens, 8 kv heads, 4 layers 59 -> 52 us.
+// No row goes through LDS, and each is read once: the blocks of a longer group exchange minimum, maximum and, where a
+// token is flagged, sums.  What bounds it: the rows and codes on their way (256 units x 4096 tokens, 2-bit: 637 MB in
+// 90 us, 7 TB/s, the Keys in part from the memory-side cache).  When every code was decided by fp32 comparisons, gathered by
+// an OR over the lanes token by token and the Values turned through LDS, it was the instructions, 1900 per block where
+// there are now about 900; when one wavefront took the blocks of a group one after the other, a second read of the Keys.
+// Whole calls, three sets of rows in turn, before all that / with the blocks one after the other / now: G = 32 183 / 161 /
+// 158 us, 4-bit 232 / 175 / 178; G = 64 187 / 167 / 159; G = 128 217 / 213 / 184, 4-bit 246 / 226 / 190.  A joining prompt of
+// 8191 tokens, 8 kv heads, 4 layers: G = 32 59 / 52 / 51.5, G = 128 - / 74 / 62.
 // Results are those of quantize_body bit for bit (same roundings in the same order; minimum, maximum and
 // the exact fp64 sums do not depend on the order they are taken in).
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -536,19 +537,23 @@ __device__ __forceinline__ uint32_t of_quad_lane(uint32_t v) {
 }
 
 template <int BITS, int G, int LAYERS, bool ONCE>
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))) prompt_quantize_kernel(
+__global__ void __launch_bounds__(4 * G) __attribute__((amdgpu_waves_per_eu(4, 8))) prompt_quantize_kernel(
     Dims d, int32_t group_index, int64_t unit_stride, const uint8_t* __restrict__ selected, int64_t selected_unit_stride,
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta, uint8_t* __restrict__ v_codes,
     uint32_t* __restrict__ v_meta, uint32_t* __restrict__ mask, int32_t n_groups, int32_t tail_n,
     __half* __restrict__ k_res, __half* __restrict__ v_res, int32_t last_first, LayerRows<LAYERS> rows) {
-  // grid (units, groups + tail blocks, layers), as quantize_kernel's
+  // grid (units, groups + tail blocks, layers), as quantize_kernel's.  Wavefronts 0 .. nblk - 1 have the Keys of a block of 32
+  // tokens each, the others the Values.
+  constexpr int nblk = G / kBlockTokens, kThreads = 128 * nblk;
+  __shared__ uint2 s_extremes[nblk][64];               // what the blocks of a longer group tell each other: minimum and
+  __shared__ __align__(16) double s_sums[nblk > 1 ? 2 : 1][nblk > 1 ? nblk : 1][kHeadDim];   // maximum of the Keys, sums of both (for means)
   const int tid = threadIdx.x;
   const int ul = blockIdx.x, by = blockIdx.y, layer = LAYERS > 1 ? blockIdx.z : 0;
   const __half* __restrict__ k_rows = rows.k[layer];
   const __half* __restrict__ v_rows = rows.v[layer];
   const int gy = last_first && by < n_groups ? n_groups - 1 - by : by;
   if (gy >= n_groups) {
-    const int i = (gy - n_groups) * 128 + tid;
+    const int i = (gy - n_groups) * kThreads + tid;
     if (i < tail_n * 16) {
       const int64_t src = (int64_t)ul * unit_stride + (int64_t)n_groups * G * kHeadDim;
       const int64_t dst = (d.unit0 + (int64_t)layer * d.layer_units + ul) * d.res_rows * kHeadDim;
@@ -559,14 +564,12 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int blk = nblk == 1 ? 0 : wave & (nblk - 1);
   const int64_t row0 = (int64_t)ul * unit_stride + (int64_t)gy * G * kHeadDim;
   const int64_t sel0 = ((int64_t)layer * d.units_per_layer + ul) * selected_unit_stride + (int64_t)gy * G;
   const GroupPlace at = place_of_group(d, ul, group_index + gy, layer);
-  constexpr int nblk = G / kBlockTokens;
   const int64_t block0 = at.row * d.blocks_per_unit + (int64_t)at.slot * nblk;   // the group's first packed block
-  // The flags of the group's tokens, as bit masks (uniform).  The rows are asked for while they come where registers allow
-  // it (in the other instances they would have to be put away into scratch memory).
-  constexpr bool kAhead = BITS == 2 && G == 32;
+  // The flags of the group's tokens, as bit masks (uniform).  The rows are asked for while they come.
   constexpr int kSelWords = (G + 63) / 64;
   unsigned long long sel[kSelWords];
   uint8_t flags[kSelWords];
@@ -583,7 +586,13 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
   auto is_sel = [&](int t) -> bool { return (sel[kSelWords == 1 ? 0 : t >> 6] >> (t & 63)) & 1ull; };
 
-  if (wave == 0) {
+  auto exchange = [&]() {                              // of the blocks of a longer group: one barrier per wavefront
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  };
+
+  if (wave < nblk) {
     // ---- Keys ------------------------------------------------------------------------------------------
     int cp, r, hi = 0, p = 0, cb = 0, v = lane & 3;    // cp: the lane's channel pair (channels 2 cp, 2 cp + 1)
     if (BITS == 2) {
@@ -595,14 +604,8 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
     }
     const uint32_t* kr = (const uint32_t*)(k_rows + row0) + cp;        // token t: kr[64 t]
     uint32_t y[32];
-    auto load_rows = [&](int blk, auto last_c) {
 #pragma unroll
-      for (int t = 0; t < 32; ++t) {                   // (longer groups are read a second time for the codes)
-        if constexpr (decltype(last_c)::value) y[t] = last_load<ONCE>(kr + (blk * 32 + t) * 64);
-        else y[t] = kr[(blk * 32 + t) * 64];
-      }
-    };
-    if (kAhead) load_rows(0, std::bool_constant<nblk == 1>{});
+    for (int t = 0; t < 32; ++t) y[t] = last_load<ONCE>(kr + (blk * 32 + t) * 64);
     auto keys = [&](auto any_c) {
       constexpr bool ANY = decltype(any_c)::value;     // some token of the group is flagged (uniform)
       double s0 = 0.0, s1 = 0.0;
@@ -611,28 +614,43 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
       // (a NaN among the rows is found out by its being the result; where it is passed over comes below)
       auto lower = [](h2 a, h2 b) { return __builtin_elementwise_minimum(a, b); };
       auto upper = [](h2 a, h2 b) { return __builtin_elementwise_maximum(a, b); };
-#pragma unroll 1
-      for (int blk = 0; blk < nblk; ++blk) {
-        if (!kAhead || blk > 0) load_rows(blk, std::bool_constant<nblk == 1>{});
 #pragma unroll
-        for (int t = 0; t < 32; ++t) {
-          const h2 x = as_h2(y[t]);
-          if (ANY) {
-            const bool s = is_sel(blk * 32 + t);
-            mn = s ? mn : lower(mn, x);
-            mx = s ? mx : upper(mx, x);
-          } else {
-            mn = lower(mn, x);
-            mx = upper(mx, x);
-          }
+      for (int t = 0; t < 32; ++t) {
+        const h2 x = as_h2(y[t]);
+        if (ANY) {
+          const bool s = is_sel(blk * 32 + t);
+          mn = s ? mn : lower(mn, x);
+          mx = s ? mx : upper(mx, x);
+        } else {
+          mn = lower(mn, x);
+          mx = upper(mx, x);
         }
-        if (ANY) {                                     // the exact sums of ALL rows as they came (two chains of
+      }
+      if (ANY) {                                       // the exact sums of ALL rows as they came (two chains of
 #pragma unroll                                         // dependent additions: few conversions in flight at a time)
-          for (int t = 0; t < 32; ++t) {
-            s0 += (double)lo_half(y[t]);
-            asm volatile("" : "+v"(s0));
-            s1 += (double)hi_half(y[t]);
-            asm volatile("" : "+v"(s1));
+        for (int t = 0; t < 32; ++t) {
+          uint32_t x = y[t];
+          asm volatile("" : "+v"(x), "+v"(s0), "+v"(s1));
+          s0 += (double)lo_half(x);
+          s1 += (double)hi_half(x);
+        }
+      }
+      if constexpr (nblk > 1) {
+        s_extremes[blk][lane] = make_uint2(as_u32(mn), as_u32(mx));
+        if (ANY) {
+          s_sums[0][blk][lane] = s0;
+          s_sums[0][blk][64 + lane] = s1;
+        }
+        exchange();
+        if (ANY) s0 = s1 = 0.0;
+#pragma unroll
+        for (int k = 0; k < nblk; ++k) {
+          const uint2 e = s_extremes[k][lane];
+          mn = lower(mn, as_h2(e.x));
+          mx = upper(mx, as_h2(e.y));
+          if (ANY) {
+            s0 += s_sums[0][k][lane];
+            s1 += s_sums[0][k][64 + lane];
           }
         }
       }
@@ -657,7 +675,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
       const float mn0 = (float)mn[0] + 0.0f, mn1 = (float)mn[1] + 0.0f;   // a zero minimum is stored as +0
       const __half st0 = step_of(mn0, (float)mx[0], BITS), st1 = step_of(mn1, (float)mx[1], BITS);
       const float h0 = half_step_of(st0), h1 = half_step_of(st1);
-      {
+      if (blk == 0) {
         uint32_t* gm = k_meta + (at.row * d.groups_per_unit + at.slot) * kHeadDim;   // fp16 step[128], then zero[128]
         gm[cp] = (uint32_t)__half_as_ushort(st0) | ((uint32_t)__half_as_ushort(st1) << 16);
         gm[64 + cp] = half_bits(mn0) | (half_bits(mn1) << 16);
@@ -680,75 +698,71 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
           acc = trade2<2>(acc, row_partner_u32<1>(acc), v & 2);
           return rotl32(acc, 2);
         } else {
-        uint32_t acc = 0;                              // code 8 * channel of the pair + token
+          uint32_t acc = 0;                            // code 8 * channel of the pair + token
 #pragma unroll
-        for (int i = 0; i < 4; ++i) gather2<false>(acc, code(i), code(4 + i), i);
-        acc = trade2<0>(acc, row_partner_u32<0>(acc), v & 1);
-        acc = trade2<1>(acc, row_partner_u32<1>(acc), v & 2);
-        acc = trade2<2>(acc, row_partner_u32<2>(acc), p);
-        return rotl32(acc, 2);
+          for (int i = 0; i < 4; ++i) gather2<false>(acc, code(i), code(4 + i), i);
+          acc = trade2<0>(acc, row_partner_u32<0>(acc), v & 1);
+          acc = trade2<1>(acc, row_partner_u32<1>(acc), v & 2);
+          acc = trade2<2>(acc, row_partner_u32<2>(acc), p);
+          return rotl32(acc, 2);
         }
       };
-#pragma unroll 1
-      for (int blk = 0; blk < nblk; ++blk) {
-        if (nblk > 1) load_rows(blk, std::true_type{});
-        uint8_t* kb = k_codes + (block0 + blk) * (int64_t)d.block_bytes;
-        if (ANY) {                                     // the flagged rows become the mean row
+      uint8_t* kb = k_codes + (block0 + blk) * (int64_t)d.block_bytes;
+      if (ANY) {                                     // the flagged rows become the mean row
 #pragma unroll
-          for (int t = 0; t < 32; ++t) y[t] = is_sel(blk * 32 + t) ? mean : y[t];
-        }
-        if constexpr (BITS == 2) {
-          if (finite) {                                // uniform
-            uint32_t word[4];
+        for (int t = 0; t < 32; ++t) y[t] = is_sel(blk * 32 + t) ? mean : y[t];
+      }
+      if constexpr (BITS == 2) {
+        if (finite) {                                // uniform
+          uint32_t word[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              word[b] = word_of([&](int t) { return codes2(y[8 * b + t], th.neg[0], th.neg[1], th.neg[2]); });
-            }
-            // the two words of a token and half (tokens 0 .. 15, 16 .. 31) to one lane
+          for (int b = 0; b < 4; ++b) {
+            word[b] = word_of([&](int t) { return codes2(y[8 * b + t], th.neg[0], th.neg[1], th.neg[2]); });
+          }
+          // the two words of a token and half (tokens 0 .. 15, 16 .. 31) to one lane
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-              typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-              const auto sw = __builtin_amdgcn_permlane32_swap(word[b], word[2 + b], false, false);
-              put_away<ONCE>(u32x2{sw[0], sw[1]}, (u32x2*)(kb + 16 * (16 * r + 8 * b + 4 * p + v) + 8 * hi));
-            }
-          } else {
-#pragma unroll 1
-            for (int b = 0; b < 4; ++b) {
-              const uint32_t w = word_of([&](int t) { return codes2_compared(row(blk * 32 + 8 * b + t), mn0, h0, mn1, h1); });
-              *(uint32_t*)(kb + 16 * (16 * r + 8 * (b & 1) + 4 * p + v) + 4 * (2 * (b >> 1) + hi)) = w;
-            }
+          for (int b = 0; b < 2; ++b) {
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            const auto sw = __builtin_amdgcn_permlane32_swap(word[b], word[2 + b], false, false);
+            put_away<ONCE>(u32x2{sw[0], sw[1]}, (u32x2*)(kb + 16 * (16 * r + 8 * b + 4 * p + v) + 8 * hi));
           }
         } else {
-          if (finite) {                                // uniform
-#pragma unroll
-            for (int th16 = 0; th16 < 2; ++th16) {     // tokens 0 .. 15, 16 .. 31
-              uint32_t word[4];
-#pragma unroll
-              for (int b = 0; b < 4; ++b)
-                word[b] = word_of([&](int t) {
-                  const uint32_t x = y[16 * th16 + 4 * b + t];
-                  return make_uint2(code4(low_less(x, sc0.mn), sc0), code4(high_less(x, sc1.mn), sc1));
-                });
-              // row i of lanes gets the words of tokens 4 i + v, all four of a token
-              trade_rows(word[0], word[1], word[2], word[3]);
-              put_away<ONCE>(u32x4{word[0], word[1], word[2], word[3]},
-                             (u32x4*)(kb + 1024 * th16 + 16 * (16 * r + 4 * cb + v)));
-            }
-          } else {
 #pragma unroll 1
-            for (int b = 0; b < 8; ++b) {
-              const uint32_t w = word_of([&](int t) {
-                const uint32_t x = row(blk * 32 + 4 * b + t);
-                return make_uint2(code4_compared(lo_half(x), mn0, h0), code4_compared(hi_half(x), mn1, h1));
-              });
-              *(uint32_t*)(kb + 1024 * (b >> 2) + 16 * (16 * r + 4 * (b & 3) + v) + 4 * cb) = w;
-            }
+          for (int b = 0; b < 4; ++b) {
+            const uint32_t w = word_of([&](int t) { return codes2_compared(row(blk * 32 + 8 * b + t), mn0, h0, mn1, h1); });
+            *(uint32_t*)(kb + 16 * (16 * r + 8 * (b & 1) + 4 * p + v) + 4 * (2 * (b >> 1) + hi)) = w;
           }
         }
-        if (lane == 0) {
-          const uint32_t mw = (uint32_t)(sel[kSelWords == 1 ? 0 : (blk * 32) >> 6] >> ((blk * 32) & 63));
-          mask[block0 + blk] = mw;
+      } else {
+        if (finite) {                                // uniform
+#pragma unroll
+          for (int th16 = 0; th16 < 2; ++th16) {     // tokens 0 .. 15, 16 .. 31
+            uint32_t word[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              word[b] = word_of([&](int t) {
+                const uint32_t x = y[16 * th16 + 4 * b + t];
+                return make_uint2(code4(low_less(x, sc0.mn), sc0), code4(high_less(x, sc1.mn), sc1));
+              });
+            // row i of lanes gets the words of tokens 4 i + v, all four of a token
+            trade_rows(word[0], word[1], word[2], word[3]);
+            put_away<ONCE>(u32x4{word[0], word[1], word[2], word[3]},
+                           (u32x4*)(kb + 1024 * th16 + 16 * (16 * r + 4 * cb + v)));
+          }
+        } else {
+#pragma unroll 1
+          for (int b = 0; b < 8; ++b) {
+            const uint32_t w = word_of([&](int t) {
+              const uint32_t x = row(blk * 32 + 4 * b + t);
+              return make_uint2(code4_compared(lo_half(x), mn0, h0), code4_compared(hi_half(x), mn1, h1));
+            });
+            *(uint32_t*)(kb + 1024 * (b >> 2) + 16 * (16 * r + 4 * (b & 3) + v) + 4 * cb) = w;
+          }
         }
+      }
+      if (lane == 0) {
+        const uint32_t mw = (uint32_t)(sel[kSelWords == 1 ? 0 : (blk * 32) >> 6] >> ((blk * 32) & 63));
+        mask[block0 + blk] = mw;
       }
     };
     if (any_flag()) keys(std::true_type{});
@@ -763,227 +777,234 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4, 8))
   const int t4 = lane >> 4, c16 = lane & 15;            // the lane's channels are 8 c16 .. + 7, its tokens 8 r + 2 t4 + s
   const __half* vr = v_rows + row0 + 8 * c16;
   u32x4 w[8];
-  auto load_rows = [&](int blk) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      // row i = 2 r + s: the lane's tokens come in pairs, as steps and zeros are stored
-      w[i] = last_load<ONCE>((const u32x4*)(vr + (blk * 32 + 8 * (i >> 1) + 2 * t4 + (i & 1)) * kHeadDim));
-    }
-  };
-  if (kAhead) load_rows(0);
+  for (int i = 0; i < 8; ++i) {                         // row i = 2 r + s: the lane's tokens come in pairs, as steps and zeros are stored
+    w[i] = last_load<ONCE>((const u32x4*)(vr + (blk * 32 + 8 * (i >> 1) + 2 * t4 + (i & 1)) * kHeadDim));
+  }
   auto values = [&](auto any_c) {
     constexpr bool ANY = decltype(any_c)::value;
     uint32_t mean4[4] = {0u, 0u, 0u, 0u};
     if (ANY) {                                          // per-channel means of the group's Value rows, exact
-      double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll 4
-      for (int t = t4; t < G; t += 4) {
-        const uint4 w = *(const uint4*)(vr + t * kHeadDim);
-        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {                     // (a channel pair at a time: few registers)
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          uint32_t x = w[i][k];
+          asm volatile("" : "+v"(x), "+v"(a), "+v"(b));
+          a += (double)lo_half(x);
+          b += (double)hi_half(x);
+        }
+        a += __shfl_xor(a, 16);
+        b += __shfl_xor(b, 16);
+        a += __shfl_xor(a, 32);
+        b += __shfl_xor(b, 32);
+        if constexpr (nblk == 1) mean4[k] = mean_half_bits(a, G) | (mean_half_bits(b, G) << 16);
+        else if (t4 == 0) *(double2*)&s_sums[1][blk][8 * c16 + 2 * k] = make_double2(a, b);
+      }
+      if constexpr (nblk > 1) {
+        exchange();
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          acc[2 * k] += (double)lo_half(ww[k]);
-          acc[2 * k + 1] += (double)hi_half(ww[k]);
+          double a = 0.0, b = 0.0;
+#pragma unroll
+          for (int i = 0; i < nblk; ++i) {
+            const double2 part = *(const double2*)&s_sums[1][i][8 * c16 + 2 * k];
+            a += part.x;
+            b += part.y;
+          }
+          mean4[k] = mean_half_bits(a, G) | (mean_half_bits(b, G) << 16);
         }
       }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        acc[k] += __shfl_xor(acc[k], 16);
-        acc[k] += __shfl_xor(acc[k], 32);
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) mean4[k] = mean_half_bits(acc[2 * k], G) | (mean_half_bits(acc[2 * k + 1], G) << 16);
+    } else if (nblk > 1) {
+      __builtin_amdgcn_s_barrier();                     // (the Keys' exchange, of which the Values need nothing)
     }
-#pragma unroll 1
-    for (int blk = 0; blk < nblk; ++blk) {
-      if (!kAhead || blk > 0) load_rows(blk);
-      if (ANY) {
+    if (ANY) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int T = blk * 32 + 8 * (i >> 1) + 2 * t4 + (i & 1);
-          if ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull)
-            w[i] = u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
-        }
+      for (int i = 0; i < 8; ++i) {
+        const int T = blk * 32 + 8 * (i >> 1) + 2 * t4 + (i & 1);
+        if ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull)
+          w[i] = u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
       }
-      // {minimum, -maximum} of the rows in each channel group: lane `own` of a quad gets those of r = own, s = 0, 1.
-      // (A NaN is found out by its being the result; where it is passed over comes below.)
-      const int own = lane & 3;
-      auto channels = [](u32x4 x, auto lower, auto upper) {   // of one row's eight
-        const h2 a = lower(lower(as_h2(x.x), as_h2(x.y)), lower(as_h2(x.z), as_h2(x.w)));
-        const h2 b = upper(upper(as_h2(x.x), as_h2(x.y)), upper(as_h2(x.z), as_h2(x.w)));
-        const uint32_t nb = as_u32(b) ^ 0x80008000u;          // the halves against each other: {a0, -b0} and {a1, -b1}
-        return as_u32(lower(as_h2(__builtin_amdgcn_perm(nb, as_u32(a), 0x05040100u)),
-                            as_h2(__builtin_amdgcn_perm(nb, as_u32(a), 0x07060302u))));
+    }
+    // {minimum, -maximum} of the rows in each channel group: lane `own` of a quad gets those of r = own, s = 0, 1.
+    // (A NaN is found out by its being the result; where it is passed over comes below.)
+    const int own = lane & 3;
+    auto channels = [](u32x4 x, auto lower, auto upper) {   // of one row's eight
+      const h2 a = lower(lower(as_h2(x.x), as_h2(x.y)), lower(as_h2(x.z), as_h2(x.w)));
+      const h2 b = upper(upper(as_h2(x.x), as_h2(x.y)), upper(as_h2(x.z), as_h2(x.w)));
+      const uint32_t nb = as_u32(b) ^ 0x80008000u;          // the halves against each other: {a0, -b0} and {a1, -b1}
+      return as_u32(lower(as_h2(__builtin_amdgcn_perm(nb, as_u32(a), 0x05040100u)),
+                          as_h2(__builtin_amdgcn_perm(nb, as_u32(a), 0x07060302u))));
+    };
+    auto quads = [&](uint32_t x, auto lower) {              // of the quads of a channel group
+      if (lanes > 4) {                             // uniform; the lane with the same place in the next quad
+        const uint32_t mirror = row_partner_u32<2>(x);
+        x = as_u32(lower(as_h2(x), as_h2((uint32_t)__builtin_amdgcn_mov_dpp((int)mirror, 0x1B, 0xf, 0xf, false))));
+      }
+      if (lanes > 8) x = as_u32(lower(as_h2(x), as_h2((uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128 /* row_ror:8 */, 0xf, 0xf, false))));
+      return x;
+    };
+    h2 pair[2];
+    {
+      auto lower = [](h2 a, h2 b) { return __builtin_elementwise_minimum(a, b); };
+      auto upper = [](h2 a, h2 b) { return __builtin_elementwise_maximum(a, b); };
+      uint32_t pr[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pr[i] = channels(w[i], lower, upper);
+      auto fold = [&](uint32_t a, uint32_t b, bool up, auto bit_c) {   // lanes with the bit keep b, the others a
+        return as_u32(lower(as_h2(up ? b : a), as_h2(row_partner_u32<decltype(bit_c)::value>(up ? a : b))));
       };
-      auto quads = [&](uint32_t x, auto lower) {              // of the quads of a channel group
-        if (lanes > 4) {                             // uniform; the lane with the same place in the next quad
-          const uint32_t mirror = row_partner_u32<2>(x);
-          x = as_u32(lower(as_h2(x), as_h2((uint32_t)__builtin_amdgcn_mov_dpp((int)mirror, 0x1B, 0xf, 0xf, false))));
-        }
-        if (lanes > 8) x = as_u32(lower(as_h2(x), as_h2((uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128 /* row_ror:8 */, 0xf, 0xf, false))));
-        return x;
-      };
-      h2 pair[2];
-      {
-        auto lower = [](h2 a, h2 b) { return __builtin_elementwise_minimum(a, b); };
-        auto upper = [](h2 a, h2 b) { return __builtin_elementwise_maximum(a, b); };
-        uint32_t pr[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) pr[i] = channels(w[i], lower, upper);
-        auto fold = [&](uint32_t a, uint32_t b, bool up, auto bit_c) {   // lanes with the bit keep b, the others a
-          return as_u32(lower(as_h2(up ? b : a), as_h2(row_partner_u32<decltype(bit_c)::value>(up ? a : b))));
-        };
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          const uint32_t r01 = fold(pr[s], pr[2 + s], own & 1, std::integral_constant<int, 0>{});
-          const uint32_t r23 = fold(pr[4 + s], pr[6 + s], own & 1, std::integral_constant<int, 0>{});
-          pair[s] = as_h2(quads(fold(r01, r23, own & 2, std::integral_constant<int, 1>{}), lower));
-        }
+      for (int s = 0; s < 2; ++s) {
+        const uint32_t r01 = fold(pr[s], pr[2 + s], own & 1, std::integral_constant<int, 0>{});
+        const uint32_t r23 = fold(pr[4 + s], pr[6 + s], own & 1, std::integral_constant<int, 0>{});
+        pair[s] = as_h2(quads(fold(r01, r23, own & 2, std::integral_constant<int, 1>{}), lower));
       }
-      auto row = [&](int r, int s) -> u32x4 {
-        const int t = 8 * r + 2 * t4 + s, T = blk * 32 + t;
-        if (ANY && ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull)) return u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
-        return *(const u32x4*)(vr + T * kHeadDim);
-      };
-      const bool finite = __ballot(not_finite(pair[0]) | not_finite(pair[1])) == 0;
-      if (!finite) {
-        auto lower = [](h2 a, h2 b) { return __builtin_elementwise_min(a, b); };
-        auto upper = [](h2 a, h2 b) { return __builtin_elementwise_max(a, b); };
+    }
+    auto row = [&](int r, int s) -> u32x4 {
+      const int t = 8 * r + 2 * t4 + s, T = blk * 32 + t;
+      if (ANY && ((sel[kSelWords == 1 ? 0 : T >> 6] >> (T & 63)) & 1ull)) return u32x4{mean4[0], mean4[1], mean4[2], mean4[3]};
+      return *(const u32x4*)(vr + T * kHeadDim);
+    };
+    const bool finite = __ballot(not_finite(pair[0]) | not_finite(pair[1])) == 0;
+    if (!finite) {
+      auto lower = [](h2 a, h2 b) { return __builtin_elementwise_min(a, b); };
+      auto upper = [](h2 a, h2 b) { return __builtin_elementwise_max(a, b); };
 #pragma unroll 1
-        for (int i = 0; i < 8; ++i) {
-          uint32_t x = channels(row(i >> 1, i & 1), lower, upper);
-          x = as_u32(lower(as_h2(x), as_h2(row_partner_u32<0>(x))));
-          x = as_u32(lower(as_h2(x), as_h2(row_partner_u32<1>(x))));
-          x = quads(x, lower);
-          pair[0] = (i >> 1) == own && !(i & 1) ? as_h2(x) : pair[0];
-          pair[1] = (i >> 1) == own && (i & 1) ? as_h2(x) : pair[1];
-        }
+      for (int i = 0; i < 8; ++i) {
+        uint32_t x = channels(row(i >> 1, i & 1), lower, upper);
+        x = as_u32(lower(as_h2(x), as_h2(row_partner_u32<0>(x))));
+        x = as_u32(lower(as_h2(x), as_h2(row_partner_u32<1>(x))));
+        x = quads(x, lower);
+        pair[0] = (i >> 1) == own && !(i & 1) ? as_h2(x) : pair[0];
+        pair[1] = (i >> 1) == own && (i & 1) ? as_h2(x) : pair[1];
       }
-      const float mn0 = (float)pair[0][0] + 0.0f, mn1 = (float)pair[1][0] + 0.0f;   // a zero minimum is stored as +0
-      const __half st0 = step_of(mn0, -(float)pair[0][1], BITS), st1 = step_of(mn1, -(float)pair[1][1], BITS);
-      const float h0 = half_step_of(st0), h1 = half_step_of(st1);
-      if ((c16 & (lanes - 1)) < 4) {                 // fp16 step[16 token pairs][NV][2], then fp16 zero[16 token pairs][NV][2]
-        uint32_t* gm = v_meta + (block0 + blk) * 32 * NV + (4 * own + t4) * NV + ((8 * c16) >> gv_shift);
-        gm[0] = (uint32_t)__half_as_ushort(st0) | ((uint32_t)__half_as_ushort(st1) << 16);
-        gm[16 * NV] = half_bits(mn0) | (half_bits(mn1) << 16);
-      }
-      uint8_t* vb = v_codes + (block0 + blk) * (int64_t)d.block_bytes;
-      if constexpr (BITS == 4) {
-        uint32_t acc[4][2] = {};                       // r, half of the lane's channels: code 4 s + channel of the four
-        if (finite) {                                  // uniform
-          const Scale4 q0 = scale4(mn0, st0), q1 = scale4(mn1, st1);
-          auto codes = [&](auto r_c) {
-            constexpr int R = decltype(r_c)::value;
-            auto of_lane = [](float x) { return __uint_as_float(of_quad_lane<R>(__float_as_uint(x))); };
-            const Scale4 q[2] = {{of_lane(q0.mn), of_lane(q0.inv), of_lane(q0.step)}, {of_lane(q1.mn), of_lane(q1.inv), of_lane(q1.step)}};
+    }
+    const float mn0 = (float)pair[0][0] + 0.0f, mn1 = (float)pair[1][0] + 0.0f;   // a zero minimum is stored as +0
+    const __half st0 = step_of(mn0, -(float)pair[0][1], BITS), st1 = step_of(mn1, -(float)pair[1][1], BITS);
+    const float h0 = half_step_of(st0), h1 = half_step_of(st1);
+    if ((c16 & (lanes - 1)) < 4) {                 // fp16 step[16 token pairs][NV][2], then fp16 zero[16 token pairs][NV][2]
+      uint32_t* gm = v_meta + (block0 + blk) * 32 * NV + (4 * own + t4) * NV + ((8 * c16) >> gv_shift);
+      gm[0] = (uint32_t)__half_as_ushort(st0) | ((uint32_t)__half_as_ushort(st1) << 16);
+      gm[16 * NV] = half_bits(mn0) | (half_bits(mn1) << 16);
+    }
+    uint8_t* vb = v_codes + (block0 + blk) * (int64_t)d.block_bytes;
+    if constexpr (BITS == 4) {
+      uint32_t acc[4][2] = {};                       // r, half of the lane's channels: code 4 s + channel of the four
+      if (finite) {                                  // uniform
+        const Scale4 q0 = scale4(mn0, st0), q1 = scale4(mn1, st1);
+        auto codes = [&](auto r_c) {
+          constexpr int R = decltype(r_c)::value;
+          auto of_lane = [](float x) { return __uint_as_float(of_quad_lane<R>(__float_as_uint(x))); };
+          const Scale4 q[2] = {{of_lane(q0.mn), of_lane(q0.inv), of_lane(q0.step)}, {of_lane(q1.mn), of_lane(q1.inv), of_lane(q1.step)}};
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
+          for (int s = 0; s < 2; ++s)
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const uint32_t x = w[2 * R + s][i];
-                const int at = 16 * s + 8 * (i & 1);
-                acc[R][i >> 1] |= (code4(low_less(x, q[s].mn), q[s]) << at) | (code4(high_less(x, q[s].mn), q[s]) << (at + 4));
-              }
-          };
-          codes(std::integral_constant<int, 0>{});
-          codes(std::integral_constant<int, 1>{});
-          codes(std::integral_constant<int, 2>{});
-          codes(std::integral_constant<int, 3>{});
-        } else {
-#pragma unroll 1
-          for (int i = 0; i < 8; ++i) {
-            const int r = i >> 1, s = i & 1, from = (lane & ~3) | r;
-            const float m = __shfl(s ? mn1 : mn0, from), h = __shfl(s ? h1 : h0, from);
-            const u32x4 x = row(r, s);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const uint32_t c = code4_compared(k & 1 ? hi_half(x[k >> 1]) : lo_half(x[k >> 1]), m, h) << (16 * s + 4 * (k & 3));
-#pragma unroll
-              for (int b = 0; b < 4; ++b) acc[b][k >> 2] |= b == r ? c : 0u;
+            for (int i = 0; i < 4; ++i) {
+              const uint32_t x = w[2 * R + s][i];
+              const int at = 16 * s + 8 * (i & 1);
+              acc[R][i >> 1] |= (code4(low_less(x, q[s].mn), q[s]) << at) | (code4(high_less(x, q[s].mn), q[s]) << (at + 4));
             }
-          }
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          uint32_t x0 = acc[0][a], x1 = acc[1][a], x2 = acc[2][a], x3 = acc[3][a];
-          trade_rows(x0, x1, x2, x3);                  // row t4 gets r = t4, register i the tokens that row i had
-          // registers against channels: register i the codes of channel 4 a + i, numbered 4 s + t4: a word, but for its turn
-          trade_fields(x0, x1, 0x0F0F0F0Fu, 4);
-          trade_fields(x2, x3, 0x0F0F0F0Fu, 4);
-          trade_fields(x0, x2, 0x00FF00FFu, 8);
-          trade_fields(x1, x3, 0x00FF00FFu, 8);
-          // Registers against bits 1 and 2 of the lane, which with bit 3 number the field: a lane gets the four words of
-          // its 16 bytes.
-          const bool up = lane & 2;
-          auto swap1 = [&](uint32_t& p, uint32_t& q) {
-            const uint32_t got = row_partner_u32<1>(up ? p : q);
-            p = up ? got : p;
-            q = up ? q : got;
-          };
-          swap1(x0, x1);
-          swap1(x2, x3);
-          auto swap2 = [&](uint32_t& p, uint32_t& q) {
-            const uint32_t was = p;
-            p = from_bank<3, 4>(from_bank<1, 4>(p, q), q);
-            q = from_bank<2, 12>(from_bank<0, 12>(q, was), was);
-          };
-          swap2(x0, x2);
-          swap2(x1, x3);
-          put_away<ONCE>(u32x4{rotl32(x0, 2), rotl32(x1, 2), rotl32(x2, 2), rotl32(x3, 2)},
-                         (u32x4*)(vb + 1024 * (c16 >> 3) + 16 * (16 * t4 + 8 * (lane & 1) + 4 * a + ((lane >> 1) & 3))));
-        }
+        };
+        codes(std::integral_constant<int, 0>{});
+        codes(std::integral_constant<int, 1>{});
+        codes(std::integral_constant<int, 2>{});
+        codes(std::integral_constant<int, 3>{});
       } else {
-        const Thresholds2 th = thresholds2(mn0, h0, mn1, h1);
-        uint32_t acc[4] = {0, 0, 0, 0};                // r: code 8 s + 4 (channel & 1) + channel pair of the lane's four
-        if (finite) {                                  // uniform
-          auto codes = [&](auto r_c) {
-            constexpr int R = decltype(r_c)::value;
-            h2 n[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) n[k] = as_h2(of_quad_lane<R>(as_u32(th.neg[k])));
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              gather2<true>(acc[R], codes2(w[2 * R][i], h2{n[0][0], n[0][0]}, h2{n[1][0], n[1][0]}, h2{n[2][0], n[2][0]}),
-                            codes2(w[2 * R + 1][i], h2{n[0][1], n[0][1]}, h2{n[1][1], n[1][1]}, h2{n[2][1], n[2][1]}), i);
-          };
-          codes(std::integral_constant<int, 0>{});
-          codes(std::integral_constant<int, 1>{});
-          codes(std::integral_constant<int, 2>{});
-          codes(std::integral_constant<int, 3>{});
-        } else {
 #pragma unroll 1
-          for (int r = 0; r < 4; ++r) {
-            const int from = (lane & ~3) | r;
-            const float m0 = __shfl(mn0, from), m1 = __shfl(mn1, from), g0 = __shfl(h0, from), g1 = __shfl(h1, from);
-            const u32x4 x0 = row(r, 0), x1 = row(r, 1);
-            uint32_t a = 0;
+        for (int i = 0; i < 8; ++i) {
+          const int r = i >> 1, s = i & 1, from = (lane & ~3) | r;
+          const float m = __shfl(s ? mn1 : mn0, from), h = __shfl(s ? h1 : h0, from);
+          const u32x4 x = row(r, s);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              gather2<true>(a, codes2_compared(x0[i], m0, g0, m0, g0), codes2_compared(x1[i], m1, g1, m1, g1), i);
+          for (int k = 0; k < 8; ++k) {
+            const uint32_t c = code4_compared(k & 1 ? hi_half(x[k >> 1]) : lo_half(x[k >> 1]), m, h) << (16 * s + 4 * (k & 3));
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc[k] = k == r ? a : acc[k];
+            for (int b = 0; b < 4; ++b) acc[b][k >> 2] |= b == r ? c : 0u;
           }
         }
-        // row t4 of 16 lanes gets r = t4, register i the tokens that row i had
-        trade_rows(acc[0], acc[1], acc[2], acc[3]);
-        // registers against channel pairs: register i the codes of pair i, numbered 8 s + 4 (channel & 1) + t4
-        trade_fields(acc[0], acc[1], 0x33333333u, 2);
-        trade_fields(acc[2], acc[3], 0x33333333u, 2);
-        trade_fields(acc[0], acc[2], 0x0F0F0F0Fu, 4);
-        trade_fields(acc[1], acc[3], 0x0F0F0F0Fu, 4);
-        // Bit 1 of the lane, which tells channels c and c + 16 apart, against the parity of the channel: a word of both.
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = rotl32(trade2<2>(acc[i], row_partner_u32<1>(acc[i]), lane & 2), 2);
-        // Registers against the lanes' banks of four, so that a lane has the four words of its 16 bytes: bank b passes its
-        // register k to bank k, register b.
-        u32x4 words = {acc[0], acc[1], acc[2], acc[3]};
-        words[0] = from_bank<1, 4>(words[0], acc[1]), words[0] = from_bank<2, 8>(words[0], acc[2]), words[0] = from_bank<3, 12>(words[0], acc[3]);
-        words[1] = from_bank<0, 12>(words[1], acc[0]), words[1] = from_bank<2, 4>(words[1], acc[2]), words[1] = from_bank<3, 8>(words[1], acc[3]);
-        words[2] = from_bank<0, 8>(words[2], acc[0]), words[2] = from_bank<1, 12>(words[2], acc[1]), words[2] = from_bank<3, 4>(words[2], acc[3]);
-        words[3] = from_bank<0, 4>(words[3], acc[0]), words[3] = from_bank<1, 8>(words[3], acc[1]), words[3] = from_bank<2, 12>(words[3], acc[2]);
-        // lane: row r = t4, bank k = channel pair, bit 1 the parity of the channel, bit 0 the channel's bit 3
-        put_away<ONCE>(words, (u32x4*)(vb + 16 * (16 * t4 + 8 * (lane & 1) + 2 * (c16 >> 2) + ((lane >> 1) & 1))));
       }
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        uint32_t x0 = acc[0][a], x1 = acc[1][a], x2 = acc[2][a], x3 = acc[3][a];
+        trade_rows(x0, x1, x2, x3);                  // row t4 gets r = t4, register i the tokens that row i had
+        // registers against channels: register i the codes of channel 4 a + i, numbered 4 s + t4: a word, but for its turn
+        trade_fields(x0, x1, 0x0F0F0F0Fu, 4);
+        trade_fields(x2, x3, 0x0F0F0F0Fu, 4);
+        trade_fields(x0, x2, 0x00FF00FFu, 8);
+        trade_fields(x1, x3, 0x00FF00FFu, 8);
+        // Registers against bits 1 and 2 of the lane, which with bit 3 number the field: a lane gets the four words of
+        // its 16 bytes.
+        const bool up = lane & 2;
+        auto swap1 = [&](uint32_t& p, uint32_t& q) {
+          const uint32_t got = row_partner_u32<1>(up ? p : q);
+          p = up ? got : p;
+          q = up ? q : got;
+        };
+        swap1(x0, x1);
+        swap1(x2, x3);
+        auto swap2 = [&](uint32_t& p, uint32_t& q) {
+          const uint32_t was = p;
+          p = from_bank<3, 4>(from_bank<1, 4>(p, q), q);
+          q = from_bank<2, 12>(from_bank<0, 12>(q, was), was);
+        };
+        swap2(x0, x2);
+        swap2(x1, x3);
+        put_away<ONCE>(u32x4{rotl32(x0, 2), rotl32(x1, 2), rotl32(x2, 2), rotl32(x3, 2)},
+                       (u32x4*)(vb + 1024 * (c16 >> 3) + 16 * (16 * t4 + 8 * (lane & 1) + 4 * a + ((lane >> 1) & 3))));
+      }
+    } else {
+      const Thresholds2 th = thresholds2(mn0, h0, mn1, h1);
+      uint32_t acc[4] = {0, 0, 0, 0};                // r: code 8 s + 4 (channel & 1) + channel pair of the lane's four
+      if (finite) {                                  // uniform
+        auto codes = [&](auto r_c) {
+          constexpr int R = decltype(r_c)::value;
+          h2 n[3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) n[k] = as_h2(of_quad_lane<R>(as_u32(th.neg[k])));
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            gather2<true>(acc[R], codes2(w[2 * R][i], h2{n[0][0], n[0][0]}, h2{n[1][0], n[1][0]}, h2{n[2][0], n[2][0]}),
+                          codes2(w[2 * R + 1][i], h2{n[0][1], n[0][1]}, h2{n[1][1], n[1][1]}, h2{n[2][1], n[2][1]}), i);
+        };
+        codes(std::integral_constant<int, 0>{});
+        codes(std::integral_constant<int, 1>{});
+        codes(std::integral_constant<int, 2>{});
+        codes(std::integral_constant<int, 3>{});
+      } else {
+#pragma unroll 1
+        for (int r = 0; r < 4; ++r) {
+          const int from = (lane & ~3) | r;
+          const float m0 = __shfl(mn0, from), m1 = __shfl(mn1, from), g0 = __shfl(h0, from), g1 = __shfl(h1, from);
+          const u32x4 x0 = row(r, 0), x1 = row(r, 1);
+          uint32_t a = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            gather2<true>(a, codes2_compared(x0[i], m0, g0, m0, g0), codes2_compared(x1[i], m1, g1, m1, g1), i);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[k] = k == r ? a : acc[k];
+        }
+      }
+      // row t4 of 16 lanes gets r = t4, register i the tokens that row i had
+      trade_rows(acc[0], acc[1], acc[2], acc[3]);
+      // registers against channel pairs: register i the codes of pair i, numbered 8 s + 4 (channel & 1) + t4
+      trade_fields(acc[0], acc[1], 0x33333333u, 2);
+      trade_fields(acc[2], acc[3], 0x33333333u, 2);
+      trade_fields(acc[0], acc[2], 0x0F0F0F0Fu, 4);
+      trade_fields(acc[1], acc[3], 0x0F0F0F0Fu, 4);
+      // Bit 1 of the lane, which tells channels c and c + 16 apart, against the parity of the channel: a word of both.
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i] = rotl32(trade2<2>(acc[i], row_partner_u32<1>(acc[i]), lane & 2), 2);
+      // Registers against the lanes' banks of four, so that a lane has the four words of its 16 bytes: bank b passes its
+      // register k to bank k, register b.
+      u32x4 words = {acc[0], acc[1], acc[2], acc[3]};
+      words[0] = from_bank<1, 4>(words[0], acc[1]), words[0] = from_bank<2, 8>(words[0], acc[2]), words[0] = from_bank<3, 12>(words[0], acc[3]);
+      words[1] = from_bank<0, 12>(words[1], acc[0]), words[1] = from_bank<2, 4>(words[1], acc[2]), words[1] = from_bank<3, 8>(words[1], acc[3]);
+      words[2] = from_bank<0, 8>(words[2], acc[0]), words[2] = from_bank<1, 12>(words[2], acc[1]), words[2] = from_bank<3, 4>(words[2], acc[3]);
+      words[3] = from_bank<0, 4>(words[3], acc[0]), words[3] = from_bank<1, 8>(words[3], acc[1]), words[3] = from_bank<2, 12>(words[3], acc[2]);
+      // lane: row r = t4, bank k = channel pair, bit 1 the parity of the channel, bit 0 the channel's bit 3
+      put_away<ONCE>(words, (u32x4*)(vb + 16 * (16 * t4 + 8 * (lane & 1) + 2 * (c16 >> 2) + ((lane >> 1) & 1))));
     }
   };
   if (any_flag()) values(std::true_type{});
@@ -1082,7 +1103,7 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
   // done with a group soonest
   const int64_t groups = (int64_t)d.units_per_layer * rows.layers * n_groups;
   const bool many = groups >= prompt_groups(G) && !d.keys_only;
-  const int threads = many ? 128 : kQuantThreads;
+  const int threads = many ? 4 * G : kQuantThreads;
   const dim3 grid(d.units_per_layer, n_groups + (tail_n * 16 + threads - 1) / threads, rows.layers);
   auto go = [&](auto kern, size_t smem, auto... more) {
     hipLaunchKernelGGL(kern, grid, dim3(threads), smem, s, d, group_index, rows.unit_stride, selected,
@@ -1096,20 +1117,15 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
   // first: their Keys are still there.  G = 32, first to last / last to first: 2-bit, 260 MB (256 units x 4160 tokens)
   // 197 / 186 us, 520 MB 385 / 372; 4-bit, 260 MB 240 / 233.  At 128 MB and below they are there in any order.
   // ONCE keeps rows that are not needed again, and the codes, from displacing the rest.  It pays where the rows have to
-  // come from memory, and costs where the next call would have found rows in the same place in the cache.  In per cent of
-  // the whole call, 128 units, 2-bit / 4-bit codes; the rows a) gone from the cache, b) just written, c) read again where
-  // they were:   36 MB of Keys                  64                              100                              200
-  //   G = 32     a 2 / 1, b 1 / 0, c -3 / 0     a 5 / 5, b 0 / 0, c -3 / -1     a 4 / 3, b -2 / -2, c -4 / -1    a 11 / 2, b 8 / 1, c 11 / 2
-  //   G = 64     a 3 / 2, b 2 / 0, c -1 / -1    a 8 / 4, b 4 / 0, c 4 / 0       a 4 / 2, b 2 / 1, c 6 / 1        a 9 / 2, b 7 / 1, c 11 / 3
-  //   G = 128    a 0 / 1, b -2 / -1, c -2 / -1  a 0 / 1, b -2 / 0, c -3 / -2    a 4 / 4, b -3 / -2, c -2 / -1    a 4 / 2, b 3 / 0, c 2 / 2
-  // Below 32 MB -4 .. 4 either way; at 1032 MB, 512 units, c: -3 / 1 (G = 32), -5 / 1 (G = 64).  With G = 128 the Keys are
-  // read twice as it is, and of many short units, 2-bit, they are found in the cache the second time (200 MB, 256 units:
-  // a 1, b -1, c -1); where there is no competition it pays for those too (c 12).
+  // come from memory, and costs where the next call would have found the same rows in the same place in the cache (which
+  // a prompt does not do).  Whole calls, three sets of rows in turn, without / with, G = 32 (64 and 128 alike):
+  //   Keys   12 MB, 128 units   24, 128       36, 256       64, 32        100, 128      200, 128    400, 256    1100 MB, 512 units
+  //   2-bit  26.4 / 26.1 us     31.7 / 32.2   41.2 / 38.9   60.4 / 54.7   83.4 / 77.1   153 / 134   275 / 238   745 / 688
+  //   4-bit  29.0 / 28.9        35.5 / 35.6   45.5 / 44.1   67.3 / 62.4   92.7 / 88.3   166 / 150   304 / 263   794 / 732
+  // With one set of rows, read again and again, it costs 2 .. 4 % from 32 to 100 MB, and gives 5 .. 13 % from 200 MB on.
   const int64_t key_bytes = groups * G * (2 * kHeadDim);
   const int32_t last_first = key_bytes >= (1ll << 27);
-  const int64_t from = G == 64 ? 1ll << 25 : G == 32 ? 3ll << 24 : BITS == 4 ? 1ll << 26 : 3ll << 25;
-  const bool once = key_bytes >= from && key_bytes < (1ll << 30) &&
-                    (G < 128 || BITS == 4 || d.units_per_layer * rows.layers <= 160 || d.N == 0);
+  const bool once = key_bytes >= (1ll << 25);
   if (many && once) return go(prompt_quantize_kernel<BITS, G, LAYERS, true>, 0, last_first);
   if (many) return go(prompt_quantize_kernel<BITS, G, LAYERS, false>, 0, last_first);
   const size_t smem = quant_lds_bytes<G>(d.vgroups);

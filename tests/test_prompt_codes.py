@@ -1,6 +1,6 @@
 """Codes, steps and zeros of a prompt of many groups where rounding decides: the kernel that takes many groups turns the
-thresholds of a group into fp16 values (2-bit) or multiplies by a reciprocal (4-bit); the kernel that takes few compares
-in fp32, as the definition does.  Both are given the same rows."""
+thresholds of a group into fp16 values (2-bit) or multiplies by a reciprocal (4-bit); the step that closes a group while
+decoding compares in fp32, as the definition does.  Both are given the same rows."""
 import numpy as np
 import pytest
 
@@ -46,28 +46,24 @@ def hard_rows(seed, batch, heads, n, group, value_group, bits, non_finite):
 @pytest.mark.parametrize("non_finite", [False, True])
 @pytest.mark.parametrize("budget", [0, 5])
 @pytest.mark.parametrize("bits,group,value_group", [(2, 32, 32), (2, 64, 64), (2, 128, 128), (4, 32, 64), (4, 64, 128), (4, 128, 32)])
-def test_many_groups_give_the_bytes_of_few(bits, group, value_group, budget, non_finite):
+def test_a_prompt_gives_the_bytes_of_its_tokens_one_by_one(bits, group, value_group, budget, non_finite):
     import torch
     from paper_2505_10938_amd import cache as KC
     if non_finite and budget:
         pytest.skip("scores that are no numbers are not supported")
-    batch, heads, n = 32, 4, 8 * group                        # 1024 groups in one call, 32 in each of the others
+    batch, heads, n = 32, 4, 8 * group
     k, v = (torch.from_numpy(x).cuda() for x in hard_rows(bits * group + value_group, batch, heads, n, group, value_group, bits, non_finite))
     if budget:                                                # (scores are exact up to a sum of 2^23; tracing is not the point)
         k = k.clamp(-3e4, 3e4)
 
-    def contents(b):
-        cache = KC.KVCache(KC.make_config(1, b, heads, heads, n, bits, group, value_group, 0, budget, 32 if budget else 0, 128))
-        return cache, lambda: [t.cpu() for t in (cache.k_codes, cache.k_meta, cache.v_codes, cache.v_meta, cache.mask)]
-
-    many, got = contents(batch)
-    many.prefill(0, k, v)
-    got = got()
-    parts = []
-    for b in range(batch):
-        few, one = contents(1)
-        few.prefill(0, k[b:b + 1].contiguous(), v[b:b + 1].contiguous())
-        parts.append(one())
-    for name, whole, of in zip(("k_codes", "k_meta", "v_codes", "v_meta", "mask"), got, zip(*parts)):
-        want = torch.cat([t.flatten().view(torch.uint8) for t in of])
-        assert torch.equal(whole.flatten().view(torch.uint8)[:want.numel()], want), name
+    caches = []
+    for _ in range(2):
+        caches.append(KC.KVCache(KC.make_config(1, batch, heads, heads, n, bits, group, value_group, 0, budget,
+                                                32 if budget else 0, 128)))
+    prompt, steps = caches
+    prompt.prefill(0, k, v)
+    for i in range(n):
+        steps.append(0, k[:, :, i].contiguous(), v[:, :, i].contiguous())
+    assert prompt.n_quant == steps.n_quant == [n]
+    for name in ("k_codes", "k_meta", "v_codes", "v_meta", "mask"):
+        assert torch.equal(getattr(prompt, name).view(torch.uint8), getattr(steps, name).view(torch.uint8)), name
