@@ -66,8 +66,12 @@ typedef unsigned long long u64;
 // the N smallest of any prefix of the entries that ends with its group or before.  The N-th smallest score
 // of the first 32, 64, 128 and 256 entries is found by bisection over coarse scores (fp32 rounded, the first
 // 8 bits of the significand: the order is kept, only some neighbours become equal), one wavefront each.
+// What takes the time is the ballots, 16 ns each.  Few members: the N-th smallest of the lanes' own smallest entries serves as
+// well, N entries are no larger, and seldom does one lane have two of the N (N = 8: a bound by 6 % too many entries).
+// 64 / 16 ballots, the whole call: a prompt of 8191 tokens that joins, 8 kv heads, 4 layers, 51.8 / 50.6 us; 32 units of 8192 tokens 54.5 / 53.2; 24 of 1500 31.9 / 31.2.
 constexpr int kPrefixes = 4;
 constexpr int kCoarseBits = 16;
+constexpr int kFewMembers = 16;
 __device__ __forceinline__ uint32_t coarse_score(double score) {
   return score < 8388608.0 ? __float_as_uint((float)score) >> (31 - kCoarseBits) : (1u << kCoarseBits) - 1u;
 }
@@ -78,12 +82,22 @@ __device__ __forceinline__ void prefix_bounds(const uint32_t* coarse, int n, int
   uint32_t v[kWords], t = 0;
 #pragma unroll
   for (int k = 0; k < kWords; ++k) v[k] = k * 64 + lane < p ? coarse[k * 64 + lane] : ~0u;
+  auto bisect = [&](auto words_c) {                      // the N-th smallest of the first `words` of each lane
+    constexpr int words = decltype(words_c)::value;
 #pragma unroll
-  for (int b = kCoarseBits - 1; b >= 0; --b) {
-    int at_most = 0;
+    for (int b = kCoarseBits - 1; b >= 0; --b) {
+      int at_most = 0;
 #pragma unroll
-    for (int k = 0; k < kWords; ++k) at_most += __popcll(__ballot(v[k] <= (t | ((1u << b) - 1u))));
-    t |= at_most < N ? 1u << b : 0u;
+      for (int k = 0; k < words; ++k) at_most += __popcll(__ballot(v[k] <= (t | ((1u << b) - 1u))));
+      t |= at_most < N ? 1u << b : 0u;
+    }
+  };
+  if (N <= kFewMembers) {
+#pragma unroll
+    for (int k = 1; k < kWords; ++k) v[0] = min(v[0], v[k]);
+    bisect(std::integral_constant<int, 1>{});
+  } else {
+    bisect(std::integral_constant<int, kWords>{});
   }
   if (lane == 0) bound[wave] = t;                      // (fewer than N entries: the largest value there is)
 }
