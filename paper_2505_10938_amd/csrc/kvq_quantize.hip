@@ -377,12 +377,12 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
 //           registers, and a lane stores 16 bytes.
 // No row goes through LDS, and each is read once: the blocks of a longer group exchange minimum, maximum and, where a
 // token is flagged, sums.  What bounds it: the rows and codes on their way (256 units x 4096 tokens, 2-bit: 637 MB in
-// 90 us, 7 TB/s, the Keys in part from the memory-side cache).  When every code was decided by fp32 comparisons, gathered by
+// 89 us, 7.1 TB/s, the Keys in part from the memory-side cache).  When every code was decided by fp32 comparisons, gathered by
 // an OR over the lanes token by token and the Values turned through LDS, it was the instructions, 1900 per block where
-// there are now about 900; when one wavefront took the blocks of a group one after the other, a second read of the Keys.
-// Whole calls, three sets of rows in turn, before all that / with the blocks one after the other / now: G = 32 183 / 161 /
-// 158 us, 4-bit 232 / 175 / 178; G = 64 187 / 167 / 159; G = 128 217 / 213 / 184, 4-bit 246 / 226 / 190.  A joining prompt of
-// 8191 tokens, 8 kv heads, 4 layers: G = 32 59 / 52 / 51.5, G = 128 - / 74 / 62.
+// there are now about 1050; when one wavefront took the blocks of a group one after the other, a second read of the Keys.
+// Whole calls, three sets of rows in turn, before all that / with the blocks one after the other / now (accesses past the
+// caches included): G = 32 183 / 161 / 156 us, 4-bit 231 / 175 / 177; G = 64 188 / 167 / 155; G = 128 217 / 213 / 160, 4-bit 248 /
+// 226 / 187.  A joining prompt of 8191 tokens, 8 kv heads, 4 layers: G = 32 59 / 52 / 51, G = 128 79 / 74 / 55.
 // Results are those of quantize_body bit for bit (same roundings in the same order; minimum, maximum and
 // the exact fp64 sums do not depend on the order they are taken in).
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -545,8 +545,9 @@ __global__ void __launch_bounds__(4 * G) __attribute__((amdgpu_waves_per_eu(4, 8
   // grid (units, groups + tail blocks, layers), as quantize_kernel's.  Wavefronts 0 .. nblk - 1 have the Keys of a block of 32
   // tokens each, the others the Values.
   constexpr int nblk = G / kBlockTokens, kThreads = 128 * nblk;
-  __shared__ uint2 s_extremes[nblk][64];               // what the blocks of a longer group tell each other: minimum and
-  __shared__ __align__(16) double s_sums[nblk > 1 ? 2 : 1][nblk > 1 ? nblk : 1][kHeadDim];   // maximum of the Keys, sums of both (for means)
+  // what the blocks of a longer group tell each other: minimum and maximum of the Keys, sums of Keys and Values (for means)
+  __shared__ uint2 s_extremes[nblk][64];
+  __shared__ __align__(16) double s_sums[nblk > 1 ? 2 : 1][nblk > 1 ? nblk : 1][kHeadDim];
   const int tid = threadIdx.x;
   const int ul = blockIdx.x, by = blockIdx.y, layer = LAYERS > 1 ? blockIdx.z : 0;
   const __half* __restrict__ k_rows = rows.k[layer];

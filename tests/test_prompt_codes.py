@@ -48,7 +48,6 @@ def hard_rows(seed, batch, heads, n, group, value_group, bits, non_finite):
 @pytest.mark.parametrize("bits,group,value_group", [(2, 32, 32), (2, 64, 64), (2, 128, 128), (4, 32, 64), (4, 64, 128), (4, 128, 32)])
 def test_a_prompt_gives_the_bytes_of_its_tokens_one_by_one(bits, group, value_group, budget, non_finite):
     import torch
-    from paper_2505_10938_amd import cache as KC
     if non_finite and budget:
         pytest.skip("scores that are no numbers are not supported")
     batch, heads, n = 32, 4, 8 * group
@@ -56,14 +55,29 @@ def test_a_prompt_gives_the_bytes_of_its_tokens_one_by_one(bits, group, value_gr
     if budget:                                                # (scores are exact up to a sum of 2^23; tracing is not the point)
         k = k.clamp(-3e4, 3e4)
 
-    caches = []
-    for _ in range(2):
-        caches.append(KC.KVCache(KC.make_config(1, batch, heads, heads, n, bits, group, value_group, 0, budget,
-                                                32 if budget else 0, 128)))
-    prompt, steps = caches
+    compare_with_steps(k, v, bits, group, value_group, budget)
+
+
+def compare_with_steps(k, v, bits, group, value_group, budget):
+    import torch
+    from paper_2505_10938_amd import cache as KC
+    batch, heads, n = k.shape[:3]
+    prompt, steps = (KC.KVCache(KC.make_config(1, batch, heads, heads, n, bits, group, value_group, 0, budget,
+                                               32 if budget else 0, 128)) for _ in range(2))
     prompt.prefill(0, k, v)
     for i in range(n):
         steps.append(0, k[:, :, i].contiguous(), v[:, :, i].contiguous())
     assert prompt.n_quant == steps.n_quant == [n]
     for name in ("k_codes", "k_meta", "v_codes", "v_meta", "mask"):
         assert torch.equal(getattr(prompt, name).view(torch.uint8), getattr(steps, name).view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("group,groups", [(32, 63), (32, 64), (32, 65), (64, 7), (64, 8), (64, 9), (128, 1), (128, 2)])
+def test_either_side_of_the_change_of_kernels(bits, group, groups):
+    """Four units: 256 groups of 32 tokens, 32 of 64 and one of 128 are the first that go to the kernel for many."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(group + groups)
+    k, v = (torch.randn(1, 4, group * groups, 128, generator=gen, device="cuda").half() for _ in range(2))
+    compare_with_steps(k, v, bits, group, 32, 3)

@@ -136,6 +136,15 @@ def plateau_keys(G, n, low, lower):
     return np.repeat((norm / 128.0)[:, None], 128, 1).astype(np.float16)
 
 
+@pytest.mark.parametrize("N", [15, 16, 17])
+@pytest.mark.parametrize("n", [32, 96, 1056, 4096])
+def test_first_look_of_few_and_of_many_members(N, n):
+    """Up to 16 members the first look bisects over the lanes' smallest entries, with more over all."""
+    rng = np.random.default_rng(n + N)
+    K = np.stack([keys(pattern, n, rng) for pattern in PATTERNS])
+    check_selection(K, rng.standard_normal(K.shape).astype(np.float16), 32, N, 64)
+
+
 @pytest.mark.parametrize("G", [32, 64, 128])
 @pytest.mark.parametrize("A", [8, 32])
 @pytest.mark.parametrize("n", [10240, 12288])
