@@ -72,8 +72,9 @@ typedef unsigned long long u64;
 constexpr int kPrefixes = 4;
 constexpr int kCoarseBits = 16;
 constexpr int kFewMembers = 16;
-__device__ __forceinline__ uint32_t coarse_score(double score) {
-  return score < 8388608.0 ? __float_as_uint((float)score) >> (31 - kCoarseBits) : (1u << kCoarseBits) - 1u;
+template <class Score>
+__device__ __forceinline__ uint32_t coarse_score(Score score) {
+  return score < (Score)8388608.0 ? __float_as_uint((float)score) >> (31 - kCoarseBits) : (1u << kCoarseBits) - 1u;
 }
 __device__ __forceinline__ void prefix_bounds(const uint32_t* coarse, int n, int N, uint32_t* bound, int wave, int lane) {
   if (wave >= kPrefixes) return;
@@ -158,27 +159,37 @@ constexpr int first_to_last(int rows, int i) {            // i with its bits in 
   return q;
 }
 template <int ROWS, int BIT = 0, class S>
-__device__ __forceinline__ double team_sums(int sub, const S& s, int q = 0) {
+__device__ __forceinline__ auto team_sums(int sub, const S& s, int q = 0) {
   if constexpr (BIT == 4) {
     return s(q);
   } else {
-    const double a = team_sums<ROWS, BIT + 1>(sub, s, q);
+    const auto a = team_sums<ROWS, BIT + 1>(sub, s, q);
     if constexpr (ROWS == 8 && BIT == 0) {
       return a + row_partner<BIT>(a);
     } else {
-      const double b = team_sums<ROWS, BIT + 1>(sub, s, q + (1 << BIT) * ROWS / 16);
+      const auto b = team_sums<ROWS, BIT + 1>(sub, s, q + (1 << BIT) * ROWS / 16);
       const bool upper = (sub >> BIT) & 1;              // (the partner's bit is the other way)
       return (upper ? b : a) + row_partner<BIT>(upper ? a : b);
     }
   }
 }
 
-// Exact fp64 L1 scores of the Key rows row(0) .. row(n - 1), handed to put(e, score) by one lane each: 16 lanes
-// per row, eight rows of a team of lanes in flight.
-template <class Row, class Put>
-__device__ __forceinline__ void score_rows(int n, int tid, Row row, Put put) {
+// About the sum of eight magnitudes, in fp32: one instruction each, where the exact sum in fp64 takes three.
+__device__ __forceinline__ float about_abs_sum8(uint4 w) {
+  float a = 0.0f, b = 0.0f;
+  auto add = [&](uint32_t x) {
+    asm("v_fma_mix_f32 %0, |%1|, 1.0, %0 op_sel_hi:[1,0,0]" : "+v"(a) : "v"(x));
+    asm("v_fma_mix_f32 %0, |%1|, 1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(b) : "v"(x));
+  };
+  add(w.x), add(w.y), add(w.z), add(w.w);
+  return a + b;
+}
+
+// L1 scores of the Key rows row(0) .. row(n - 1), the sums of `sum8` of their eighths, handed to put(e, score) by one lane
+// each: 16 lanes per row, kInFlight (8 or 16) rows of a team of lanes in flight.
+template <int kInFlight, class Sum8, class Row, class Put>
+__device__ __forceinline__ void score_rows(int n, int tid, Sum8 sum8, Row row, Put put) {
   constexpr int kTeams = kSegment / 16;
-  constexpr int kInFlight = 8;
   const int team = tid >> 4, sub = tid & 15;
   // (a whole segment: 64 rows next to each other per wavefront, four at a time, as in prompt_compete_kernel)
   const int first = n == kSegment ? (team >> 2) * 64 + (team & 3) : team, step = n == kSegment ? 4 : kTeams;
@@ -189,9 +200,9 @@ __device__ __forceinline__ void score_rows(int n, int tid, Row row, Put put) {
       const int q = first_to_last(kInFlight, i);
       w[q] = *(const uint4*)(row(min(first + (i0 + q) * step, n - 1)) + sub * 8);
     }
-    const double sc = team_sums<kInFlight>(sub, [&](int q) { return trace_core::abs_sum8(w[q]); });
-    const int e = first + (i0 + (sub >> 1)) * step;
-    if (!(sub & 1) && e < n) put(e, sc);
+    const auto sc = team_sums<kInFlight>(sub, [&](int q) { return sum8(w[q]); });
+    const int e = first + (i0 + sub * kInFlight / 16) * step;
+    if ((kInFlight == 16 || !(sub & 1)) && e < n) put(e, sc);
   }
 }
 
@@ -281,16 +292,23 @@ __device__ __forceinline__ int compete_round(CompeteLds<T>& L, int n, bool may, 
 }
 
 // Is entry e, token idx (n entries, `at(p)` = token of entry p), among those that the first look lets through?
+// `margin`: coarse scores by which the bounds are too low at worst.
 template <int G, class At>
-__device__ __forceinline__ bool may_be_selected(const uint32_t* coarse, const uint32_t* bound, int n, int e, int idx, At at) {
-  uint32_t b = ~0u;
+__device__ __forceinline__ bool may_be_selected(const uint32_t* coarse, const uint32_t* bound, int n, int e, int idx, At at,
+                                                uint32_t margin = 0) {
+  uint32_t b = (1u << kCoarseBits) - 1u;
 #pragma unroll
   for (int i = 0; i < kPrefixes; ++i)
     if ((32 << i) <= n && at((32 << i) - 1) <= (idx | (G - 1))) b = bound[i];   // (bounds fall with the prefix)
-  return coarse[e] <= b;
+  return coarse[e] <= b + margin;
 }
 
-// grid (units, segments, layers).  Requires N > 0.
+// grid (units, segments, layers).  Requires N > 0.  The scores are sums in fp32: at most 127 roundings, 2^-17 of the sum,
+// so that a coarse score is one off at most, the bounds too, and what is at or below a bound by exact scores is at or
+// below it by two more.
+// (Exact sums, eight rows of a team in flight / fp32 sums, sixteen in flight, so that a workgroup makes one trip to memory:
+// a prompt of 8191 tokens joining, 8 kv heads, 4 layers, 51.3 / 50.7 us, of 8000 in one layer 29.4 / 27.4, of 3000, 4 kv
+// heads, 4 layers 30.4 / 28.3; 64 units x 16384 180.5 / 170.4 (fp32 sums with eight rows: 185.5).)
 template <int G, int LAYERS>
 __global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int32_t n_tok, int64_t unit_stride,
                                                                      uint8_t* __restrict__ selected,
@@ -303,14 +321,15 @@ __global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int
   const int ul = blockIdx.x, t0 = blockIdx.y * kSegment, layer = LAYERS > 1 ? blockIdx.z : 0;
   const int n = min(kSegment, n_tok - t0);
   const __half* rows = src.k[layer] + (int64_t)ul * unit_stride + (int64_t)t0 * kHeadDim;
-  score_rows(n, tid, [&](int e) { return rows + e * kHeadDim; }, [&](int e, double sc) { coarse[e] = coarse_score(sc); });
+  score_rows<16>(n, tid, about_abs_sum8, [&](int e) { return rows + e * kHeadDim; },
+                 [&](int e, float sc) { coarse[e] = coarse_score(sc); });
   __syncthreads();
   prefix_bounds(coarse, n, d.N, bound, wave, lane);
   __syncthreads();
   // (segments begin with a group: token numbers inside the segment number its groups as well)
   if (tid < n)
     selected[((int64_t)layer * d.units_per_layer + ul) * n_tok + t0 + tid] =
-        may_be_selected<G>(coarse, bound, n, tid, tid, [](int p) { return p; }) ? 1 : 0;
+        may_be_selected<G>(coarse, bound, n, tid, tid, [](int p) { return p; }, 2u) ? 1 : 0;
 }
 
 // grid (units, 1, layers).  FLAGGED: the tokens that can be selected are flagged in `selected`, else all of them are looked at, T
@@ -423,7 +442,7 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) pro
         }
       }
       __syncthreads();
-      score_rows(n, tid, [&](int e) { return kr + (int64_t)L.idx[e] * kHeadDim; }, put_score);
+      score_rows<8>(n, tid, trace_core::abs_sum8, [&](int e) { return kr + (int64_t)L.idx[e] * kHeadDim; }, put_score);
     } else {
       n = min(T, n_tok - t0);
       next = t0 + n;
