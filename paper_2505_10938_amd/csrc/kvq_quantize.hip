@@ -664,10 +664,9 @@ __global__ void __launch_bounds__(4 * G) __attribute__((amdgpu_waves_per_eu(4, 8
       auto row = [&](int t) -> uint32_t { return ANY && is_sel(t) ? mean : kr[t * 64]; };
       const bool finite = __ballot(not_finite(mn) | not_finite(mx)) == 0;
       if (!finite) {                                   // (uniform; such rows are not supported, and nothing here is made to be fast)
-        mn = h2{(_Float16)__builtin_inff(), (_Float16)__builtin_inff()};
-        mx = -mn;
+        mn = mx = as_h2(row(0));                       // (from a row on, not from infinity: all NaN gives NaN)
 #pragma unroll 1
-        for (int t = 0; t < G; ++t) {
+        for (int t = 1; t < G; ++t) {
           const h2 x = as_h2(row(t));
           mn = __builtin_elementwise_min(mn, x);
           mx = __builtin_elementwise_max(mx, x);

@@ -34,6 +34,7 @@ def hard_rows(seed, batch, heads, n, group, value_group, bits, non_finite):
         if non_finite:
             hit = (rng.random((count, 1)) < 0.02) & (rng.random((count, size)) < 0.1)
             x = np.where(hit, rng.choice([np.inf, -np.inf, np.nan], (count, size)), x)
+            x = np.where(rng.random((count, 1)) < 0.01, np.nan, x)                # not one number in the group
         with np.errstate(over="ignore"):
             return np.clip(f16(x), f16(-65504), f16(65504)) if not non_finite else f16(x)
 
