@@ -306,13 +306,15 @@ __device__ __forceinline__ bool may_be_selected(const uint32_t* coarse, const ui
 // grid (units, segments, layers).  Requires N > 0.  The scores are sums in fp32: at most 127 roundings, 2^-17 of the sum,
 // so that a coarse score is one off at most, the bounds too, and what is at or below a bound by exact scores is at or
 // below it by two more.
-// (Exact sums, eight rows of a team in flight / fp32 sums, sixteen in flight, so that a workgroup makes one trip to memory:
-// a prompt of 8191 tokens joining, 8 kv heads, 4 layers, 51.3 / 50.7 us, of 8000 in one layer 29.4 / 27.4, of 3000, 4 kv
-// heads, 4 layers 30.4 / 28.3; 64 units x 16384 180.5 / 170.4 (fp32 sums with eight rows: 185.5).)
+// Sixteen rows of a team in flight, so that a workgroup makes one trip to memory; in 64 registers, so that two workgroups fit
+// a compute unit.  Whole calls, G = 32, N = 8, three sets of rows in turn, exact sums with eight rows / fp32 sums with eight /
+// with sixteen in 67 registers / in 64: joining prompts of 8000 tokens, 8 kv heads, one layer 30.8 / 28.4 / 28.3 / 28.2 us, of
+// 3000, 4 kv heads, 4 layers 30.8 / 28.7 / 28.5 / 28.6, of 8191, 8 kv heads, 8 layers (512 workgroups) 87.5 / 87.1 / 87.2 / 86.1;
+// 384 workgroups (96 units x 4096 tokens, 48 x 8192) 66.7 / 66.2 / 67.2 / 65.7 and 68.4 / 67.7 / 68.7 / 67.3; 512 (64 x 8192)
+// 83.8 / 83.3 / 84.2 / 82.8; 1024 (64 x 16384) 164.7 / 163.7 / 166.1 / 164.1.
 template <int G, int LAYERS>
-__global__ void __launch_bounds__(kSegment) prompt_candidates_kernel(Dims d, int32_t n_tok, int64_t unit_stride,
-                                                                     uint8_t* __restrict__ selected,
-                                                                     LayerRows<LAYERS> src) {
+__global__ void __launch_bounds__(kSegment) __attribute__((amdgpu_waves_per_eu(8))) prompt_candidates_kernel(
+    Dims d, int32_t n_tok, int64_t unit_stride, uint8_t* __restrict__ selected, LayerRows<LAYERS> src) {
   __shared__ uint32_t coarse[kSegment];
   __shared__ uint32_t bound[kPrefixes];
   const int tid = threadIdx.x;

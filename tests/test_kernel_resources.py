@@ -64,3 +64,9 @@ def test_rows_on_their_way_to_lds_do_not_pass_through_scratch_memory(kernel, ins
     found = {n: k[".private_segment_fixed_size"] for n, k in kernels().items() if kernel in n}
     assert len(found) >= instances
     assert found == {n: bytes_of_scratch(n) for n in found}
+
+
+def test_two_workgroups_that_look_for_candidates_fit_a_compute_unit():
+    """1024 threads are four wavefronts per SIMD, whose 512 registers eight share with 64 each."""
+    found = {n: k[".vgpr_count"] for n, k in kernels().items() if "24prompt_candidates_kernelILi" in n}
+    assert len(found) >= 6 and max(found.values()) <= 64, found
