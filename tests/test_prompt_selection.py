@@ -145,6 +145,43 @@ def test_first_look_of_few_and_of_many_members(N, n):
     check_selection(K, rng.standard_normal(K.shape).astype(np.float16), 32, N, 64)
 
 
+def rows_around(c):
+    """Rows A and B (fp16 [128]) with L1 norms a little below c, A's the smaller one.  Summed up in fp32, channel by channel,
+    A's is c and B's the number below it.  (u: the distance of fp32 numbers below c.)"""
+    u = float(c - np.nextafter(np.float32(c), np.float32(0)))
+    a, b = np.zeros((2, 128), np.float16)
+    a[[0, 2, 4, 6]] = c - 2 ** 13 * u, 2 ** 12 * u, 2 ** 12 * u - 2 ** 9 * u, 2 ** 9 * u - u / 4
+    b[[0, 2, 4, 6]] = c - 2 ** 13 * u, 2 ** 12 * u, 2 ** 11 * u, 2 ** 11 * u - u
+    b[[1, 8]] = 0.49 * u
+    return a, b
+
+
+# Groups, members, tokens: with few units and this many auxiliary places the candidates are looked for first.
+AROUND = [(32, 3, 2048), (32, 8, 2048), (32, 8, 4096 + 96), (64, 16, 3072), (32, 17, 2048 + 64), (128, 40, 2048 + 256)]
+
+
+def rows_around_bounds(G, N, n):
+    """Keys fp16 [units, n, 128], one unit per c, a number whose last 15 bits are zero: there the first look's scores change.
+    Each stretch of 1024 tokens begins with N rows B, which make its bounds, and has a row A a group or two later; the
+    norm of all others is 4 c."""
+    c = np.array([256.0, 384.0, 448.0, 1028.0, 2560.0, 32768.0])
+    K = np.repeat(np.repeat(c[:, None, None] / 32, n, 1), 128, 2).astype(np.float16)
+    at = G * -(-N // G) + 8
+    for h, x in enumerate(c):
+        a, b = rows_around(x)
+        for t in range(0, n, 1024):
+            K[h, t:t + N] = b
+            K[h, t + at] = a
+    return c, K, at
+
+
+@pytest.mark.parametrize("G,N,n", AROUND)
+def test_first_look_allows_for_the_rounding_of_its_sums(G, N, n):
+    """The candidates' scores are fp32 sums.  A row that has to be selected is above the bound by those, below it exactly."""
+    _, K, at = rows_around_bounds(G, N, n)
+    check_selection(K, np.random.default_rng(n + N).standard_normal(K.shape).astype(np.float16), G, N, 64)
+
+
 @pytest.mark.parametrize("G", [32, 64, 128])
 @pytest.mark.parametrize("A", [8, 32])
 @pytest.mark.parametrize("n", [10240, 12288])
