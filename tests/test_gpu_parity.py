@@ -262,8 +262,8 @@ def test_batch_128_stack_layer_sampled_units(bits, context):
     (2, 128, 128, 3, False), (4, 128, 64, 40, False), (2, 32, 64, 0, False),
     (2, 32, 32, 8, True), (4, 64, 64, 8, True)])                       # through a page table
 def test_prompts_of_many_groups_all_settings(bits, G, Gv, N, use_pages):
-    """A prompt of 64 units x 16 groups in one call: from 1024 groups on the library quantizes with the kernel
-    that gives a group two wavefronts (Keys / Values) instead of 1024 threads.  Every bit width, group size and
+    """A prompt of 64 units x 16 groups in one call, which the library quantizes with the kernel that gives every 32
+    tokens of a group two wavefronts (Keys / Values) instead of a group 1024 threads.  Every bit width, group size and
     value-group size; groups with and without flagged tokens (N = 40: most groups have several); sampled units
     against the oracle, state bit for bit and the attention."""
     import torch

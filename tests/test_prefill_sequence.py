@@ -3,8 +3,10 @@ import ctypes as C
 
 import pytest
 
+import kvq_synth as S
 import paper_2505_10938_amd as P
 from paper_2505_10938_amd import binding as B, cache as KC
+from tests import helpers as H
 
 NAMES = ("k_codes", "k_meta", "v_codes", "v_meta", "mask", "k_res", "v_res", "pool_k", "pool_v", "pool_idx",
          "pool_score", "pool_count", "aux_count", "frozen")
@@ -109,13 +111,17 @@ def test_rows_given_back_before_a_side_stream_reads_them():
 @pytest.mark.parametrize("bits,G,groups", [
     (2, 32, 127), (2, 32, 128), (4, 64, 64), (2, 128, 32),
     (2, 32, 47), (2, 32, 48), (4, 32, 48), (2, 64, 15), (2, 64, 16), (4, 64, 16), (2, 128, 23), (2, 128, 24), (4, 128, 16),
+    (2, 32, 31), (2, 32, 32), (4, 32, 31), (4, 32, 32), (4, 64, 15), (2, 128, 7), (2, 128, 8), (4, 128, 7), (4, 128, 8),
 ])
 def test_a_large_batch_equals_each_sequence_on_its_own(bits, G, groups):
-    """128 units: from 4096 quantized tokens each (2^27 bytes of Keys) the quantization takes the last groups first; from
-    1024 .. 3072, by code and group size, its loads and stores leave the caches alone."""
+    """128 units: from 4096 quantized tokens each (2^27 bytes of Keys) the quantization takes the last groups first, from
+    1024 (2^25) its loads and stores leave the caches alone.  Each sequence on its own, 8 units, does neither, but goes
+    through the same kernel: two units are compared with the oracle as well."""
     import torch
     n = groups * G + 43
+    w = S.Workload("batch", 1, 16, 8, 8, n, bits, G, residual=43)
     cfg = KC.make_config(1, 16, 8, 8, groups * G, bits, G, residual=43)
+    assert w.n_quant == groups * G
     gen = torch.Generator(device="cuda")
     gen.manual_seed(groups)
     k, v = (torch.randn(16, 8, n, 128, generator=gen, device="cuda").half() for _ in range(2))
@@ -126,6 +132,8 @@ def test_a_large_batch_equals_each_sequence_on_its_own(bits, G, groups):
     torch.cuda.synchronize()
     for x in NAMES:
         assert torch.equal(getattr(a, x), getattr(b, x)), x
+    units = [5, 126]
+    H.compare_state(a, H.oracle_states(w, k.cpu().numpy(), v.cpu().numpy(), w.n_quant, units), w, w.n_quant, units=units)
 
 
 @pytest.mark.gpu

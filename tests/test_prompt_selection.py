@@ -193,11 +193,13 @@ def test_a_group_competes_as_a_whole_wherever_the_prompt_is_cut(G, A, n):
     check_selection(K, np.random.default_rng(G + A).standard_normal(K.shape).astype(np.float16), G, 8, A)
 
 
-@pytest.mark.parametrize("bits,G,Gv", [(2, 32, 32), (4, 32, 64), (2, 64, 128)])
-@pytest.mark.parametrize("batch", [47, 48, 49])
+@pytest.mark.parametrize("bits,G,Gv,batch", [
+    (bits, G, Gv, batch) for bits, G, Gv, batches in [(2, 32, 32, (15, 16, 17)), (4, 32, 64, (15, 16, 17)), (2, 64, 128, (1, 2, 3)),
+                                                      (4, 64, 32, (1, 2, 3)), (2, 32, 32, (48, 49)), (4, 32, 64, (49,)), (2, 64, 128, (49,))]
+    for batch in batches])
 def test_many_prompts_in_one_call_equal_each_on_its_own(bits, G, Gv, batch):
-    """752, 768 and 784 groups in one call, on both sides of where the quantization changes kernels, against the
-    same prompts one sequence at a time (16 groups per call)."""
+    """16 groups per sequence.  240, 256 and 272 groups of 32 tokens, 16, 32 and 48 of 64 in one call, on both sides of where
+    the quantization changes kernels, against the same prompts one sequence at a time (16 groups per call)."""
     import torch
     from paper_2505_10938_amd import cache as KC
     heads, groups, R = 4, 4, 32
