@@ -84,10 +84,18 @@ __device__ inline float lo_half(uint32_t w) { return __half2float(__ushort_as_ha
 __device__ inline float hi_half(uint32_t w) { return __half2float(__ushort_as_half((unsigned short)(w >> 16))); }
 
 constexpr int kQuantThreads = 1024;
-// From this many groups in one launch on, prompt_quantize_kernel takes them.  Whole calls of a prompt, quantize_kernel /
-// prompt_quantize_kernel, 2-bit (4-bit alike): G = 32, 64 / 192 / 384 / 640 groups 23.0 / 22.9, 22.2 / 22.5, 21.0 / 20.6, 26.1 / 22.4 us;
-// G = 64, 16 / 64 / 384 / 640 22.1 / 22.6, 22.4 / 22.0, 24.9 / 21.2, 39.9 / 33.5; G = 128, 4 / 32 / 256 / 640 22.8 / 22.5, 28.8 / 24.2,
-// 28.3 / 23.0, 52.0 / 39.0 (1024 threads keep a group of 128 tokens longest, and one workgroup of them fills half a compute unit).
+// From this many groups in one launch on, prompt_quantize_kernel takes them (1024 threads keep a group of 128 tokens longest,
+// and one workgroup of them fills half a compute unit).  Us of calls recorded in a graph, three sets of rows in turn,
+// quantize_kernel / prompt_quantize_kernel; 2-bit, then 4-bit codes:
+//   prompt without a pool   G = 32, 128 groups 6.7 / 5.7, 6.9 / 6.3   256 7.0 / 5.8, 7.2 / 6.5    512 9.0 / 7.2, 9.5 / 8.6    768 11.8 / 8.6, 12.4 / 10.0
+//                           G = 64,  32 groups 7.8 / 5.9, 8.2 / 6.5   512 12.9 / 9.3, 14.0 / 11.0
+//                           G = 128,  8 groups 10.8 / 6.5, 11.7 / 7.7 256 14.1 / 9.4, 15.3 / 11.0
+//   with a pool, N = 8      G = 32, 256 groups 17.5 / 16.5, 17.7 / 17.2;  G = 64, 32 14.3 / 12.0, 14.7 / 12.8;  G = 128, 8 17.4 / 12.4, 18.3 / 13.6
+//   kvq_quantize_group      G = 32, 256 units 5.0 / 4.0, 5.2 / 4.5;  G = 64, 32 5.8 / 3.9, 6.1 / 4.5;  G = 128, one 8.5 / 4.4, 9.5 / 5.4
+// Its code is 29 .. 37 KB, the other's 5 .. 6.  With a decode step, products and elementwise kernels ahead of each call, so
+// that neither finds its code in the instruction cache, a group of 128 tokens still gains 4 us and one of 64 tokens 1 .. 2.  With
+// G = 32 the two are even at 256 groups (ten shapes, N = 0 and 8: 2-bit 0.5 us faster in the mean, -0.9 .. 1.3, 4-bit 0.3 slower,
+// -1.6 .. 0.8); from 320 on it is ahead there too (4-bit 0.3 .. 1.1 us, from 640 on 2 .. 3).
 constexpr int64_t prompt_groups(int G) { return G == 32 ? 256 : G == 64 ? 32 : 1; }
 
 // Minimum and maximum over groups of `n` adjacent lanes (n = 4, 8 or 16).
@@ -376,8 +384,8 @@ __global__ void __launch_bounds__(kQuantThreads) quantize_kernel(
 //           and thresholds it works out for the quad.  Codes become words by trades between lanes and between
 //           registers, and a lane stores 16 bytes.
 // No row goes through LDS, and each is read once: the blocks of a longer group exchange minimum, maximum and, where a
-// token is flagged, sums.  What bounds it: the rows and codes on their way (256 units x 4096 tokens, 2-bit: 637 MB in
-// 89 us, 7.1 TB/s, the Keys in part from the memory-side cache).  When every code was decided by fp32 comparisons, gathered by
+// token is flagged, sums.  What bounds it: the rows and codes on their way (256 units x 4096 tokens, 2-bit: 653 MB in
+// 89 us, 7.3 TB/s, the Keys in part from the memory-side cache).  When every code was decided by fp32 comparisons, gathered by
 // an OR over the lanes token by token and the Values turned through LDS, it was the instructions, 1900 per block where
 // there are now about 1050; when one wavefront took the blocks of a group one after the other, a second read of the Keys.
 // Whole calls, three sets of rows in turn, before all that / with the blocks one after the other / now (accesses past the
@@ -1114,15 +1122,25 @@ hipError_t launch_quantize_one(const Dims& d, int32_t group_index, int32_t n_gro
   };
   // Two rules on the Keys' size.  (Times of the whole call, MB of 2^20 bytes; the memory-side cache holds 256.)
   // Where the competition has just read more Keys than the cache keeps besides everything else, the last groups come
-  // first: their Keys are still there.  G = 32, first to last / last to first: 2-bit, 260 MB (256 units x 4160 tokens)
-  // 197 / 186 us, 520 MB 385 / 372; 4-bit, 260 MB 240 / 233.  At 128 MB and below they are there in any order.
+  // first: their Keys are still there.  First to last / last to first, three sets of rows in turn, G = 32 2-bit, 4-bit, G = 128
+  // 2-bit: 128 units x 4096 tokens (128 MB) 82.8 / 81.9 us, 96.2 / 94.9, 92.4 / 90.4; 256 x 4096 150.4 / 149.3, 173.9 / 171.2,
+  // 170.4 / 167.6; 256 x 8192 286.0 / 285.0, 316.2 / 312.5, 324.0 / 321.6; 512 x 4096 319.4 / 317.7, 344.5 / 348.9, 340.5 / 340.2.
   // ONCE keeps rows that are not needed again, and the codes, from displacing the rest.  It pays where the rows have to
   // come from memory, and costs where the next call would have found the same rows in the same place in the cache (which
   // a prompt does not do).  Whole calls, three sets of rows in turn, without / with, G = 32 (64 and 128 alike):
   //   Keys   12 MB, 128 units   24, 128       36, 256       64, 32        100, 128      200, 128    400, 256    1100 MB, 512 units
   //   2-bit  26.4 / 26.1 us     31.7 / 32.2   41.2 / 38.9   60.4 / 54.7   83.4 / 77.1   153 / 134   275 / 238   745 / 688
   //   4-bit  29.0 / 28.9        35.5 / 35.6   45.5 / 44.1   67.3 / 62.4   92.7 / 88.3   166 / 150   304 / 263   794 / 732
-  // With one set of rows, read again and again, it costs 2 .. 4 % from 32 to 100 MB, and gives 5 .. 13 % from 200 MB on.
+  // With one set of rows, read again and again, it costs 2 .. 4 % from 32 to 100 MB, and gives 5 .. 13 % from 200 MB on.  Without
+  // a pool, three sets that the cache holds together (32 MB): 18.5 / 20.9.  Rows that a copy has just written (the copies are
+  // in the times), 128 units, without / with:
+  //   Keys              32 MB         48           64              96              128             192
+  //   G = 32, 2-bit     54.4 / 54.5   78.4 / 74.2  105.4 / 104.8   150.5 / 153.4   198.9 / 191.9   297.8 / 280.8
+  //   G = 32, 4-bit     58.7 / 59.2   87.5 / 82.0  111.3 / 113.0   159.3 / 162.2   211.0 / 204.8   362.1 / 349.7
+  //   G = 64, 2-bit     55.6 / 55.7   77.9 / 75.8  104.5 / 105.4   150.9 / 154.9   231.6 / 227.3   347.6 / 332.3
+  //   G = 128, 2-bit    56.7 / 56.5   80.5 / 79.1  109.6 / 110.2   155.1 / 157.1   237.6 / 232.7   353.5 / 341.8
+  //   no pool, G = 32   41.2 / 40.9   55.5 / 55.0  81.9 / 79.3     122.5 / 121.4   166.3 / 155.7   253.7 / 239.8
+  // So it costs up to 4 us of about 75 there around 96 MB, where rows that are not so new gain 6, and gives on either side.
   const int64_t key_bytes = groups * G * (2 * kHeadDim);
   const int32_t last_first = key_bytes >= (1ll << 27);
   const bool once = key_bytes >= (1ll << 25);

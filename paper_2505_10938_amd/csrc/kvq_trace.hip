@@ -49,13 +49,15 @@ __global__ void __launch_bounds__(trace_core::kWorkers) trace_kernel(
 // the scores and flags the tokens that may be selected, judged by the segment alone (for N = 8 and random scores about
 // 50 of 1024); prompt_compete_kernel then gathers the flagged ones.  It reads all Keys, however early tracing stops.
 //
-// Us of a prompt's whole call (G = 32, N = 8; the quantization, about 125 us per 256 x 4096 tokens, included), with one
-// wavefront per unit that walked the groups and inserted one token at a time / by segments / one workgroup per unit:
-//   8 units x 8192 tokens, A = 32       101 /  34 /  93
-//   64 x 16384, A = 32; A = 16          300 / 209 / 285; 181 / 200 / 157
-//   256 x 4096, A = 32; A = 16          205 / 190 / 189; 183 / 187 / 165
-//   1024 x 4096, A = 32; A = 16         767 / 775 / 743; 677 / 777 / 616   (T = 512)
-//   1024 x 300, A = 32; N = 1, A = 0     85 /  92 /  64;  58 /  81 /  53   (T = 256)
+// Us of a prompt's whole call (G = 32, N = 8, 2-bit; the quantization, 89 us per 256 x 4096 tokens, included), three sets of rows
+// in turn, by segments / one workgroup per unit:
+//   8 units x 8192 tokens; 32 x 8192, A = 32     29 /  66;  50 /  87
+//   128 x 4096, A = 32; A = 16                   82 /  88;  81 /  78
+//   256 x 4096, A = 32; A = 16                  159 / 150; 158 / 143
+//   128 x 8192; 192 x 8192, A = 32              157 / 164; 242 / 219
+//   64 x 16384, A = 32; A = 16                  163 / 226; 163 / 158
+//   1024 x 4096, A = 32; A = 16                 758 / 703; 710 / 565   (T = 512)
+//   1024 x 1120, A = 32                         239 / 201              (T = 512)
 
 constexpr int kSegment = 1024;                         // tokens of a workgroup of prompt_candidates_kernel
 constexpr int kRound = 128;                            // tokens ranked at a time: at least a whole group
@@ -69,6 +71,8 @@ typedef unsigned long long u64;
 // What takes the time is the ballots, 16 ns each.  Few members: the N-th smallest of the lanes' own smallest entries serves as
 // well, N entries are no larger, and seldom does one lane have two of the N (N = 8: a bound by 6 % too many entries).
 // 64 / 16 ballots, the whole call: a prompt of 8191 tokens that joins, 8 kv heads, 4 layers, 51.8 / 50.6 us; 32 units of 8192 tokens 54.5 / 53.2; 24 of 1500 31.9 / 31.2.
+// (Short prompts of few units, 4 .. 32 units of 200 .. 500 tokens: 0.4 .. 0.5 us of 11 .. 15 less with few members; with N = 32, which
+// gains nothing by the second way and by the order of rows below, 0.1 .. 0.2 more.)
 constexpr int kPrefixes = 4;
 constexpr int kCoarseBits = 16;
 constexpr int kFewMembers = 16;
@@ -588,12 +592,14 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) pro
 
 // Do the segments of a prompt go to workgroups of their own (if there are several)?  By segments a call's Keys take
 // 10 us per 250 units and segment plus about 20 us for two launches one after the other, by unit 10 us per segment and
-// about 12: `early` is the number of segments at which the two are even (whole call, 4096 tokens, by segments / by
-// unit: 128 units 97 / 105 us, 192 137 / 143, 256 190 / 189; 16384 tokens: 192 units 628 / 623).
+// about 12: `early` is the number of segments at which the two are even.  (These were the times when the line was drawn.  One
+// workgroup per unit has gained more since: whole call, A = 32, by segments / by unit, 4096 tokens: 128 units 82 / 88 us, 160
+// 99 / 100, 192 117 / 116, 256 159 / 150; 8192: 128 157 / 164, 160 201 / 192, 192 242 / 219; 16384: 192 525 / 471.  From 160 units on
+// the line lies too far towards the segments, by up to a tenth of the call.)
 // By unit it is as well if tracing has stopped by then in all units, to be expected with a small auxiliary pool: were
 // the scores independent, group i would displace N / i tokens on average, about Poisson, E = N ln(groups, or tokens / N)
 // in all; Chernoff's bound on at most A of them, for all units, is held against e^-2.  (If that is wrong for the
-// prompt at hand the call is as long as with the walk above, or reads what it need not.)
+// prompt at hand one workgroup per unit reads all of it after all, or the segments read what they need not.)
 bool by_segments(const Dims& d, int32_t units, int32_t n_tok) {
   if (d.N == 0 || n_tok <= kSegment) return false;
   const double segments = (double)n_tok / kSegment, early = 0.75 + units * segments / 250.0;
